@@ -114,10 +114,21 @@ def _gradients(gen, rows, cols, kind):
     return (g / (chi / 3.0).sqrt_() * 1e-3).to(torch.bfloat16)
 
 
-def prepare(case, seed):
-    M, N, K, calls = case["M"], case["N"], case["K"], case["calls"]
+def _tensors(case, seed):
+    """X, W and, where the case has a backward call, dY and the dW it starts from."""
+    M, N, K = case["M"], case["N"], case["K"]
     gen = torch.Generator(device="cuda")
     gen.manual_seed(seed)
+    x, w, dy, dw = _activations(gen, M, K, case["x"]), _normal(gen, N, K, 0.02), None, None
+    if case["calls"] not in ("fwd", "kept"):
+        dy = _gradients(gen, M, N, case["dy"])
+        # (with accumulation: the gradient of the microbatches before this one)
+        dw = torch.randn((N, K), generator=gen, device="cuda") * 1e-2
+    return x, w, dy, dw
+
+
+def prepare(case, seed):
+    M, N, K, calls = case["M"], case["N"], case["K"], case["calls"]
     out = mx.OUT_FP32 if case["out"] == "fp32" else mx.OUT_BF16
     dtype = torch.float32 if case["out"] == "fp32" else torch.bfloat16
     fprop, dgrad, wgrad = (FORMATS[c] for c in case["stages"])
@@ -125,8 +136,8 @@ def prepare(case, seed):
                       dw_dtype=mx.OUT_FP32, dw_accumulate=case["accumulate"],
                       geometry=mx.GEOM_2D if case["geometry"] == "2d" else mx.GEOM_1D,
                       fprop_format=fprop, dgrad_format=dgrad, wgrad_format=wgrad)
-    s = {"calls": calls, "cfg": cfg, "K": K, "out": out,
-         "x": _activations(gen, M, K, case["x"]), "w": _normal(gen, N, K, 0.02)}
+    x, w, dy, dw = _tensors(case, seed)
+    s = {"calls": calls, "cfg": cfg, "K": K, "out": out, "x": x, "w": w}
     bytes_of = dict(dtype=torch.uint8, device="cuda")
     if calls != "wgrad":
         s["y"] = torch.empty((M, N), dtype=dtype, device="cuda")
@@ -137,10 +148,8 @@ def prepare(case, seed):
     if calls != "wgrad":
         s["ws_f"] = torch.empty(mx.mxfp4_linear_workspace_bytes(M, N, K, cfg, False), **bytes_of)
     if calls != "fwd":
-        s["dy"] = _gradients(gen, M, N, case["dy"])
+        s["dy"], s["dw"] = dy, dw
         s["ws_b"] = torch.empty(mx.mxfp4_linear_workspace_bytes(M, N, K, cfg, True), **bytes_of)
-        # (with accumulation: the gradient of the microbatches before this one)
-        s["dw"] = torch.randn((N, K), generator=gen, device="cuda") * 1e-2
         if calls != "wgrad":
             s["dx"] = torch.empty((M, K), dtype=dtype, device="cuda")
     if calls == "step":
@@ -191,3 +200,83 @@ def tolerance(case):
     if case["out"] == "fp32":
         return {"rel": 1e-6, "max": 1e-5}
     return {"rel": 1e-4, "max": 8e-3}
+
+
+# ---- the same results in plain torch: operands quantised by their definition, products summed in 64 bits ----------
+
+def _mix(v):
+    v = (v ^ (v >> 16)) * 0x9E3779B9 & 0xFFFFFFFF
+    v = (v ^ (v >> 15)) * 0xBB67AE85 & 0xFFFFFFFF
+    return v ^ (v >> 16)
+
+
+def _rand32(seed, low, high):
+    key = _mix((seed >> 32 & 0xFFFFFFFF) ^ 0x6A09E667)
+    return _mix(_mix((low + (seed & 0xFFFFFFFF) * 0x9E3779B9) & 0xFFFFFFFF) ^ high ^ key)
+
+
+def _rotate(v, had, seed):
+    """Blocks of 32 along the last axis: sign diagonal, butterflies and one multiply, every operation in fp32."""
+    if had.startswith("sign"):
+        mask = _rand32(seed & 0xFFFFFFFFFFFF, 0xFFFFFFFF, 0xFFFFFFFF)
+        v = v * torch.tensor([1.0 - 2.0 * (mask >> i & 1) for i in range(32)], device=v.device)
+    if had == "none":
+        return v
+    points = 32 if had.endswith("32") else 16
+    h = 1
+    while h < points:
+        p = v.view(v.shape[:-1] + (32 // (2 * h), 2, h))
+        v = torch.stack((p[..., 0, :] + p[..., 1, :], p[..., 0, :] - p[..., 1, :]), dim=-2).reshape(v.shape)
+        h *= 2
+    return v * torch.tensor(32.0 ** -0.5 if points == 32 else 0.25, dtype=torch.float32, device=v.device)
+
+
+def _quantised(case, x, stream, bits, seed):
+    """The values that x [R][C] has as a quantised operand with blocks of 32 along its last axis, in 64 bits."""
+    R, C = x.shape
+    seed = (seed & (2**64 - 1)) ^ (stream << 48)
+    out = torch.empty((R, C), dtype=torch.float64, device=x.device)
+    step = max(32, (1 << 25) // C // 32 * 32)
+    for r in range(0, R, step):
+        v = x[r:r + step].float().reshape(-1, C // 32, 32)
+        if bits == "4":
+            v = _rotate(v, case["had"], seed)
+        amax = v.abs().amax(dim=-1)
+        if case["geometry"] == "2d":
+            amax = amax.view(-1, 32, C // 32).amax(dim=1).repeat_interleave(32, dim=0)
+        exponent = ((amax.view(torch.int32) >> 23) - (2 if bits == "4" else 8)).clamp(min=0) - 127
+        scale = ((exponent.long() + 1023) << 52).view(torch.float64).unsqueeze(-1)  # 2^exponent
+        t = v.double() / scale
+        if bits == "8":
+            t = t.clamp(-448.0, 448.0).float().to(torch.float8_e4m3fn).double()
+        else:
+            a = t.abs().clamp(max=6.0)
+            grid = torch.where(a < 2.0, 0.5, torch.where(a < 4.0, 1.0, 2.0))
+            a = a / grid
+            if case["rnd"] == "sr":
+                index = torch.arange(r * C, r * C + a.numel(), device=x.device).view(a.shape)
+                u = (2 * (_rand32(seed, index & 0xFFFFFFFF, index >> 32) >> 9) + 1).double() * 2.0**-24
+                a = a.floor() + (u < a - a.floor()).double()
+            else:
+                a = a.round()
+            t = torch.copysign(a * grid, t)
+        out[r:r + step] = (t * scale).view(-1, C)
+    return out
+
+
+def exact(case, seed):
+    x, w, dy, dw0 = _tensors(case, seed)
+    calls, (fprop, dgrad, wgrad) = case["calls"], case["stages"]
+    X, W, DY, WT, DYT, XT = range(6)
+    if calls != "wgrad":
+        y = _quantised(case, x, X, fprop, seed) @ _quantised(case, w, W, fprop, seed).T
+        if calls in ("fwd", "kept"):
+            return y
+    dw = (_quantised(case, dy.T.contiguous(), DYT, wgrad, seed) @
+          _quantised(case, x.T.contiguous(), XT, wgrad, seed).T)
+    if case["accumulate"]:
+        dw += dw0
+    if calls == "wgrad":
+        return dw
+    dx = _quantised(case, dy, DY, dgrad, seed) @ _quantised(case, w.T.contiguous(), WT, dgrad, seed).T
+    return {"y": y, "dx": dx, "dw": dw}
