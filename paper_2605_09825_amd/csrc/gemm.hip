@@ -44,7 +44,7 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
-// ---- any-shape kernel --------------------------------------------------------------------
+// ---- any-shape kernel: operands of different formats, and sizes beyond the ragged-shape kernel's grid and offsets ----
 // 256 threads = 2x2 waves, each wave a 32x32 output tile (2x2 instruction tiles); operands
 // come straight from global memory.  Rows beyond the matrix are clamped (their results
 // are dropped), K blocks beyond C/32 are fed as zeros.
@@ -795,6 +795,264 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_pair_kernel(const TileGemm p
                                             (lw - n0) * 8 + xcd, (uint32_t)(32 - n0) * 8, smem, lds0);
 }
 
+// ---- ragged-shape kernel: any row and column counts, any C % 32 == 0 --------------------------
+// 2 x NWN waves on a (64 WM) x (32 WN NWN) output tile, V_MFMA_SCALE_F32_32X32X64_F8F6F4, WM x WN of them per wave and
+// K-step.  It is bound by how fast operands reach the matrix unit: the kernel it took over from read every fragment
+// straight from global memory, 16 rows x 64 bytes per instruction and each row by two waves, with nothing in flight
+// while it multiplied.  Here codes go global -> LDS in whole 128-byte row pieces (one stage = 128 bytes of every row,
+// NBUF stage buffers), each row piece once per workgroup, under the swizzle of the tiled kernel above.
+// What makes it any-shape:
+//   * rows beyond the matrix are clamped to the last one (their results are dropped by the store);
+//   * a 16-byte chunk beyond the end of a row is clamped to the row's last chunk, and the scale bytes of the blocks
+//     beyond C/32 are 0 in LDS for both operands: every product under them is below 2^-254 * 2^24, which is 0 in fp32,
+//     so the last stage runs the same code as the others;
+//   * scale rows are C/32 bytes apart, at any alignment: they come through registers (16-byte loads, bytes at a row's
+//     ragged end) into LDS, 32 bytes per row (1024 elements of K) at a time, double-buffered.
+// FMT as in gemm_tile_body.  Built as 64 x 64 (4 stage buffers, 72 KiB of LDS, two workgroups per CU), 128 x 64 (2, 60 KiB)
+// and 128 x 256 tiles (8 waves, 2, 120 KiB); 128 x 128 tiles on 4 waves were never the fastest, 256 x 256 tiles on 8 waves
+// were slower for MXFP4 (210 against 156 us at 8192 x 6112 x 4064).
+// Measured, bf16 output, the kernel before / this one: MXFP4 8192 x 6112 x 4064 911 / 156 us (2.6 PFLOP/s), 16000 x 1000 x
+// 3008 237 / 43, 2080 x 4320 x 1440 66.7 / 22.4, 2048 x 3072 x 768 33.6 / 8.9, 200 x 4096 x 4096 31.2 / 9.4, 24 x 6144 x
+// 4096 23.5 / 8.9, 256 x 512 x 512 6.2 / 4.1; MXFP8 8192 x 6112 x 4064 1337 / 271, 200 x 4096 x 4096 45.2 / 13.4 us.
+template <int WM, int WN, int NWN, int NBUF>
+struct EdgeTile {
+    static constexpr int WAVES = 2 * NWN, TM = 64 * WM, TN = 32 * WN * NWN, ROWS = TM + TN;
+    static constexpr int STAGE = ROWS * 128;          // bytes of codes per stage
+    static constexpr int NL = ROWS / 8 / WAVES;              // direct-to-LDS loads per wave and stage
+    static constexpr int OFF_S = NBUF * STAGE, SBUF = ROWS * 32;
+    static constexpr int LDS = OFF_S + 2 * SBUF;
+};
+
+struct EdgeGemm {
+    const uint8_t *aq, *as, *bq, *bs;
+    int64_t Ra, Rb, C;
+    void *out;
+    int64_t ld;
+    int tiles_m, tiles_n, vec;  // vec: four consecutive outputs may be stored at once
+};
+
+template <bool OUT_FP32, bool ACC, int FMT, int WM, int WN, int NWN, int NBUF>
+__global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm p)
+{
+    using Tile = EdgeTile<WM, WN, NWN, NBUF>;
+    constexpr int TM = Tile::TM, TN = Tile::TN, NL = Tile::NL, ROWS = Tile::ROWS, WAVES = Tile::WAVES;
+    constexpr int NLA = TM / 8 / WAVES;  // loads of A among a wave's NL
+    constexpr int BATCH = FMT ? 8 : 4;  // stages per scale batch
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[Tile::LDS];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / NWN, wn = wave % NWN;
+
+    // tile of this workgroup: each XCD (workgroup id mod 8) takes a contiguous run of the tile sequence, which walks
+    // the grid in groups of GROUP_M tile rows (as the tiled kernel does)
+    const int T = p.tiles_m * p.tiles_n, xcd = blockIdx.x & 7, per = T >> 3, rem = T & 7;
+    const int L = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + (int)(blockIdx.x >> 3);
+    const int span = GROUP_M * p.tiles_n, grp = L / span, first = grp * GROUP_M, in = L - grp * span;
+    const int gm = p.tiles_m - first < GROUP_M ? p.tiles_m - first : GROUP_M;
+    const int64_t m0 = (int64_t)(first + in % gm) * TM, n0 = (int64_t)(in / gm) * TN;
+
+    const int64_t rowbytes = FMT ? p.C : (p.C >> 1);
+    const int nkb = (int)(p.C >> 5);
+    const int nstages = (int)((rowbytes + 127) >> 7);
+    const int nbatches = (nkb + 31) >> 5;
+    const uint8_t *abase = p.aq + m0 * rowbytes, *bbase = p.bq + n0 * rowbytes;
+
+    // direct-to-LDS loads: load n of wave w moves the 8-row group WAVES n + w (A's rows, then B's)
+    const int drr = lane >> 3, chunk = ((lane & 7) ^ drr ^ (wave & 1)) << 4;
+    uint32_t roff[NL];
+#pragma unroll
+    for (int n = 0; n < NL; ++n) {
+        const bool isb = n >= NLA;
+        const int64_t r0 = isb ? n0 : m0, R = isb ? p.Rb : p.Ra;
+        const int64_t want = (int64_t)((n - (isb ? NLA : 0)) * WAVES + wave) * 8 + drr, last = R - 1 - r0;
+        roff[n] = (uint32_t)((want < last ? want : last) * rowbytes);
+    }
+    auto issue = [&](int s) {
+        const uint32_t at = (uint32_t)s * 128u + (uint32_t)chunk, end = (uint32_t)rowbytes - 16u;
+        const uint32_t koff = at < end ? at : end;
+        const uint32_t dst = lds0 + (uint32_t)(s % NBUF) * Tile::STAGE + (uint32_t)wave * 1024u;
+#pragma unroll
+        for (int n = 0; n < NL; ++n) dma16(dst + n * (WAVES * 1024u), roff[n] + koff, n >= NLA ? bbase : abase);
+    };
+
+    // scale bytes: piece j of this thread = 16 bytes (half (tid * NP + j) & 1 of its row's 32) of a batch
+    constexpr int NP = (ROWS * 2 + 64 * WAVES - 1) / (64 * WAVES);
+    struct __attribute__((packed, aligned(1))) Piece { uint32_t v[4]; };
+    uint4 piece[NP];
+    auto load_scales = [&](int b) {
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            const int idx = tid * NP + j, r = idx >> 1;
+            const bool isb = r >= TM;
+            const int64_t want = isb ? n0 + r - TM : m0 + r, last = (isb ? p.Rb : p.Ra) - 1;
+            const int o = b * 32 + (idx & 1) * 16, left = nkb - o;
+            const uint8_t *src = (isb ? p.bs : p.as) + (want < last ? want : last) * (int64_t)nkb;
+            if (left >= 16) {
+                const Piece t = *reinterpret_cast<const Piece *>(src + o);
+                piece[j] = make_uint4(t.v[0], t.v[1], t.v[2], t.v[3]);
+            } else {  // the ragged end of a row: zeros behind it
+                uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+                for (int k = 0; k < 16; ++k) {
+                    const uint32_t byte = src[k < left ? o + k : nkb - 1];
+                    w[k >> 2] |= (k < left ? byte : 0u) << (8 * (k & 3));
+                }
+                piece[j] = make_uint4(w[0], w[1], w[2], w[3]);
+            }
+        }
+    };
+    // 8-byte slot t (0..3) of a row sits at slot t ^ (row / 8 % 4): the fragment reads of 32 rows touch every bank once
+    auto write_scales = [&](int b) {
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            const int idx = tid * NP + j, r = idx >> 1, sw = (r >> 3) & 3, t = (idx & 1) * 2;
+            if (ROWS * 2 % (64 * WAVES) != 0 && r >= ROWS) break;  // (128 x 64 tile: 192 rows on 256 threads)
+            uint8_t *dst = smem + Tile::OFF_S + (b & 1) * Tile::SBUF + r * 32;
+            *reinterpret_cast<uint2 *>(dst + ((t ^ sw) << 3)) = make_uint2(piece[j].x, piece[j].y);
+            *reinterpret_cast<uint2 *>(dst + (((t + 1) ^ sw) << 3)) = make_uint2(piece[j].z, piece[j].w);
+        }
+    };
+
+    // fragment reads
+    const int fr = lane & 31, fh = lane >> 5;
+    const int fm = (fr & 7) ^ ((fr >> 3) & 1);
+    const uint32_t fl0 = (uint32_t)((fr >> 3) * 1024 + (fr & 7) * 128);
+    uint32_t foff[4];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) foff[kk] = fl0 + (uint32_t)((((kk << 1) | fh) ^ fm) << 4);
+    const uint32_t perm_sel = FMT ? (fh ? 0x03010301u : 0x02000200u) : (fh ? 0x07050301u : 0x06040200u);
+    auto frag_scale = [&](int s, int row) {  // the lane's scale bytes of stage s, byte k = instruction K-step k
+        const int b = s / BATCH, slot = FMT ? (s & 7) >> 1 : s & 3;
+        const uint8_t *q = smem + Tile::OFF_S + (b & 1) * Tile::SBUF + row * 32 + ((slot ^ ((row >> 3) & 3)) << 3);
+        if (FMT) return (int)__builtin_amdgcn_perm(0u, *reinterpret_cast<const uint32_t *>(q + (s & 1) * 4), perm_sel);
+        const uint2 w = *reinterpret_cast<const uint2 *>(q);
+        return (int)__builtin_amdgcn_perm(w.y, w.x, perm_sel);
+    };
+
+    v16f acc[WM][WN];
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int j = 0; j < WN; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+
+    if (nstages > 0) {
+        load_scales(0);
+#pragma unroll
+        for (int s = 0; s < NBUF - 1; ++s)
+            if (s < nstages) issue(s);
+        write_scales(0);
+    }
+    for (int s = 0; s < nstages; ++s) {
+        // stage s has landed (the loads of the stages after it may be out), everyone is done with stage s-1
+        if (NBUF > 2 && s + NBUF - 2 < nstages)
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NL * (NBUF - 2)) : "memory");
+        else
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        const int b = s / BATCH, in_batch = s % BATCH;
+        if (in_batch == 0 && b + 1 < nbatches) load_scales(b + 1);
+        if (s + NBUF - 1 < nstages) issue(s + NBUF - 1);
+        const uint8_t *buf = smem + (s % NBUF) * Tile::STAGE;
+        int sa[WM], sb[WN];
+#pragma unroll
+        for (int i = 0; i < WM; ++i) sa[i] = frag_scale(s, wm * 32 * WM + 32 * i + fr);
+#pragma unroll
+        for (int j = 0; j < WN; ++j) sb[j] = frag_scale(s, TM + wn * 32 * WN + 32 * j + fr);
+        const uint8_t *pa = buf + wm * WM * 4096, *pb = buf + TM * 128 + wn * WN * 4096;
+        auto frag = [&](const uint8_t *q, int t, int kk) {
+            return *reinterpret_cast<const v4i *>(q + t * 4096 + foff[kk]);
+        };
+#define MXFP4_EDGE_STEP(KK)                                                                                          \
+        {                                                                                                            \
+            v4i fa[WM], fb[WN];                                                                                      \
+            _Pragma("unroll") for (int i = 0; i < WM; ++i) fa[i] = frag(pa, i, KK);                                  \
+            _Pragma("unroll") for (int j = 0; j < WN; ++j) fb[j] = frag(pb, j, KK);                                  \
+            _Pragma("unroll") for (int i = 0; i < WM; ++i) _Pragma("unroll") for (int j = 0; j < WN; ++j)            \
+                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(                                         \
+                    (v8i){fb[j].x, fb[j].y, fb[j].z, fb[j].w, 0, 0, 0, 0},                                           \
+                    (v8i){fa[i].x, fa[i].y, fa[i].z, fa[i].w, 0, 0, 0, 0}, acc[i][j], 4, 4, KK, sb[j], KK, sa[i]);   \
+        }
+#define MXFP8_EDGE_STEP(KS)                                                                                          \
+        {                                                                                                            \
+            v4i fa[WM][2], fb[WN][2];                                                                                \
+            _Pragma("unroll") for (int h = 0; h < 2; ++h) {                                                          \
+                _Pragma("unroll") for (int i = 0; i < WM; ++i) fa[i][h] = frag(pa, i, 2 * KS + h);                   \
+                _Pragma("unroll") for (int j = 0; j < WN; ++j) fb[j][h] = frag(pb, j, 2 * KS + h);                   \
+            }                                                                                                        \
+            _Pragma("unroll") for (int i = 0; i < WM; ++i) _Pragma("unroll") for (int j = 0; j < WN; ++j)            \
+                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(                                         \
+                    (v8i){fb[j][0].x, fb[j][0].y, fb[j][0].z, fb[j][0].w, fb[j][1].x, fb[j][1].y, fb[j][1].z,        \
+                          fb[j][1].w},                                                                               \
+                    (v8i){fa[i][0].x, fa[i][0].y, fa[i][0].z, fa[i][0].w, fa[i][1].x, fa[i][1].y, fa[i][1].z,        \
+                          fa[i][1].w},                                                                               \
+                    acc[i][j], 0, 0, KS, sb[j], KS, sa[i]);                                                          \
+        }
+        if constexpr (FMT == 0) {
+            MXFP4_EDGE_STEP(0) MXFP4_EDGE_STEP(1) MXFP4_EDGE_STEP(2) MXFP4_EDGE_STEP(3)
+        } else {
+            MXFP8_EDGE_STEP(0) MXFP8_EDGE_STEP(1)
+        }
+#undef MXFP4_EDGE_STEP
+#undef MXFP8_EDGE_STEP
+        if (in_batch == BATCH - 1 && b + 1 < nbatches) write_scales(b + 1);
+    }
+
+    // epilogue: every wave transposes 32 rows at a time through its own slice of the stage buffers (row of 128 WN bytes,
+    // 16-byte chunk c of row r at chunk c ^ r) and stores whole row pieces
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    constexpr int PITCH = 128 * WN, CHUNKS = 8 * WN;
+    static_assert(WAVES * 32 * PITCH <= NBUF * Tile::STAGE, "32 rows of every wave must fit the stage buffers");
+    uint8_t *epi = smem + wave * (32 * PITCH);
+    constexpr int RPI = 64 / CHUNKS;  // rows per store instruction
+    const int rl = lane / CHUNKS, ch = lane % CHUNKS;
+    const int64_t col = n0 + wn * 32 * WN + ch * 4;
+    const int64_t left = p.Rb - col;
+    const bool whole = p.vec && left >= 4;
+#pragma unroll
+    for (int i = 0; i < WM; ++i) {
+#pragma unroll
+      for (int j = 0; j < WN; ++j)
+#pragma unroll
+        for (int qd = 0; qd < 4; ++qd) {
+            const int c = j * 8 + qd * 2 + fh;
+            *reinterpret_cast<v4f *>(epi + fr * PITCH + ((c ^ (fr & (CHUNKS - 1))) << 4)) =
+                (v4f){acc[i][j][4 * qd + 0], acc[i][j][4 * qd + 1], acc[i][j][4 * qd + 2], acc[i][j][4 * qd + 3]};
+        }
+#pragma unroll
+      for (int u = 0; u < 32 / RPI; ++u) {
+        const int r = u * RPI + rl;
+        const int64_t row = m0 + wm * 32 * WM + 32 * i + r;
+        const v4f v = *reinterpret_cast<const v4f *>(epi + r * PITCH + ((ch ^ (r & (CHUNKS - 1))) << 4));
+        if (row >= p.Ra) continue;
+        if (OUT_FP32) {
+            float *o = reinterpret_cast<float *>(p.out) + row * p.ld + col;
+            if (whole) {
+                v4f t = v;
+                if (ACC) t += *reinterpret_cast<const v4f *>(o);
+                __builtin_nontemporal_store(t, reinterpret_cast<v4f *>(o));
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (e < left) o[e] = ACC ? (o[e] + v[e]) : v[e];
+            }
+        } else {
+            uint16_t *o = reinterpret_cast<uint16_t *>(p.out) + row * p.ld + col;
+            const uint32_t lo = pack_bf16(v[0], v[1]), hi = pack_bf16(v[2], v[3]);
+            if (whole) {
+                typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+                __builtin_nontemporal_store((u32x2){lo, hi}, reinterpret_cast<u32x2 *>(o));
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (e < left) o[e] = (uint16_t)((e & 2 ? hi : lo) >> (16 * (e & 1)));
+            }
+        }
+      }
+    }
+}
+
 }  // namespace
 
 // Compute units of the current device (MI355X: 256); asked once per process and device.
@@ -848,8 +1106,53 @@ static hipError_t launch_any_f(const GemmArgs &g, hipStream_t st)
     return hipGetLastError();
 }
 
+template <int FMT, int WM, int WN, int NWN, int NBUF>
+static hipError_t launch_edge_f(const GemmArgs &g, hipStream_t st)
+{
+    using Tile = EdgeTile<WM, WN, NWN, NBUF>;
+    const EdgeGemm p{g.aq, g.as, g.bq, g.bs, g.Ra, g.Rb, g.C, g.out, g.ld, (int)((g.Ra + Tile::TM - 1) / Tile::TM),
+                     (int)((g.Rb + Tile::TN - 1) / Tile::TN),
+                     (g.ld % 4) == 0 && (reinterpret_cast<uintptr_t>(g.out) % (g.out_fp32 ? 16 : 8)) == 0};
+    dim3 grid((unsigned)(p.tiles_m * p.tiles_n));
+    if (g.out_fp32) {
+        if (g.accumulate)
+            hipLaunchKernelGGL((gemm_edge_kernel<true, true, FMT, WM, WN, NWN, NBUF>), grid, dim3(64 * Tile::WAVES), 0, st, p);
+        else
+            hipLaunchKernelGGL((gemm_edge_kernel<true, false, FMT, WM, WN, NWN, NBUF>), grid, dim3(64 * Tile::WAVES), 0, st, p);
+    } else {
+        hipLaunchKernelGGL((gemm_edge_kernel<false, false, FMT, WM, WN, NWN, NBUF>), grid, dim3(64 * Tile::WAVES), 0, st, p);
+    }
+    return hipGetLastError();
+}
+
+// Estimated microseconds of gemm_edge_kernel on tm x tn tiles: rounds of the tiles that the chip holds at once, each
+// `full` per kilobyte of code row (half of that where at most one of two workgroups per CU is there) plus what filling
+// and emptying the pipeline costs.  The constants were fitted to kernel times at 24 to 16000 rows, 512 to 28640 columns,
+// C = 512 to 8000; they only rank the three tile shapes.  Where they matter: few tiles (200 x 4096 x 4096: 64 x 64 9.4,
+// 128 x 64 12.6, 128 x 256 25 us), a round just overfull (2080 x 4320 x 1440: 29.4, 22.4, 24.8 us), many tiles (8192 x
+// 28640 x 4064: 298, 208, 156 us for a fifth of it).
+static double edge_cost(const GemmArgs &g, int tm, int tn, int slots, double full, double fixed)
+{
+    const int64_t t = ((g.Ra + tm - 1) / tm) * ((g.Rb + tn - 1) / tn), left = t % slots;
+    const double kb = (double)(g.a_fmt ? g.C : g.C / 2) / 1000.0;
+    double us = (double)(t / slots) * (full * kb + fixed);
+    if (left) us += (slots > NUM_CUS && left <= NUM_CUS ? 0.5 : 1.0) * full * kb + fixed;
+    return us;
+}
+
 static hipError_t launch_any(const GemmArgs &g, hipStream_t st)
 {
+    // operands of one format: the ragged-shape kernel (lane offsets hold 127 rows in 32 bits, the grid the tiles)
+    const int64_t t64 = ((g.Ra + 63) / 64) * ((g.Rb + 63) / 64);
+    if (g.a_fmt == g.b_fmt && g.C < (int64_t(1) << 24) && g.Ra < (int64_t(1) << 31) && t64 < (int64_t(1) << 30)) {
+        const double small = edge_cost(g, 64, 64, 512, 6.4, 1.5), mid = edge_cost(g, 128, 64, 512, 9.3, 1.5),
+                     large = edge_cost(g, 128, 256, 256, 11.2, 3.0);
+        if (large <= mid && large <= small)
+            return g.a_fmt ? launch_edge_f<1, 2, 2, 4, 2>(g, st) : launch_edge_f<0, 2, 2, 4, 2>(g, st);
+        if (mid <= small)
+            return g.a_fmt ? launch_edge_f<1, 2, 1, 2, 2>(g, st) : launch_edge_f<0, 2, 1, 2, 2>(g, st);
+        return g.a_fmt ? launch_edge_f<1, 1, 1, 2, 4>(g, st) : launch_edge_f<0, 1, 1, 2, 4>(g, st);
+    }
     if (g.a_fmt == 0) return g.b_fmt == 0 ? launch_any_f<0, 0>(g, st) : launch_any_f<0, 1>(g, st);
     return g.b_fmt == 0 ? launch_any_f<1, 0>(g, st) : launch_any_f<1, 1>(g, st);
 }
@@ -912,7 +1215,7 @@ static hipError_t launch_tiled_tail(const GemmArgs &g, int64_t main_tiles, hipSt
 //     the whole rounds);
 //   * a column count in whole 128s but not 256s: 256 x 128 tiles throughout.
 // Ragged row or column counts: the 256-aligned interior as above, the right and bottom edge strips (less than one
-// tile wide) on the any-shape kernel; everything else on the any-shape kernel.
+// tile wide) and everything else as GEMM_ANY (see launch_any).
 static void plan_tiled(const GemmArgs &g, int64_t r0, int64_t rows, int64_t cols, int64_t cus, GemmPlan &plan)
 {
     auto add = [&](int kind, int64_t main_tiles) {
