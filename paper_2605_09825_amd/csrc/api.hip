@@ -454,23 +454,35 @@ static int quantize_operand_pair(const mxfp4_linear_cfg *cfg, const void *x0, in
     return e == hipSuccess ? MXFP4_OK : MXFP4_EDEVICE;
 }
 
-// The column-wise MXFP4 quantisations of two dense tensors (W and X of a backward call) in one launch.
-static int quantize_cols_pair(const mxfp4_linear_cfg *cfg, const void *x0, int64_t rows0, int64_t cols0, int st0,
+// The row-wise (axis LAST: X and W of a forward call) or column-wise (FIRST: W and X of a backward call) MXFP4
+// quantisations of two dense tensors in one launch.
+static int quantize_axis_pair(int axis, const mxfp4_linear_cfg *cfg, const void *x0, int64_t rows0, int64_t cols0, int st0,
                               uint8_t *q0, uint8_t *s0, const void *x1, int64_t rows1, int64_t cols1, int st1,
                               uint8_t *q1, uint8_t *s1, void *hip_stream)
 {
-    int rc = check_quantize(x0, rows0, cols0, cols0, MXFP4_AXIS_FIRST, cfg->hadamard, cfg->rounding, q0, s0);
+    int rc = check_quantize(x0, rows0, cols0, cols0, axis, cfg->hadamard, cfg->rounding, q0, s0);
     if (rc >= 0) return rc;  // (an error; the linear calls pass no empty tensors)
-    rc = check_quantize(x1, rows1, cols1, cols1, MXFP4_AXIS_FIRST, cfg->hadamard, cfg->rounding, q1, s1);
+    rc = check_quantize(x1, rows1, cols1, cols1, axis, cfg->hadamard, cfg->rounding, q1, s1);
     if (rc >= 0) return rc;
-    const int64_t groups = ((cols0 + 127) / 128) * ((rows0 / 32 + 7) / 8) + ((cols1 + 127) / 128) * ((rows1 / 32 + 7) / 8);
-    if (groups >= (int64_t(1) << 31)) return MXFP4_ESHAPE;  // the two grids share one launch
+    const int64_t groups = axis == MXFP4_AXIS_LAST
+                               ? (rows0 * (cols0 / 32) + 255) / 256 + (rows1 * (cols1 / 32) + 255) / 256
+                               : ((cols0 + 127) / 128) * ((rows0 / 32 + 7) / 8) + ((cols1 + 127) / 128) * ((rows1 / 32 + 7) / 8);
+    if (axis == MXFP4_AXIS_FIRST && groups >= (int64_t(1) << 31)) return MXFP4_ESHAPE;  // the two grids share one launch
     if (!device_ok()) return MXFP4_EDEVICE;
     const QuantArgs a{static_cast<const uint16_t *>(x0), rows0, cols0, cols0, cfg->hadamard, cfg->rounding,
                       operand_seed(cfg, st0), q0, s0};
     const QuantArgs b{static_cast<const uint16_t *>(x1), rows1, cols1, cols1, cfg->hadamard, cfg->rounding,
                       operand_seed(cfg, st1), q1, s1};
-    hipError_t e = launch_quantize_cols(a, static_cast<hipStream_t>(hip_stream), &b);
+    hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    hipError_t e;
+    if (axis == MXFP4_AXIS_FIRST) {
+        e = launch_quantize_cols(a, st, &b);
+    } else if (groups < (int64_t(1) << 31)) {
+        e = launch_quantize_rows(a, st, &b);
+    } else {  // too many workgroups for one grid
+        e = launch_quantize_rows(a, st);
+        if (e == hipSuccess) e = launch_quantize_rows(b, st);
+    }
     return e == hipSuccess ? MXFP4_OK : MXFP4_EDEVICE;
 }
 
@@ -530,10 +542,17 @@ int mxfp4_linear_fwd(const void *x, const void *w, void *y, int64_t M, int64_t N
     if (workspace_bytes < L.total) return MXFP4_EWORKSPACE;
     if (!aligned(workspace, 256) || !aligned(x, 16) || !aligned(w, 16) || !aligned(y, 16)) return MXFP4_EALIGN;
     uint8_t *ws = static_cast<uint8_t *>(workspace);
-    rc = quantize_operand(cfg, x, M, K, F.fprop, STREAM_X, ws + L.xq, ws + L.xs, 0, 0, nullptr, nullptr, hip_stream);
-    if (rc != MXFP4_OK) return rc;
-    rc = quantize_operand(cfg, w, N, K, F.fprop, STREAM_W, ws + L.wq, ws + L.ws, 0, 0, nullptr, nullptr, hip_stream);
-    if (rc != MXFP4_OK) return rc;
+    if (F.fprop == MXFP4_FMT_E2M1 && cfg->geometry == MXFP4_GEOM_1D) {
+        // X and W, both row-wise in MXFP4: one launch for the two tensors
+        rc = quantize_axis_pair(MXFP4_AXIS_LAST, cfg, x, M, K, STREAM_X, ws + L.xq, ws + L.xs, w, N, K, STREAM_W,
+                                ws + L.wq, ws + L.ws, hip_stream);
+        if (rc != MXFP4_OK) return rc;
+    } else {
+        rc = quantize_operand(cfg, x, M, K, F.fprop, STREAM_X, ws + L.xq, ws + L.xs, 0, 0, nullptr, nullptr, hip_stream);
+        if (rc != MXFP4_OK) return rc;
+        rc = quantize_operand(cfg, w, N, K, F.fprop, STREAM_W, ws + L.wq, ws + L.ws, 0, 0, nullptr, nullptr, hip_stream);
+        if (rc != MXFP4_OK) return rc;
+    }
     return mxfp4_gemm_fmt(ws + L.xq, ws + L.xs, F.fprop, ws + L.wq, ws + L.ws, F.fprop, M, N, K, y, N, cfg->y_dtype, 0,
                           hip_stream);
 }
@@ -607,8 +626,8 @@ int mxfp4_linear_bwd(const void *dy, const void *x, const void *w, void *dx, voi
     if (rc != MXFP4_OK) return rc;
     if (dx && dw && F.dgrad == MXFP4_FMT_E2M1 && F.wgrad == MXFP4_FMT_E2M1 && cfg->geometry == MXFP4_GEOM_1D) {
         // W and X, both column-wise in MXFP4: one launch for the two tensors
-        rc = quantize_cols_pair(cfg, w, N, K, STREAM_WT, ws + L.wtq, ws + L.wts, x, M, K, STREAM_XT, ws + L.xtq,
-                                ws + L.xts, hip_stream);
+        rc = quantize_axis_pair(MXFP4_AXIS_FIRST, cfg, w, N, K, STREAM_WT, ws + L.wtq, ws + L.wts, x, M, K, STREAM_XT,
+                                ws + L.xtq, ws + L.xts, hip_stream);
         if (rc != MXFP4_OK) return rc;
     } else {
         if (dx) {

@@ -850,7 +850,9 @@ __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm 
     const int L = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + (int)(blockIdx.x >> 3);
     const int span = GROUP_M * p.tiles_n, grp = L / span, first = grp * GROUP_M, in = L - grp * span;
     const int gm = p.tiles_m - first < GROUP_M ? p.tiles_m - first : GROUP_M;
-    const int64_t m0 = (int64_t)(first + in % gm) * TM, n0 = (int64_t)(in / gm) * TN;
+    // (uniform, but the division ran in the vector unit: put them where the loads want their base)
+    const int64_t m0 = (int64_t)__builtin_amdgcn_readfirstlane(first + in % gm) * TM;
+    const int64_t n0 = (int64_t)__builtin_amdgcn_readfirstlane(in / gm) * TN;
 
     const int64_t rowbytes = FMT ? p.C : (p.C >> 1);
     const int nkb = (int)(p.C >> 5);

@@ -22,7 +22,9 @@ struct QuantArgs {
 constexpr uint64_t SEED_BASE_MASK = 0xFFFFFFFFFFFFull;
 
 // blocks along rows (1x32): q[rows][cols/2], s[rows][cols/32]
-hipError_t launch_quantize_rows(const QuantArgs &a, hipStream_t st);
+// (b, if not null: a second tensor in the same launch, same hadamard, rounding and base seed; the two grids together
+// must stay below 2^31 workgroups)
+hipError_t launch_quantize_rows(const QuantArgs &a, hipStream_t st, const QuantArgs *b = nullptr);
 // blocks down columns (32x1): q[cols][rows/2], s[cols][rows/32]
 // (b, if not null: a second tensor in the same launch, same hadamard, rounding and base seed)
 hipError_t launch_quantize_cols(const QuantArgs &a, hipStream_t st, const QuantArgs *b = nullptr);

@@ -38,15 +38,32 @@ __device__ __forceinline__ void encode_block(float (&v)[32], uint32_t sign_mask,
 
 // ---- row-wise (1x32) ---------------------------------------------------------------------
 // One lane per block.  nblocks = rows * (cols/32); block g is row g / bpr, column block g % bpr.
+// A launch may carry two tensors (the two operands of a GEMM): workgroups 0 .. groups-1 of the first job, then those of
+// the second.  Small tensors cost a launch and little else: a forward call of 256 x 512 x 512 went from 15.0 to 11.4 us
+// with one launch for X and W, one of 200 x 4096 x 4096 from 19.4 to 17.3 us.
+struct RowJob {
+    const uint16_t *x;
+    int64_t nblocks, bpr, ld;
+    uint8_t *q, *s;
+    uint32_t groups;
+    int dense;
+    RngKey key;
+};
+
 // STREAM: tensor larger than the last-level cache: non-temporal code stores.
 template <int HAD, int RND, int STREAM>
-__global__ __launch_bounds__(256) void quantize_rows_kernel(const uint16_t *__restrict__ x, int64_t nblocks,
-                                                            int64_t bpr, int64_t ld, int dense,
-                                                            uint32_t sign_mask, RngKey key,
-                                                            uint8_t *__restrict__ q, uint8_t *__restrict__ s)
+__global__ __launch_bounds__(256) void quantize_rows_kernel(const RowJob job0, const RowJob job1, uint32_t sign_mask)
 {
     constexpr int streaming = STREAM;
-    int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const bool second = blockIdx.x >= job0.groups;  // uniform: everything below is selected per workgroup
+    const uint16_t *__restrict__ x = second ? job1.x : job0.x;
+    const int64_t nblocks = second ? job1.nblocks : job0.nblocks, bpr = second ? job1.bpr : job0.bpr;
+    const int64_t ld = second ? job1.ld : job0.ld;
+    const int dense = second ? job1.dense : job0.dense;
+    uint8_t *__restrict__ q = second ? job1.q : job0.q;
+    uint8_t *__restrict__ s = second ? job1.s : job0.s;
+    const RngKey key = second ? job1.key : job0.key;
+    int64_t g = (int64_t)(blockIdx.x - (second ? job0.groups : 0u)) * 256 + threadIdx.x;
     if (g >= nblocks) return;
     const uint16_t *src;
     if (dense) {
@@ -306,18 +323,38 @@ __global__ __launch_bounds__(512) void quantize_cols_kernel(const TileJob job0, 
     }
 }
 
-template <int HAD>
-hipError_t launch_rows_h(const QuantArgs &a, hipStream_t st)
+RowJob make_row_job(const QuantArgs &a)
 {
-    const int64_t bpr = a.cols / 32, nblocks = a.rows * bpr;
-    const unsigned grid = (unsigned)((nblocks + 255) / 256);
-    const RngKey key = make_key(a.seed);
+    RowJob j;
+    j.x = a.x;
+    j.bpr = a.cols / 32;
+    j.nblocks = a.rows * j.bpr;
+    j.ld = a.ld;
+    j.q = a.q;
+    j.s = a.s;
+    j.groups = (uint32_t)((j.nblocks + 255) / 256);
+    j.dense = (a.ld == a.cols);
+    j.key = make_key(a.seed);
+    return j;
+}
+
+// b == nullptr: one tensor.  Otherwise both tensors in one launch (same rotation, rounding and base seed).
+template <int HAD>
+hipError_t launch_rows_h(const QuantArgs &a, const QuantArgs *b, hipStream_t st)
+{
+    const RowJob j0 = make_row_job(a);
+    RowJob j1 = j0;
+    j1.groups = 0;
+    if (b) j1 = make_row_job(*b);
+    const unsigned grid = j0.groups + j1.groups;
     const uint32_t sign_mask = sign_mask_of(a.seed);
-    const int dense = (a.ld == a.cols);
-    const int streaming = a.rows * a.cols * 2 > LLC_BYTES;
-#define MXFP4_LAUNCH_ROWS(R, S)                                                                              \
-    hipLaunchKernelGGL((quantize_rows_kernel<HAD, R, S>), dim3(grid), dim3(256), 0, st, a.x, nblocks, bpr, a.ld, \
-                       dense, sign_mask, key, a.q, a.s)
+    const bool streaming = a.rows * a.cols * 2 > LLC_BYTES;
+    if (b && streaming != (b->rows * b->cols * 2 > LLC_BYTES)) {  // the store policy is the launch's: one each
+        const hipError_t e = launch_rows_h<HAD>(a, nullptr, st);
+        return e == hipSuccess ? launch_rows_h<HAD>(*b, nullptr, st) : e;
+    }
+#define MXFP4_LAUNCH_ROWS(R, S) \
+    hipLaunchKernelGGL((quantize_rows_kernel<HAD, R, S>), dim3(grid), dim3(256), 0, st, j0, j1, sign_mask)
     if (a.rounding == RND_RNE) {
         if (streaming) MXFP4_LAUNCH_ROWS(RND_RNE, 1); else MXFP4_LAUNCH_ROWS(RND_RNE, 0);
     } else {
@@ -383,14 +420,14 @@ hipError_t launch_cols_mode(const QuantArgs &a, const QuantArgs *b, hipStream_t 
 
 }  // namespace
 
-hipError_t launch_quantize_rows(const QuantArgs &a, hipStream_t st)
+hipError_t launch_quantize_rows(const QuantArgs &a, hipStream_t st, const QuantArgs *b)
 {
     switch (a.hadamard) {
-        case HAD_NONE: return launch_rows_h<HAD_NONE>(a, st);
-        case HAD_DET: return launch_rows_h<HAD_DET>(a, st);
-        case HAD_RANDSIGN: return launch_rows_h<HAD_RANDSIGN>(a, st);
-        case HAD_RANDSIGN16: return launch_rows_h<HAD_RANDSIGN16>(a, st);
-        default: return launch_rows_h<HAD_DET16>(a, st);
+        case HAD_NONE: return launch_rows_h<HAD_NONE>(a, b, st);
+        case HAD_DET: return launch_rows_h<HAD_DET>(a, b, st);
+        case HAD_RANDSIGN: return launch_rows_h<HAD_RANDSIGN>(a, b, st);
+        case HAD_RANDSIGN16: return launch_rows_h<HAD_RANDSIGN16>(a, b, st);
+        default: return launch_rows_h<HAD_DET16>(a, b, st);
     }
 }
 
