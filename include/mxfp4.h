@@ -228,8 +228,10 @@ int mxfp4_gemm_pair(const void *a0_q, const void *a0_s, const void *b0_q, const 
  * Which kernels mxfp4_gemm_fmt cuts a product of this shape into on a device with `compute_units` compute
  * units (256 on MI355X), for operands and an output aligned as those calls demand: the tiled kernel of the
  * block-scaled FP4 GEMM (Sec. 2.1) on 256 x 256 tiles or, where those would leave compute units idle, on
- * 256 x 128 tiles, and a slower any-shape kernel for edge strips and for contraction lengths below 1024 or
- * not in whole 256s (MXFP8: 128s).  Host-only: touches no device.
+ * 256 x 128 tiles, and the kernels for ragged shapes for edge strips and for contraction lengths below 1024 or
+ * not in whole 256s (MXFP8: 128s).  A call whose product is too small for these blocks to fill the device (it is
+ * estimated to take longer block by block) runs as one block on the kernels for ragged shapes, with the same result.
+ * Host-only: touches no device.
  *   parts[6 * i ..] = kind, first row, rows, first column, columns of block i of the output, main tiles;
  *   kind: 0 any-shape, 1 tiled 256 x 256, 2 tiled 256 x 128, 3 one launch that runs `main tiles` tiles (whole
  *   rounds over the compute units) on 256 x 256 and the rest of the block, a last round at most half full, as

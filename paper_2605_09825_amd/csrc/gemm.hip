@@ -807,9 +807,9 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_pair_kernel(const TileGemm p
 //     beyond C/32 are 0 in LDS for both operands: every product under them is below 2^-254 * 2^24, which is 0 in fp32,
 //     so the last stage runs the same code as the others;
 //   * scale rows are C/32 bytes apart, at any alignment: they come through registers (16-byte loads, bytes at a row's
-//     ragged end) into LDS, 32 bytes per row (1024 elements of K) at a time, double-buffered.
-// FMT as in gemm_tile_body.  Built as 64 x 64 (4 stage buffers, 72 KiB of LDS, two workgroups per CU), 128 x 64 (2, 60 KiB)
-// and 128 x 256 tiles (8 waves, 2, 120 KiB); 128 x 128 tiles on 4 waves were never the fastest, 256 x 256 tiles on 8 waves
+//     ragged end) into LDS, 32 bytes per row (1024 elements of K) at a time.
+// FMT as in gemm_tile_body.  Built as 64 x 64 (4 stage buffers, 68 KiB of LDS, two workgroups per CU), 128 x 64 (3, 78 KiB,
+// two) and 128 x 256 tiles (8 waves, 3, 156 KiB; with two stage buffers 8192 x 6112 x 4064 took 185 us, with three 173); 128 x 128 tiles on 4 waves were never the fastest, 256 x 256 tiles on 8 waves
 // were slower for MXFP4 (210 against 156 us at 8192 x 6112 x 4064).
 // Measured, bf16 output, the kernel before / this one: MXFP4 8192 x 6112 x 4064 911 / 156 us (2.6 PFLOP/s), 16000 x 1000 x
 // 3008 237 / 43, 2080 x 4320 x 1440 66.7 / 22.4, 2048 x 3072 x 768 33.6 / 8.9, 200 x 4096 x 4096 31.2 / 9.4, 24 x 6144 x
@@ -819,8 +819,8 @@ struct EdgeTile {
     static constexpr int WAVES = 2 * NWN, TM = 64 * WM, TN = 32 * WN * NWN, ROWS = TM + TN;
     static constexpr int STAGE = ROWS * 128;          // bytes of codes per stage
     static constexpr int NL = ROWS / 8 / WAVES;              // direct-to-LDS loads per wave and stage
-    static constexpr int OFF_S = NBUF * STAGE, SBUF = ROWS * 32;
-    static constexpr int LDS = OFF_S + 2 * SBUF;
+    static constexpr int OFF_S = NBUF * STAGE;
+    static constexpr int LDS = OFF_S + ROWS * 32;
 };
 
 struct EdgeGemm {
@@ -828,12 +828,17 @@ struct EdgeGemm {
     int64_t Ra, Rb, C;
     void *out;
     int64_t ld;
-    int tiles_m, tiles_n, vec;  // vec: four consecutive outputs may be stored at once
+    int tiles_m, tiles_n;
+    int out_fp32, accumulate, vec;  // vec: four consecutive outputs may be stored at once
 };
 
-template <bool OUT_FP32, bool ACC, int FMT, int WM, int WN, int NWN, int NBUF>
-__global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm p)
+// A launch may carry two independent problems: workgroups 0 .. groups0-1 (a multiple of 8) work on p0, the others on p1.
+template <int FMT, int WM, int WN, int NWN, int NBUF>
+__global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm p0, const EdgeGemm p1, const uint32_t groups0)
 {
+    const bool second = blockIdx.x >= groups0;  // uniform
+    const EdgeGemm p = second ? p1 : p0;
+    const uint32_t bid = blockIdx.x - (second ? groups0 : 0u);
     using Tile = EdgeTile<WM, WN, NWN, NBUF>;
     constexpr int TM = Tile::TM, TN = Tile::TN, NL = Tile::NL, ROWS = Tile::ROWS, WAVES = Tile::WAVES;
     constexpr int NLA = TM / 8 / WAVES;  // loads of A among a wave's NL
@@ -846,8 +851,9 @@ __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm 
 
     // tile of this workgroup: each XCD (workgroup id mod 8) takes a contiguous run of the tile sequence, which walks
     // the grid in groups of GROUP_M tile rows (as the tiled kernel does)
-    const int T = p.tiles_m * p.tiles_n, xcd = blockIdx.x & 7, per = T >> 3, rem = T & 7;
-    const int L = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + (int)(blockIdx.x >> 3);
+    const int T = p.tiles_m * p.tiles_n, xcd = bid & 7, per = T >> 3, rem = T & 7;
+    if ((int)(bid >> 3) >= per + (xcd < rem ? 1 : 0)) return;  // (the grid is padded to whole rows of 8)
+    const int L = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + (int)(bid >> 3);
     const int span = GROUP_M * p.tiles_n, grp = L / span, first = grp * GROUP_M, in = L - grp * span;
     const int gm = p.tiles_m - first < GROUP_M ? p.tiles_m - first : GROUP_M;
     // (uniform, but the division ran in the vector unit: put them where the loads want their base)
@@ -870,10 +876,10 @@ __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm 
         const int64_t want = (int64_t)((n - (isb ? NLA : 0)) * WAVES + wave) * 8 + drr, last = R - 1 - r0;
         roff[n] = (uint32_t)((want < last ? want : last) * rowbytes);
     }
-    auto issue = [&](int s) {
+    auto issue = [&](int s, int to) {
         const uint32_t at = (uint32_t)s * 128u + (uint32_t)chunk, end = (uint32_t)rowbytes - 16u;
         const uint32_t koff = at < end ? at : end;
-        const uint32_t dst = lds0 + (uint32_t)(s % NBUF) * Tile::STAGE + (uint32_t)wave * 1024u;
+        const uint32_t dst = lds0 + (uint32_t)to * Tile::STAGE + (uint32_t)wave * 1024u;
 #pragma unroll
         for (int n = 0; n < NL; ++n) dma16(dst + n * (WAVES * 1024u), roff[n] + koff, n >= NLA ? bbase : abase);
     };
@@ -905,12 +911,12 @@ __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm 
         }
     };
     // 8-byte slot t (0..3) of a row sits at slot t ^ (row / 8 % 4): the fragment reads of 32 rows touch every bank once
-    auto write_scales = [&](int b) {
+    auto write_scales = [&]() {
 #pragma unroll
         for (int j = 0; j < NP; ++j) {
             const int idx = tid * NP + j, r = idx >> 1, sw = (r >> 3) & 3, t = (idx & 1) * 2;
             if (ROWS * 2 % (64 * WAVES) != 0 && r >= ROWS) break;  // (128 x 64 tile: 192 rows on 256 threads)
-            uint8_t *dst = smem + Tile::OFF_S + (b & 1) * Tile::SBUF + r * 32;
+            uint8_t *dst = smem + Tile::OFF_S + r * 32;
             *reinterpret_cast<uint2 *>(dst + ((t ^ sw) << 3)) = make_uint2(piece[j].x, piece[j].y);
             *reinterpret_cast<uint2 *>(dst + (((t + 1) ^ sw) << 3)) = make_uint2(piece[j].z, piece[j].w);
         }
@@ -925,8 +931,8 @@ __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm 
     for (int kk = 0; kk < 4; ++kk) foff[kk] = fl0 + (uint32_t)((((kk << 1) | fh) ^ fm) << 4);
     const uint32_t perm_sel = FMT ? (fh ? 0x03010301u : 0x02000200u) : (fh ? 0x07050301u : 0x06040200u);
     auto frag_scale = [&](int s, int row) {  // the lane's scale bytes of stage s, byte k = instruction K-step k
-        const int b = s / BATCH, slot = FMT ? (s & 7) >> 1 : s & 3;
-        const uint8_t *q = smem + Tile::OFF_S + (b & 1) * Tile::SBUF + row * 32 + ((slot ^ ((row >> 3) & 3)) << 3);
+        const int slot = FMT ? (s & 7) >> 1 : s & 3;
+        const uint8_t *q = smem + Tile::OFF_S + row * 32 + ((slot ^ ((row >> 3) & 3)) << 3);
         if (FMT) return (int)__builtin_amdgcn_perm(0u, *reinterpret_cast<const uint32_t *>(q + (s & 1) * 4), perm_sel);
         const uint2 w = *reinterpret_cast<const uint2 *>(q);
         return (int)__builtin_amdgcn_perm(w.y, w.x, perm_sel);
@@ -940,23 +946,27 @@ __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm 
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-    if (nstages > 0) {
-        load_scales(0);
+    int cur = 0;                // stage buffer of stage s
+    if (nstages > 0) load_scales(0);
 #pragma unroll
-        for (int s = 0; s < NBUF - 1; ++s)
-            if (s < nstages) issue(s);
-        write_scales(0);
-    }
+    for (int s = 0; s < NBUF - 1; ++s)
+        if (s < nstages) issue(s, s);
     for (int s = 0; s < nstages; ++s) {
         // stage s has landed (the loads of the stages after it may be out), everyone is done with stage s-1
-        if (NBUF > 2 && s + NBUF - 2 < nstages)
+        if (s + NBUF - 2 < nstages)
             asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NL * (NBUF - 2)) : "memory");
         else
             asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        const int b = s / BATCH, in_batch = s % BATCH;
-        if (in_batch == 0 && b + 1 < nbatches) load_scales(b + 1);
-        if (s + NBUF - 1 < nstages) issue(s + NBUF - 1);
-        const uint8_t *buf = smem + (s % NBUF) * Tile::STAGE;
+        const int b = s / BATCH;
+        if (s % BATCH == 0) {  // (the compiler waits for the bytes, and with them for all loads that are out)
+            write_scales();
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            if (b + 1 < nbatches) load_scales(b + 1);
+        }
+        const int free_buf = cur == 0 ? NBUF - 1 : cur - 1;
+        if (s + NBUF - 1 < nstages) issue(s + NBUF - 1, free_buf);
+        const uint8_t *buf = smem + cur * Tile::STAGE;
+        cur = cur == NBUF - 1 ? 0 : cur + 1;
         int sa[WM], sb[WN];
 #pragma unroll
         for (int i = 0; i < WM; ++i) sa[i] = frag_scale(s, wm * 32 * WM + 32 * i + fr);
@@ -998,7 +1008,6 @@ __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm 
         }
 #undef MXFP4_EDGE_STEP
 #undef MXFP8_EDGE_STEP
-        if (in_batch == BATCH - 1 && b + 1 < nbatches) write_scales(b + 1);
     }
 
     // epilogue: every wave transposes 32 rows at a time through its own slice of the stage buffers (row of 128 WN bytes,
@@ -1028,16 +1037,16 @@ __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm 
         const int64_t row = m0 + wm * 32 * WM + 32 * i + r;
         const v4f v = *reinterpret_cast<const v4f *>(epi + r * PITCH + ((ch ^ (r & (CHUNKS - 1))) << 4));
         if (row >= p.Ra) continue;
-        if (OUT_FP32) {
+        if (p.out_fp32) {
             float *o = reinterpret_cast<float *>(p.out) + row * p.ld + col;
             if (whole) {
                 v4f t = v;
-                if (ACC) t += *reinterpret_cast<const v4f *>(o);
+                if (p.accumulate) t += *reinterpret_cast<const v4f *>(o);
                 __builtin_nontemporal_store(t, reinterpret_cast<v4f *>(o));
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
-                    if (e < left) o[e] = ACC ? (o[e] + v[e]) : v[e];
+                    if (e < left) o[e] = p.accumulate ? (o[e] + v[e]) : v[e];
             }
         } else {
             uint16_t *o = reinterpret_cast<uint16_t *>(p.out) + row * p.ld + col;
@@ -1109,21 +1118,18 @@ static hipError_t launch_any_f(const GemmArgs &g, hipStream_t st)
 }
 
 template <int FMT, int WM, int WN, int NWN, int NBUF>
-static hipError_t launch_edge_f(const GemmArgs &g, hipStream_t st)
+static hipError_t launch_edge_f(const GemmArgs &g0, const GemmArgs *g1, hipStream_t st)
 {
     using Tile = EdgeTile<WM, WN, NWN, NBUF>;
-    const EdgeGemm p{g.aq, g.as, g.bq, g.bs, g.Ra, g.Rb, g.C, g.out, g.ld, (int)((g.Ra + Tile::TM - 1) / Tile::TM),
-                     (int)((g.Rb + Tile::TN - 1) / Tile::TN),
-                     (g.ld % 4) == 0 && (reinterpret_cast<uintptr_t>(g.out) % (g.out_fp32 ? 16 : 8)) == 0};
-    dim3 grid((unsigned)(p.tiles_m * p.tiles_n));
-    if (g.out_fp32) {
-        if (g.accumulate)
-            hipLaunchKernelGGL((gemm_edge_kernel<true, true, FMT, WM, WN, NWN, NBUF>), grid, dim3(64 * Tile::WAVES), 0, st, p);
-        else
-            hipLaunchKernelGGL((gemm_edge_kernel<true, false, FMT, WM, WN, NWN, NBUF>), grid, dim3(64 * Tile::WAVES), 0, st, p);
-    } else {
-        hipLaunchKernelGGL((gemm_edge_kernel<false, false, FMT, WM, WN, NWN, NBUF>), grid, dim3(64 * Tile::WAVES), 0, st, p);
-    }
+    auto args = [](const GemmArgs &g) {
+        return EdgeGemm{g.aq, g.as, g.bq, g.bs, g.Ra, g.Rb, g.C, g.out, g.ld, (int)((g.Ra + Tile::TM - 1) / Tile::TM),
+                        (int)((g.Rb + Tile::TN - 1) / Tile::TN), g.out_fp32, g.accumulate,
+                        (g.ld % 4) == 0 && (reinterpret_cast<uintptr_t>(g.out) % (g.out_fp32 ? 16 : 8)) == 0};
+    };
+    auto groups = [](const EdgeGemm &p) { return ((uint32_t)(p.tiles_m * p.tiles_n) + 7u) & ~7u; };
+    const EdgeGemm p0 = args(g0), p1 = args(g1 ? *g1 : g0);
+    const uint32_t n0 = groups(p0), n1 = g1 ? groups(p1) : 0u;
+    hipLaunchKernelGGL((gemm_edge_kernel<FMT, WM, WN, NWN, NBUF>), dim3(n0 + n1), dim3(64 * Tile::WAVES), 0, st, p0, p1, n0);
     return hipGetLastError();
 }
 
@@ -1133,28 +1139,43 @@ static hipError_t launch_edge_f(const GemmArgs &g, hipStream_t st)
 // C = 512 to 8000; they only rank the three tile shapes.  Where they matter: few tiles (200 x 4096 x 4096: 64 x 64 9.4,
 // 128 x 64 12.6, 128 x 256 25 us), a round just overfull (2080 x 4320 x 1440: 29.4, 22.4, 24.8 us), many tiles (8192 x
 // 28640 x 4064: 298, 208, 156 us for a fifth of it).
-static double edge_cost(const GemmArgs &g, int tm, int tn, int slots, double full, double fixed)
+static double edge_cost(const GemmArgs &g0, const GemmArgs *g1, int tm, int tn, int slots, double full, double fixed)
 {
-    const int64_t t = ((g.Ra + tm - 1) / tm) * ((g.Rb + tn - 1) / tn), left = t % slots;
-    const double kb = (double)(g.a_fmt ? g.C : g.C / 2) / 1000.0;
+    auto tiles = [&](const GemmArgs &g) { return ((g.Ra + tm - 1) / tm) * ((g.Rb + tn - 1) / tn); };
+    auto kbytes = [](const GemmArgs &g) { return (double)(g.a_fmt ? g.C : g.C / 2) / 1000.0; };
+    const int64_t t0 = tiles(g0), t1 = g1 ? tiles(*g1) : 0, t = t0 + t1, left = t % slots;
+    const double kb = ((double)t0 * kbytes(g0) + (g1 ? (double)t1 * kbytes(*g1) : 0.0)) / (double)t;
     double us = (double)(t / slots) * (full * kb + fixed);
     if (left) us += (slots > NUM_CUS && left <= NUM_CUS ? 0.5 : 1.0) * full * kb + fixed;
     return us;
 }
 
+// What gemm_edge_kernel takes: both operands of one format, lane offsets of 127 rows in 32 bits, tiles in a grid.
+static bool edge_eligible(const GemmArgs &g)
+{
+    return g.a_fmt == g.b_fmt && g.C < (int64_t(1) << 24) && g.Ra < (int64_t(1) << 31) &&
+           ((g.Ra + 63) / 64) * ((g.Rb + 63) / 64) < (int64_t(1) << 29);
+}
+
+// One product, or two of one format side by side, on the tile shape with the lowest estimate; *us: only the estimate.
+static hipError_t launch_edge(const GemmArgs &g0, const GemmArgs *g1, hipStream_t st, double *us = nullptr)
+{
+    const double small = edge_cost(g0, g1, 64, 64, 512, 6.4, 1.5), mid = edge_cost(g0, g1, 128, 64, 512, 9.3, 1.5),
+                 large = edge_cost(g0, g1, 128, 256, 256, 11.2, 3.0);
+    if (us) {
+        *us = large < mid ? (large < small ? large : small) : (mid < small ? mid : small);
+        return hipSuccess;
+    }
+    if (large <= mid && large <= small)
+        return g0.a_fmt ? launch_edge_f<1, 2, 2, 4, 3>(g0, g1, st) : launch_edge_f<0, 2, 2, 4, 3>(g0, g1, st);
+    if (mid <= small)
+        return g0.a_fmt ? launch_edge_f<1, 2, 1, 2, 3>(g0, g1, st) : launch_edge_f<0, 2, 1, 2, 3>(g0, g1, st);
+    return g0.a_fmt ? launch_edge_f<1, 1, 1, 2, 4>(g0, g1, st) : launch_edge_f<0, 1, 1, 2, 4>(g0, g1, st);
+}
+
 static hipError_t launch_any(const GemmArgs &g, hipStream_t st)
 {
-    // operands of one format: the ragged-shape kernel (lane offsets hold 127 rows in 32 bits, the grid the tiles)
-    const int64_t t64 = ((g.Ra + 63) / 64) * ((g.Rb + 63) / 64);
-    if (g.a_fmt == g.b_fmt && g.C < (int64_t(1) << 24) && g.Ra < (int64_t(1) << 31) && t64 < (int64_t(1) << 30)) {
-        const double small = edge_cost(g, 64, 64, 512, 6.4, 1.5), mid = edge_cost(g, 128, 64, 512, 9.3, 1.5),
-                     large = edge_cost(g, 128, 256, 256, 11.2, 3.0);
-        if (large <= mid && large <= small)
-            return g.a_fmt ? launch_edge_f<1, 2, 2, 4, 2>(g, st) : launch_edge_f<0, 2, 2, 4, 2>(g, st);
-        if (mid <= small)
-            return g.a_fmt ? launch_edge_f<1, 2, 1, 2, 2>(g, st) : launch_edge_f<0, 2, 1, 2, 2>(g, st);
-        return g.a_fmt ? launch_edge_f<1, 1, 1, 2, 4>(g, st) : launch_edge_f<0, 1, 1, 2, 4>(g, st);
-    }
+    if (edge_eligible(g)) return launch_edge(g, nullptr, st);
     if (g.a_fmt == 0) return g.b_fmt == 0 ? launch_any_f<0, 0>(g, st) : launch_any_f<0, 1>(g, st);
     return g.b_fmt == 0 ? launch_any_f<1, 0>(g, st) : launch_any_f<1, 1>(g, st);
 }
@@ -1256,9 +1277,50 @@ GemmPlan plan_gemm(const GemmArgs &g, int cus)
     return plan;
 }
 
+// Estimated microseconds of a plan, on the scale of edge_cost (a launch behind another costs 4 us): rounds of 256 x 256
+// tiles at 1.63 us (MXFP8: 1.9) per stage and 4.5 us per tile, of 256 x 128 tiles at 0.9 us and 3 us.
+static double plan_cost(const GemmArgs &g, const GemmPlan &plan, int cus)
+{
+    const double kb = (double)(g.a_fmt ? g.C : g.C / 2) / 1000.0;
+    const double wide = (g.a_fmt ? 14.8 : 12.7) * kb + 4.5, narrow = 7.0 * kb + 3.0;
+    auto rounds = [&](int64_t tiles) { return (double)((tiles + cus - 1) / cus); };
+    double us = 4.0 * (plan.n - 1);
+    for (int i = 0; i < plan.n; ++i) {
+        const GemmPart &p = plan.part[i];
+        const int64_t tiles = (p.rows / TILE) * (p.cols / TILE);
+        if (p.kind == GEMM_TILED_256) us += rounds(tiles) * wide;
+        else if (p.kind == GEMM_TILED_128) us += rounds((p.rows / TILE) * (p.cols / (TILE / 2))) * narrow;
+        else if (p.kind == GEMM_TILED_256_TAIL_128) us += rounds(p.main_tiles) * wide + narrow;
+        else {
+            double edge;
+            const GemmArgs h = sub_block(g, p.r0, p.rows, p.c0, p.cols);
+            if (!edge_eligible(h)) return 1e30;
+            (void)launch_edge(h, nullptr, nullptr, &edge);
+            us += edge;
+        }
+    }
+    return us;
+}
+
+// The plan, or the whole product on the ragged-shape kernel where that is estimated to take less: products with too few
+// 256 x 128 tiles for the chip (512 x 4096 x 4096: 16.8 us on 64 tiles, 13.1 us on 128 x 64 ones; in MXFP8, which has no narrow tile, 42.1 and 19.4) and small ones that the plan
+// cuts into several launches (300 x 520 x 1024: 15.5 us in three, 5.5 us in one).
+static bool edge_whole(const GemmArgs &g, const GemmPlan &plan, int cus, double *us)
+{
+    *us = plan_cost(g, plan, cus);
+    if (!edge_eligible(g)) return false;
+    double edge;
+    (void)launch_edge(g, nullptr, nullptr, &edge);
+    if (edge >= *us) return false;
+    *us = edge;
+    return true;
+}
+
 hipError_t launch_gemm(const GemmArgs &g, hipStream_t st)
 {
     const GemmPlan plan = plan_gemm(g, device_cus());
+    double us;
+    if (edge_whole(g, plan, device_cus(), &us)) return launch_edge(g, nullptr, st);
     for (int i = 0; i < plan.n; ++i) {
         const GemmPart &p = plan.part[i];
         const GemmArgs h = sub_block(g, p.r0, p.rows, p.c0, p.cols);
@@ -1318,6 +1380,17 @@ hipError_t launch_gemm_pair(const GemmArgs &g0, const GemmArgs &g1, hipStream_t 
 #undef MXFP4_PAIR
             return hipGetLastError();
         }
+    }
+    // Both in one launch of the ragged-shape kernel, the longer contraction first, where that is estimated to take less
+    // than one after the other: ragged widths, small layers (a step
+    // of 2048 x 3072 x 768: 50 -> 37 us with its two products in one launch).
+    if (!g0.accumulate && g0.a_fmt == g1.a_fmt && edge_eligible(g0) && edge_eligible(g1)) {
+        const int cus = device_cus();
+        double us0, us1, both;
+        edge_whole(g0, plan_gemm(g0, cus), cus, &us0);
+        edge_whole(g1, plan_gemm(g1, cus), cus, &us1);
+        (void)launch_edge(g0, &g1, nullptr, &both);
+        if (both < us0 + us1 + 4.0) return g1.C > g0.C ? launch_edge(g1, &g0, st) : launch_edge(g0, &g1, st);
     }
     hipError_t e = launch_gemm(g0, st);
     if (e != hipSuccess) return e;

@@ -31,3 +31,30 @@ def test_forward_operands_equal_the_single_quantiser_calls(shape, rnd):
     for o, t in zip(off, (xq, xs, wq, wsc)):
         assert torch.equal(ws[o:o + t.numel()], t.flatten())
     assert torch.equal(y, mx.mxfp4_gemm(xq, xs, wq, wsc, out_dtype=mx.OUT_BF16))
+
+
+# Dgrad and Wgrad in one launch: on each tile shape, ragged everywhere, of very different lengths, one of them in whole
+# tiles; MXFP8 as well; fp32 and bf16 dX, dW accumulated or not
+@pytest.mark.parametrize("shape", [(32, 32, 32), (64, 96, 160), (2048, 32, 64), (96, 2080, 1440), (2048, 768, 3072),
+                                   (1056, 2080, 4320)])
+@pytest.mark.parametrize("fmt", [mx.FMT_E2M1, mx.FMT_E4M3])
+@pytest.mark.parametrize("dx_dtype,accumulate", [(mx.OUT_BF16, True), (mx.OUT_FP32, False)])
+def test_backward_products_equal_the_single_gemm_calls(shape, fmt, dx_dtype, accumulate):
+    M, N, K = shape
+    print(f"[bwd products] M={M} N={N} K={K} fmt={fmt} dx={dx_dtype} accumulate={accumulate}", flush=True)
+    x, w, dy = tensor(M, K, 1.0, 1), tensor(N, K, 0.02, 2), tensor(M, N, 1e-3, 3)
+    cfg = mx.make_cfg(mx.HAD_DET, mx.RNE, 5, dx_dtype=dx_dtype, dw_accumulate=accumulate, dgrad_format=fmt,
+                      wgrad_format=fmt)
+    dw0 = torch.randn((N, K), device=DEV)
+    dx, dw, ws = mx.mxfp4_linear_bwd(dy, x, w, cfg, dw=dw0.clone())
+    off = mx.mxfp4_linear_workspace_layout(M, N, K, True, cfg)
+
+    def operand(i, R, C):
+        row = C if fmt == mx.FMT_E4M3 else C // 2
+        return (ws[off[i]:off[i] + R * row].view(R, row), ws[off[i + 1]:off[i + 1] + R * (C // 32)].view(R, C // 32))
+    (gq, gs), (wq, wsc), (tq, ts), (xq, xs) = operand(0, M, N), operand(2, K, N), operand(4, N, M), operand(6, K, M)
+    fmts = dict(a_format=fmt, b_format=fmt)
+    assert torch.equal(dx, mx.mxfp4_gemm(gq, gs, wq, wsc, out_dtype=dx_dtype, **fmts))
+    want = dw0.clone()
+    mx.mxfp4_gemm(tq, ts, xq, xs, out=want, out_dtype=mx.OUT_FP32, accumulate=accumulate, **fmts)
+    assert torch.equal(dw, want)
