@@ -811,9 +811,12 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_pair_kernel(const TileGemm p
 // FMT as in gemm_tile_body.  Built as 64 x 64 (4 stage buffers, 68 KiB of LDS, two workgroups per CU), 128 x 64 (3, 78 KiB,
 // two) and 128 x 256 tiles (8 waves, 3, 156 KiB; with two stage buffers 8192 x 6112 x 4064 took 185 us, with three 173); 128 x 128 tiles on 4 waves were never the fastest, 256 x 256 tiles on 8 waves
 // were slower for MXFP4 (210 against 156 us at 8192 x 6112 x 4064).
-// Measured, bf16 output, the kernel before / this one: MXFP4 8192 x 6112 x 4064 911 / 156 us (2.6 PFLOP/s), 16000 x 1000 x
-// 3008 237 / 43, 2080 x 4320 x 1440 66.7 / 22.4, 2048 x 3072 x 768 33.6 / 8.9, 200 x 4096 x 4096 31.2 / 9.4, 24 x 6144 x
-// 4096 23.5 / 8.9, 256 x 512 x 512 6.2 / 4.1; MXFP8 8192 x 6112 x 4064 1337 / 271, 200 x 4096 x 4096 45.2 / 13.4 us.
+// What bounds it now: at 8192 x 6144 x 4096 (139 us, 3.0 PFLOP/s, against 99 us of the tiled kernel) LDS traffic, 176 KiB
+// per 128 x 256 stage against 1024 clocks of matrix instructions; rows that are not whole cache lines apart cost another
+// 20 % (C = 4064: 170 us), because every 128-byte row piece then takes two line requests.
+// Measured, bf16 output, the kernel before / this one: MXFP4 8192 x 6144 x 4064 906 / 170 us, 16000 x 1000 x 3008 237 / 45,
+// 2080 x 4320 x 1440 67.6 / 23.2, 2048 x 3072 x 768 33.7 / 9.8, 200 x 4096 x 4096 31.2 / 9.4, 24 x 6144 x 4096 23.7 / 9.2,
+// 256 x 512 x 512 6.4 / 5.0; MXFP8 8192 x 6144 x 4064 1340 / 261, 200 x 4096 x 4096 45.2 / 13.0 us.
 template <int WM, int WN, int NWN, int NBUF>
 struct EdgeTile {
     static constexpr int WAVES = 2 * NWN, TM = 64 * WM, TN = 32 * WN * NWN, ROWS = TM + TN;
@@ -889,25 +892,56 @@ __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm 
     struct __attribute__((packed, aligned(1))) Piece { uint32_t v[4]; };
     uint4 piece[NP];
     auto load_scales = [&](int b) {
+        const uint8_t *base[NP];
+        int64_t at[NP], total[NP];
 #pragma unroll
         for (int j = 0; j < NP; ++j) {
             const int idx = tid * NP + j, r = idx >> 1;
             const bool isb = r >= TM;
-            const int64_t want = isb ? n0 + r - TM : m0 + r, last = (isb ? p.Rb : p.Ra) - 1;
-            const int o = b * 32 + (idx & 1) * 16, left = nkb - o;
-            const uint8_t *src = (isb ? p.bs : p.as) + (want < last ? want : last) * (int64_t)nkb;
-            if (left >= 16) {
-                const Piece t = *reinterpret_cast<const Piece *>(src + o);
-                piece[j] = make_uint4(t.v[0], t.v[1], t.v[2], t.v[3]);
-            } else {  // the ragged end of a row: zeros behind it
-                uint32_t w[4] = {0, 0, 0, 0};
+            const int64_t R = isb ? p.Rb : p.Ra, want = isb ? n0 + r - TM : m0 + r;
+            base[j] = isb ? p.bs : p.as;
+            at[j] = (want < R - 1 ? want : R - 1) * (int64_t)nkb + b * 32 + (idx & 1) * 16;
+            total[j] = R * (int64_t)nkb;
+        }
+        if (b * 32 + 32 <= nkb) {  // (the same for all: both loads are out before anything waits)
 #pragma unroll
-                for (int k = 0; k < 16; ++k) {
-                    const uint32_t byte = src[k < left ? o + k : nkb - 1];
-                    w[k >> 2] |= (k < left ? byte : 0u) << (8 * (k & 3));
-                }
-                piece[j] = make_uint4(w[0], w[1], w[2], w[3]);
+            for (int j = 0; j < NP; ++j) {
+                const Piece t = *reinterpret_cast<const Piece *>(base[j] + at[j]);
+                piece[j] = make_uint4(t.v[0], t.v[1], t.v[2], t.v[3]);
             }
+            return;
+        }
+        // The ragged end of a row, zeros behind it: 16 bytes from the row's place or from the end of the whole array,
+        // whichever comes first, shifted and masked.  (A load per byte took 5 us of every 128 x 256 tile: 64 requests an
+        // instruction.)
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            const int left = nkb - b * 32 - ((tid * NP + j) & 1) * 16;
+            const int64_t from = at[j] < total[j] - 16 ? at[j] : total[j] - 16;
+            uint64_t lo = 0, hi = 0;
+            if (left > 0 && from >= 0) {
+                const Piece t = *reinterpret_cast<const Piece *>(base[j] + from);
+                const int sh = 8 * (int)(at[j] - from);  // 0 .. 120: at least one byte of the row is among the 16
+                lo = t.v[0] | (uint64_t)t.v[1] << 32;
+                hi = t.v[2] | (uint64_t)t.v[3] << 32;
+                if (sh >= 64) {
+                    lo = hi >> (sh - 64);
+                    hi = 0;
+                } else if (sh > 0) {
+                    lo = lo >> sh | hi << (64 - sh);
+                    hi >>= sh;
+                }
+                if (left < 8) lo &= (uint64_t(1) << (8 * left)) - 1;
+                if (left <= 8) hi = 0;
+                else if (left < 16) hi &= (uint64_t(1) << (8 * (left - 8))) - 1;
+            } else if (left > 0) {  // an array of less than 16 bytes
+                for (int k = 0; k < left; ++k) {
+                    const uint64_t byte = base[j][at[j] + k];
+                    if (k < 8) lo |= byte << (8 * k);
+                    else hi |= byte << (8 * (k - 8));
+                }
+            }
+            piece[j] = make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
         }
     };
     // 8-byte slot t (0..3) of a row sits at slot t ^ (row / 8 % 4): the fragment reads of 32 rows touch every bank once
@@ -946,68 +980,105 @@ __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm 
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-    int cur = 0;                // stage buffer of stage s
-    if (nstages > 0) load_scales(0);
+    // One phase multiplies one set of fragments while the next set is read.  E2M1: a stage is four phases of one K-step;
+    // E4M3: two, of one K-step of two fragments.  The barrier stands before a stage's last phase: by then everyone holds
+    // the stage's last fragments, so its buffer is free, and the reads of the next stage's first fragments and scale
+    // bytes run under the last phase's matrix instructions.
+    constexpr int PH = FMT ? 2 : 4, NF = FMT ? 2 : 1;
+    v4i fa[2][WM][NF], fb[2][WN][NF];
+    int sa[WM], sb[WN], sa_next[WM], sb_next[WN];
+    int cur = 0;  // stage buffer of stage s
+    auto read_frags = [&](int buf, int ph, int set) {
+        const uint8_t *pa = smem + buf * Tile::STAGE + wm * WM * 4096;
+        const uint8_t *pb = smem + buf * Tile::STAGE + TM * 128 + wn * WN * 4096;
 #pragma unroll
-    for (int s = 0; s < NBUF - 1; ++s)
-        if (s < nstages) issue(s, s);
-    for (int s = 0; s < nstages; ++s) {
-        // stage s has landed (the loads of the stages after it may be out), everyone is done with stage s-1
-        if (s + NBUF - 2 < nstages)
-            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NL * (NBUF - 2)) : "memory");
-        else
-            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        const int b = s / BATCH;
-        if (s % BATCH == 0) {  // (the compiler waits for the bytes, and with them for all loads that are out)
-            write_scales();
-            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-            if (b + 1 < nbatches) load_scales(b + 1);
-        }
-        const int free_buf = cur == 0 ? NBUF - 1 : cur - 1;
-        if (s + NBUF - 1 < nstages) issue(s + NBUF - 1, free_buf);
-        const uint8_t *buf = smem + cur * Tile::STAGE;
-        cur = cur == NBUF - 1 ? 0 : cur + 1;
-        int sa[WM], sb[WN];
+        for (int h = 0; h < NF; ++h) {
 #pragma unroll
-        for (int i = 0; i < WM; ++i) sa[i] = frag_scale(s, wm * 32 * WM + 32 * i + fr);
+            for (int j = 0; j < WN; ++j)
+                fb[set][j][h] = *reinterpret_cast<const v4i *>(pb + j * 4096 + foff[ph * NF + h]);
 #pragma unroll
-        for (int j = 0; j < WN; ++j) sb[j] = frag_scale(s, TM + wn * 32 * WN + 32 * j + fr);
-        const uint8_t *pa = buf + wm * WM * 4096, *pb = buf + TM * 128 + wn * WN * 4096;
-        auto frag = [&](const uint8_t *q, int t, int kk) {
-            return *reinterpret_cast<const v4i *>(q + t * 4096 + foff[kk]);
-        };
-#define MXFP4_EDGE_STEP(KK)                                                                                          \
-        {                                                                                                            \
-            v4i fa[WM], fb[WN];                                                                                      \
-            _Pragma("unroll") for (int i = 0; i < WM; ++i) fa[i] = frag(pa, i, KK);                                  \
-            _Pragma("unroll") for (int j = 0; j < WN; ++j) fb[j] = frag(pb, j, KK);                                  \
-            _Pragma("unroll") for (int i = 0; i < WM; ++i) _Pragma("unroll") for (int j = 0; j < WN; ++j)            \
-                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(                                         \
-                    (v8i){fb[j].x, fb[j].y, fb[j].z, fb[j].w, 0, 0, 0, 0},                                           \
-                    (v8i){fa[i].x, fa[i].y, fa[i].z, fa[i].w, 0, 0, 0, 0}, acc[i][j], 4, 4, KK, sb[j], KK, sa[i]);   \
+            for (int i = 0; i < WM; ++i)
+                fa[set][i][h] = *reinterpret_cast<const v4i *>(pa + i * 4096 + foff[ph * NF + h]);
         }
-#define MXFP8_EDGE_STEP(KS)                                                                                          \
-        {                                                                                                            \
-            v4i fa[WM][2], fb[WN][2];                                                                                \
-            _Pragma("unroll") for (int h = 0; h < 2; ++h) {                                                          \
-                _Pragma("unroll") for (int i = 0; i < WM; ++i) fa[i][h] = frag(pa, i, 2 * KS + h);                   \
-                _Pragma("unroll") for (int j = 0; j < WN; ++j) fb[j][h] = frag(pb, j, 2 * KS + h);                   \
-            }                                                                                                        \
-            _Pragma("unroll") for (int i = 0; i < WM; ++i) _Pragma("unroll") for (int j = 0; j < WN; ++j)            \
-                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(                                         \
-                    (v8i){fb[j][0].x, fb[j][0].y, fb[j][0].z, fb[j][0].w, fb[j][1].x, fb[j][1].y, fb[j][1].z,        \
-                          fb[j][1].w},                                                                               \
-                    (v8i){fa[i][0].x, fa[i][0].y, fa[i][0].z, fa[i][0].w, fa[i][1].x, fa[i][1].y, fa[i][1].z,        \
-                          fa[i][1].w},                                                                               \
-                    acc[i][j], 0, 0, KS, sb[j], KS, sa[i]);                                                          \
+    };
+    auto read_scales = [&](int s) {
+#pragma unroll
+        for (int i = 0; i < WM; ++i) sa_next[i] = frag_scale(s, wm * 32 * WM + 32 * i + fr);
+#pragma unroll
+        for (int j = 0; j < WN; ++j) sb_next[j] = frag_scale(s, TM + wn * 32 * WN + 32 * j + fr);
+    };
+    auto take_scales = [&]() {
+#pragma unroll
+        for (int i = 0; i < WM; ++i) sa[i] = sa_next[i];
+#pragma unroll
+        for (int j = 0; j < WN; ++j) sb[j] = sb_next[j];
+    };
+    auto multiply = [&](auto phase) {  // (the byte of the scale register is an instruction field)
+        constexpr int ph = decltype(phase)::value, set = ph & 1;
+#pragma unroll
+        for (int i = 0; i < WM; ++i)
+#pragma unroll
+            for (int j = 0; j < WN; ++j) {
+                const v4i b0 = fb[set][j][0], a0 = fa[set][i][0];
+                v8i b8 = {b0.x, b0.y, b0.z, b0.w, 0, 0, 0, 0}, a8 = {a0.x, a0.y, a0.z, a0.w, 0, 0, 0, 0};
+                if constexpr (FMT) {
+                    const v4i b1 = fb[set][j][NF - 1], a1 = fa[set][i][NF - 1];
+                    b8 = (v8i){b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+                    a8 = (v8i){a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
+                }
+                acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(b8, a8, acc[i][j], FMT ? 0 : 4, FMT ? 0 : 4,
+                                                                            ph, sb[j], ph, sa[i]);
+            }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto all_but_last = [&]() {  // phases 0 .. PH-2 of the stage in buffer cur
+        read_frags(cur, 1, 1);
+        multiply(IC<0>{});
+        if constexpr (PH == 4) {
+            read_frags(cur, 2, 0);
+            multiply(IC<1>{});
+            read_frags(cur, 3, 1);
+            multiply(IC<2>{});
         }
-        if constexpr (FMT == 0) {
-            MXFP4_EDGE_STEP(0) MXFP4_EDGE_STEP(1) MXFP4_EDGE_STEP(2) MXFP4_EDGE_STEP(3)
-        } else {
-            MXFP8_EDGE_STEP(0) MXFP8_EDGE_STEP(1)
+    };
+    if (nstages > 0) {
+        load_scales(0);
+#pragma unroll
+        for (int s = 0; s < NBUF; ++s)
+            if (s < nstages) issue(s, s);
+        write_scales();  // (the compiler waits for the bytes, and with them for all loads that are out)
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (nbatches > 1) load_scales(1);
+        read_frags(0, 0, 0);
+        read_scales(0);
+        take_scales();
+        for (int s = 0; s + 1 < nstages; ++s) {
+            all_but_last();
+            // (a use of the sums: keeps the compiler from moving the matrix instructions behind the branches below)
+#pragma unroll
+            for (int i = 0; i < WM; ++i)
+#pragma unroll
+                for (int j = 0; j < WN; ++j) asm volatile("" : "+v"(acc[i][j]));
+            // stage s+1 has landed (the loads of the stages after it may be out), everyone is done with buffer cur
+            if (s + NBUF - 1 < nstages)
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NL * (NBUF - 2)) : "memory");
+            else
+                asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            if ((s + 1) % BATCH == 0) {
+                write_scales();
+                asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+                if ((s + 1) / BATCH + 1 < nbatches) load_scales((s + 1) / BATCH + 1);
+            }
+            const int next = cur == NBUF - 1 ? 0 : cur + 1;
+            read_frags(next, 0, 0);
+            read_scales(s + 1);
+            if (s + NBUF < nstages) issue(s + NBUF, cur);
+            multiply(IC<PH - 1>{});
+            take_scales();
+            cur = next;
         }
-#undef MXFP4_EDGE_STEP
-#undef MXFP8_EDGE_STEP
+        all_but_last();
+        multiply(IC<PH - 1>{});
     }
 
     // epilogue: every wave transposes 32 rows at a time through its own slice of the stage buffers (row of 128 WN bytes,
