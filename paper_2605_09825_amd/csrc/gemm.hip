@@ -23,6 +23,7 @@ namespace {
 
 typedef int v8i __attribute__((ext_vector_type(8)));
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef unsigned int v4u __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ uint16_t f32_to_bf16(float f)
@@ -203,7 +204,13 @@ using IC = std::integral_constant<int, V>;
 struct TileSrc {
     const uint8_t *a, *b, *as, *bs;
     int64_t m0, n0;
+    int dm, dn;  // RAG: rows and columns at the tile's start that belong to its neighbours
 };
+
+// 16 or 8 bytes at any address
+struct __attribute__((packed, aligned(1))) Bytes16 { uint32_t v[4]; };
+struct __attribute__((packed, aligned(1))) Bytes8 { uint32_t v[2]; };
+struct __attribute__((packed, aligned(1))) Bytes4 { uint32_t v; };
 
 // The whole tiled GEMM as seen by one workgroup: `wg` of `nwg` workgroups share the problem (the ids are
 // virtual: a launch may run two problems side by side on disjoint sets of CUs).  smem: the workgroup's
@@ -222,13 +229,19 @@ struct TileSrc {
 // HALVES (narrow tile only): tiles_n and the sequence are those of the 256 x 256 grid, and every one of those
 // tiles is worked on as two 256 x 128 tiles, left half then right half: the part-filled last round of a launch
 // that ran its whole rounds on 256 x 256 tiles.
-template <bool OUT_FP32, bool ACC, int FMT, int NJ, bool HALVES = false>
+// RAG: Ra >= 256 rows and Rb >= 256 columns in no whole tiles, C >= 1024 in no whole stages.  The last tile row and
+// column are moved back to end with the matrix and store only what is theirs; the last stage is moved back to end with
+// the row, and the scale bytes of the blocks it repeats are set to 0 in both operands (products below 2^-254 * 2^24: 0
+// in fp32).  Scale rows then start at any byte, so they go through registers: a 16-byte load per lane takes the place of
+// every direct-to-LDS scale load, and its bytes are written to LDS one stage later, right behind the barrier that has
+// waited for all loads anyway; hence the loads run two stages ahead, not one.
+template <bool OUT_FP32, bool ACC, int FMT, int NJ, bool HALVES = false, bool RAG = false>
 __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, const uint8_t *__restrict__ as,
                                                const uint8_t *__restrict__ bq, const uint8_t *__restrict__ bs,
                                                int64_t C, void *__restrict__ out, int64_t ld, int tiles_m,
                                                int tiles_n, const uint32_t wg, const uint32_t nwg,
                                                uint8_t *const smem, const uint32_t lds0, const int l_lo = 0,
-                                               const int l_hi = -1)
+                                               const int l_hi = -1, const int64_t Ra = 0, const int64_t Rb = 0)
 {
     static_assert(!HALVES || NJ == 2, "only the narrow tile works on halves of 256 x 256 tiles");
 
@@ -241,7 +254,7 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
     const int64_t rowbytes = FMT ? C : (C >> 1), nkb = C >> 5;
-    const int nstages = (int)(rowbytes / (STAGE_K / 2));  // >= 4 (E2M1) or >= 8 (E4M3): the host checks
+    const int nstages = (int)((rowbytes + (RAG ? STAGE_K / 2 - 1 : 0)) / (STAGE_K / 2));  // >= 4 (E2M1) or >= 8 (E4M3): the host checks
     constexpr int BATCH = FMT ? 8 : 4;   // stages per scale batch (32 scale bytes per row)
     constexpr int SC_STAGE = FMT ? 4 : 8;  // scale bytes per row and stage
 
@@ -266,6 +279,12 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
         TileSrc t;
         t.m0 = (int64_t)(first + in % gm) * TILE;
         t.n0 = HALVES ? (int64_t)(in / gm) * TILE + (Lr & 1) * TILE_N : (int64_t)(in / gm) * TILE_N;
+        t.dm = t.dn = 0;
+        if (RAG) {
+            const int64_t mx = Ra - TILE, nx = Rb - TILE_N;
+            if (t.m0 > mx) t.dm = (int)(t.m0 - mx), t.m0 = mx;
+            if (t.n0 > nx) t.dn = (int)(t.n0 - nx), t.n0 = nx;
+        }
         t.a = aq + (t.m0 + wave * 64) * rowbytes;
         t.b = bq + (t.n0 + wave * BROWS) * rowbytes;
         t.as = as + (t.m0 + wave * 64) * nkb;
@@ -296,7 +315,8 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
         constexpr int n = decltype(nc)::value, op = (n >> 2) & 1, g = (n >> 3) * 4 + (n & 3);
         static_assert(n < NLOADS, "no such load for this tile shape");
         constexpr bool setm0 = decltype(force)::value || (n & 3) == 0;
-        const int64_t koff = (int64_t)s * (STAGE_K / 2);
+        int64_t koff = (int64_t)s * (STAGE_K / 2);
+        if (RAG && koff > rowbytes - STAGE_K / 2) koff = rowbytes - STAGE_K / 2;
         dma16_run<(g - 4) * 1024, setm0>((op ? lds_wave_b : lds_wave_a) + buf * STAGE_BYTES + 4096, dvo[g],
                                          (op ? t.b : t.a) + koff);
     };
@@ -324,6 +344,19 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
         dma16(scales_dst(b, j, par), svoff, scales_src(t, b, j));
     };
 
+    // RAG: the same pieces through registers; sp[4] is the piece on its way in the steady state
+    uint4 sp[5];
+    auto rag_first = [&](int b) { return 32 * b < (int)nkb - 32 ? 32 * b : (int)nkb - 32; };  // first byte of a batch
+    auto rag_load = [&](const TileSrc &t, int b, int j) {
+        if (NJ == 2 && j == 3) j = 2;
+        const uint8_t *src = ((j >> 1) ? t.bs : t.as) + (int64_t)(j & 1) * 32 * nkb + rag_first(b);
+        const Bytes16 v = *reinterpret_cast<const Bytes16 *>(src + svoff);
+        return make_uint4(v.v[0], v.v[1], v.v[2], v.v[3]);
+    };
+    auto rag_store = [&](int b, int j, int par, const uint4 &v) {
+        *reinterpret_cast<uint4 *>(smem + (scales_dst(b, j, par) - lds0) + lane * 16) = v;
+    };
+
     // ---- fragment reads: per-lane offsets ---------------------------------------------------
     const int fr = lane & 31, fh = lane >> 5;
     const int fm = (fr & 7) ^ ((fr >> 3) & 1);
@@ -331,6 +364,13 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
     uint32_t foff[4];
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) foff[kk] = fl0 + (uint32_t)((((kk << 1) | fh) ^ fm) << 4);
+    // RAG: keeps the scale bytes of the blocks that the last stage does not repeat (byte k: block 2k + fh of the stage)
+    uint32_t last_mask = 0xFFFFFFFFu;
+    if (RAG) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (2 * k + fh < nstages * SC_STAGE - (int)nkb) last_mask &= ~(0xFFu << (8 * k));
+    }
     const uint32_t a_frag0 = OFF_A + wm * 16 * 1024, b_frag0 = OFF_B + wn * (NJ * 4) * 1024;
     const uint32_t sa_frag0 = OFF_SC + (wm * 128 + fr) * 32;
     const uint32_t sb_frag0 = OFF_SC + SC_OP_BYTES + (wn * (32 * NJ) + fr) * 32;
@@ -351,6 +391,18 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
     // The 8 scale bytes of stage s for fragment row f (0..7: A0,B0,A1,B1,...), raw.
     auto read_scale_one = [&](int s, int f, int par) {
         const int b = s / BATCH;
+        if constexpr (RAG) {
+            const int at = s * SC_STAGE < (int)nkb - SC_STAGE ? s * SC_STAGE : (int)nkb - SC_STAGE;
+            const uint8_t *p = smem + ((b ^ par) & 1) * SC_BUF_BYTES + (at - rag_first(b)) + (f >> 1) * 1024 +
+                               ((f & 1) ? sb_frag0 : sa_frag0);
+            if (FMT) {
+                sraw[f] = make_uint2(reinterpret_cast<const Bytes4 *>(p)->v, 0u);
+            } else {
+                const Bytes8 v = *reinterpret_cast<const Bytes8 *>(p);
+                sraw[f] = make_uint2(v.v[0], v.v[1]);
+            }
+            return;
+        }
         const uint8_t *p = smem + ((b ^ par) & 1) * SC_BUF_BYTES + (s - batch_first(b)) * SC_STAGE + (f >> 1) * 1024;
         if (FMT)
             sraw[f] = make_uint2(*reinterpret_cast<const uint32_t *>(p + ((f & 1) ? sb_frag0 : sa_frag0)), 0u);
@@ -457,11 +509,11 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
 #define MXFP4_K1(N)                                                                              \
         if (FMT && (N) < 8) read_one(buf, 3, 3, (N));                                            \
         if (MXFP4_FRAG_SLOT(N)) read_one(buf, 2, 0, MXFP4_FRAG_OF(N));                           \
-        if ((MODE == 0 || MODE == 3) && (N) == (NJ == 4 ? 9 : 4)) {                              \
+        if (!RAG && (MODE == 0 || MODE == 3) && (N) == (NJ == 4 ? 9 : 4)) {                              \
             sc_dst = scales_dst((s + 1) / BATCH + 1, (s + 1) & 3, par);                          \
             asm volatile("" : "+s"(sc_dst));                                                     \
         }                                                                                        \
-        if ((MODE == 0 || MODE == 3) && (N) == (NJ == 4 ? 12 : 6)) {                             \
+        if (!RAG && (MODE == 0 || MODE == 3) && (N) == (NJ == 4 ? 12 : 6)) {                             \
             sc_src = scales_src(cur, (s + 1) / BATCH + 1, (s + 1) & 3);                          \
             asm volatile("" : "+s"(sc_src));                                                     \
         }                                                                                        \
@@ -484,15 +536,22 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
         if (FMT && MODE != 2 && (N) < 8) read_one(buf ^ 1, 1, 1, (N));                            \
         if (MODE != 2 && NJ == 4 && (N) < 8) read_scale_one(s + 1, (N), par);                     \
         if (MODE != 2 && NJ == 2 && (N) < 6) read_scale_one(s + 1, MXFP4_FRAG_OF(N), par);        \
-        if ((MODE == 0 || MODE == 3) && (N) == 0) dma16(sc_dst, svoff, sc_src);                  \
+        if (!RAG && (MODE == 0 || MODE == 3) && (N) == 0) dma16(sc_dst, svoff, sc_src);          \
+        if (RAG && (MODE == 0 || MODE == 3) && (N) == 0) {                                       \
+            rag_store((s + 1) / BATCH + 1, (s + 1) & 3, par, sp[4]);                             \
+            sp[4] = rag_load(cur, (s + 2) / BATCH + 1, (s + 2) & 3);                             \
+        }                                                                                        \
+        if (RAG && MODE == 1 && (N) < 5) sp[(N) < 5 ? (N) : 0] = rag_load(nxt, (N) / 4, (N) & 3); \
+        if (RAG && MODE == 2 && (N) < 5) rag_store((N) / 4, (N) & 3, par_nxt, sp[(N) < 5 ? (N) : 0]); \
+        if (RAG && MODE == 2 && (N) == 5) sp[4] = rag_load(nxt, 1, 1);                           \
         if constexpr ((MODE == 0 || MODE == 3) && MXFP4_LOAD3_SLOT(N))                           \
             issue_load(cur, s + 2, buf, IC<MXFP4_LOAD3_OF(N)>{}, no_force{});                    \
         if (MODE != 2 && NJ == 4 && (N) == 13) __builtin_amdgcn_s_waitcnt(FMT ? 0xC07F : 0xC37F); /* lgkmcnt(0 / 3): see below */ \
         if (MODE != 2 && NJ == 2 && (N) == 6) __builtin_amdgcn_s_waitcnt(0xC07F); /* lgkmcnt(0) */ \
         if constexpr (MODE == 1 && MXFP4_LOAD3_SLOT(N))                                          \
             issue_load(nxt, 0, buf, IC<MXFP4_LOAD3_OF(N)>{}, force_m0{});                        \
-        if (MODE == 1 && !((N) & 1) && (N) < 2 * (NJ == 4 ? 4 : 3)) issue_scales(nxt, 0, (N) >> 1, par_nxt); \
-        if (MODE == 2 && (N) == 1) issue_scales(nxt, 1, 0, par_nxt);                             \
+        if (!RAG && MODE == 1 && !((N) & 1) && (N) < 2 * (NJ == 4 ? 4 : 3)) issue_scales(nxt, 0, (N) >> 1, par_nxt); \
+        if (!RAG && MODE == 2 && (N) == 1) issue_scales(nxt, 1, 0, par_nxt);                             \
         MXFP4_SLOT_MMA(3, N, false) MXFP4_PIN()
         MXFP4_16(MXFP4_K3)
 #undef MXFP4_K3
@@ -500,6 +559,13 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
         // in slot 13 -- for everything but the E2M1 schedule's three younger fragment reads -- tells the compiler
         // so, which otherwise puts a counter wait in front of every permute)
         if (MODE != 2) permute_scales();
+        if (RAG && MODE == 1) {  // (the scales of the last stage)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                sa_cur[i] &= (int)last_mask;
+                if (i < NJ) sb_cur[i] &= (int)last_mask;
+            }
+        }
     };
     using mode_main = std::integral_constant<int, 0>;
     using mode_penult = std::integral_constant<int, 1>;
@@ -512,9 +578,17 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
 #define MXFP4_FILL(N) if constexpr ((N) < NLOADS) issue_load(cur, 0, 0, IC<((N) < NLOADS ? (N) : 0)>{}, no_force{});
     MXFP4_16(MXFP4_FILL)
 #undef MXFP4_FILL
+    if constexpr (RAG) {
 #pragma unroll
-    for (int j = 0; j < (NJ == 4 ? 4 : 3); ++j) issue_scales(cur, 0, j, 0);
-    issue_scales(cur, 1, 0, 0);
+        for (int j = 0; j < 5; ++j) sp[j] = rag_load(cur, j / 4, j & 3);
+#pragma unroll
+        for (int j = 0; j < 5; ++j) rag_store(j / 4, j & 3, 0, sp[j]);
+        sp[4] = rag_load(cur, 1, 1);
+    } else {
+#pragma unroll
+        for (int j = 0; j < (NJ == 4 ? 4 : 3); ++j) issue_scales(cur, 0, j, 0);
+        issue_scales(cur, 1, 0, 0);
+    }
     int par = 0;
     const int b_last = (nstages - 1) / BATCH;
 
@@ -562,6 +636,23 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
         // conflict-free.
         uint8_t *epi = smem + ((((nstages - 1) & 1) ^ bp) ? STAGE_BYTES : 0) + wave * 16384;
         const int64_t row0 = cur.m0 + wm * 128, col0 = cur.n0 + wn * (32 * NJ);
+        // RAG: a tile that was moved back stores only what is its own: the others' pieces get an offset beyond the buffer,
+        // which the hardware drops (a branch per store costs the registers: the sums then no longer fit).  row, col: within
+        // the wave's sub-tile.
+        constexpr int ESIZE = OUT_FP32 ? 4 : 2;
+        __amdgpu_buffer_rsrc_t rsrc;
+        if constexpr (RAG)
+            rsrc = __builtin_amdgcn_make_buffer_rsrc(static_cast<uint8_t *>(out) + (row0 * ld + col0) * ESIZE, 0, 0x7FFFFFFF,
+                                                     0x00020000);
+        auto rag_offset = [&](int row, int col) {
+            const bool mine = wm * 128 + row >= cur.dm && wn * (32 * NJ) + col >= cur.dn;
+            return mine ? (row * (int)ld + col) * ESIZE : (int)0x80000000u;
+        };
+        auto rag_put = [&](int row, int col, auto v) {
+            const int off = rag_offset(row, col);
+            if constexpr (ACC) v += __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0));
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), rsrc, off, 0, 2 /* nt */);
+        };
         if constexpr (NJ == 2 && !OUT_FP32) {
             // Narrow tile, bf16: the wave's 128 rows x 64 columns are 16 KiB, one pass.  A row is 8 chunks of 16
             // bytes; chunk c of row r sits at position c ^ ((r >> 1) & 7): the 8-byte writes of a quarter wave
@@ -580,7 +671,8 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
                         if (qd == 3) __builtin_amdgcn_sched_barrier(0);
                     }
             // 8 lanes x 16 bytes = one 128-byte row segment; 8 rows per instruction
-            const int rl = lane >> 3, ch = lane & 7;
+            int rl = lane >> 3, ch = lane & 7;
+            if (RAG) asm volatile("" : "+v"(rl), "+v"(ch));  // (else every offset is worked out ahead of the tile loop)
             uint16_t *obase = reinterpret_cast<uint16_t *>(out) + (row0 + rl) * ld + col0 + ch * 8;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
@@ -593,7 +685,8 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
-                    __builtin_nontemporal_store(buf[u], reinterpret_cast<v4i *>(obase + (int64_t)((8 * h + u) * 8) * ld));
+                    if constexpr (RAG) rag_put((8 * h + u) * 8 + rl, ch * 8, buf[u]);
+                    else __builtin_nontemporal_store(buf[u], reinterpret_cast<v4i *>(obase + (int64_t)((8 * h + u) * 8) * ld));
                 __builtin_amdgcn_sched_barrier(0);
             }
         } else if constexpr (NJ == 2) {
@@ -615,7 +708,8 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
                             if (qd == 3) __builtin_amdgcn_sched_barrier(0);
                         }
                 // 16 lanes x 16 bytes = one 256-byte row segment; 4 rows per instruction
-                const int rl = lane >> 4, ch = lane & 15;
+                int rl = lane >> 4, ch = lane & 15;
+                if (RAG) asm volatile("" : "+v"(rl), "+v"(ch));  // (else every offset is worked out ahead of the tile loop)
                 float *obase = reinterpret_cast<float *>(out) + (row0 + pass * 64 + rl) * ld + col0 + ch * 4;
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
@@ -628,6 +722,10 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int u = 0; u < 8; ++u) {
+                        if constexpr (RAG) {
+                            rag_put(pass * 64 + (8 * h + u) * 4 + rl, ch * 4, buf[u]);
+                            continue;
+                        }
                         v4f *o = reinterpret_cast<v4f *>(obase + (int64_t)((8 * h + u) * 4) * ld);
                         v4f v = buf[u];
                         if (ACC) v += *o;
@@ -657,7 +755,8 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
                 // 16 lanes x 16 bytes = one 256-byte row segment; 4 rows per instruction.  Eight LDS reads are
                 // issued before the first store needs its data, so their latencies overlap; the row pointer
                 // is one per-lane base plus a scalar multiple of the leading dimension.
-                const int rl = lane >> 4, ch = lane & 15;
+                int rl = lane >> 4, ch = lane & 15;
+                if (RAG) asm volatile("" : "+v"(rl), "+v"(ch));  // (else every offset is worked out ahead of the tile loop)
                 uint32_t roff[4];  // LDS offset of this lane's chunk in rows rl, 4 + rl, 8 + rl, 12 + rl
 #pragma unroll
                 for (int k = 0; k < 4; ++k) roff[k] = (uint32_t)((4 * k + rl) * 256 + ((ch ^ (4 * k + rl)) << 4));
@@ -676,7 +775,8 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
                         const int r4 = (8 * h + u) * 4;
                         v4i v = buf[u];
                         if ((r4 >> 4) & 1) v = (v4i){v.z, v.w, v.x, v.y};
-                        __builtin_nontemporal_store(v, reinterpret_cast<v4i *>(obase + (int64_t)r4 * ld));
+                        if constexpr (RAG) rag_put(pass * 64 + r4 + rl, ch * 8, v);
+                        else __builtin_nontemporal_store(v, reinterpret_cast<v4i *>(obase + (int64_t)r4 * ld));
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -696,7 +796,8 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
                     }
                 // 32 lanes x 16 bytes = one 512-byte row segment; 2 rows per instruction; reads batched by
                 // eight as above
-                const int rl = lane >> 5, ch = lane & 31;
+                int rl = lane >> 5, ch = lane & 31;
+                if (RAG) asm volatile("" : "+v"(rl), "+v"(ch));  // (else every offset is worked out ahead of the tile loop)
                 float *obase = reinterpret_cast<float *>(out) + (row0 + pass * 32 + rl) * ld + col0 + ch * 4;
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
@@ -709,6 +810,10 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
                     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int u = 0; u < 8; ++u) {
+                        if constexpr (RAG) {
+                            rag_put(pass * 32 + (8 * h + u) * 2 + rl, ch * 4, buf[u]);
+                            continue;
+                        }
                         v4f *o = reinterpret_cast<v4f *>(obase + (int64_t)((8 * h + u) * 2) * ld);
                         v4f v = buf[u];
                         if (ACC) v += *o;
@@ -770,6 +875,26 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_tail_kernel(const TileGemm p
     __syncthreads();  // (every wave is done with the LDS of the first phase)
     gemm_tile_body<OUT_FP32, ACC, 0, 2, true>(p.aq, p.as, p.bq, p.bs, p.C, p.out, p.ld, p.tiles_m, p.tiles_n,
                                               blockIdx.x, gridDim.x, smem, lds0, t_main, p.tiles_m * p.tiles_n);
+}
+
+// Ragged sizes on the same tiles: t_main tiles of the sequence on 256 x 256, then (MXFP4) the rest in halves.  Measured,
+// bf16 output, against gemm_edge_kernel: 8192 x 6144 x 4064 173 / 116 us (3.5 PFLOP/s; MXFP8 252 / 189), 8192 x 28640 x
+// 4064 771 / 523, 4096 x 4096 x 4000 53 / 40; 4010 x 6144 x 4096 55 us, against 63 as a tiled interior and a strip.
+template <bool OUT_FP32, bool ACC, int FMT>
+__global__ __launch_bounds__(256, 1) void gemm_tile_rag_kernel(const TileGemm p, const int64_t Ra, const int64_t Rb,
+                                                               const int t_main)
+{
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[LDS_BYTES];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem;
+    gemm_tile_body<OUT_FP32, ACC, FMT, 4, false, true>(p.aq, p.as, p.bq, p.bs, p.C, p.out, p.ld, p.tiles_m, p.tiles_n,
+                                                       blockIdx.x, gridDim.x, smem, lds0, 0, t_main, Ra, Rb);
+    if constexpr (FMT == 0) {
+        if (t_main == p.tiles_m * p.tiles_n) return;
+        __syncthreads();  // (every wave is done with the LDS of the first phase)
+        gemm_tile_body<OUT_FP32, ACC, 0, 2, true, true>(p.aq, p.as, p.bq, p.bs, p.C, p.out, p.ld, p.tiles_m, p.tiles_n,
+                                                        blockIdx.x, gridDim.x, smem, lds0, t_main,
+                                                        p.tiles_m * p.tiles_n, Ra, Rb);
+    }
 }
 
 // Two independent GEMMs in one launch of 256 workgroups (Dgrad and Wgrad of one layer): on every XCD the
@@ -1232,7 +1357,7 @@ static bool edge_eligible(const GemmArgs &g)
 static hipError_t launch_edge(const GemmArgs &g0, const GemmArgs *g1, hipStream_t st, double *us = nullptr)
 {
     const double small = edge_cost(g0, g1, 64, 64, 512, 6.4, 1.5), mid = edge_cost(g0, g1, 128, 64, 512, 9.3, 1.5),
-                 large = edge_cost(g0, g1, 128, 256, 256, 11.2, 3.0);
+                 large = edge_cost(g0, g1, 128, 256, 256, 10.5, 3.5);
     if (us) {
         *us = large < mid ? (large < small ? large : small) : (mid < small ? mid : small);
         return hipSuccess;
@@ -1301,6 +1426,46 @@ static hipError_t launch_tiled_tail(const GemmArgs &g, int64_t main_tiles, hipSt
     return hipGetLastError();
 }
 
+// whole 256 x 256 tiles not asked for: see RAG at gemm_tile_body (128 output rows of ld elements in 31-bit offsets)
+static bool rag_eligible(const GemmArgs &g)
+{
+    return g.a_fmt == g.b_fmt && g.C >= 1024 && g.C < (int64_t(1) << 24) && g.Ra >= TILE && g.Rb >= TILE &&
+           (g.Rb % 8) == 0 && (g.ld % 8) == 0 && g.ld < (1 << 21) && ((g.Ra + TILE - 1) / TILE) * ((g.Rb + TILE - 1) / TILE) < (1 << 29);
+}
+
+// tiles of 256 x 256 of the launch, and how many of them run whole (the rule of plan_tiled)
+static void rag_tiles(const GemmArgs &g, int cus, int64_t *tiles, int64_t *whole)
+{
+    const int64_t T = ((g.Ra + TILE - 1) / TILE) * ((g.Rb + TILE - 1) / TILE), rem = T % cus;
+    *tiles = *whole = T;
+    if (g.a_fmt) return;
+    if (T < cus) *whole = 0;
+    else if (rem != 0 && 2 * rem <= cus && T / cus <= 4) *whole = T - rem;
+}
+
+static hipError_t launch_rag(const GemmArgs &g, hipStream_t st)
+{
+    int64_t tiles, whole;
+    const int cus = device_cus();
+    rag_tiles(g, cus, &tiles, &whole);
+    const TileGemm p{g.aq, g.as, g.bq, g.bs, g.C, g.out, g.ld, (int)((g.Ra + TILE - 1) / TILE),
+                     (int)((g.Rb + TILE - 1) / TILE)};
+    const dim3 grid((unsigned)cus);
+#define MXFP4_RAG(O, A, F) \
+    hipLaunchKernelGGL((gemm_tile_rag_kernel<O, A, F>), grid, dim3(256), 0, st, p, g.Ra, g.Rb, (int)whole)
+    if (g.a_fmt) {
+        if (!g.out_fp32) MXFP4_RAG(false, false, 1);
+        else if (g.accumulate) MXFP4_RAG(true, true, 1);
+        else MXFP4_RAG(true, false, 1);
+    } else {
+        if (!g.out_fp32) MXFP4_RAG(false, false, 0);
+        else if (g.accumulate) MXFP4_RAG(true, true, 0);
+        else MXFP4_RAG(true, false, 0);
+    }
+#undef MXFP4_RAG
+    return hipGetLastError();
+}
+
 // Which kernels a GEMM is cut into (host logic only: no device is touched; cus = compute units of the device).
 // Whole 256 x 256 tiles run on the tiled kernel, except where that would leave compute units idle (E2M1 operands):
 //   * fewer tiles than compute units: 256 x 128 tiles (twice as many);
@@ -1348,20 +1513,21 @@ GemmPlan plan_gemm(const GemmArgs &g, int cus)
     return plan;
 }
 
-// Estimated microseconds of a plan, on the scale of edge_cost (a launch behind another costs 4 us): rounds of 256 x 256
-// tiles at 1.63 us (MXFP8: 1.9) per stage and 4.5 us per tile, of 256 x 128 tiles at 0.9 us and 3 us.
+// Estimated microseconds, on the scale of edge_cost (a launch behind another costs 4 us).  A round of 256 x 256 tiles
+// takes 1.63 us (MXFP8: 1.9) per stage and 4.5 us, one of 256 x 128 tiles 0.9 us and 3 us.
+static double wide_round(const GemmArgs &g) { return (g.a_fmt ? 14.8 : 6.35) * (double)g.C / 1000.0 + 4.5; }
+static double narrow_round(const GemmArgs &g) { return 3.5 * (double)g.C / 1000.0 + 3.0; }
+static double rounds_of(int64_t tiles, int cus) { return (double)((tiles + cus - 1) / cus); }
+
 static double plan_cost(const GemmArgs &g, const GemmPlan &plan, int cus)
 {
-    const double kb = (double)(g.a_fmt ? g.C : g.C / 2) / 1000.0;
-    const double wide = (g.a_fmt ? 14.8 : 12.7) * kb + 4.5, narrow = 7.0 * kb + 3.0;
-    auto rounds = [&](int64_t tiles) { return (double)((tiles + cus - 1) / cus); };
     double us = 4.0 * (plan.n - 1);
     for (int i = 0; i < plan.n; ++i) {
         const GemmPart &p = plan.part[i];
         const int64_t tiles = (p.rows / TILE) * (p.cols / TILE);
-        if (p.kind == GEMM_TILED_256) us += rounds(tiles) * wide;
-        else if (p.kind == GEMM_TILED_128) us += rounds((p.rows / TILE) * (p.cols / (TILE / 2))) * narrow;
-        else if (p.kind == GEMM_TILED_256_TAIL_128) us += rounds(p.main_tiles) * wide + narrow;
+        if (p.kind == GEMM_TILED_256) us += rounds_of(tiles, cus) * wide_round(g);
+        else if (p.kind == GEMM_TILED_128) us += rounds_of((p.rows / TILE) * (p.cols / (TILE / 2)), cus) * narrow_round(g);
+        else if (p.kind == GEMM_TILED_256_TAIL_128) us += rounds_of(p.main_tiles, cus) * wide_round(g) + narrow_round(g);
         else {
             double edge;
             const GemmArgs h = sub_block(g, p.r0, p.rows, p.c0, p.cols);
@@ -1373,25 +1539,45 @@ static double plan_cost(const GemmArgs &g, const GemmPlan &plan, int cus)
     return us;
 }
 
-// The plan, or the whole product on the ragged-shape kernel where that is estimated to take less: products with too few
-// 256 x 128 tiles for the chip (512 x 4096 x 4096: 16.8 us on 64 tiles, 13.1 us on 128 x 64 ones; in MXFP8, which has no narrow tile, 42.1 and 19.4) and small ones that the plan
-// cuts into several launches (300 x 520 x 1024: 15.5 us in three, 5.5 us in one).
-static bool edge_whole(const GemmArgs &g, const GemmPlan &plan, int cus, double *us)
+// (rows that are not whole cache lines apart: every 128-byte piece is two line requests, of which the narrow tile has half
+// as many again per product)
+static double rag_cost(const GemmArgs &g, int cus)
 {
+    if (!rag_eligible(g)) return 1e30;
+    int64_t tiles, whole;
+    rag_tiles(g, cus, &tiles, &whole);
+    const bool split_lines = (g.a_fmt ? g.C : g.C / 2) % 128 != 0;
+    return rounds_of(whole, cus) * wide_round(g) * (split_lines ? 1.2 : 1.05) +
+           rounds_of(2 * (tiles - whole), cus) * narrow_round(g) * (split_lines ? 1.3 : 1.05) + 1.0;
+}
+
+// How a call runs: its plan, or the whole product as one block on the ragged-shape kernel or on the tiled kernel for
+// ragged sizes, whichever is estimated to take least.  The plan loses with too few 256 x 128 tiles for the chip (512 x 4096
+// x 4096: 16.8 us on 64 tiles, 11.6 us on 128 x 64 ones; in MXFP8, which has no narrow tile, 42.1 and 19.4), where it
+// cuts a small product into several launches (300 x 520 x 1024: 15.5 us in three, 5.5 us in one) and where strips beside a
+// large interior cost a launch and a poorly filled chip (4010 x 6144 x 4096: 63 us, 55 in one).
+enum GemmRoute { ROUTE_PLAN, ROUTE_EDGE, ROUTE_RAG };
+static GemmRoute choose_route(const GemmArgs &g, const GemmPlan &plan, int cus, double *us)
+{
+    GemmRoute route = ROUTE_PLAN;
     *us = plan_cost(g, plan, cus);
-    if (!edge_eligible(g)) return false;
-    double edge;
-    (void)launch_edge(g, nullptr, nullptr, &edge);
-    if (edge >= *us) return false;
-    *us = edge;
-    return true;
+    if (edge_eligible(g)) {
+        double edge;
+        (void)launch_edge(g, nullptr, nullptr, &edge);
+        if (edge < *us) *us = edge, route = ROUTE_EDGE;
+    }
+    const double rag = rag_cost(g, cus);
+    if (rag < *us) *us = rag, route = ROUTE_RAG;
+    return route;
 }
 
 hipError_t launch_gemm(const GemmArgs &g, hipStream_t st)
 {
     const GemmPlan plan = plan_gemm(g, device_cus());
     double us;
-    if (edge_whole(g, plan, device_cus(), &us)) return launch_edge(g, nullptr, st);
+    const GemmRoute route = choose_route(g, plan, device_cus(), &us);
+    if (route == ROUTE_EDGE) return launch_edge(g, nullptr, st);
+    if (route == ROUTE_RAG) return launch_rag(g, st);
     for (int i = 0; i < plan.n; ++i) {
         const GemmPart &p = plan.part[i];
         const GemmArgs h = sub_block(g, p.r0, p.rows, p.c0, p.cols);
@@ -1458,8 +1644,8 @@ hipError_t launch_gemm_pair(const GemmArgs &g0, const GemmArgs &g1, hipStream_t 
     if (!g0.accumulate && g0.a_fmt == g1.a_fmt && edge_eligible(g0) && edge_eligible(g1)) {
         const int cus = device_cus();
         double us0, us1, both;
-        edge_whole(g0, plan_gemm(g0, cus), cus, &us0);
-        edge_whole(g1, plan_gemm(g1, cus), cus, &us1);
+        (void)choose_route(g0, plan_gemm(g0, cus), cus, &us0);
+        (void)choose_route(g1, plan_gemm(g1, cus), cus, &us1);
         (void)launch_edge(g0, &g1, nullptr, &both);
         if (both < us0 + us1 + 4.0) return g1.C > g0.C ? launch_edge(g1, &g0, st) : launch_edge(g0, &g1, st);
     }

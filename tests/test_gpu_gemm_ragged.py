@@ -19,10 +19,14 @@ SMALL = [(1, 1, 32), (63, 65, 224), (64, 64, 256), (65, 127, 288), (129, 8, 96),
          (70, 66, 1056), (100, 136, 2016), (8, 24, 3232), (96, 64, 128), (96, 64, 160)]
 # enough tiles for 128 x 64 and for 128 x 256 ones: ragged on both sides
 LARGE = [(1000, 1700, 288), (1010, 1537, 1120), (2049, 1290, 2080), (2008, 3100, 736), (2001, 3075, 1056)]
+# enough of everything for the 256 x 256 tiles of the tiled kernel, moved back at the edges: halves of tiles only, a last
+# round in halves, several whole tiles per workgroup; C in whole blocks of 32, 64, 128 and 256, odd and even stage counts;
+# only the rows or only the contraction ragged
+TILED = [(2300, 3000, 2080), (4200, 4104, 1056), (4900, 4904, 1120), (4352, 4352, 1408), (4300, 4352, 1280)]
 
 
 @pytest.mark.parametrize("fmt", [0, 1])
-@pytest.mark.parametrize("shape", SMALL + LARGE)
+@pytest.mark.parametrize("shape", SMALL + LARGE + TILED)
 def test_every_output_once_and_nothing_outside(shape, fmt):
     Ra, Rb, C = shape
     print(f"[ragged] Ra={Ra} Rb={Rb} C={C} fmt={fmt}", flush=True)
@@ -51,7 +55,7 @@ def test_every_output_once_and_nothing_outside(shape, fmt):
     assert torch.equal(results[0], results[1])
 
 
-@pytest.mark.parametrize("shape", [(70, 66, 1056), (2001, 3075, 1056)])
+@pytest.mark.parametrize("shape", [(70, 66, 1056), (2001, 3075, 1056), (4200, 4104, 1056)])
 def test_scale_byte_ff_in_the_ragged_last_block_marks_its_row_only(shape):
     Ra, Rb, C = shape
     rng = np.random.default_rng(5)
