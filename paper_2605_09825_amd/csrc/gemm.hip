@@ -1353,25 +1353,30 @@ static bool edge_eligible(const GemmArgs &g)
            ((g.Ra + 63) / 64) * ((g.Rb + 63) / 64) < (int64_t(1) << 29);
 }
 
-// One product, or two of one format side by side, on the tile shape with the lowest estimate; *us: only the estimate.
-static hipError_t launch_edge(const GemmArgs &g0, const GemmArgs *g1, hipStream_t st, double *us = nullptr)
+// The tile shape with the lowest estimate for one product, or two of one format side by side.
+struct EdgeChoice {
+    int tile;  // 0: 64 x 64, 1: 128 x 64, 2: 128 x 256
+    double us;
+};
+static EdgeChoice choose_edge(const GemmArgs &g0, const GemmArgs *g1 = nullptr)
 {
-    const double small = edge_cost(g0, g1, 64, 64, 512, 6.4, 1.5), mid = edge_cost(g0, g1, 128, 64, 512, 9.3, 1.5),
-                 large = edge_cost(g0, g1, 128, 256, 256, 10.5, 3.5);
-    if (us) {
-        *us = large < mid ? (large < small ? large : small) : (mid < small ? mid : small);
-        return hipSuccess;
-    }
-    if (large <= mid && large <= small)
-        return g0.a_fmt ? launch_edge_f<1, 2, 2, 4, 3>(g0, g1, st) : launch_edge_f<0, 2, 2, 4, 3>(g0, g1, st);
-    if (mid <= small)
-        return g0.a_fmt ? launch_edge_f<1, 2, 1, 2, 3>(g0, g1, st) : launch_edge_f<0, 2, 1, 2, 3>(g0, g1, st);
+    EdgeChoice best{0, edge_cost(g0, g1, 64, 64, 512, 6.4, 1.5)};
+    const double mid = edge_cost(g0, g1, 128, 64, 512, 9.3, 1.5), large = edge_cost(g0, g1, 128, 256, 256, 10.5, 3.5);
+    if (mid <= best.us) best = EdgeChoice{1, mid};
+    if (large <= best.us) best = EdgeChoice{2, large};
+    return best;
+}
+
+static hipError_t launch_edge(const GemmArgs &g0, const GemmArgs *g1, int tile, hipStream_t st)
+{
+    if (tile == 2) return g0.a_fmt ? launch_edge_f<1, 2, 2, 4, 3>(g0, g1, st) : launch_edge_f<0, 2, 2, 4, 3>(g0, g1, st);
+    if (tile == 1) return g0.a_fmt ? launch_edge_f<1, 2, 1, 2, 3>(g0, g1, st) : launch_edge_f<0, 2, 1, 2, 3>(g0, g1, st);
     return g0.a_fmt ? launch_edge_f<1, 1, 1, 2, 4>(g0, g1, st) : launch_edge_f<0, 1, 1, 2, 4>(g0, g1, st);
 }
 
 static hipError_t launch_any(const GemmArgs &g, hipStream_t st)
 {
-    if (edge_eligible(g)) return launch_edge(g, nullptr, st);
+    if (edge_eligible(g)) return launch_edge(g, nullptr, choose_edge(g).tile, st);
     if (g.a_fmt == 0) return g.b_fmt == 0 ? launch_any_f<0, 0>(g, st) : launch_any_f<0, 1>(g, st);
     return g.b_fmt == 0 ? launch_any_f<1, 0>(g, st) : launch_any_f<1, 1>(g, st);
 }
@@ -1443,10 +1448,9 @@ static void rag_tiles(const GemmArgs &g, int cus, int64_t *tiles, int64_t *whole
     else if (rem != 0 && 2 * rem <= cus && T / cus <= 4) *whole = T - rem;
 }
 
-static hipError_t launch_rag(const GemmArgs &g, hipStream_t st)
+static hipError_t launch_rag(const GemmArgs &g, int cus, hipStream_t st)
 {
     int64_t tiles, whole;
-    const int cus = device_cus();
     rag_tiles(g, cus, &tiles, &whole);
     const TileGemm p{g.aq, g.as, g.bq, g.bs, g.C, g.out, g.ld, (int)((g.Ra + TILE - 1) / TILE),
                      (int)((g.Rb + TILE - 1) / TILE)};
@@ -1529,11 +1533,9 @@ static double plan_cost(const GemmArgs &g, const GemmPlan &plan, int cus)
         else if (p.kind == GEMM_TILED_128) us += rounds_of((p.rows / TILE) * (p.cols / (TILE / 2)), cus) * narrow_round(g);
         else if (p.kind == GEMM_TILED_256_TAIL_128) us += rounds_of(p.main_tiles, cus) * wide_round(g) + narrow_round(g);
         else {
-            double edge;
             const GemmArgs h = sub_block(g, p.r0, p.rows, p.c0, p.cols);
             if (!edge_eligible(h)) return 1e30;
-            (void)launch_edge(h, nullptr, nullptr, &edge);
-            us += edge;
+            us += choose_edge(h).us;
         }
     }
     return us;
@@ -1557,27 +1559,34 @@ static double rag_cost(const GemmArgs &g, int cus)
 // cuts a small product into several launches (300 x 520 x 1024: 15.5 us in three, 5.5 us in one) and where strips beside a
 // large interior cost a launch and a poorly filled chip (4010 x 6144 x 4096: 63 us, 55 in one).
 enum GemmRoute { ROUTE_PLAN, ROUTE_EDGE, ROUTE_RAG };
-static GemmRoute choose_route(const GemmArgs &g, const GemmPlan &plan, int cus, double *us)
+struct GemmChoice {
+    GemmRoute route;
+    int tile;  // of ROUTE_EDGE
+    double us;
+};
+static GemmChoice choose_route(const GemmArgs &g, const GemmPlan &plan, int cus)
 {
-    GemmRoute route = ROUTE_PLAN;
-    *us = plan_cost(g, plan, cus);
+    GemmChoice c{ROUTE_PLAN, 0, 1e30};
     if (edge_eligible(g)) {
-        double edge;
-        (void)launch_edge(g, nullptr, nullptr, &edge);
-        if (edge < *us) *us = edge, route = ROUTE_EDGE;
+        const EdgeChoice edge = choose_edge(g);
+        c = GemmChoice{ROUTE_EDGE, edge.tile, edge.us};
+    }
+    if (c.route != ROUTE_EDGE || plan.n != 1 || plan.part[0].kind != GEMM_ANY) {
+        const double us = plan_cost(g, plan, cus);
+        if (us <= c.us) c = GemmChoice{ROUTE_PLAN, 0, us};
     }
     const double rag = rag_cost(g, cus);
-    if (rag < *us) *us = rag, route = ROUTE_RAG;
-    return route;
+    if (rag < c.us) c = GemmChoice{ROUTE_RAG, 0, rag};
+    return c;
 }
 
 hipError_t launch_gemm(const GemmArgs &g, hipStream_t st)
 {
-    const GemmPlan plan = plan_gemm(g, device_cus());
-    double us;
-    const GemmRoute route = choose_route(g, plan, device_cus(), &us);
-    if (route == ROUTE_EDGE) return launch_edge(g, nullptr, st);
-    if (route == ROUTE_RAG) return launch_rag(g, st);
+    const int cus = device_cus();
+    const GemmPlan plan = plan_gemm(g, cus);
+    const GemmChoice choice = choose_route(g, plan, cus);
+    if (choice.route == ROUTE_EDGE) return launch_edge(g, nullptr, choice.tile, st);
+    if (choice.route == ROUTE_RAG) return launch_rag(g, cus, st);
     for (int i = 0; i < plan.n; ++i) {
         const GemmPart &p = plan.part[i];
         const GemmArgs h = sub_block(g, p.r0, p.rows, p.c0, p.cols);
@@ -1643,11 +1652,9 @@ hipError_t launch_gemm_pair(const GemmArgs &g0, const GemmArgs &g1, hipStream_t 
     // of 2048 x 3072 x 768: 50 -> 37 us with its two products in one launch).
     if (!g0.accumulate && g0.a_fmt == g1.a_fmt && edge_eligible(g0) && edge_eligible(g1)) {
         const int cus = device_cus();
-        double us0, us1, both;
-        (void)choose_route(g0, plan_gemm(g0, cus), cus, &us0);
-        (void)choose_route(g1, plan_gemm(g1, cus), cus, &us1);
-        (void)launch_edge(g0, &g1, nullptr, &both);
-        if (both < us0 + us1 + 4.0) return g1.C > g0.C ? launch_edge(g1, &g0, st) : launch_edge(g0, &g1, st);
+        const EdgeChoice both = choose_edge(g0, &g1);
+        if (both.us < choose_route(g0, plan_gemm(g0, cus), cus).us + choose_route(g1, plan_gemm(g1, cus), cus).us + 4.0)
+            return g1.C > g0.C ? launch_edge(g1, &g0, both.tile, st) : launch_edge(g0, &g1, both.tile, st);
     }
     hipError_t e = launch_gemm(g0, st);
     if (e != hipSuccess) return e;
