@@ -877,6 +877,29 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_tail_kernel(const TileGemm p
                                               blockIdx.x, gridDim.x, smem, lds0, t_main, p.tiles_m * p.tiles_n);
 }
 
+// Two independent products of which one (pn) has at most one 256 x 128 tile for each of some compute units and the other
+// (pw) many 256 x 256 ones (Wgrad and Dgrad of a k or v projection): on every XCD the first n1 of the 32 workgroups take
+// one tile of pn each and then walk tiles 0 .. cut-1 of pw, the others walk the rest of pw.  One after the other, half the
+// chip idled under pn: the step of an 8B
+// k projection (Dgrad 8192 x 4096 x 1024, Wgrad 1024 x 4096 x 8192) went from 114.1 to 104.9 us.
+template <bool OUTN, bool ACCN, bool OUTW, bool ACCW>
+__global__ __launch_bounds__(256, 1) void gemm_tile_mix_kernel(const TileGemm pn, const TileGemm pw, const int n1,
+                                                               const int cut)
+{
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[LDS_BYTES];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem;
+    const int xcd = blockIdx.x & 7, lw = blockIdx.x >> 3;
+    const bool first = lw < n1;
+    if (first) {
+        gemm_tile_body<OUTN, ACCN, 0, 2>(pn.aq, pn.as, pn.bq, pn.bs, pn.C, pn.out, pn.ld, pn.tiles_m, pn.tiles_n,
+                                         lw * 8 + xcd, (uint32_t)n1 * 8, smem, lds0);
+        __syncthreads();  // (every wave is done with the LDS of the first product)
+    }
+    gemm_tile_body<OUTW, ACCW, 0, 4>(pw.aq, pw.as, pw.bq, pw.bs, pw.C, pw.out, pw.ld, pw.tiles_m, pw.tiles_n,
+                                     (first ? lw : lw - n1) * 8 + xcd, (uint32_t)(first ? n1 : 32 - n1) * 8, smem, lds0,
+                                     first ? 0 : cut, first ? cut : pw.tiles_m * pw.tiles_n);
+}
+
 // Ragged sizes on the same tiles: t_main tiles of the sequence on 256 x 256, then (MXFP4) the rest in halves.  Measured,
 // bf16 output, against gemm_edge_kernel: 8192 x 6144 x 4064 173 / 116 us (3.5 PFLOP/s; MXFP8 252 / 189), 8192 x 28640 x
 // 4064 771 / 523, 4096 x 4096 x 4000 53 / 40; 4010 x 6144 x 4096 55 us, against 63 as a tiled interior and a strip.
@@ -1604,6 +1627,48 @@ hipError_t launch_gemm(const GemmArgs &g, hipStream_t st)
     return hipSuccess;
 }
 
+// How gn (narrow tiles first) and gw share a launch of gemm_tile_mix_kernel: the number of rounds of gw that the
+// workgroups with a tile of gn add is the one with the lowest estimate.
+struct MixChoice {
+    int n1, cut;
+    double us;
+};
+static MixChoice choose_mix(const GemmArgs &gn, const GemmArgs &gw, int cus)
+{
+    MixChoice best{0, 0, 1e30};
+    if (cus != NUM_CUS || gn.a_fmt || gw.a_fmt || !tile_eligible(gn, TILE / 2) || !tile_eligible(gw)) return best;
+    const int64_t tn = (gn.Ra / TILE) * (gn.Rb / (TILE / 2)), tw = (gw.Ra / TILE) * (gw.Rb / TILE);
+    if (tn > NUM_CUS - 8) return best;
+    const int n1 = (int)((tn + 7) / 8), with = 8 * n1, without = NUM_CUS - with;
+    for (int extra = 0; extra < 8; ++extra) {
+        const int64_t cut = (int64_t)extra * with < tw ? (int64_t)extra * with : tw;
+        const double a = narrow_round(gn) + extra * wide_round(gw), b = rounds_of(tw - cut, without) * wide_round(gw);
+        const double us = a > b ? a : b;
+        if (us < best.us) best = MixChoice{n1, (int)cut, us};
+        if (cut == tw) break;
+    }
+    return best;
+}
+
+static hipError_t launch_mix(const GemmArgs &gn, const GemmArgs &gw, const MixChoice &c, hipStream_t st)
+{
+    const TileGemm pn = tile_args(gn, TILE / 2), pw = tile_args(gw);
+#define MXFP4_MIX(ON, AN, OW, AW) \
+    hipLaunchKernelGGL((gemm_tile_mix_kernel<ON, AN, OW, AW>), dim3(NUM_CUS), dim3(256), 0, st, pn, pw, c.n1, c.cut)
+    // (one of the two, problem 0 of the pair, never accumulates)
+    if (gn.accumulate) {
+        if (gw.out_fp32) MXFP4_MIX(true, true, true, false); else MXFP4_MIX(true, true, false, false);
+    } else if (gw.accumulate) {
+        if (gn.out_fp32) MXFP4_MIX(true, false, true, true); else MXFP4_MIX(false, false, true, true);
+    } else if (gn.out_fp32) {
+        if (gw.out_fp32) MXFP4_MIX(true, false, true, false); else MXFP4_MIX(true, false, false, false);
+    } else {
+        if (gw.out_fp32) MXFP4_MIX(false, false, true, false); else MXFP4_MIX(false, false, false, false);
+    }
+#undef MXFP4_MIX
+    return hipGetLastError();
+}
+
 // g0 (no accumulation) and g1 on the same stream, no dependence between them.  Side by side in one launch
 // when both fit the tiled kernel and together fill the chip; otherwise one after the other.
 hipError_t launch_gemm_pair(const GemmArgs &g0, const GemmArgs &g1, hipStream_t st)
@@ -1647,13 +1712,17 @@ hipError_t launch_gemm_pair(const GemmArgs &g0, const GemmArgs &g1, hipStream_t 
             return hipGetLastError();
         }
     }
-    // Both in one launch of the ragged-shape kernel, the longer contraction first, where that is estimated to take less
-    // than one after the other: ragged widths, small layers (a step
-    // of 2048 x 3072 x 768: 50 -> 37 us with its two products in one launch).
+    // Otherwise by estimate: one after the other, few narrow tiles beside many wide ones, or both on the ragged-shape
+    // kernel, the longer contraction first (ragged widths, small layers: a step of 2048 x 3072 x 768 went from 50 to 37 us).
     if (!g0.accumulate && g0.a_fmt == g1.a_fmt && edge_eligible(g0) && edge_eligible(g1)) {
         const int cus = device_cus();
         const EdgeChoice both = choose_edge(g0, &g1);
-        if (both.us < choose_route(g0, plan_gemm(g0, cus), cus).us + choose_route(g1, plan_gemm(g1, cus), cus).us + 4.0)
+        const MixChoice mix1 = choose_mix(g1, g0, cus), mix0 = choose_mix(g0, g1, cus);
+        const double mix = mix1.us < mix0.us ? mix1.us : mix0.us;
+        const double apart = choose_route(g0, plan_gemm(g0, cus), cus).us + choose_route(g1, plan_gemm(g1, cus), cus).us + 4.0;
+        if (mix < apart && mix < both.us)
+            return mix1.us <= mix0.us ? launch_mix(g1, g0, mix1, st) : launch_mix(g0, g1, mix0, st);
+        if (both.us < apart)
             return g1.C > g0.C ? launch_edge(g1, &g0, both.tile, st) : launch_edge(g0, &g1, both.tile, st);
     }
     hipError_t e = launch_gemm(g0, st);

@@ -34,9 +34,11 @@ def test_forward_operands_equal_the_single_quantiser_calls(shape, rnd):
 
 
 # Dgrad and Wgrad in one launch: on each tile shape, ragged everywhere, of very different lengths, one of them in whole
-# tiles; MXFP8 as well; fp32 and bf16 dX, dW accumulated or not
+# tiles; few narrow tiles of the one beside the other (Wgrad in 128 of them, all of Dgrad beside it or part of it behind
+# it; Dgrad in 128; in 32); MXFP8 as well; fp32 and bf16 dX, dW accumulated or not
 @pytest.mark.parametrize("shape", [(32, 32, 32), (64, 96, 160), (2048, 32, 64), (96, 2080, 1440), (2048, 768, 3072),
-                                   (1056, 2080, 4320)])
+                                   (1056, 2080, 4320), (4096, 1024, 4096), (8192, 1024, 4096), (1024, 4096, 4096),
+                                   (8192, 1024, 1024)])
 @pytest.mark.parametrize("fmt", [mx.FMT_E2M1, mx.FMT_E4M3])
 @pytest.mark.parametrize("dx_dtype,accumulate", [(mx.OUT_BF16, True), (mx.OUT_FP32, False)])
 def test_backward_products_equal_the_single_gemm_calls(shape, fmt, dx_dtype, accumulate):
