@@ -620,10 +620,22 @@ int mxfp4_linear_bwd(const void *dy, const void *x, const void *w, void *dx, voi
         return MXFP4_EALIGN;
     if ((N % 8) != 0 || (K % 8) != 0) return MXFP4_EALIGN;  // dense bf16 rows must stay 16-byte aligned
     uint8_t *ws = static_cast<uint8_t *>(workspace);
-    // dY is needed row-wise for Dgrad and column-wise for Wgrad: one pass when both are asked
-    rc = quantize_operand(cfg, dy, M, N, F.dgrad, STREAM_DY, dx ? ws + L.gq : nullptr, dx ? ws + L.gs : nullptr,
-                          F.wgrad, STREAM_DYT, dw ? ws + L.gtq : nullptr, dw ? ws + L.gts : nullptr, hip_stream);
-    if (rc != MXFP4_OK) return rc;
+    // (dY and X in one launch: one grid, and one store policy, which differs for tensors beyond the last-level cache)
+    const int64_t llc = int64_t(256) << 20;
+    const bool dw_alone = dw && !dx && F.wgrad == MXFP4_FMT_E2M1 && cfg->geometry == MXFP4_GEOM_1D &&
+                          (M * N * 2 > llc) == (M * K * 2 > llc) && M < (int64_t(1) << 31) && N < (int64_t(1) << 31) &&
+                          K < (int64_t(1) << 31) &&
+                          ((N + 127) / 128 + (K + 127) / 128) * ((M / 32 + 7) / 8) < (int64_t(1) << 31);
+    if (dw_alone) {  // dY and X, both column-wise in MXFP4: one launch for the two tensors
+        rc = quantize_axis_pair(MXFP4_AXIS_FIRST, cfg, dy, M, N, STREAM_DYT, ws + L.gtq, ws + L.gts, x, M, K, STREAM_XT,
+                                ws + L.xtq, ws + L.xts, hip_stream);
+        if (rc != MXFP4_OK) return rc;
+    } else {
+        // dY is needed row-wise for Dgrad and column-wise for Wgrad: one pass when both are asked
+        rc = quantize_operand(cfg, dy, M, N, F.dgrad, STREAM_DY, dx ? ws + L.gq : nullptr, dx ? ws + L.gs : nullptr,
+                              F.wgrad, STREAM_DYT, dw ? ws + L.gtq : nullptr, dw ? ws + L.gts : nullptr, hip_stream);
+        if (rc != MXFP4_OK) return rc;
+    }
     if (dx && dw && F.dgrad == MXFP4_FMT_E2M1 && F.wgrad == MXFP4_FMT_E2M1 && cfg->geometry == MXFP4_GEOM_1D) {
         // W and X, both column-wise in MXFP4: one launch for the two tensors
         rc = quantize_axis_pair(MXFP4_AXIS_FIRST, cfg, w, N, K, STREAM_WT, ws + L.wtq, ws + L.wts, x, M, K, STREAM_XT,
@@ -635,7 +647,7 @@ int mxfp4_linear_bwd(const void *dy, const void *x, const void *w, void *dx, voi
                                   hip_stream);
             if (rc != MXFP4_OK) return rc;
         }
-        if (dw) {
+        if (dw && !dw_alone) {
             rc = quantize_operand(cfg, x, M, K, 0, 0, nullptr, nullptr, F.wgrad, STREAM_XT, ws + L.xtq, ws + L.xts,
                                   hip_stream);
             if (rc != MXFP4_OK) return rc;

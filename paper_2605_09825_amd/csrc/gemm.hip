@@ -954,11 +954,11 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_pair_kernel(const TileGemm p
 //   * a 16-byte chunk beyond the end of a row is clamped to the row's last chunk, and the scale bytes of the blocks
 //     beyond C/32 are 0 in LDS for both operands: every product under them is below 2^-254 * 2^24, which is 0 in fp32,
 //     so the last stage runs the same code as the others;
-//   * scale rows are C/32 bytes apart, at any alignment: they come through registers (16-byte loads, bytes at a row's
-//     ragged end) into LDS, 32 bytes per row (1024 elements of K) at a time.
+//   * scale rows are C/32 bytes apart, at any alignment: they come through registers (16-byte loads, shifted and
+//     masked at a row's ragged end) into LDS, 32 bytes per row (1024 elements of K) at a time.
 // FMT as in gemm_tile_body.  Built as 64 x 64 (4 stage buffers, 68 KiB of LDS, two workgroups per CU), 128 x 64 (3, 78 KiB,
-// two) and 128 x 256 tiles (8 waves, 3, 156 KiB; with two stage buffers 8192 x 6112 x 4064 took 185 us, with three 173); 128 x 128 tiles on 4 waves were never the fastest, 256 x 256 tiles on 8 waves
-// were slower for MXFP4 (210 against 156 us at 8192 x 6112 x 4064).
+// two) and 128 x 256 tiles (8 waves, 3, 156 KiB; with two stage buffers 8192 x 6112 x 4064 took 185 us, with three 173);
+// 128 x 128 tiles on 4 waves were never the fastest, 256 x 256 tiles on 8 waves were slower for MXFP4 (210 against 156 us).
 // What bounds it now: at 8192 x 6144 x 4096 (139 us, 3.0 PFLOP/s, against 99 us of the tiled kernel) LDS traffic, 176 KiB
 // per 128 x 256 stage against 1024 clocks of matrix instructions; rows that are not whole cache lines apart cost another
 // 20 % (C = 4064: 170 us), because every 128-byte row piece then takes two line requests.
@@ -1357,7 +1357,7 @@ static hipError_t launch_edge_f(const GemmArgs &g0, const GemmArgs *g1, hipStrea
 // and emptying the pipeline costs.  The constants were fitted to kernel times at 24 to 16000 rows, 512 to 28640 columns,
 // C = 512 to 8000; they only rank the three tile shapes.  Where they matter: few tiles (200 x 4096 x 4096: 64 x 64 9.4,
 // 128 x 64 12.6, 128 x 256 25 us), a round just overfull (2080 x 4320 x 1440: 29.4, 22.4, 24.8 us), many tiles (8192 x
-// 28640 x 4064: 298, 208, 156 us for a fifth of it).
+// 6112 x 4064: 298, 208, 156 us).
 static double edge_cost(const GemmArgs &g0, const GemmArgs *g1, int tm, int tn, int slots, double full, double fixed)
 {
     auto tiles = [&](const GemmArgs &g) { return ((g.Ra + tm - 1) / tm) * ((g.Rb + tn - 1) / tn); };
@@ -1369,7 +1369,7 @@ static double edge_cost(const GemmArgs &g0, const GemmArgs *g1, int tm, int tn, 
     return us;
 }
 
-// What gemm_edge_kernel takes: both operands of one format, lane offsets of 127 rows in 32 bits, tiles in a grid.
+// What gemm_edge_kernel takes: both operands of one format, lane offsets of 255 rows in 32 bits, tiles in a grid.
 static bool edge_eligible(const GemmArgs &g)
 {
     return g.a_fmt == g.b_fmt && g.C < (int64_t(1) << 24) && g.Ra < (int64_t(1) << 31) &&

@@ -60,3 +60,20 @@ def test_backward_products_equal_the_single_gemm_calls(shape, fmt, dx_dtype, acc
     want = dw0.clone()
     mx.mxfp4_gemm(tq, ts, xq, xs, out=want, out_dtype=mx.OUT_FP32, accumulate=accumulate, **fmts)
     assert torch.equal(dw, want)
+
+
+# the weight gradient alone: dY and X in one launch, or (X beyond the last-level cache, dY not) in two
+@pytest.mark.parametrize("shape", [(32, 8, 8), (288, 136, 1000), (4096, 64, 32896)])
+@pytest.mark.parametrize("rnd", [mx.RNE, mx.SR])
+def test_wgrad_operands_equal_the_single_quantiser_calls(shape, rnd):
+    M, N, K = shape
+    print(f"[wgrad operands] M={M} N={N} K={K} rnd={rnd}", flush=True)
+    x, dy = tensor(M, K, 1.0, 1), tensor(M, N, 1e-3, 3)
+    cfg = mx.make_cfg(mx.HAD_RANDSIGN16, rnd, 99)
+    _, dw, ws = mx.mxfp4_linear_bwd(dy, x, None, cfg, need_dx=False)
+    off = mx.mxfp4_linear_workspace_layout(M, N, K, True)[4:]
+    gq, gs = mx.mxfp4_quantize(dy, mx.AXIS_FIRST, mx.HAD_RANDSIGN16, rnd, 99 ^ (4 << 48))
+    xq, xs = mx.mxfp4_quantize(x, mx.AXIS_FIRST, mx.HAD_RANDSIGN16, rnd, 99 ^ (5 << 48))
+    for o, t in zip(off, (gq, gs, xq, xs)):
+        assert torch.equal(ws[o:o + t.numel()], t.flatten())
+    assert torch.equal(dw, mx.mxfp4_gemm(gq, gs, xq, xs, out_dtype=mx.OUT_FP32))
