@@ -623,8 +623,8 @@ int mxfp4_linear_bwd(const void *dy, const void *x, const void *w, void *dx, voi
     // (dY and X in one launch: one grid, and one store policy, which differs for tensors beyond the last-level cache)
     const int64_t llc = int64_t(256) << 20;
     const bool dw_alone = dw && !dx && F.wgrad == MXFP4_FMT_E2M1 && cfg->geometry == MXFP4_GEOM_1D &&
-                          (M * N * 2 > llc) == (M * K * 2 > llc) && M < (int64_t(1) << 31) && N < (int64_t(1) << 31) &&
-                          K < (int64_t(1) << 31) &&
+                          M < (int64_t(1) << 31) && N < (int64_t(1) << 31) && K < (int64_t(1) << 31) &&
+                          (M * N * 2 > llc) == (M * K * 2 > llc) &&
                           ((N + 127) / 128 + (K + 127) / 128) * ((M / 32 + 7) / 8) < (int64_t(1) << 31);
     if (dw_alone) {  // dY and X, both column-wise in MXFP4: one launch for the two tensors
         rc = quantize_axis_pair(MXFP4_AXIS_FIRST, cfg, dy, M, N, STREAM_DYT, ws + L.gtq, ws + L.gts, x, M, K, STREAM_XT,
