@@ -212,9 +212,9 @@ int mxfp4_gemm(const void *a_q, const void *a_s, const void *b_q, const void *b_
  * Two independent MXFP4 GEMMs enqueued together: the Dgrad and the Wgrad product of one layer share no
  * operand buffer and no output (App. C.2, C.3; Fig. 3), so they can run side by side.  Each problem is
  * described as in mxfp4_gemm (E2M1 operands); problem 0 never accumulates, problem 1 may (fp32 output).
- * When both shapes fit the tiled kernel and together fill the chip, one launch runs them on disjoint sets
- * of compute units split in proportion to their work; otherwise the call is mxfp4_gemm on problem 0
- * followed by mxfp4_gemm on problem 1.  Results are bit for bit those of the two separate calls.
+ * One launch runs both where that is estimated to be the faster (mxfp4_gemm_pair_route tells how), otherwise
+ * the call is mxfp4_gemm on problem 0 followed by mxfp4_gemm on problem 1.  Results are bit for bit those of
+ * the two separate calls.
  * The two outputs must not overlap each other or any operand.  Arguments are checked for both problems
  * before anything is enqueued.
  */
@@ -225,12 +225,12 @@ int mxfp4_gemm_pair(const void *a0_q, const void *a0_s, const void *b0_q, const 
                     void *hip_stream);
 
 /*
- * Which kernels mxfp4_gemm_fmt cuts a product of this shape into on a device with `compute_units` compute
- * units (256 on MI355X), for operands and an output aligned as those calls demand: the tiled kernel of the
+ * The blocks of the output that a product of this shape is cut into on a device with `compute_units` compute
+ * units (256 on MI355X), for operands and an output aligned as the GEMM calls demand: the tiled kernel of the
  * block-scaled FP4 GEMM (Sec. 2.1) on 256 x 256 tiles or, where those would leave compute units idle, on
- * 256 x 128 tiles, and the kernels for ragged shapes for edge strips and for contraction lengths below 1024 or
- * not in whole 256s (MXFP8: 128s).  A call whose product is too small for these blocks to fill the device (it is
- * estimated to take longer block by block) runs as one block on the kernels for ragged shapes, with the same result.
+ * 256 x 128 tiles, and the kernels for other shapes for edge strips and for contraction lengths below 1024 or
+ * not in whole 256s (MXFP8: 128s).  mxfp4_gemm_fmt runs the product block by block only where mxfp4_gemm_route
+ * says MXFP4_ROUTE_BLOCKS; otherwise one launch of another kernel computes the whole product, with the same result.
  * Host-only: touches no device.
  *   parts[6 * i ..] = kind, first row, rows, first column, columns of block i of the output, main tiles;
  *   kind: 0 any-shape, 1 tiled 256 x 256, 2 tiled 256 x 128, 3 one launch that runs `main tiles` tiles (whole
@@ -241,6 +241,43 @@ int mxfp4_gemm_pair(const void *a0_q, const void *a0_s, const void *b0_q, const 
  */
 int mxfp4_gemm_plan(int64_t R_a, int64_t R_b, int64_t C, int a_format, int b_format, int64_t ld_out,
                     int compute_units, int *n_parts, int64_t parts[24]);
+
+/*
+ * What mxfp4_gemm_fmt launches for a product of this shape: *route receives an mxfp4_gemm_route_kind.  The choice
+ * is the one with the lowest estimated time; results do not depend on it.  Host-only, operands and output taken as
+ * aligned as the call demands.  Returns what the call would for its sizes and types, or MXFP4_EINVAL.
+ */
+typedef enum {
+    MXFP4_ROUTE_NONE = -1,         /* an empty product: nothing                                              */
+    MXFP4_ROUTE_BLOCKS = 0,        /* the blocks of mxfp4_gemm_plan, a launch each                           */
+    MXFP4_ROUTE_ANY_SHAPE = 1,     /* the any-shape kernel                                                   */
+    MXFP4_ROUTE_EDGE_64 = 2,       /* the ragged-shape kernel on 64 x 64,                                    */
+    MXFP4_ROUTE_EDGE_128 = 3,      /*   on 128 x 64                                                          */
+    MXFP4_ROUTE_EDGE_256 = 4,      /*   or on 128 x 256 tiles                                                */
+    MXFP4_ROUTE_RAGGED_TILED = 5   /* the tiled kernel with its last row and column of tiles moved back      */
+} mxfp4_gemm_route_kind;
+int mxfp4_gemm_route(int64_t R_a, int64_t R_b, int64_t C, int a_format, int b_format, int64_t ld_out, int out_dtype,
+                     int accumulate, int compute_units, int *route);
+
+/*
+ * What mxfp4_gemm_pair, and the backward calls with both gradients (whose products may be MXFP8: format0, format1),
+ * launch for two products:
+ *   route[0] an mxfp4_gemm_pair_kind;
+ *   route[1] NARROW_BESIDE_WIDE: the problem on narrow tiles; EDGE: the problem whose tiles start first; else 0;
+ *   route[2] SIDE_BY_SIDE: workgroups per XCD (of 32) that problem 0 gets; NARROW_BESIDE_WIDE: those that take a narrow
+ *            tile first; EDGE: 0, 1, 2 for 64 x 64, 128 x 64, 128 x 256 tiles; else 0;
+ *   route[3] NARROW_BESIDE_WIDE: tiles of the other problem that those workgroups add; else 0.
+ * Host-only.  Returns what mxfp4_gemm_pair would for these sizes and types, or MXFP4_EINVAL.
+ */
+typedef enum {
+    MXFP4_PAIR_APART = 0,              /* one after the other (mxfp4_gemm_route of each), or one of them empty    */
+    MXFP4_PAIR_SIDE_BY_SIDE = 1,       /* both on 256 x 256 tiles, on disjoint sets of compute units              */
+    MXFP4_PAIR_NARROW_BESIDE_WIDE = 2, /* few 256 x 128 tiles of the one beside many 256 x 256 ones of the other  */
+    MXFP4_PAIR_EDGE = 3                /* both on the ragged-shape kernel                                         */
+} mxfp4_gemm_pair_kind;
+int mxfp4_gemm_pair_route(int64_t R_a0, int64_t R_b0, int64_t C0, int format0, int64_t ld_out0, int out_dtype0,
+                          int64_t R_a1, int64_t R_b1, int64_t C1, int format1, int64_t ld_out1, int out_dtype1,
+                          int accumulate1, int compute_units, int route[4]);
 
 /*
  * Fprop of one linear layer (App. C.1): Y[M][N] = Q(X H) Q(W H)^T, contraction over K.

@@ -27,7 +27,8 @@ FMT_E2M1, FMT_E4M3 = 0, 1
 
 EXPORTS = ("mxfp4_quantize", "mxfp4_quantize_dual", "mxfp4_quantize_2d", "mxfp4_quantize_fp8",
            "mxfp4_quantize_fp8_dual", "mxfp4_gemm",
-           "mxfp4_gemm_fmt", "mxfp4_gemm_pair", "mxfp4_gemm_plan", "mxfp4_linear_fwd", "mxfp4_linear_fwd_static", "mxfp4_linear_bwd",
+           "mxfp4_gemm_fmt", "mxfp4_gemm_pair", "mxfp4_gemm_plan", "mxfp4_gemm_route",
+           "mxfp4_gemm_pair_route", "mxfp4_linear_fwd", "mxfp4_linear_fwd_static", "mxfp4_linear_bwd",
            "mxfp4_linear_fwd_save", "mxfp4_linear_bwd_saved", "mxfp4_linear_saved_bytes",
            "mxfp4_linear_saved_layout", "mxfp4_linear_workspace_bytes", "mxfp4_linear_workspace_layout",
            "mxfp4_status_string")
@@ -88,6 +89,10 @@ def lib() -> ctypes.CDLL:
                                       [vp, vp, vp, vp, i64, i64, i64, vp, i64, ci, ci] + [vp])
         L.mxfp4_gemm_plan.restype = ci
         L.mxfp4_gemm_plan.argtypes = [i64, i64, i64, ci, ci, i64, ci, ctypes.POINTER(ci), ctypes.POINTER(i64)]
+        L.mxfp4_gemm_route.restype = ci
+        L.mxfp4_gemm_route.argtypes = [i64, i64, i64, ci, ci, i64, ci, ci, ci, ctypes.POINTER(ci)]
+        L.mxfp4_gemm_pair_route.restype = ci
+        L.mxfp4_gemm_pair_route.argtypes = ([i64, i64, i64, ci, i64, ci] * 2) + [ci, ci, ctypes.POINTER(ci)]
         L.mxfp4_linear_fwd_static.restype = ci
         L.mxfp4_linear_fwd_static.argtypes = [vp, vp, vp, i64, i64, i64, ctypes.POINTER(LinearCfg), vp]
         L.mxfp4_linear_bwd.restype = ci
@@ -261,6 +266,32 @@ def mxfp4_gemm_plan(Ra: int, Rb: int, C: int, a_format: int = FMT_E2M1, b_format
     _check("mxfp4_gemm_plan", lib().mxfp4_gemm_plan(Ra, Rb, C, a_format, b_format, Rb if ld_out is None else ld_out,
                                                     compute_units, ctypes.byref(n), parts))
     return [tuple(int(parts[6 * i + k]) for k in range(6)) for i in range(n.value)]
+
+
+ROUTE_NONE, ROUTE_BLOCKS, ROUTE_ANY_SHAPE, ROUTE_EDGE_64, ROUTE_EDGE_128, ROUTE_EDGE_256, ROUTE_RAGGED_TILED = range(-1, 6)
+PAIR_APART, PAIR_SIDE_BY_SIDE, PAIR_NARROW_BESIDE_WIDE, PAIR_EDGE = range(4)
+
+
+def mxfp4_gemm_route(Ra: int, Rb: int, C: int, a_format: int = FMT_E2M1, b_format: int = FMT_E2M1,
+                     ld_out: Optional[int] = None, out_dtype: int = OUT_BF16, accumulate: bool = False,
+                     compute_units: int = 256) -> int:
+    """What mxfp4_gemm launches for a product of this shape (ROUTE_*).  Host-only."""
+    route = ctypes.c_int(0)
+    _check("mxfp4_gemm_route", lib().mxfp4_gemm_route(Ra, Rb, C, a_format, b_format, Rb if ld_out is None else ld_out,
+                                                      out_dtype, int(accumulate), compute_units, ctypes.byref(route)))
+    return route.value
+
+
+def mxfp4_gemm_pair_route(shape0, shape1, formats=(FMT_E2M1, FMT_E2M1), out_dtypes=(OUT_BF16, OUT_FP32),
+                          accumulate1: bool = False, compute_units: int = 256):
+    """What mxfp4_gemm_pair, or a backward call with both gradients, launches for products of shapes (Ra, Rb, C) with
+    dense outputs: (PAIR_*, first, n, cut).  Host-only."""
+    route = (ctypes.c_int * 4)()
+    (a0, b0, c0), (a1, b1, c1) = shape0, shape1
+    _check("mxfp4_gemm_pair_route", lib().mxfp4_gemm_pair_route(
+        a0, b0, c0, formats[0], b0, out_dtypes[0], a1, b1, c1, formats[1], b1, out_dtypes[1], int(accumulate1),
+        compute_units, route))
+    return tuple(int(v) for v in route)
 
 
 def mxfp4_linear_workspace_bytes(M: int, N: int, K: int, cfg: LinearCfg, bwd: bool) -> int:

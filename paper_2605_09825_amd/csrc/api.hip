@@ -360,6 +360,57 @@ int mxfp4_gemm_plan(int64_t R_a, int64_t R_b, int64_t C, int a_format, int b_for
     return MXFP4_OK;
 }
 
+// the argument rules of the GEMM calls for a product whose operands and output are there and aligned
+static int check_gemm_shape(int64_t Ra, int64_t Rb, int64_t C, int64_t ld, int dt, int acc)
+{
+    alignas(16) static char there[16];
+    return check_gemm(there, there, there, there, Ra, Rb, C, there, ld, dt, acc);
+}
+
+int mxfp4_gemm_route(int64_t R_a, int64_t R_b, int64_t C, int a_format, int b_format, int64_t ld_out, int out_dtype,
+                     int accumulate, int compute_units, int *route)
+{
+    if (!route || compute_units <= 0) return MXFP4_EINVAL;
+    if ((a_format != MXFP4_FMT_E2M1 && a_format != MXFP4_FMT_E4M3) ||
+        (b_format != MXFP4_FMT_E2M1 && b_format != MXFP4_FMT_E4M3))
+        return MXFP4_EINVAL;
+    const int rc = check_gemm_shape(R_a, R_b, C, ld_out, out_dtype, accumulate);
+    if (rc > 0) return rc;
+    *route = MXFP4_ROUTE_NONE;
+    if (rc == 0) return MXFP4_OK;
+    const GemmArgs g{nullptr, nullptr, nullptr, nullptr, R_a, R_b, C, nullptr, ld_out, out_dtype == MXFP4_OUT_FP32,
+                     accumulate, a_format, b_format};
+    *route = route_gemm(g, compute_units).kind;
+    return MXFP4_OK;
+}
+
+int mxfp4_gemm_pair_route(int64_t R_a0, int64_t R_b0, int64_t C0, int format0, int64_t ld_out0, int out_dtype0,
+                          int64_t R_a1, int64_t R_b1, int64_t C1, int format1, int64_t ld_out1, int out_dtype1,
+                          int accumulate1, int compute_units, int route[4])
+{
+    if (!route || compute_units <= 0) return MXFP4_EINVAL;
+    if ((format0 != MXFP4_FMT_E2M1 && format0 != MXFP4_FMT_E4M3) ||
+        (format1 != MXFP4_FMT_E2M1 && format1 != MXFP4_FMT_E4M3))
+        return MXFP4_EINVAL;
+    const int rc0 = check_gemm_shape(R_a0, R_b0, C0, ld_out0, out_dtype0, 0);
+    if (rc0 > 0) return rc0;
+    const int rc1 = check_gemm_shape(R_a1, R_b1, C1, ld_out1, out_dtype1, accumulate1);
+    if (rc1 > 0) return rc1;
+    GemmPairRoute r{PAIR_APART, 0, 0, 0};  // (also with one of the two empty)
+    if (rc0 < 0 && rc1 < 0) {
+        const GemmArgs g0{nullptr, nullptr, nullptr, nullptr, R_a0, R_b0, C0, nullptr, ld_out0,
+                          out_dtype0 == MXFP4_OUT_FP32, 0, format0, format0};
+        const GemmArgs g1{nullptr, nullptr, nullptr, nullptr, R_a1, R_b1, C1, nullptr, ld_out1,
+                          out_dtype1 == MXFP4_OUT_FP32, accumulate1, format1, format1};
+        r = route_gemm_pair(g0, g1, compute_units);
+    }
+    route[0] = r.kind;
+    route[1] = r.first;
+    route[2] = r.n;
+    route[3] = r.cut;
+    return MXFP4_OK;
+}
+
 int mxfp4_gemm(const void *a_q, const void *a_s, const void *b_q, const void *b_s, int64_t R_a, int64_t R_b,
                int64_t C, void *out, int64_t ld_out, int out_dtype, int accumulate, void *hip_stream)
 {

@@ -1581,35 +1581,33 @@ static double rag_cost(const GemmArgs &g, int cus)
 // x 4096: 16.8 us on 64 tiles, 11.6 us on 128 x 64 ones; in MXFP8, which has no narrow tile, 42.1 and 19.4), where it
 // cuts a small product into several launches (300 x 520 x 1024: 15.5 us in three, 5.5 us in one) and where strips beside a
 // large interior cost a launch and a poorly filled chip (4010 x 6144 x 4096: 63 us, 55 in one).
-enum GemmRoute { ROUTE_PLAN, ROUTE_EDGE, ROUTE_RAG };
-struct GemmChoice {
-    GemmRoute route;
-    int tile;  // of ROUTE_EDGE
-    double us;
-};
-static GemmChoice choose_route(const GemmArgs &g, const GemmPlan &plan, int cus)
+static GemmRoute choose_route(const GemmArgs &g, const GemmPlan &plan, int cus)
 {
-    GemmChoice c{ROUTE_PLAN, 0, 1e30};
+    const bool one_any = plan.n == 1 && plan.part[0].kind == GEMM_ANY;
+    GemmRoute c{one_any ? ROUTE_ANY_SHAPE : ROUTE_BLOCKS, 1e30};
     if (edge_eligible(g)) {
         const EdgeChoice edge = choose_edge(g);
-        c = GemmChoice{ROUTE_EDGE, edge.tile, edge.us};
+        c = GemmRoute{ROUTE_EDGE_64 + edge.tile, edge.us};
     }
-    if (c.route != ROUTE_EDGE || plan.n != 1 || plan.part[0].kind != GEMM_ANY) {
+    if (!one_any) {
         const double us = plan_cost(g, plan, cus);
-        if (us <= c.us) c = GemmChoice{ROUTE_PLAN, 0, us};
+        if (us <= c.us) c = GemmRoute{ROUTE_BLOCKS, us};
     }
     const double rag = rag_cost(g, cus);
-    if (rag < c.us) c = GemmChoice{ROUTE_RAG, 0, rag};
+    if (rag < c.us) c = GemmRoute{ROUTE_RAGGED_TILED, rag};
     return c;
 }
+
+GemmRoute route_gemm(const GemmArgs &g, int cus) { return choose_route(g, plan_gemm(g, cus), cus); }
 
 hipError_t launch_gemm(const GemmArgs &g, hipStream_t st)
 {
     const int cus = device_cus();
     const GemmPlan plan = plan_gemm(g, cus);
-    const GemmChoice choice = choose_route(g, plan, cus);
-    if (choice.route == ROUTE_EDGE) return launch_edge(g, nullptr, choice.tile, st);
-    if (choice.route == ROUTE_RAG) return launch_rag(g, cus, st);
+    const GemmRoute route = choose_route(g, plan, cus);
+    if (route.kind >= ROUTE_EDGE_64 && route.kind <= ROUTE_EDGE_256)
+        return launch_edge(g, nullptr, route.kind - ROUTE_EDGE_64, st);
+    if (route.kind == ROUTE_RAGGED_TILED) return launch_rag(g, cus, st);
     for (int i = 0; i < plan.n; ++i) {
         const GemmPart &p = plan.part[i];
         const GemmArgs h = sub_block(g, p.r0, p.rows, p.c0, p.cols);
@@ -1650,11 +1648,11 @@ static MixChoice choose_mix(const GemmArgs &gn, const GemmArgs &gw, int cus)
     return best;
 }
 
-static hipError_t launch_mix(const GemmArgs &gn, const GemmArgs &gw, const MixChoice &c, hipStream_t st)
+static hipError_t launch_mix(const GemmArgs &gn, const GemmArgs &gw, int n1, int cut, hipStream_t st)
 {
     const TileGemm pn = tile_args(gn, TILE / 2), pw = tile_args(gw);
 #define MXFP4_MIX(ON, AN, OW, AW) \
-    hipLaunchKernelGGL((gemm_tile_mix_kernel<ON, AN, OW, AW>), dim3(NUM_CUS), dim3(256), 0, st, pn, pw, c.n1, c.cut)
+    hipLaunchKernelGGL((gemm_tile_mix_kernel<ON, AN, OW, AW>), dim3(NUM_CUS), dim3(256), 0, st, pn, pw, n1, cut)
     // (one of the two, problem 0 of the pair, never accumulates)
     if (gn.accumulate) {
         if (gw.out_fp32) MXFP4_MIX(true, true, true, false); else MXFP4_MIX(true, true, false, false);
@@ -1669,18 +1667,17 @@ static hipError_t launch_mix(const GemmArgs &gn, const GemmArgs &gw, const MixCh
     return hipGetLastError();
 }
 
-// g0 (no accumulation) and g1 on the same stream, no dependence between them.  Side by side in one launch
-// when both fit the tiled kernel and together fill the chip; otherwise one after the other.
-hipError_t launch_gemm_pair(const GemmArgs &g0, const GemmArgs &g1, hipStream_t st)
+// How two products (g0 without accumulation) that do not depend on each other run: side by side when both fit the tiled
+// kernel and together fill the chip; otherwise by estimate.
+GemmPairRoute route_gemm_pair(const GemmArgs &g0, const GemmArgs &g1, int cus)
 {
+    GemmPairRoute r{PAIR_APART, 0, 0, 0};
     // (the split below counts on 8 XCDs of 32 compute units each)
     // Formats: both problems MXFP4 (every combination of output types); or the second, or both, MXFP8 with the
     // output types of a backward pass (bf16 from problem 0, fp32 from problem 1): the stage-wise recipes of Table 1.
     const bool fmt_ok = g0.a_fmt == g0.b_fmt && g1.a_fmt == g1.b_fmt && (g0.a_fmt == 0 || g1.a_fmt == 1) &&
                         (g1.a_fmt == 0 || (!g0.out_fp32 && g1.out_fp32));
-    const bool side_by_side = !g0.accumulate && fmt_ok && tile_eligible(g0) && tile_eligible(g1) &&
-                              device_cus() == NUM_CUS;
-    if (side_by_side) {
+    if (!g0.accumulate && fmt_ok && tile_eligible(g0) && tile_eligible(g1) && cus == NUM_CUS) {
         const TileGemm p0 = tile_args(g0), p1 = tile_args(g1);
         const int64_t t0 = (int64_t)p0.tiles_m * p0.tiles_n, t1 = (int64_t)p1.tiles_m * p1.tiles_n;
         // (an E4M3 element costs the matrix unit twice the time of an E2M1 element)
@@ -1690,41 +1687,55 @@ hipError_t launch_gemm_pair(const GemmArgs &g0, const GemmArgs &g1, hipStream_t 
         n0 = n0 < 1 ? 1 : (n0 > 31 ? 31 : n0);
         // worth it only if both shares have enough tiles to keep their CUs busy
         if (t0 >= (int64_t)n0 * 8 && t1 >= (int64_t)(32 - n0) * 8) {
-            dim3 grid(NUM_CUS);
-#define MXFP4_PAIR(O0, O1, A1, F0, F1) \
-    hipLaunchKernelGGL((gemm_tile_pair_kernel<O0, O1, A1, F0, F1>), grid, dim3(256), 0, st, p0, p1, n0)
-            if (g1.a_fmt) {
-                if (g0.a_fmt) {
-                    if (g1.accumulate) MXFP4_PAIR(false, true, true, 1, 1); else MXFP4_PAIR(false, true, false, 1, 1);
-                } else {
-                    if (g1.accumulate) MXFP4_PAIR(false, true, true, 0, 1); else MXFP4_PAIR(false, true, false, 0, 1);
-                }
-            } else if (g0.out_fp32) {
-                if (!g1.out_fp32) MXFP4_PAIR(true, false, false, 0, 0);
-                else if (g1.accumulate) MXFP4_PAIR(true, true, true, 0, 0);
-                else MXFP4_PAIR(true, true, false, 0, 0);
-            } else {
-                if (!g1.out_fp32) MXFP4_PAIR(false, false, false, 0, 0);
-                else if (g1.accumulate) MXFP4_PAIR(false, true, true, 0, 0);
-                else MXFP4_PAIR(false, true, false, 0, 0);
-            }
-#undef MXFP4_PAIR
-            return hipGetLastError();
+            r.kind = PAIR_SIDE_BY_SIDE;
+            r.n = n0;
+            return r;
         }
     }
     // Otherwise by estimate: one after the other, few narrow tiles beside many wide ones, or both on the ragged-shape
     // kernel, the longer contraction first (ragged widths, small layers: a step of 2048 x 3072 x 768 went from 50 to 37 us).
     if (!g0.accumulate && g0.a_fmt == g1.a_fmt && edge_eligible(g0) && edge_eligible(g1)) {
-        const int cus = device_cus();
         const EdgeChoice both = choose_edge(g0, &g1);
         const MixChoice mix1 = choose_mix(g1, g0, cus), mix0 = choose_mix(g0, g1, cus);
-        const double mix = mix1.us < mix0.us ? mix1.us : mix0.us;
-        const double apart = choose_route(g0, plan_gemm(g0, cus), cus).us + choose_route(g1, plan_gemm(g1, cus), cus).us + 4.0;
-        if (mix < apart && mix < both.us)
-            return mix1.us <= mix0.us ? launch_mix(g1, g0, mix1, st) : launch_mix(g0, g1, mix0, st);
-        if (both.us < apart)
-            return g1.C > g0.C ? launch_edge(g1, &g0, both.tile, st) : launch_edge(g0, &g1, both.tile, st);
+        const MixChoice mix = mix1.us <= mix0.us ? mix1 : mix0;
+        const double apart = route_gemm(g0, cus).us + route_gemm(g1, cus).us + 4.0;
+        if (mix.us < apart && mix.us < both.us)
+            r = GemmPairRoute{PAIR_NARROW_BESIDE_WIDE, mix1.us <= mix0.us ? 1 : 0, mix.n1, mix.cut};
+        else if (both.us < apart)
+            r = GemmPairRoute{PAIR_EDGE, g1.C > g0.C ? 1 : 0, both.tile, 0};
     }
+    return r;
+}
+
+hipError_t launch_gemm_pair(const GemmArgs &g0, const GemmArgs &g1, hipStream_t st)
+{
+    const GemmPairRoute r = route_gemm_pair(g0, g1, device_cus());
+    if (r.kind == PAIR_SIDE_BY_SIDE) {
+        const TileGemm p0 = tile_args(g0), p1 = tile_args(g1);
+        dim3 grid(NUM_CUS);
+#define MXFP4_PAIR(O0, O1, A1, F0, F1) \
+    hipLaunchKernelGGL((gemm_tile_pair_kernel<O0, O1, A1, F0, F1>), grid, dim3(256), 0, st, p0, p1, r.n)
+        if (g1.a_fmt) {
+            if (g0.a_fmt) {
+                if (g1.accumulate) MXFP4_PAIR(false, true, true, 1, 1); else MXFP4_PAIR(false, true, false, 1, 1);
+            } else {
+                if (g1.accumulate) MXFP4_PAIR(false, true, true, 0, 1); else MXFP4_PAIR(false, true, false, 0, 1);
+            }
+        } else if (g0.out_fp32) {
+            if (!g1.out_fp32) MXFP4_PAIR(true, false, false, 0, 0);
+            else if (g1.accumulate) MXFP4_PAIR(true, true, true, 0, 0);
+            else MXFP4_PAIR(true, true, false, 0, 0);
+        } else {
+            if (!g1.out_fp32) MXFP4_PAIR(false, false, false, 0, 0);
+            else if (g1.accumulate) MXFP4_PAIR(false, true, true, 0, 0);
+            else MXFP4_PAIR(false, true, false, 0, 0);
+        }
+#undef MXFP4_PAIR
+        return hipGetLastError();
+    }
+    if (r.kind == PAIR_NARROW_BESIDE_WIDE)
+        return r.first ? launch_mix(g1, g0, r.n, r.cut, st) : launch_mix(g0, g1, r.n, r.cut, st);
+    if (r.kind == PAIR_EDGE) return r.first ? launch_edge(g1, &g0, r.n, st) : launch_edge(g0, &g1, r.n, st);
     hipError_t e = launch_gemm(g0, st);
     if (e != hipSuccess) return e;
     return launch_gemm(g1, st);

@@ -71,6 +71,26 @@ struct GemmPlan {
 // host logic only (no device call); cus: compute units of the device the launch is planned for
 GemmPlan plan_gemm(const GemmArgs &g, int cus);
 
+// How a GEMM runs: as the blocks of its plan, or as one launch for the whole product (the any-shape kernel, the
+// ragged-shape kernel on 64 x 64, 128 x 64 or 128 x 256 tiles, the tiled kernel for ragged sizes).  us: its estimate.
+// Host logic only, as plan_gemm; the launches below ask the same functions.
+enum GemmRouteKind {
+    ROUTE_BLOCKS = 0, ROUTE_ANY_SHAPE = 1, ROUTE_EDGE_64 = 2, ROUTE_EDGE_128 = 3, ROUTE_EDGE_256 = 4, ROUTE_RAGGED_TILED = 5
+};
+struct GemmRoute {
+    int kind;
+    double us;
+};
+GemmRoute route_gemm(const GemmArgs &g, int cus);
+// How two independent GEMMs run.  first: the problem on narrow tiles (PAIR_NARROW_BESIDE_WIDE) or the one whose tiles start
+// first (PAIR_EDGE); n: workgroups per XCD of problem 0 (PAIR_SIDE_BY_SIDE) or of the narrow one, or the edge tile shape
+// (0, 1, 2); cut: tiles of the wide product that the workgroups with a narrow tile add.
+enum GemmPairKind { PAIR_APART = 0, PAIR_SIDE_BY_SIDE = 1, PAIR_NARROW_BESIDE_WIDE = 2, PAIR_EDGE = 3 };
+struct GemmPairRoute {
+    int kind, first, n, cut;
+};
+GemmPairRoute route_gemm_pair(const GemmArgs &g0, const GemmArgs &g1, int cus);
+
 hipError_t launch_gemm(const GemmArgs &g, hipStream_t st);
 // two GEMMs that do not depend on each other (g0.accumulate must be 0); may share one launch
 hipError_t launch_gemm_pair(const GemmArgs &g0, const GemmArgs &g1, hipStream_t st);

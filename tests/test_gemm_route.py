@@ -1,0 +1,64 @@
+"""CPU-only checks of the rule that decides which kernel a product, or a pair of products, runs on (256 compute units; no
+device is touched).  GPU tests that are about one kernel ask the same functions, so that they cannot leave it unnoticed."""
+import ctypes
+
+import paper_2605_09825_amd as mx
+
+route, pair = mx.mxfp4_gemm_route, mx.mxfp4_gemm_pair_route
+FP8 = dict(a_format=mx.FMT_E4M3, b_format=mx.FMT_E4M3)
+
+
+def test_whole_tiles_that_fill_the_chip_run_as_planned():
+    for shape in [(8192, 6144, 4096), (6144, 4096, 8192), (8192, 1024, 4096), (4096, 14336, 16384)]:
+        assert route(*shape) == mx.ROUTE_BLOCKS
+        assert route(*shape, out_dtype=mx.OUT_FP32, accumulate=True) == mx.ROUTE_BLOCKS
+    assert route(8192, 6144, 4096, **FP8) == mx.ROUTE_BLOCKS
+
+
+def test_large_ragged_products_leave_the_plan():
+    # (the plan of the first is a tiled interior and a strip, of the second one block on the kernels for other shapes)
+    assert len(mx.mxfp4_gemm_plan(4010, 6144, 4096)) == 2
+    for shape in [(4010, 6144, 4096), (8192, 6144, 4064), (8192, 28640, 4064)]:
+        assert route(*shape) == mx.ROUTE_RAGGED_TILED
+    assert route(8192, 6144, 4064, **FP8) == mx.ROUTE_RAGGED_TILED
+    assert route(8192, 6144, 4064, ld_out=6148) == mx.ROUTE_EDGE_256    # rows of the output not 16-byte aligned
+
+
+def test_products_too_small_for_whole_tiles():
+    assert route(24, 6144, 4096) == mx.ROUTE_EDGE_64
+    assert route(2080, 4320, 1440) == mx.ROUTE_EDGE_128
+    assert route(300, 520, 1024) == mx.ROUTE_EDGE_64
+    assert route(512, 4096, 4096, **FP8) == mx.ROUTE_EDGE_128
+    assert route(0, 16, 32) == route(16, 0, 32) == mx.ROUTE_NONE
+    for f in [dict(a_format=mx.FMT_E4M3), dict(b_format=mx.FMT_E4M3)]:  # operands of different formats
+        assert route(24, 6144, 4096, **f) == route(8192, 6144, 4096, **f) == mx.ROUTE_ANY_SHAPE
+
+
+def test_pairs():
+    dgrad_wgrad = lambda M, N, K: ((M, K, N), (N, K, M))
+    assert pair(*dgrad_wgrad(8192, 6144, 4096)) == (mx.PAIR_SIDE_BY_SIDE, 0, 16, 0)
+    # few narrow tiles of the one beside many wide ones of the other: of Wgrad, of Dgrad
+    assert pair(*dgrad_wgrad(8192, 1024, 4096)) == (mx.PAIR_NARROW_BESIDE_WIDE, 1, 16, 128)
+    assert pair(*dgrad_wgrad(1024, 4096, 4096))[:3] == (mx.PAIR_NARROW_BESIDE_WIDE, 0, 16)
+    assert pair(*dgrad_wgrad(2080, 4320, 1440))[0] == mx.PAIR_EDGE
+    assert pair((64, 64, 32), (64, 64, 4096))[:2] == (mx.PAIR_EDGE, 1)  # the longer contraction starts first
+    assert pair((300, 520, 1024), (0, 64, 64))[0] == mx.PAIR_APART     # one of them empty
+    # a smaller chip: no launch that counts on 8 XCDs of 32 compute units
+    assert pair(*dgrad_wgrad(8192, 6144, 4096), compute_units=128)[0] in (mx.PAIR_APART, mx.PAIR_EDGE)
+
+
+def test_argument_errors():
+    L, r, p4 = mx.lib(), ctypes.c_int(7), (ctypes.c_int * 4)()
+    ok = (16, 16, 32, 0, 0, 16, mx.OUT_FP32, 0)
+    one = lambda *a, cus=256, out=ctypes.byref(r): L.mxfp4_gemm_route(*a, cus, out)
+    assert one(*ok) == mx.OK
+    assert one(*ok, out=None) == one(*ok, cus=0) == one(16, 16, 32, 7, *ok[4:]) == mx.EINVAL
+    assert one(*ok[:6], mx.OUT_BF16, 1) == one(*ok[:6], 5, 0) == mx.EINVAL
+    assert one(16, 16, 48, *ok[3:]) == one(-1, *ok[1:]) == one(*ok[:5], 8, *ok[6:]) == mx.ESHAPE
+    assert one((1 << 36) + 1, *ok[1:]) == mx.ESHAPE
+    half = (16, 16, 32, 0, 16, mx.OUT_FP32)
+    two = lambda a, b, acc=0, cus=256, out=p4: L.mxfp4_gemm_pair_route(*a, *b, acc, cus, out)
+    assert two(half, half) == mx.OK
+    assert two(half, half, out=None) == two(half, half, cus=0) == two(half, half, acc=2) == mx.EINVAL
+    assert two(half, (16, 16, 32, 3, 16, 1)) == two((16, 16, 32, 0, 16, 9), half) == mx.EINVAL
+    assert two((16, 16, 48, 0, 16, 1), half) == two(half, (16, 16, 32, 0, 8, 1)) == mx.ESHAPE
