@@ -1369,25 +1369,39 @@ static double edge_cost(const GemmArgs &g0, const GemmArgs *g1, int tm, int tn, 
     return us;
 }
 
-// What gemm_edge_kernel takes: both operands of one format, lane offsets of 255 rows in 32 bits, tiles in a grid.
+// What gemm_edge_kernel takes: both operands of one format, lane offsets of 255 rows in 32 bits.
 static bool edge_eligible(const GemmArgs &g)
 {
-    return g.a_fmt == g.b_fmt && g.C < (int64_t(1) << 24) && g.Ra < (int64_t(1) << 31) &&
-           ((g.Ra + 63) / 64) * ((g.Rb + 63) / 64) < (int64_t(1) << 29);
+    return g.a_fmt == g.b_fmt && g.C < (int64_t(1) << 24) && g.Ra < (int64_t(1) << 31);
 }
 
-// The tile shape with the lowest estimate for one product, or two of one format side by side.
+// The tile shape with the lowest estimate for one product, or two of one format side by side, among those whose tiles, a
+// workgroup each, make a grid that can be launched (us = NO_ROUTE: none does).
+constexpr double NO_ROUTE = 1e30;
 struct EdgeChoice {
     int tile;  // 0: 64 x 64, 1: 128 x 64, 2: 128 x 256
     double us;
 };
 static EdgeChoice choose_edge(const GemmArgs &g0, const GemmArgs *g1 = nullptr)
 {
-    EdgeChoice best{0, edge_cost(g0, g1, 64, 64, 512, 6.4, 1.5)};
-    const double mid = edge_cost(g0, g1, 128, 64, 512, 9.3, 1.5), large = edge_cost(g0, g1, 128, 256, 256, 10.5, 3.5);
+    auto cost = [&](int tm, int tn, int threads, int slots, double full, double fixed) {
+        auto groups = [&](const GemmArgs &g) { return ((g.Ra + tm - 1) / tm * ((g.Rb + tn - 1) / tn) + 7) & ~int64_t(7); };
+        if (!grid_fits(groups(g0) + (g1 ? groups(*g1) : 0), threads)) return NO_ROUTE;
+        return edge_cost(g0, g1, tm, tn, slots, full, fixed);
+    };
+    EdgeChoice best{0, cost(64, 64, 256, 512, 6.4, 1.5)};
+    const double mid = cost(128, 64, 256, 512, 9.3, 1.5), large = cost(128, 256, 512, 256, 10.5, 3.5);
     if (mid <= best.us) best = EdgeChoice{1, mid};
     if (large <= best.us) best = EdgeChoice{2, large};
     return best;
+}
+
+// A block that is not for the tiled kernels: the ragged-shape kernel or, where that cannot, the any-shape kernel.
+static GemmRoute any_route(const GemmArgs &g)
+{
+    if (!edge_eligible(g)) return GemmRoute{ROUTE_ANY_SHAPE, NO_ROUTE};
+    const EdgeChoice edge = choose_edge(g);
+    return edge.us < NO_ROUTE ? GemmRoute{ROUTE_EDGE_64 + edge.tile, edge.us} : GemmRoute{ROUTE_ANY_SHAPE, NO_ROUTE};
 }
 
 static hipError_t launch_edge(const GemmArgs &g0, const GemmArgs *g1, int tile, hipStream_t st)
@@ -1399,7 +1413,8 @@ static hipError_t launch_edge(const GemmArgs &g0, const GemmArgs *g1, int tile, 
 
 static hipError_t launch_any(const GemmArgs &g, hipStream_t st)
 {
-    if (edge_eligible(g)) return launch_edge(g, nullptr, choose_edge(g).tile, st);
+    const GemmRoute r = any_route(g);
+    if (r.kind != ROUTE_ANY_SHAPE) return launch_edge(g, nullptr, r.kind - ROUTE_EDGE_64, st);
     if (g.a_fmt == 0) return g.b_fmt == 0 ? launch_any_f<0, 0>(g, st) : launch_any_f<0, 1>(g, st);
     return g.b_fmt == 0 ? launch_any_f<1, 0>(g, st) : launch_any_f<1, 1>(g, st);
 }
@@ -1555,11 +1570,7 @@ static double plan_cost(const GemmArgs &g, const GemmPlan &plan, int cus)
         if (p.kind == GEMM_TILED_256) us += rounds_of(tiles, cus) * wide_round(g);
         else if (p.kind == GEMM_TILED_128) us += rounds_of((p.rows / TILE) * (p.cols / (TILE / 2)), cus) * narrow_round(g);
         else if (p.kind == GEMM_TILED_256_TAIL_128) us += rounds_of(p.main_tiles, cus) * wide_round(g) + narrow_round(g);
-        else {
-            const GemmArgs h = sub_block(g, p.r0, p.rows, p.c0, p.cols);
-            if (!edge_eligible(h)) return 1e30;
-            us += choose_edge(h).us;
-        }
+        else us += any_route(sub_block(g, p.r0, p.rows, p.c0, p.cols)).us;
     }
     return us;
 }
@@ -1568,7 +1579,7 @@ static double plan_cost(const GemmArgs &g, const GemmPlan &plan, int cus)
 // as many again per product)
 static double rag_cost(const GemmArgs &g, int cus)
 {
-    if (!rag_eligible(g)) return 1e30;
+    if (!rag_eligible(g)) return NO_ROUTE;
     int64_t tiles, whole;
     rag_tiles(g, cus, &tiles, &whole);
     const bool split_lines = (g.a_fmt ? g.C : g.C / 2) % 128 != 0;
@@ -1583,13 +1594,8 @@ static double rag_cost(const GemmArgs &g, int cus)
 // large interior cost a launch and a poorly filled chip (4010 x 6144 x 4096: 63 us, 55 in one).
 static GemmRoute choose_route(const GemmArgs &g, const GemmPlan &plan, int cus)
 {
-    const bool one_any = plan.n == 1 && plan.part[0].kind == GEMM_ANY;
-    GemmRoute c{one_any ? ROUTE_ANY_SHAPE : ROUTE_BLOCKS, 1e30};
-    if (edge_eligible(g)) {
-        const EdgeChoice edge = choose_edge(g);
-        c = GemmRoute{ROUTE_EDGE_64 + edge.tile, edge.us};
-    }
-    if (!one_any) {
+    GemmRoute c = any_route(g);
+    if (plan.n != 1 || plan.part[0].kind != GEMM_ANY) {
         const double us = plan_cost(g, plan, cus);
         if (us <= c.us) c = GemmRoute{ROUTE_BLOCKS, us};
     }
@@ -1633,7 +1639,7 @@ struct MixChoice {
 };
 static MixChoice choose_mix(const GemmArgs &gn, const GemmArgs &gw, int cus)
 {
-    MixChoice best{0, 0, 1e30};
+    MixChoice best{0, 0, NO_ROUTE};
     if (cus != NUM_CUS || gn.a_fmt || gw.a_fmt || !tile_eligible(gn, TILE / 2) || !tile_eligible(gw)) return best;
     const int64_t tn = (gn.Ra / TILE) * (gn.Rb / (TILE / 2)), tw = (gw.Ra / TILE) * (gw.Rb / TILE);
     if (tn > NUM_CUS - 8) return best;

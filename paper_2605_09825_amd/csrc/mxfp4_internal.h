@@ -7,6 +7,9 @@
 
 namespace mxfp4 {
 
+// HIP refuses a launch of 2^32 or more threads along one dimension of the grid.
+constexpr bool grid_fits(int64_t groups, int threads) { return groups < (int64_t(1) << 32) / threads; }
+
 struct QuantArgs {
     const uint16_t *x;  // bf16 [rows][ld]
     int64_t rows, cols, ld;

@@ -47,6 +47,18 @@ def test_pairs():
     assert pair(*dgrad_wgrad(8192, 6144, 4096), compute_units=128)[0] in (mx.PAIR_APART, mx.PAIR_EDGE)
 
 
+def test_more_tiles_than_a_grid_can_hold():
+    # A launch holds fewer than 2^32 threads along a dimension: 2^24 workgroups on 64 x 64 or 128 x 64 tiles, 2^23 on
+    # 128 x 256 ones.  Beyond that the next larger tile, then the any-shape kernel, whose grid has two dimensions.
+    assert route(64 * (2**24 - 8), 64, 32) == mx.ROUTE_EDGE_128
+    assert route(720_000_000, 130, 32) == mx.ROUTE_EDGE_256             # (16.9 million tiles of 128 x 64)
+    assert route(2**30 - 64, 300, 32) == mx.ROUTE_ANY_SHAPE             # (16.8 million tiles of 128 x 256)
+    assert route(2**30 - 64, 300, 32, **FP8) == mx.ROUTE_ANY_SHAPE
+    # a pair shares one grid: each fits, both do not
+    assert pair((720_000_000, 130, 32), (64, 64, 64))[0] == mx.PAIR_EDGE
+    assert pair((720_000_000, 130, 32), (720_000_000, 130, 64))[0] == mx.PAIR_APART
+
+
 def test_argument_errors():
     L, r, p4 = mx.lib(), ctypes.c_int(7), (ctypes.c_int * 4)()
     ok = (16, 16, 32, 0, 0, 16, mx.OUT_FP32, 0)
