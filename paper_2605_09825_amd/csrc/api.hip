@@ -45,8 +45,7 @@ int check_quantize(const void *x, int64_t rows, int64_t cols, int64_t ld, int ax
     if (axis == MXFP4_AXIS_FIRST && ((rows % 32) != 0 || (cols % 2) != 0)) return MXFP4_ESHAPE;
     if (rows > (int64_t(1) << 40) || cols > (int64_t(1) << 40)) return MXFP4_ESHAPE;
     {   // the 1-D launch grids hold at most 2^31 - 1 workgroups
-        const int64_t groups = (axis == MXFP4_AXIS_LAST) ? (rows * (cols / 32) + 255) / 256
-                                                         : ((cols + 127) / 128) * ((rows / 32 + 7) / 8);
+        const int64_t groups = (axis == MXFP4_AXIS_LAST) ? rows_groups(rows, cols) : cols_groups(rows, cols);
         if (groups >= (int64_t(1) << 31)) return MXFP4_ESHAPE;
     }
     if (!aligned(q, 16)) return MXFP4_EALIGN;
@@ -493,10 +492,9 @@ static int quantize_operand_pair(const mxfp4_linear_cfg *cfg, const void *x0, in
     if (!device_ok()) return MXFP4_EDEVICE;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     hipError_t e;
-    auto tiles = [](const QuantArgs &t) { return ((t.cols + 127) / 128) * ((t.rows / 32 + 7) / 8); };
     if (rc == 0 || rc1 == 0) {  // one of them is empty
         e = g2 ? launch_quantize_2d(rc == 0 ? b : a, nullptr, st) : launch_quantize_dual(rc == 0 ? b : a, nullptr, st);
-    } else if (tiles(a) + tiles(b) >= (int64_t(1) << 31)) {  // too many workgroups for one grid
+    } else if (!grid_fits(cols_groups(a.rows, a.cols) + cols_groups(b.rows, b.cols), COLS_THREADS)) {  // as below
         e = g2 ? launch_quantize_2d(a, nullptr, st) : launch_quantize_dual(a, nullptr, st);
         if (e == hipSuccess) e = g2 ? launch_quantize_2d(b, nullptr, st) : launch_quantize_dual(b, nullptr, st);
     } else {
@@ -515,24 +513,23 @@ static int quantize_axis_pair(int axis, const mxfp4_linear_cfg *cfg, const void 
     if (rc >= 0) return rc;  // (an error; the linear calls pass no empty tensors)
     rc = check_quantize(x1, rows1, cols1, cols1, axis, cfg->hadamard, cfg->rounding, q1, s1);
     if (rc >= 0) return rc;
-    const int64_t groups = axis == MXFP4_AXIS_LAST
-                               ? (rows0 * (cols0 / 32) + 255) / 256 + (rows1 * (cols1 / 32) + 255) / 256
-                               : ((cols0 + 127) / 128) * ((rows0 / 32 + 7) / 8) + ((cols1 + 127) / 128) * ((rows1 / 32 + 7) / 8);
-    if (axis == MXFP4_AXIS_FIRST && groups >= (int64_t(1) << 31)) return MXFP4_ESHAPE;  // the two grids share one launch
+    const bool last = axis == MXFP4_AXIS_LAST;
+    const int64_t groups = last ? rows_groups(rows0, cols0) + rows_groups(rows1, cols1)
+                                : cols_groups(rows0, cols0) + cols_groups(rows1, cols1);
+    if (!last && groups >= (int64_t(1) << 31)) return MXFP4_ESHAPE;
     if (!device_ok()) return MXFP4_EDEVICE;
     const QuantArgs a{static_cast<const uint16_t *>(x0), rows0, cols0, cols0, cfg->hadamard, cfg->rounding,
                       operand_seed(cfg, st0), q0, s0};
     const QuantArgs b{static_cast<const uint16_t *>(x1), rows1, cols1, cols1, cfg->hadamard, cfg->rounding,
                       operand_seed(cfg, st1), q1, s1};
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
+    auto launch = last ? launch_quantize_rows : launch_quantize_cols;
     hipError_t e;
-    if (axis == MXFP4_AXIS_FIRST) {
-        e = launch_quantize_cols(a, st, &b);
-    } else if (groups < (int64_t(1) << 31)) {
-        e = launch_quantize_rows(a, st, &b);
+    if (grid_fits(groups, last ? ROWS_THREADS : COLS_THREADS)) {
+        e = launch(a, st, &b);
     } else {  // too many workgroups for one grid
-        e = launch_quantize_rows(a, st);
-        if (e == hipSuccess) e = launch_quantize_rows(b, st);
+        e = launch(a, st, nullptr);
+        if (e == hipSuccess) e = launch(b, st, nullptr);
     }
     return e == hipSuccess ? MXFP4_OK : MXFP4_EDEVICE;
 }
@@ -671,12 +668,8 @@ int mxfp4_linear_bwd(const void *dy, const void *x, const void *w, void *dx, voi
         return MXFP4_EALIGN;
     if ((N % 8) != 0 || (K % 8) != 0) return MXFP4_EALIGN;  // dense bf16 rows must stay 16-byte aligned
     uint8_t *ws = static_cast<uint8_t *>(workspace);
-    // (dY and X in one launch: one grid, and one store policy, which differs for tensors beyond the last-level cache)
-    const int64_t llc = int64_t(256) << 20;
     const bool dw_alone = dw && !dx && F.wgrad == MXFP4_FMT_E2M1 && cfg->geometry == MXFP4_GEOM_1D &&
-                          M < (int64_t(1) << 31) && N < (int64_t(1) << 31) && K < (int64_t(1) << 31) &&
-                          (M * N * 2 > llc) == (M * K * 2 > llc) &&
-                          ((N + 127) / 128 + (K + 127) / 128) * ((M / 32 + 7) / 8) < (int64_t(1) << 31);
+                          wgrad_operands_share_launch(M, N, K);
     if (dw_alone) {  // dY and X, both column-wise in MXFP4: one launch for the two tensors
         rc = quantize_axis_pair(MXFP4_AXIS_FIRST, cfg, dy, M, N, STREAM_DYT, ws + L.gtq, ws + L.gts, x, M, K, STREAM_XT,
                                 ws + L.xtq, ws + L.xts, hip_stream);

@@ -5,10 +5,9 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-namespace mxfp4 {
+#include "launch_limits.h"
 
-// HIP refuses a launch of 2^32 or more threads along one dimension of the grid.
-constexpr bool grid_fits(int64_t groups, int threads) { return groups < (int64_t(1) << 32) / threads; }
+namespace mxfp4 {
 
 struct QuantArgs {
     const uint16_t *x;  // bf16 [rows][ld]
@@ -26,14 +25,13 @@ constexpr uint64_t SEED_BASE_MASK = 0xFFFFFFFFFFFFull;
 
 // blocks along rows (1x32): q[rows][cols/2], s[rows][cols/32]
 // (b, if not null: a second tensor in the same launch, same hadamard, rounding and base seed; the two grids together
-// must stay below 2^31 workgroups)
+// must fit one, see launch_limits.h)
 hipError_t launch_quantize_rows(const QuantArgs &a, hipStream_t st, const QuantArgs *b = nullptr);
 // blocks down columns (32x1): q[cols][rows/2], s[cols][rows/32]
-// (b, if not null: a second tensor in the same launch, same hadamard, rounding and base seed)
+// (b, if not null: as above)
 hipError_t launch_quantize_cols(const QuantArgs &a, hipStream_t st, const QuantArgs *b = nullptr);
 // both from one pass over x: q, s as launch_quantize_cols; q_row, s_row as launch_quantize_rows
-// (b, if not null: a second tensor in the same launch, same hadamard, rounding and seed; the two grids together
-// must stay below 2^31 workgroups)
+// (b, if not null: as above)
 hipError_t launch_quantize_dual(const QuantArgs &a, const QuantArgs *b, hipStream_t st);
 // one scale per 32 x 32 region; the pair q, s (column-wise layout) or the pair q_row, s_row (row-wise layout)
 // may be null

@@ -25,7 +25,6 @@
 namespace mxfp4 {
 namespace {
 
-constexpr int64_t LLC_BYTES = int64_t(256) << 20;  // MI355X Infinity Cache
 
 // v: the block widened to fp32, in contraction order; 1D scaling (one scale per block).
 template <int HAD, int RND>
@@ -332,7 +331,7 @@ RowJob make_row_job(const QuantArgs &a)
     j.ld = a.ld;
     j.q = a.q;
     j.s = a.s;
-    j.groups = (uint32_t)((j.nblocks + 255) / 256);
+    j.groups = (uint32_t)rows_groups(a.rows, a.cols);
     j.dense = (a.ld == a.cols);
     j.key = make_key(a.seed);
     return j;
@@ -348,13 +347,13 @@ hipError_t launch_rows_h(const QuantArgs &a, const QuantArgs *b, hipStream_t st)
     if (b) j1 = make_row_job(*b);
     const unsigned grid = j0.groups + j1.groups;
     const uint32_t sign_mask = sign_mask_of(a.seed);
-    const bool streaming = a.rows * a.cols * 2 > LLC_BYTES;
-    if (b && streaming != (b->rows * b->cols * 2 > LLC_BYTES)) {  // the store policy is the launch's: one each
+    const bool streaming = beyond_llc(a.rows, a.cols);
+    if (b && streaming != beyond_llc(b->rows, b->cols)) {  // the store policy is the launch's: one each
         const hipError_t e = launch_rows_h<HAD>(a, nullptr, st);
         return e == hipSuccess ? launch_rows_h<HAD>(*b, nullptr, st) : e;
     }
 #define MXFP4_LAUNCH_ROWS(R, S) \
-    hipLaunchKernelGGL((quantize_rows_kernel<HAD, R, S>), dim3(grid), dim3(256), 0, st, j0, j1, sign_mask)
+    hipLaunchKernelGGL((quantize_rows_kernel<HAD, R, S>), dim3(grid), dim3(ROWS_THREADS), 0, st, j0, j1, sign_mask)
     if (a.rounding == RND_RNE) {
         if (streaming) MXFP4_LAUNCH_ROWS(RND_RNE, 1); else MXFP4_LAUNCH_ROWS(RND_RNE, 0);
     } else {
@@ -375,7 +374,7 @@ TileJob make_job(const QuantArgs &a)
     j.col_groups = (uint32_t)((a.cols + CT_COLS - 1) / CT_COLS);
     j.nblocks = (uint32_t)(j.col_groups * ((nrb + CT_RB - 1) / CT_RB));
     j.band_rows = j.nblocks < 2048 ? 0u : (MODE == MODE_COLS ? 16u : 2u);
-    j.streaming = a.rows * a.cols * 2 > LLC_BYTES;
+    j.streaming = beyond_llc(a.rows, a.cols);
     j.s_vec8 = ((nrb % 8) == 0) && ((reinterpret_cast<uintptr_t>(a.s) % 8) == 0);
     j.s_row_vec4 = MODE != MODE_COLS && a.s_row != nullptr && (((a.cols / 32) % 4) == 0) &&
                    ((reinterpret_cast<uintptr_t>(a.s_row) % 4) == 0);
@@ -396,7 +395,7 @@ hipError_t launch_cols_h(const QuantArgs &a, const QuantArgs *b, hipStream_t st)
     const uint32_t sign_mask = sign_mask_of(a.seed);
     const bool streaming = j0.streaming && (!b || j1.streaming);  // (two tensors in one launch: only if both want it)
 #define MXFP4_LAUNCH_COLS(R, S) \
-    hipLaunchKernelGGL((quantize_cols_kernel<HAD, R, MODE, S>), grid, dim3(512), 0, st, j0, j1, sign_mask)
+    hipLaunchKernelGGL((quantize_cols_kernel<HAD, R, MODE, S>), grid, dim3(COLS_THREADS), 0, st, j0, j1, sign_mask)
     if (a.rounding == RND_RNE) {
         if (streaming) MXFP4_LAUNCH_COLS(RND_RNE, 1); else MXFP4_LAUNCH_COLS(RND_RNE, 0);
     } else {

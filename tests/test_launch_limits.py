@@ -1,0 +1,35 @@
+"""CPU-only checks of the host rules about launch grids (plain C++ constants): which tensors share a launch."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2605_09825_amd", "csrc")
+
+
+def holds(condition):
+    cxx = shutil.which("g++") or shutil.which("c++")
+    if cxx is None:
+        pytest.skip("no host C++ compiler")
+    src = '#include "launch_limits.h"\nusing namespace mxfp4;\nconstexpr int64_t ONE = 1;\nstatic_assert(%s, "");\n' % condition
+    return subprocess.run([cxx, "-std=c++17", "-fsyntax-only", "-I", CSRC, "-x", "c++", "-"], input=src, text=True,
+                          capture_output=True).returncode == 0
+
+
+@pytest.mark.parametrize("condition", [
+    # fewer than 2^32 threads along a dimension
+    "grid_fits((ONE << 24) - 1, 256) && !grid_fits(ONE << 24, 256)",
+    "grid_fits((ONE << 23) - 1, 512) && !grid_fits(ONE << 23, 512)",
+    # workgroups of the quantisers: one block, a last workgroup of one block, one column more than a tile
+    "rows_groups(1, 32) == 1 && rows_groups(257, 32) == 2 && rows_groups(8, 96) == 1",
+    "cols_groups(32, 2) == 1 && cols_groups(256, 128) == 1 && cols_groups(288, 130) == 4",
+    # dY and X of the weight gradient alone: together while one grid holds both
+    "wgrad_operands_share_launch(32, 8, 8) && wgrad_operands_share_launch(16384, 4096, 4096)",
+    "wgrad_operands_share_launch((ONE << 30) - 256, 8, 8) && !wgrad_operands_share_launch(ONE << 30, 8, 8)",
+    "!wgrad_operands_share_launch(ONE << 31, 8, 8) && !wgrad_operands_share_launch(32, ONE << 40, 8)",
+    # ... and while both are stored alike: one of them beyond the last-level cache
+    "!wgrad_operands_share_launch(4096, 64, 32896) && wgrad_operands_share_launch(4096, 32776, 32896)",
+])
+def test_rule(condition):
+    assert holds(condition) and not holds("!(%s)" % condition)
