@@ -34,6 +34,32 @@ def test_products_too_small_for_whole_tiles():
         assert route(24, 6144, 4096, **f) == route(8192, 6144, 4096, **f) == mx.ROUTE_ANY_SHAPE
 
 
+def test_short_products_stay_on_the_any_shape_kernel():
+    ANY = mx.ROUTE_ANY_SHAPE
+    fp32 = dict(out_dtype=mx.OUT_FP32)
+    # rows of the output in no whole 4s: below 256 bytes of codes per row, at most a tile of 64 x 64 per compute unit
+    for C, f in [(480, {}), (224, FP8)]:
+        assert route(1000, 1000, C, ld_out=1003, **f) == ANY
+        assert route(1000, 1000, C + 32, ld_out=1003, **f) == mx.ROUTE_EDGE_64
+        assert route(1000, 1000, C, ld_out=1003, out_dtype=mx.OUT_FP32, accumulate=True, **f) == ANY
+        assert route(1000, 1000, C, **f) == mx.ROUTE_EDGE_64
+    assert route(1000, 1000, 256, ld_out=1003) == mx.ROUTE_EDGE_64 and route(32, 1000, 256, ld_out=1003) == ANY
+    assert route(10736, 88, 128, ld_out=91) == ANY and route(10736, 88, 160, ld_out=91) != ANY       # 336 tiles
+    assert route(64 * 385, 30, 128, ld_out=31) != ANY
+    # few rows or columns
+    assert route(32, 1000, 256) == route(1000, 32, 256) == route(32, 1000, 256, **fp32) == ANY
+    assert route(33, 1000, 256) == route(32, 1000, 256, accumulate=True, **fp32) == mx.ROUTE_EDGE_64
+    assert route(1000, 16, 608, accumulate=True, **fp32) == route(16, 1000, 288, **FP8) == ANY
+    assert route(1000, 16, 512) == route(16, 1000, 512) == mx.ROUTE_EDGE_64
+    assert route(1000, 16, 640) == route(1000, 17, 512) == route(16, 1000, 320, **FP8) == mx.ROUTE_EDGE_64
+    assert route(64 * 384, 16, 32) == ANY and route(64 * 384 + 1, 16, 32) != ANY
+    assert route(1000, 20, 256, accumulate=True, **fp32) == mx.ROUTE_EDGE_64
+    # one K-step, columns in no whole 16s
+    assert route(200, 200, 128) == ANY and route(200, 208, 128) == route(200, 200, 160) == mx.ROUTE_EDGE_64
+    # a pair is one launch all the same
+    assert pair((200, 200, 128), (32, 64, 128))[0] == mx.PAIR_EDGE
+
+
 def test_pairs():
     dgrad_wgrad = lambda M, N, K: ((M, K, N), (N, K, M))
     assert pair(*dgrad_wgrad(8192, 6144, 4096)) == (mx.PAIR_SIDE_BY_SIDE, 0, 16, 0)
