@@ -60,6 +60,15 @@ def test_short_products_stay_on_the_any_shape_kernel():
     assert pair((200, 200, 128), (32, 64, 128))[0] == mx.PAIR_EDGE
 
 
+def test_short_rows_take_small_tiles_while_the_chip_holds_them():
+    for C, f in [(1024, {}), (512, FP8)]:
+        assert route(64 * 64, 64 * 8, C, **f) == mx.ROUTE_EDGE_64          # 512 tiles of 64 x 64, 512 bytes per row
+        assert route(64 * 64, 64 * 8, C + 32, **f) == mx.ROUTE_EDGE_128
+        assert route(64 * 64 + 1, 64 * 8, C, **f) != mx.ROUTE_EDGE_64
+    assert pair((64 * 32, 64 * 8, 1024), (64 * 32, 64 * 8, 512)) == (mx.PAIR_EDGE, 0, 0, 0)
+    assert pair((64 * 32, 64 * 8, 1056), (64 * 32, 64 * 8, 512)) == (mx.PAIR_EDGE, 0, 1, 0)
+
+
 def test_pairs():
     dgrad_wgrad = lambda M, N, K: ((M, K, N), (N, K, M))
     assert pair(*dgrad_wgrad(8192, 6144, 4096)) == (mx.PAIR_SIDE_BY_SIDE, 0, 16, 0)
