@@ -1405,18 +1405,18 @@ static EdgeChoice choose_edge(const GemmArgs &g0, const GemmArgs *g1 = nullptr)
 
 // Short products that one workgroup per CU covers stay on the any-shape kernel where its launch, 1 us shorter (no LDS, no
 // stages), outweighs its stores of 2 or 4 bytes and its loads in the open: less than two whole stages (256 bytes) of codes
-// per row, or 257 to 319 bytes where the output has at most 16 rows or columns, and
+// per row, in MXFP8 less than three where the output has at most 16 rows or columns, and
 //   * at most 16 columns (also with a workgroup on every other CU more), or without accumulation at most 32 rows or columns:
-//     any-shape time over ragged-shape time 0.60 to 1.07, 0.78 on average;
+//     any-shape time over ragged-shape time 0.60 to 1.11, 0.78 on average;
 //   * rows of the output that the ragged-shape kernel cannot store 4 elements at a time either, except one whole stage (up
 //     to 64 bytes also with a workgroup on every other CU more): 0.70 to 1.19, 0.88;
 //   * at most 64 bytes, columns in no whole 16s, no accumulation, half the CUs: 0.77 to 1.08, 0.91.
-// Elsewhere 0.69 to 5, 1.35.  Measured back to back in a graph over 2400 sizes up to 20000 x 20000 x 2048: 16 x 16 x 32 2.0 us
+// Elsewhere 0.79 to 5, 1.36.  Measured back to back in a graph over 2400 sizes up to 20000 x 20000 x 2048: 16 x 16 x 32 2.0 us
 // against 3.1, 1000 x 1000 x 128 with 1003 elements per row 4.0 against 4.4.  Both kernels give the same bits.
 static bool short_product(const GemmArgs &g)
 {
     const int64_t bytes = g.a_fmt ? g.C : g.C / 2, tiles = (g.Ra + 63) / 64 * ((g.Rb + 63) / 64);
-    if (bytes == 256 || bytes >= (g.Ra <= 16 || g.Rb <= 16 ? 320 : 256)) return false;
+    if (bytes >= (g.a_fmt && (g.Ra <= 16 || g.Rb <= 16) ? 384 : 256)) return false;
     if (g.Rb <= 16) return tiles <= NUM_CUS * 3 / 2;
     if (tiles <= NUM_CUS && !g.accumulate && (g.Ra <= 32 || g.Rb <= 32)) return true;
     if (g.ld % 4 != 0) return tiles <= NUM_CUS ? bytes != 128 : bytes <= 64 && tiles <= NUM_CUS * 3 / 2;
