@@ -1620,14 +1620,19 @@ static double rag_cost(const GemmArgs &g, int cus)
 // x 4096: 16.8 us on 64 tiles, 11.6 us on 128 x 64 ones; in MXFP8, which has no narrow tile, 42.1 and 19.4), where it
 // cuts a small product into several launches (300 x 520 x 1024: 15.5 us in three, 5.5 us in one) and where strips beside a
 // large interior cost a launch and a poorly filled chip (4010 x 6144 x 4096: 63 us, 55 in one).
+// Whole 128s of columns but not 256s: the estimates of 256 x 128 tiles throughout and of 256 x 256 ones moved back lie within
+// a few per cent of each other, and decide except for a bf16 output and C < 2048.  Where they prefer the moved-back tiles
+// (430 sizes on two cards), these take on average, against the others: bf16 1.04 times as long for C < 2048 (14848 x 3456 x
+// 1024 50.8 us, 42.8), 1.01 at 2048, 0.97 beyond; fp32 0.98 at every C.
 static GemmRoute choose_route(const GemmArgs &g, const GemmPlan &plan, int cus)
 {
     GemmRoute c = any_route(g);
     if (plan.n != 1 || plan.part[0].kind != GEMM_ANY) {
         const double us = plan_cost(g, plan, cus);
-        if (us <= c.us) c = GemmRoute{ROUTE_BLOCKS, us};
+        if (us <= c.us || c.kind == ROUTE_ANY_SHAPE) c = GemmRoute{ROUTE_BLOCKS, us};
     }
-    const double rag = rag_cost(g, cus);
+    const bool narrow = plan.n == 1 && plan.part[0].kind == GEMM_TILED_128 && !g.out_fp32 && g.C < 2048;
+    const double rag = narrow ? NO_ROUTE : rag_cost(g, cus);
     if (rag < c.us) c = GemmRoute{ROUTE_RAGGED_TILED, rag};
     return c;
 }

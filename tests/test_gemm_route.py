@@ -24,6 +24,14 @@ def test_large_ragged_products_leave_the_plan():
     assert route(8192, 6144, 4064, ld_out=6148) == mx.ROUTE_EDGE_256    # rows of the output not 16-byte aligned
 
 
+def test_whole_128s_of_columns():
+    for shape in [(14848, 3456, 1024), (7168, 10368, 1024), (6144, 5760, 1792)]:
+        assert route(*shape) == mx.ROUTE_BLOCKS and mx.mxfp4_gemm_plan(*shape)[0][0] == mx.GEMM_TILED_128
+        assert route(*shape, out_dtype=mx.OUT_FP32) == mx.ROUTE_RAGGED_TILED
+    assert route(6144, 5760, 2048) == mx.ROUTE_RAGGED_TILED
+    assert route(14592, 3448, 1056) == mx.ROUTE_RAGGED_TILED            # no whole tiles of either width
+
+
 def test_products_too_small_for_whole_tiles():
     assert route(24, 6144, 4096) == mx.ROUTE_EDGE_64
     assert route(2080, 4320, 1440) == mx.ROUTE_EDGE_128
