@@ -39,3 +39,15 @@ def first_mismatch(a: np.ndarray, b: np.ndarray) -> str:
         return "equal"
     i = tuple(bad[0])
     return f"{len(bad)} of {a.size} differ; first at {i}: gpu {a[i]:#x} vs oracle {b[i]:#x}"
+
+
+def assert_runs_on(kernel, Ra, Rb, C, fmt=0, **kw):
+    """The kernel that a product of this shape runs on is the one that the test is about (kernel: a name below)."""
+    routes = {"any": mx.ROUTE_ANY_SHAPE, "64x64": mx.ROUTE_EDGE_64, "128x64": mx.ROUTE_EDGE_128,
+              "128x256": mx.ROUTE_EDGE_256, "moved back": mx.ROUTE_RAGGED_TILED}
+    kinds = {"wide": mx.GEMM_TILED_256, "narrow": mx.GEMM_TILED_128, "tail": mx.GEMM_TILED_256_TAIL_128}
+    got = mx.mxfp4_gemm_route(Ra, Rb, C, fmt, fmt, **kw)
+    assert got == routes.get(kernel, mx.ROUTE_BLOCKS), (kernel, got)
+    if kernel in kinds:
+        plan = mx.mxfp4_gemm_plan(Ra, Rb, C, fmt, fmt)
+        assert len(plan) == 1 and plan[0][0] == kinds[kernel], (kernel, plan)

@@ -11,7 +11,7 @@ import torch
 import oracle
 import paper_2605_09825_amd as mx
 from paper_2605_09825_amd import synth
-from gpu_util import first_mismatch
+from gpu_util import assert_runs_on, first_mismatch
 from test_gpu_gemm import assert_close, close_bf16, gpu, structured_check
 
 pytestmark = pytest.mark.gpu
@@ -151,6 +151,7 @@ def test_fp8_many_tiles_per_workgroup_whole_output(C):
     # 17 x 17 = 289 tiles of 256 x 256: more than one tile per CU, so tiles hand over inside a workgroup;
     # narrow exponent range, so the MXFP4 bound applies; every element compared
     Ra = Rb = 256 * 17
+    assert_runs_on("wide", Ra, Rb, C, mx.FMT_E4M3)
     rng = np.random.default_rng(C)
 
     def narrow(R):
@@ -167,6 +168,21 @@ def test_fp8_many_tiles_per_workgroup_whole_output(C):
     torch.cuda.synchronize()
     assert_close(f32.cpu().numpy(), want, absum)
     assert torch.equal(b16, f32.to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("shape,kernel", [((30, 48, 96), "any"), ((300, 520, 1024), "64x64"), ((4096, 4096, 1024), "wide"),
+                                          ((4300, 4352, 1280), "moved back")])
+def test_fp8_scale_byte_ff_marks_its_row_only(shape, kernel):
+    # 0xFF, the NaN of the scale format, over live codes (all finite): its row of A or row of B is NaN, nothing else
+    Ra, Rb, C = shape
+    assert_runs_on(kernel, Ra, Rb, C, mx.FMT_E4M3, out_dtype=mx.OUT_FP32)
+    rng = np.random.default_rng(C)
+    (aq, as_), (bq, bs) = rand_fp8(rng, Ra, C), rand_fp8(rng, Rb, C)
+    as_[3, C // 32 - 1] = 0xFF
+    bs[Rb - 1, 0] = 0xFF
+    got = mx.mxfp4_gemm(gpu(aq), gpu(as_), gpu(bq), gpu(bs), out_dtype=mx.OUT_FP32, a_format=1, b_format=1).cpu().numpy()
+    nan = np.isnan(got)
+    assert nan[3].all() and nan[:, Rb - 1].all() and nan.sum() == Ra + Rb - 1
 
 
 def test_fp8_linear_stage_on_real_operands():
@@ -274,6 +290,8 @@ def test_backward_side_by_side_launch_with_mxfp8_stages(fmts):
     # alone (launches of their own), and against the oracle on a patch in every tile plus whole rows and columns.
     M = N = K = 4096
     fF, fD, fW = fmts
+    for acc in (False, True):
+        assert mx.mxfp4_gemm_pair_route((M, K, N), (N, K, M), (fD, fW), accumulate1=acc)[0] == mx.PAIR_SIDE_BY_SIDE
     x = synth.normal(M, K, 1.0, 2, synth.STREAM_X)
     w = synth.normal(N, K, 0.02, 2, synth.STREAM_W)
     dy = synth.normal(M, N, 1e-3, 2, synth.STREAM_DY)
@@ -326,8 +344,9 @@ def _e4m3(v):
     raise ValueError(v)
 
 
-@pytest.mark.parametrize("shape", [(16, 16, 128), (256, 256, 1024)])  # any-shape kernel, tiled kernel
-def test_e4m3_products_below_2_to_minus_13_of_their_group_maximum_are_dropped(shape):
+@pytest.mark.parametrize("shape,kernel", [((16, 16, 128), "any"), ((256, 256, 1024), "64x64"),
+                                          ((4096, 4096, 1024), "wide"), ((4300, 4352, 1280), "moved back")])
+def test_e4m3_products_below_2_to_minus_13_of_their_group_maximum_are_dropped(shape, kernel):
     # One row of A holds 256 at k = 0 and a small value at k = k0, everything else 0; B is all ones.  The exact result
     # is 256 + small.  Observed on the MI355X matrix unit and asserted here: inside a group of 8 consecutive K-elements
     # the products are aligned to the exponent of the largest and what lies below 2^-13 of that power of two is
@@ -335,6 +354,7 @@ def test_e4m3_products_below_2_to_minus_13_of_their_group_maximum_are_dropped(sh
     # the FP8 stages, 7 * 2^-13 * sum|a||b| + the MXFP4 bound: seven of a group's eight products can each lose
     # less than 2^-13 of the largest.
     Ra, Rb, C = shape
+    assert_runs_on(kernel, Ra, Rb, C, mx.FMT_E4M3, out_dtype=mx.OUT_FP32)
     ones = np.full((Rb, C), E4M3_ONE, dtype=np.uint8)
     s127a = np.full((Ra, C // 32), 127, dtype=np.uint8)
     s127b = np.full((Rb, C // 32), 127, dtype=np.uint8)
@@ -347,7 +367,7 @@ def test_e4m3_products_below_2_to_minus_13_of_their_group_maximum_are_dropped(sh
         torch.cuda.synchronize()
         o = out.cpu().numpy()
         assert np.all(o[0] == o[0, 0]) and np.all(o[1:] == 0)
-        want, absum = oracle.gemm_fmt(a, s127a, 1, ones, s127b, 1)
+        want, absum = oracle.gemm_fmt(a[:1], s127a[:1], 1, ones[:1], s127b[:1], 1)
         assert want[0, 0] == 256.0 + small
         assert abs(float(o[0, 0]) - want[0, 0]) <= FP8_RTOL * absum[0, 0]     # the documented bound always holds
         return float(o[0, 0])
@@ -359,7 +379,7 @@ def test_e4m3_products_below_2_to_minus_13_of_their_group_maximum_are_dropped(sh
             assert result(3 * 2.0 ** -6, k0) == 256.0 + 2.0 ** -5  # truncated, not rounded (would be 256.0625)
         for k0 in (8, 9, 15, 16, 31, 32, 64, 127):                # another group: an exact fp32 addition
             assert result(2.0 ** -6, k0) == 256.0 + 2.0 ** -6
-    else:                # the 32x32x64 instruction of the tiled kernel: the bound, and exactness above 2^-13
+    else:                # the 32x32x64 instruction of the other kernels: the bound, and exactness above 2^-13
         for k0 in (1, 7, 8, 33, 500, 1023):
             assert result(2.0 ** -5, k0) == 256.0 + 2.0 ** -5
             got = result(2.0 ** -6, k0)

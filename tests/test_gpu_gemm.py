@@ -7,6 +7,7 @@ import torch
 import oracle
 import paper_2605_09825_amd as mx
 from paper_2605_09825_amd import synth
+from gpu_util import assert_runs_on
 
 pytestmark = pytest.mark.gpu
 RTOL = 1e-5
@@ -82,12 +83,15 @@ def as_f32(want):
         return want.astype(np.float32)
 
 
-@pytest.mark.parametrize("shape", [(64, 48, 32), (256, 256, 1024)])
-def test_wide_scale_range_and_exactness_on_small_sums(shape):
+@pytest.mark.parametrize("shape,kernel", [((64, 48, 32), "64x64"), ((30, 48, 32), "any"), ((256, 256, 1024), "64x64"),
+                                          ((4096, 4096, 1024), "wide"), ((2048, 2560, 1024), "narrow"),
+                                          ((4352, 4352, 1024), "tail"), ((4200, 4104, 1056), "moved back")])
+def test_wide_scale_range_and_exactness_on_small_sums(shape, kernel):
     # one live block per row: at most 32 products, partial sums < 2^24 in units of the smallest product, so the
     # fp32 result must be exact -- also where it is a subnormal number (the matrix unit does not flush them) or
     # overflows (to infinity).  Scale bytes 60..200 put results between 2^-136 and beyond 2^128.
     Ra, Rb, C = shape
+    assert_runs_on(kernel, Ra, Rb, C, out_dtype=mx.OUT_FP32)
     rng = np.random.default_rng(1)
     aq, as_ = rand_operand(rng, Ra, C, 60, 200)
     bq, bs = rand_operand(rng, Rb, C, 60, 190)
@@ -114,13 +118,16 @@ def test_results_in_the_subnormal_range_are_not_flushed():
     assert np.array_equal(got.astype(np.float64), want)
 
 
-@pytest.mark.parametrize("shape", [(64, 48, 96), (512, 256, 1024)])  # any-shape kernel, tiled kernel
+@pytest.mark.parametrize("shape,kernel", [((64, 48, 96), "64x64"), ((30, 48, 96), "any"), ((512, 256, 1024), "64x64"),
+                                          ((4096, 4096, 1024), "wide"), ((2048, 2560, 1024), "narrow"),
+                                          ((4352, 4352, 1024), "tail")])
 @pytest.mark.parametrize("out_dtype", [mx.OUT_FP32, mx.OUT_BF16])
-def test_scale_byte_ff_gives_nan(shape, out_dtype):
+def test_scale_byte_ff_gives_nan(shape, kernel, out_dtype):
     # 0xFF is the NaN of the E8M0 scale format (the quantiser writes it for a block that held a NaN or an
     # infinity, with all codes 0): every output whose row of A or row of B contains such a block is NaN, whatever
     # the codes under it, and nothing else is
     Ra, Rb, C = shape
+    assert_runs_on(kernel, Ra, Rb, C, out_dtype=out_dtype)
     rng = np.random.default_rng(8)
     aq, as_ = rand_operand(rng, Ra, C)
     bq, bs = rand_operand(rng, Rb, C)
@@ -242,6 +249,7 @@ def test_many_tiles_per_workgroup_whole_output(C):
     # workgroup; 4, 5 and 9 K-stages of 256 (with an odd count the stage buffers swap roles from one tile of a
     # workgroup to the next).  Every element of the output is compared, fp32 and bf16.
     Ra = Rb = 256 * 17
+    assert_runs_on("tail", Ra, Rb, C)
     rng = np.random.default_rng(5)
     aq, as_ = rand_operand(rng, Ra, C)
     bq, bs = rand_operand(rng, Rb, C)
@@ -264,6 +272,8 @@ def test_narrow_tiles_whole_output(shape):
     # the chip has compute units, run on 256 x 128 tiles; with 289 and 315 of them a workgroup hands over from tile
     # to tile (odd and even numbers of K stages).  Every element, fp32, bf16 and accumulating.
     Ra, Rb, C = shape
+    assert_runs_on("narrow", Ra, Rb, C)
+    assert_runs_on("narrow", Ra, Rb, C, out_dtype=mx.OUT_FP32, ld_out=Rb + 8)
     rng = np.random.default_rng(Ra + Rb + C)
     aq, as_ = rand_operand(rng, Ra, C)
     bq, bs = rand_operand(rng, Rb, C)
@@ -289,7 +299,7 @@ def test_part_filled_last_round_runs_on_narrow_tiles(shape):
     # halves on 256 x 128 tiles in the same launch (896 tiles: the cut after 768 falls inside a row of 56 tiles);
     # every element of the output against the oracle, also when the product is added to the output
     Ra, Rb, C = shape
-    assert mx.mxfp4_gemm_plan(Ra, Rb, C)[0][0] == mx.GEMM_TILED_256_TAIL_128
+    assert_runs_on("tail", Ra, Rb, C)
     rng = np.random.default_rng(Ra * 3 + Rb + C)
     aq, as_ = rand_operand(rng, Ra, C)
     bq, bs = rand_operand(rng, Rb, C)
@@ -319,12 +329,15 @@ def test_config2_shape_every_tile():
 @pytest.mark.parametrize("shapes,acc", [
     (((4096, 2048, 4096), (4096, 2048, 4096)), False),   # 128 + 128 tiles, equal work: side by side, 128 CUs each
     (((4096, 4096, 1024), (2048, 4096, 1024)), True),    # 256 + 128 tiles: split 21 : 11 per XCD, second accumulating
-    (((512, 256, 1024), (96, 160, 224)), False),         # too few tiles / ragged: one after the other
+    (((512, 256, 1024), (96, 160, 224)), False),         # too few tiles / ragged: both on the ragged-shape kernel
+    (((8192, 1024, 1024), (1024, 1024, 8192)), True),    # one after the other
     (((300, 520, 1024), (0, 64, 64)), False),            # the second product empty
 ])
 def test_gemm_pair_equals_the_two_separate_calls(shapes, acc):
     # two independent products (App. C.2, C.3) in one call: bit for bit the results of two mxfp4_gemm calls, and
     # the first of them against the oracle
+    kinds = {4096: mx.PAIR_SIDE_BY_SIDE, 512: mx.PAIR_EDGE, 8192: mx.PAIR_APART, 300: mx.PAIR_APART}
+    assert mx.mxfp4_gemm_pair_route(*shapes, accumulate1=acc)[0] == kinds[shapes[0][0]]
     rng = np.random.default_rng(sum(shapes[0]) + sum(shapes[1]))
     ops = []
     for Ra, Rb, C in shapes:
@@ -343,11 +356,16 @@ def test_gemm_pair_equals_the_two_separate_calls(shapes, acc):
 
 
 @pytest.mark.parametrize("fmt", [mx.FMT_E2M1, mx.FMT_E4M3])
-@pytest.mark.parametrize("shape", [(512, 768, 1024), (512, 640, 1024), (768, 2560, 1024), (4096, 4096, 1024)])
-def test_every_output_variant_of_the_tiled_kernels_agrees_with_the_fp32_result(shape, fmt):
-    # 256 x 128 tiles (MXFP4 below 256 tiles), 256 x 256 tiles (MXFP8; MXFP4 at 256 tiles) and a strided output: the bf16 output is the
-    # rounding of the fp32 output, and the accumulating call adds the fp32 output to what the buffer held, bit for bit
+@pytest.mark.parametrize("shape,kernel4,kernel8", [
+    ((512, 768, 1024), "64x64", "64x64"), ((512, 640, 1024), "64x64", "64x64"), ((768, 2560, 1024), "64x64", "128x64"),
+    ((2048, 2560, 1024), "narrow", "128x256"), ((4096, 2176, 1280), "narrow", "moved back"),
+    ((4096, 4096, 1024), "wide", "wide"), ((4352, 4352, 1024), "tail", "wide")])
+def test_every_output_variant_of_the_tiled_kernels_agrees_with_the_fp32_result(shape, kernel4, kernel8, fmt):
+    # each kernel's epilogues, and a strided output: the bf16 output is the rounding of the fp32 output, and the
+    # accumulating call adds the fp32 output to what the buffer held, bit for bit
     Ra, Rb, C = shape
+    for dt, acc in ((mx.OUT_FP32, False), (mx.OUT_BF16, False), (mx.OUT_FP32, True)):
+        assert_runs_on(kernel8 if fmt else kernel4, Ra, Rb, C, fmt, out_dtype=dt, accumulate=acc)
     rng = np.random.default_rng(Ra + Rb + fmt)
     if fmt == mx.FMT_E2M1:
         a, b = rand_operand(rng, Ra, C), rand_operand(rng, Rb, C)
@@ -366,12 +384,15 @@ def test_every_output_variant_of_the_tiled_kernels_agrees_with_the_fp32_result(s
     assert torch.equal(big[:, :Rb], f32 + 0.375) and bool((big[:, Rb:] == 0.375).all())
 
 
+@pytest.mark.parametrize("shapes,kind", [
+    (((4096, 4096, 1024), (2048, 4096, 2048)), mx.PAIR_SIDE_BY_SIDE),   # 256 and 128 tiles, equal work: 128 compute units each
+    (((2048, 4096, 1024), (4096, 2048, 1280)), mx.PAIR_APART)])         # 128 tiles each, too few for one of the shares
 @pytest.mark.parametrize("dt0,dt1,acc1", [(mx.OUT_BF16, mx.OUT_BF16, False), (mx.OUT_BF16, mx.OUT_FP32, False),
                                           (mx.OUT_BF16, mx.OUT_FP32, True), (mx.OUT_FP32, mx.OUT_BF16, False),
                                           (mx.OUT_FP32, mx.OUT_FP32, False), (mx.OUT_FP32, mx.OUT_FP32, True)])
-def test_every_output_variant_of_the_side_by_side_launch(dt0, dt1, acc1):
-    # two problems of 128 tiles each: side by side on 128 compute units each; every combination of output types
-    shapes = ((2048, 4096, 1024), (4096, 2048, 1280))
+def test_every_output_variant_of_the_side_by_side_launch(dt0, dt1, acc1, shapes, kind):
+    # every combination of output types
+    assert mx.mxfp4_gemm_pair_route(*shapes, out_dtypes=(dt0, dt1), accumulate1=acc1)[0] == kind
     rng = np.random.default_rng(dt0 * 4 + dt1 * 2 + acc1)
     ops = [tuple(gpu(t) for t in rand_operand(rng, Ra, C) + rand_operand(rng, Rb, C)) for Ra, Rb, C in shapes]
     (a0q, a0s, b0q, b0s), (a1q, a1s, b1q, b1s) = ops
@@ -383,3 +404,44 @@ def test_every_output_variant_of_the_side_by_side_launch(dt0, dt1, acc1):
     mx.mxfp4_gemm_pair((a0q, a0s), (b0q, b0s), out0, (a1q, a1s), (b1q, b1s), out1, accumulate1=acc1)
     torch.cuda.synchronize()
     assert torch.equal(out0, want0) and torch.equal(out1, want1)
+
+
+def test_short_mxfp4_products_on_the_any_shape_kernel_equal_the_ragged_shape_kernel():
+    # which of the two runs depends on the length of an output row: every remainder of 128 elements and of the tile
+    # sizes up to the line between them, bit for bit
+    rng = np.random.default_rng(12)
+    for Ra, Rb, C in [(33, 48, 32), (64, 80, 96), (130, 112, 160), (63, 208, 288), (70, 144, 480)]:
+        aq, as_ = rand_operand(rng, Ra, C, 100, 150)
+        bq, bs = rand_operand(rng, Rb, C, 100, 150)
+        ops = [gpu(t) for t in (aq, as_, bq, bs)]
+        for dt, acc in ((mx.OUT_FP32, False), (mx.OUT_BF16, False), (mx.OUT_FP32, True)):
+            canvas = {ld: torch.full((Ra, ld), 0.5, dtype=torch.float32 if dt else torch.bfloat16, device="cuda:0")
+                      for ld in (Rb + 1, Rb + 12)}
+            for ld, o in canvas.items():
+                assert_runs_on("any" if ld % 4 else "64x64", Ra, Rb, C, ld_out=ld, out_dtype=dt, accumulate=acc)
+                mx.mxfp4_gemm(*ops, out=o[:, :Rb], out_dtype=dt, accumulate=acc)
+            assert torch.equal(canvas[Rb + 1][:, :Rb], canvas[Rb + 12][:, :Rb])
+            assert all(bool((o[:, Rb:] == 0.5).all()) for o in canvas.values())
+
+
+@pytest.mark.parametrize("fmt", [mx.FMT_E2M1, mx.FMT_E4M3])
+def test_contraction_beyond_the_ragged_shape_kernels_offsets(fmt):
+    # C = 2^24: the any-shape kernel; one live element in each of 96 blocks spread over the row and its end, products
+    # and sums exact
+    Ra, Rb, C = 3, 2, 1 << 24
+    assert_runs_on("any", Ra, Rb, C, fmt, out_dtype=mx.OUT_FP32)
+    blocks = np.linspace(0, C // 32 - 1, 96).astype(np.int64)
+    rng = np.random.default_rng(13)
+    one = {mx.FMT_E2M1: (0x2, 0xA), mx.FMT_E4M3: (0x38, 0xB8)}[fmt]     # +1, -1
+
+    def operand(R):
+        q = np.zeros((R, C // 32, 16 if fmt == mx.FMT_E2M1 else 32), dtype=np.uint8)
+        v = rng.integers(0, 2, size=(R, len(blocks)))
+        q[:, blocks, 0] = np.where(v, one[0], one[1])
+        s = np.full((R, C // 32), 127, dtype=np.uint8)
+        e = rng.integers(0, 5, size=(R, len(blocks)))
+        s[:, blocks] = 127 + e
+        return q.reshape(R, -1), s, np.where(v, 1.0, -1.0) * 2.0 ** e
+    (aq, as_, av), (bq, bs, bv) = operand(Ra), operand(Rb)
+    got = mx.mxfp4_gemm(gpu(aq), gpu(as_), gpu(bq), gpu(bs), out_dtype=mx.OUT_FP32, a_format=fmt, b_format=fmt)
+    assert np.array_equal(got.cpu().numpy().astype(np.float64), av @ bv.T)

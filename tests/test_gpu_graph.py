@@ -11,11 +11,16 @@ from paper_2605_09825_amd import synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("shape,had,rnd", [((512, 768, 1024), mx.HAD_DET, mx.RNE),
-                                           ((512, 768, 1024), mx.HAD_NONE, mx.SR),
-                                           ((96, 160, 224), mx.HAD_RANDSIGN, mx.RNE)])
-def test_recorded_training_step_replays_bit_exactly(shape, had, rnd):
+# small tiles; gradients on the tiled kernel side by side, on narrow beside wide tiles, ragged
+@pytest.mark.parametrize("shape,had,rnd,pair", [((512, 768, 1024), mx.HAD_DET, mx.RNE, mx.PAIR_EDGE),
+                                                ((512, 768, 1024), mx.HAD_NONE, mx.SR, mx.PAIR_EDGE),
+                                                ((96, 160, 224), mx.HAD_RANDSIGN, mx.RNE, mx.PAIR_EDGE),
+                                                ((2048, 2048, 4096), mx.HAD_DET, mx.RNE, mx.PAIR_SIDE_BY_SIDE),
+                                                ((2048, 1280, 2560), mx.HAD_DET16, mx.RNE, mx.PAIR_NARROW_BESIDE_WIDE),
+                                                ((2080, 4320, 1440), mx.HAD_DET, mx.SR, mx.PAIR_EDGE)])
+def test_recorded_training_step_replays_bit_exactly(shape, had, rnd, pair):
     M, N, K = shape
+    assert mx.mxfp4_gemm_pair_route((M, K, N), (N, K, M))[0] == pair
     dev = "cuda:0"
     cfg = mx.make_cfg(had, rnd, 5, y_dtype=mx.OUT_BF16, dx_dtype=mx.OUT_BF16, dw_dtype=mx.OUT_FP32)
     inputs = [(synth.normal(M, K, 1.0, i, synth.STREAM_X).to(dev), synth.normal(N, K, 0.02, i, synth.STREAM_W).to(dev),

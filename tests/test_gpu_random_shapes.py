@@ -85,7 +85,7 @@ def test_gemm_on_random_shapes_around_the_tile_sizes(seed):
 def test_linear_calls_on_random_shapes_and_modes():
     rng = np.random.default_rng(31)
     for it in range(20):
-        big = it % 5 == 0   # every fifth case reaches the tiled GEMM kernels
+        big = it % 5 == 0   # every fifth case is in whole tiles (too few of them for the tiled GEMM kernels)
         M = 256 * int(rng.integers(1, 6)) if big else 32 * int(rng.integers(1, 12))
         N = 256 * int(rng.integers(1, 6)) if big else 32 * int(rng.integers(1, 12))
         K = 256 * int(rng.integers(4, 8)) if big else 32 * int(rng.integers(1, 12))

@@ -40,7 +40,7 @@ def fwd_both_ways(M, N, K, had, rnd, y_dtype, seed):
 
 
 def test_static_scratch_forward_equals_workspace_forward_twice():
-    # first call: 3 x 3 tiles of the tiled GEMM plus ragged edges, rotated, fp32 out; the second is smaller
+    # first call: ragged edges, rotated, fp32 out; the second is smaller
     # (its operands overwrite only the front of the array, the rest still holds the first call's bytes)
     a, b = fwd_both_ways(800, 832, 1280, mx.HAD_DET, mx.RNE, mx.OUT_FP32, 1)
     assert np.array_equal(a, b)
@@ -48,6 +48,10 @@ def test_static_scratch_forward_equals_workspace_forward_twice():
     assert np.array_equal(a, b)
     # and a larger one again after the small one
     a, b = fwd_both_ways(512, 768, 2048, mx.HAD_DET16, mx.RNE, mx.OUT_BF16, 3)
+    assert np.array_equal(a, b)
+    # one that runs on the tiled GEMM
+    assert mx.mxfp4_gemm_route(2048, 2560, 1024) == mx.ROUTE_BLOCKS
+    a, b = fwd_both_ways(2048, 2560, 1024, mx.HAD_DET, mx.RNE, mx.OUT_BF16, 4)
     assert np.array_equal(a, b)
 
 
