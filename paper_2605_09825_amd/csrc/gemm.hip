@@ -902,8 +902,8 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_mix_kernel(const TileGemm pn
 }
 
 // Ragged sizes on the same tiles: t_main tiles of the sequence on 256 x 256, then (MXFP4) the rest in halves.  Measured,
-// bf16 output, against gemm_edge_kernel: 8192 x 6144 x 4064 173 / 116 us (3.5 PFLOP/s; MXFP8 252 / 189), 8192 x 28640 x
-// 4064 771 / 523, 4096 x 4096 x 4000 53 / 40; 4010 x 6144 x 4096 55 us, against 63 as a tiled interior and a strip.
+// bf16 output, gemm_edge_kernel / this one: 8192 x 6144 x 4064 181 / 121 us (3.4 PFLOP/s; MXFP8 273 / 199), 8192 x 28640 x
+// 4064 806 / 540, 4096 x 4096 x 4000 58 / 43; 4010 x 6144 x 4096 60 us, against 68 as a tiled interior and a strip.
 template <bool OUT_FP32, bool ACC, int FMT>
 __global__ __launch_bounds__(256, 1) void gemm_tile_rag_kernel(const TileGemm p, const int64_t Ra, const int64_t Rb,
                                                                const int t_main)
@@ -960,12 +960,13 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_pair_kernel(const TileGemm p
 // FMT as in gemm_tile_body.  Built as 64 x 64 (4 stage buffers, 68 KiB of LDS, two workgroups per CU), 128 x 64 (3, 78 KiB,
 // two) and 128 x 256 tiles (8 waves, 3, 156 KiB; with two stage buffers 8192 x 6112 x 4064 took 185 us, with three 173);
 // 128 x 128 tiles on 4 waves were never the fastest, 256 x 256 tiles on 8 waves were slower for MXFP4 (210 against 156 us).
-// What bounds it now: at 8192 x 6144 x 4096 (139 us, 3.0 PFLOP/s, against 99 us of the tiled kernel) LDS traffic, 176 KiB
+// What bounds it now: at 8192 x 6144 x 4096 (153 us, 2.7 PFLOP/s, against 104 us of the tiled kernel) LDS traffic, 176 KiB
 // per 128 x 256 stage against 1024 clocks of matrix instructions; rows that are not whole cache lines apart cost another
-// 20 % (C = 4064: 170 us), because every 128-byte row piece then takes two line requests.
-// Measured, bf16 output, the kernel before / this one: MXFP4 8192 x 6144 x 4064 906 / 170 us, 16000 x 1000 x 3008 237 / 45,
-// 2080 x 4320 x 1440 67.6 / 23.2, 2048 x 3072 x 768 33.7 / 9.8, 200 x 4096 x 4096 31.2 / 9.4, 24 x 6144 x 4096 23.7 / 9.2,
-// 256 x 512 x 512 6.4 / 5.0; MXFP8 8192 x 6144 x 4064 1340 / 261, 200 x 4096 x 4096 45.2 / 13.0 us.
+// 20 % (C = 4064: 181 us), because every 128-byte row piece then takes two line requests.
+// Measured back to back in a graph, bf16 output, the any-shape kernel / the fastest tile of this one: MXFP4 8192 x 6144 x 4064
+// 902 / 181 us (now on moved-back tiles, 121), 16000 x 1000 x 3008 238 / 47, 2080 x 4320 x 1440 69 / 21, 2048 x 3072 x 768
+// 33 / 9, 200 x 4096 x 4096 31 / 8.5, 24 x 6144 x 4096 23.5 / 7.9, 256 x 512 x 512 6.3 / 3.8; MXFP8 8192 x 6144 x 4064
+// 1335 / 273 (on moved-back tiles 199), 200 x 4096 x 4096 45.5 / 11.9 us.
 template <int WM, int WN, int NWN, int NBUF>
 struct EdgeTile {
     static constexpr int WAVES = 2 * NWN, TM = 64 * WM, TN = 32 * WN * NWN, ROWS = TM + TN;
@@ -1038,7 +1039,6 @@ __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm 
 
     // scale bytes: piece j of this thread = 16 bytes (half (tid * NP + j) & 1 of its row's 32) of a batch
     constexpr int NP = (ROWS * 2 + 64 * WAVES - 1) / (64 * WAVES);
-    struct __attribute__((packed, aligned(1))) Piece { uint32_t v[4]; };
     uint4 piece[NP];
     auto load_scales = [&](int b) {
         const uint8_t *base[NP];
@@ -1055,7 +1055,7 @@ __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm 
         if (b * 32 + 32 <= nkb) {  // (the same for all: both loads are out before anything waits)
 #pragma unroll
             for (int j = 0; j < NP; ++j) {
-                const Piece t = *reinterpret_cast<const Piece *>(base[j] + at[j]);
+                const Bytes16 t = *reinterpret_cast<const Bytes16 *>(base[j] + at[j]);
                 piece[j] = make_uint4(t.v[0], t.v[1], t.v[2], t.v[3]);
             }
             return;
@@ -1069,7 +1069,7 @@ __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm 
             const int64_t from = at[j] < total[j] - 16 ? at[j] : total[j] - 16;
             uint64_t lo = 0, hi = 0;
             if (left > 0 && from >= 0) {
-                const Piece t = *reinterpret_cast<const Piece *>(base[j] + from);
+                const Bytes16 t = *reinterpret_cast<const Bytes16 *>(base[j] + from);
                 const int sh = 8 * (int)(at[j] - from);  // 0 .. 120: at least one byte of the row is among the 16
                 lo = t.v[0] | (uint64_t)t.v[1] << 32;
                 hi = t.v[2] | (uint64_t)t.v[3] << 32;
@@ -1355,10 +1355,12 @@ static hipError_t launch_edge_f(const GemmArgs &g0, const GemmArgs *g1, hipStrea
 
 // Estimated microseconds of gemm_edge_kernel on tm x tn tiles: rounds of the tiles that the chip holds at once, each
 // `full` per kilobyte of code row (half of that where at most one of two workgroups per CU is there) plus what filling
-// and emptying the pipeline costs.  The constants were fitted to kernel times at 24 to 16000 rows, 512 to 28640 columns,
-// C = 512 to 8000; they only rank the three tile shapes.  Where they matter: few tiles (200 x 4096 x 4096: 64 x 64 9.4,
-// 128 x 64 12.6, 128 x 256 25 us), a round just overfull (2080 x 4320 x 1440: 29.4, 22.4, 24.8 us), many tiles (8192 x
-// 6112 x 4064: 298, 208, 156 us).
+// and emptying the pipeline costs.  They only rank the three tile shapes and this kernel among the others: the constants of
+// the two small tiles are older than its third stage buffer, and over 548 sizes (256 to 16384 rows and columns, C = 1024 to
+// 14336) the estimates are 1.16, 1.11 and 1.10 times the measured time of 64 x 64, 128 x 64 and 128 x 256 tiles on average
+// (four in five between 0.86 and 1.44; 0.1 to 0.2 less where rows are not whole cache lines apart).  Where they matter: few
+// tiles (200 x 4096 x 4096: 64 x 64 8.5, 128 x 64 10.1, 128 x 256 18.6 us), a round just overfull (2080 x 4320 x 1440: 27.6,
+// 21.2, 23.2 us), many tiles (8192 x 6112 x 4064: 290, 254, 179 us).
 static double edge_cost(const GemmArgs &g0, const GemmArgs *g1, int tm, int tn, int slots, double full, double fixed)
 {
     auto tiles = [&](const GemmArgs &g) { return ((g.Ra + tm - 1) / tm) * ((g.Rb + tn - 1) / tn); };
@@ -1393,7 +1395,8 @@ static EdgeChoice choose_edge(const GemmArgs &g0, const GemmArgs *g1 = nullptr)
     EdgeChoice best{0, cost(64, 64, 256, 512, 6.4, 1.5)};
     // Short rows are bound by the stores at a tile's end, which the estimates do not tell apart: while the chip holds all the
     // 64 x 64 tiles at once, they are done first.  128 x 64 over 64 x 64, 257 to 512 tiles, up to 512 bytes of codes per row:
-    // 0.96 to 1.22, 1.06 on average, and where the output is added to 1.04 to 1.50, 1.28 (10736 x 88 x 384 12.3 us, 8.6).
+    // 0.96 to 1.22, 1.06 on average, and where the output is added to 1.04 to 1.50, 1.28 (10736 x 88 x 384, rows of 91
+    // elements: 12.3 us, 8.6).
     auto tiles = [](const GemmArgs &g) { return (g.Ra + 63) / 64 * ((g.Rb + 63) / 64); };
     auto short_rows = [](const GemmArgs &g) { return (g.a_fmt ? g.C : g.C / 2) <= 512; };
     if (short_rows(g0) && (!g1 || short_rows(*g1)) && tiles(g0) + (g1 ? tiles(*g1) : 0) <= 2 * NUM_CUS) return best;
@@ -1617,9 +1620,9 @@ static double rag_cost(const GemmArgs &g, int cus)
 
 // How a call runs: its plan, or the whole product as one block on the ragged-shape kernel or on the tiled kernel for
 // ragged sizes, whichever is estimated to take least.  The plan loses with too few 256 x 128 tiles for the chip (512 x 4096
-// x 4096: 16.8 us on 64 tiles, 11.6 us on 128 x 64 ones; in MXFP8, which has no narrow tile, 42.1 and 19.4), where it
-// cuts a small product into several launches (300 x 520 x 1024: 15.5 us in three, 5.5 us in one) and where strips beside a
-// large interior cost a launch and a poorly filled chip (4010 x 6144 x 4096: 63 us, 55 in one).
+// x 4096: 14.5 us on 64 tiles, 11.1 us on 128 x 64 ones; in MXFP8, which has no narrow tile, 41.8 and 17.9), where it
+// cuts a small product into several launches (300 x 520 x 1024: 15.4 us in three, 4.8 us in one) and where strips beside a
+// large interior cost a launch and a poorly filled chip (4010 x 6144 x 4096: 68 us, 60 in one).
 // Whole 128s of columns but not 256s: the estimates of 256 x 128 tiles throughout and of 256 x 256 ones moved back lie within
 // a few per cent of each other, and decide except for a bf16 output and C < 2048.  Where they prefer the moved-back tiles
 // (430 sizes on two cards), these take on average, against the others: bf16 1.04 times as long for C < 2048 (14848 x 3456 x
