@@ -251,7 +251,7 @@ typedef enum {
     MXFP4_ROUTE_NONE = -1,         /* an empty product: nothing                                              */
     MXFP4_ROUTE_BLOCKS = 0,        /* the blocks of mxfp4_gemm_plan, a launch each                           */
     MXFP4_ROUTE_ANY_SHAPE = 1,     /* the any-shape kernel                                                   */
-    MXFP4_ROUTE_EDGE_64 = 2,       /* the ragged-shape kernel on 64 x 64,                                    */
+    MXFP4_ROUTE_EDGE_64 = 2,       /* the ragged-shape kernel on 64 x 64 (few outputs: 32 x 32),             */
     MXFP4_ROUTE_EDGE_128 = 3,      /*   on 128 x 64                                                          */
     MXFP4_ROUTE_EDGE_256 = 4,      /*   or on 128 x 256 tiles                                                */
     MXFP4_ROUTE_RAGGED_TILED = 5   /* the tiled kernel with its last row and column of tiles moved back      */
@@ -265,7 +265,8 @@ int mxfp4_gemm_route(int64_t R_a, int64_t R_b, int64_t C, int a_format, int b_fo
  *   route[0] an mxfp4_gemm_pair_kind;
  *   route[1] NARROW_BESIDE_WIDE: the problem on narrow tiles; EDGE: the problem whose tiles start first; else 0;
  *   route[2] SIDE_BY_SIDE: workgroups per XCD (of 32) that problem 0 gets; NARROW_BESIDE_WIDE: those that take a narrow
- *            tile first; EDGE: 0, 1, 2 for 64 x 64, 128 x 64, 128 x 256 tiles; else 0;
+ *            tile first; EDGE: 0, 1, 2 for 64 x 64 (few outputs: 32 x 32), 128 x 64, 128 x 256 tiles;
+ *            else 0;
  *   route[3] NARROW_BESIDE_WIDE: tiles of the other problem that those workgroups add; else 0.
  * Host-only.  Returns what mxfp4_gemm_pair would for these sizes and types, or MXFP4_EINVAL.
  */

@@ -985,6 +985,49 @@ struct EdgeGemm {
     int out_fp32, accumulate, vec;  // vec: four consecutive outputs may be stored at once
 };
 
+// The tile (tm x tn) of workgroup `bid`: each XCD (workgroup id mod 8) takes a contiguous run of the tile sequence, which walks the grid in
+// groups of GROUP_M tile rows (as the tiled kernel does).  False: no tile (the grid is padded to whole rows of 8).
+__device__ __forceinline__ bool edge_tile(const EdgeGemm &p, uint32_t bid, int tm, int tn, int64_t &m0, int64_t &n0)
+{
+    const int T = p.tiles_m * p.tiles_n, xcd = bid & 7, per = T >> 3, rem = T & 7;
+    if ((int)(bid >> 3) >= per + (xcd < rem ? 1 : 0)) return false;
+    const int L = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + (int)(bid >> 3);
+    const int span = GROUP_M * p.tiles_n, grp = L / span, first = grp * GROUP_M, in = L - grp * span;
+    const int gm = p.tiles_m - first < GROUP_M ? p.tiles_m - first : GROUP_M;
+    // (uniform, but the division ran in the vector unit: put them where the loads want their base)
+    m0 = (int64_t)__builtin_amdgcn_readfirstlane(first + in % gm) * tm;
+    n0 = (int64_t)__builtin_amdgcn_readfirstlane(in / gm) * tn;
+    return true;
+}
+
+// four consecutive outputs of one row from column col on, at once (whole) or as many of them as are left
+__device__ __forceinline__ void store4(const EdgeGemm &p, int64_t row, int64_t col, int64_t left, bool whole, const v4f v)
+{
+    if (p.out_fp32) {
+        float *o = reinterpret_cast<float *>(p.out) + row * p.ld + col;
+        if (whole) {
+            v4f t = v;
+            if (p.accumulate) t += *reinterpret_cast<const v4f *>(o);
+            __builtin_nontemporal_store(t, reinterpret_cast<v4f *>(o));
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (e < left) o[e] = p.accumulate ? (o[e] + v[e]) : v[e];
+        }
+    } else {
+        uint16_t *o = reinterpret_cast<uint16_t *>(p.out) + row * p.ld + col;
+        const uint32_t lo = pack_bf16(v[0], v[1]), hi = pack_bf16(v[2], v[3]);
+        if (whole) {
+            typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+            __builtin_nontemporal_store((u32x2){lo, hi}, reinterpret_cast<u32x2 *>(o));
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (e < left) o[e] = (uint16_t)((e & 2 ? hi : lo) >> (16 * (e & 1)));
+        }
+    }
+}
+
 // A launch may carry two independent problems: workgroups 0 .. groups0-1 (a multiple of 8) work on p0, the others on p1.
 template <int FMT, int WM, int WN, int NWN, int NBUF>
 __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm p0, const EdgeGemm p1, const uint32_t groups0)
@@ -1002,16 +1045,8 @@ __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / NWN, wn = wave % NWN;
 
-    // tile of this workgroup: each XCD (workgroup id mod 8) takes a contiguous run of the tile sequence, which walks
-    // the grid in groups of GROUP_M tile rows (as the tiled kernel does)
-    const int T = p.tiles_m * p.tiles_n, xcd = bid & 7, per = T >> 3, rem = T & 7;
-    if ((int)(bid >> 3) >= per + (xcd < rem ? 1 : 0)) return;  // (the grid is padded to whole rows of 8)
-    const int L = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + (int)(bid >> 3);
-    const int span = GROUP_M * p.tiles_n, grp = L / span, first = grp * GROUP_M, in = L - grp * span;
-    const int gm = p.tiles_m - first < GROUP_M ? p.tiles_m - first : GROUP_M;
-    // (uniform, but the division ran in the vector unit: put them where the loads want their base)
-    const int64_t m0 = (int64_t)__builtin_amdgcn_readfirstlane(first + in % gm) * TM;
-    const int64_t n0 = (int64_t)__builtin_amdgcn_readfirstlane(in / gm) * TN;
+    int64_t m0, n0;
+    if (!edge_tile(p, bid, TM, TN, m0, n0)) return;
 
     const int64_t rowbytes = FMT ? p.C : (p.C >> 1);
     const int nkb = (int)(p.C >> 5);
@@ -1257,31 +1292,245 @@ __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm 
         const int64_t row = m0 + wm * 32 * WM + 32 * i + r;
         const v4f v = *reinterpret_cast<const v4f *>(epi + r * PITCH + ((ch ^ (r & (CHUNKS - 1))) << 4));
         if (row >= p.Ra) continue;
-        if (p.out_fp32) {
-            float *o = reinterpret_cast<float *>(p.out) + row * p.ld + col;
-            if (whole) {
-                v4f t = v;
-                if (p.accumulate) t += *reinterpret_cast<const v4f *>(o);
-                __builtin_nontemporal_store(t, reinterpret_cast<v4f *>(o));
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (e < left) o[e] = p.accumulate ? (o[e] + v[e]) : v[e];
-            }
-        } else {
-            uint16_t *o = reinterpret_cast<uint16_t *>(p.out) + row * p.ld + col;
-            const uint32_t lo = pack_bf16(v[0], v[1]), hi = pack_bf16(v[2], v[3]);
-            if (whole) {
-                typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-                __builtin_nontemporal_store((u32x2){lo, hi}, reinterpret_cast<u32x2 *>(o));
-            } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (e < left) o[e] = (uint16_t)((e & 2 ? hi : lo) >> (16 * (e & 1)));
-            }
-        }
+        store4(p, row, col, left, whole, v);
       }
     }
+}
+
+// ---- ragged-shape kernel, 32 x 32 tiles: few outputs --------------------------------------------
+// 24 x 6144 x 4096 makes 96 tiles of 64 x 64, and a tile of them is one serial chain: 730 clocks per stage of 128 bytes of K (8.0 us),
+// most of it fragment reads waited for one K-step at a time, and two thirds of the chip idle.  Here a stage's chain is as short
+// as could be made:
+//   * four waves on a 32 x 32 tile, V_MFMA_SCALE_F32_16X16X128_F8F6F4, one accumulator each (17 clocks per instruction in a chain on one
+//     accumulator, 24 to 33 where several alternate); the next stage's fragments are read under this one's instructions;
+//   * one barrier per stage and no branch in it: a stage that does not exist is "loaded" with no lane active, so that the wait
+//     counts stay constants; the ragged last stage is moved back to end with the row;
+//   * a fifth wave brings the scale bytes (8-byte loads at any alignment, 64 bytes per row in a batch, written to LDS a batch ahead):
+//     its waits hold up nobody's direct-to-LDS loads.
+// NBUF stage buffers: 4 (40 KiB, four workgroups per compute unit) or 8 (72 KiB).
+// Measured back to back in a graph, bf16 output, 64 x 64 tiles / this: MXFP4 24 x 6144 x 4096 8.0 / 5.6 us, 256 x 512 x 512
+// 4.1 / 3.6, 100 x 1000 x 14336 20.9 / 11.3, 500 x 1000 x 1440 6.3 / 5.5; MXFP8 24 x 6144 x 4096 11.1 / 7.2.  What is left at 24 x 6144
+// x 4096: 1.7 us of launch, 1.4 us until the first stage and its scale bytes are there, 0.12 us per stage.
+// The same on 64 x 64 tiles (V_MFMA_SCALE_F32_32X32X64_F8F6F4) was 20 % faster than gemm_edge_kernel's from 32 stages on and
+// slower below 16: not built.
+constexpr int SMALL = 32;                        // output tile edge
+constexpr int SMALL_STAGE = 2 * SMALL * 128;     // bytes of codes per stage: A's 32 rows, then B's
+constexpr int SMALL_SC = 2 * SMALL * 64;         // a batch of scale bytes
+
+template <int FMT, int NBUF>
+__global__ __launch_bounds__(320) void gemm_small_kernel(const EdgeGemm p0, const EdgeGemm p1, const uint32_t groups0)
+{
+    const bool second = blockIdx.x >= groups0;  // uniform
+    const EdgeGemm &p = second ? p1 : p0;
+    const uint32_t bid = blockIdx.x - (second ? groups0 : 0u);
+    constexpr int T = SMALL, OFF_SB = NBUF * SMALL_STAGE;
+    constexpr int SB = FMT ? 4 : 8;   // scale bytes per row and stage
+    constexpr int BATCH_STAGES = 64 / SB;
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[OFF_SB + 2 * SMALL_SC];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    int64_t m0, n0;
+    if (!edge_tile(p, bid, T, T, m0, n0)) return;
+    const int rowbytes = (int)(FMT ? p.C : (p.C >> 1)), nkb = (int)(p.C >> 5);
+    const int nstages = (rowbytes + 127) >> 7;
+
+    if (wave == 4) {
+        // ---- the wave that brings the scale bytes ----
+        // piece j of a batch: a lane's 8 bytes (slot lane % 8 of the batch's 64) of row 8 j + lane / 8 (A's rows, then B's)
+        constexpr int NP = 2 * T / 8;
+        const int nbatches = (nkb + 63) >> 6;
+        const int valid = nkb - SB * (nstages - 1);  // bytes of the last stage
+        uint2 piece[NP];
+        auto load = [&](int b) {
+            const int col = b * 64 + (lane & 7) * 8;
+            int last[2], lastrow[2];  // of A, of B
+            const uint8_t *base[2];
+#pragma unroll
+            for (int o = 0; o < 2; ++o) {
+                const int64_t r0 = o ? n0 : m0, R = o ? p.Rb : p.Ra, room = (R - r0) * nkb;
+                base[o] = (o ? p.bs : p.as) + r0 * nkb;
+                lastrow[o] = (int)(R - r0 < T ? R - r0 : T) - 1;
+                last[o] = (int)(room < (1 << 30) ? room : (1 << 30)) - 8;  // the last place that 8 bytes can be loaded from
+            }
+            auto place = [&](int j) {
+                const int o = j >= NP / 2, want = (j % (NP / 2)) * 8 + (lane >> 3);
+                return (want < lastrow[o] ? want : lastrow[o]) * nkb + (col < nkb ? col : 0);
+            };
+            if ((p.Ra < p.Rb ? p.Ra : p.Rb) * nkb >= 8) {
+#pragma unroll
+                for (int j = 0; j < NP; ++j) {
+                    const int o = j >= NP / 2, at = place(j);
+                    const Bytes8 t = *reinterpret_cast<const Bytes8 *>(base[o] + (at < last[o] ? at : last[o]));
+                    piece[j] = make_uint2(t.v[0], t.v[1]);
+                }
+                // (the last bytes of a whole array are loaded from further ahead)
+                const int64_t end = (int64_t)(T - 1) * nkb + (nkb + 7) / 8 * 8;
+                if (last[0] + 8 < end || last[1] + 8 < end) {
+#pragma unroll
+                    for (int j = 0; j < NP; ++j) {
+                        const int o = j >= NP / 2, at = place(j);
+                        const uint64_t v = (piece[j].x | (uint64_t)piece[j].y << 32) >> (at > last[o] ? 8 * (at - last[o]) : 0);
+                        piece[j] = make_uint2((uint32_t)v, (uint32_t)(v >> 32));
+                    }
+                }
+            } else {  // an array of less than 8 bytes
+#pragma unroll
+                for (int j = 0; j < NP; ++j) {
+                    const int at = place(j);
+                    uint64_t v = 0;
+#pragma unroll 1
+                    for (int k = 0; k < 8 && k < nkb - col; ++k) v |= (uint64_t)base[j >= NP / 2][at + k] << (8 * k);
+                    piece[j] = make_uint2((uint32_t)v, (uint32_t)(v >> 32));
+                }
+            }
+        };
+        auto write = [&](int b) {
+            if (b == nbatches - 1 && valid < SB) {
+                // the last stage's codes are moved back to end with the row: so are its scale bytes, zeros in front of them for the
+                // blocks that the stage before has had (products below 2^-254 * 2^24); a row of less than a stage has them behind
+                auto fix = [&](uint64_t v) { return nkb < SB ? v & ((uint64_t(1) << (8 * valid)) - 1) : v << (8 * (SB - valid)); };
+#pragma unroll
+                for (int j = 0; j < NP; ++j) {
+                    const int s = b * BATCH_STAGES + (lane & 7) * (FMT ? 2 : 1);
+                    uint32_t x = piece[j].x, y = piece[j].y;
+                    if (FMT) {
+                        if (s == nstages - 1) x = (uint32_t)fix(x);
+                        if (s + 1 == nstages - 1) y = (uint32_t)fix(y);
+                    } else if (s == nstages - 1) {
+                        const uint64_t v = fix(x | (uint64_t)y << 32);
+                        x = (uint32_t)v, y = (uint32_t)(v >> 32);
+                    }
+                    piece[j] = make_uint2(x, y);
+                }
+            }
+            // slot t of a row sits at slot t ^ (row % 16) / 4: the reads of 16 rows touch every bank once
+#pragma unroll
+            for (int j = 0; j < NP; ++j) {
+                const int r = j * 8 + (lane >> 3);
+                *reinterpret_cast<uint2 *>(smem + OFF_SB + (b & 1) * SMALL_SC + r * 64 + (((lane & 7) ^ ((r & 15) >> 2)) << 3)) = piece[j];
+            }
+        };
+        if (nstages == 0) return;
+        load(0);
+        write(0);
+        if (nbatches > 1) load(1);
+        for (int s = 0; s <= nstages; ++s) {  // (as many barriers as the others have)
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            if (s % BATCH_STAGES == 0 && s / BATCH_STAGES + 1 < nbatches) {  // nobody reads the batch before the last any more
+                write(s / BATCH_STAGES + 1);
+                if (s / BATCH_STAGES + 2 < nbatches) load(s / BATCH_STAGES + 2);
+            }
+        }
+        return;
+    }
+
+    // ---- the four waves that multiply ----
+    const int wm = wave >> 1, wn = wave & 1;
+    // Direct-to-LDS loads: waves 0 and 1 bring A's rows, 2 and 3 B's, 16 rows each; load n of a wave moves 8 (its immediate offset,
+    // which the instruction adds to both addresses, is taken off the lane's).  Chunk c of row r of 8-row group g sits at slot
+    // c ^ r ^ 5 (g & 1) of the row, which spreads the 16-byte reads of 16 rows over all banks.
+    const bool isb = wave >= 2;
+    const int64_t r0 = isb ? n0 : m0, rows = (isb ? p.Rb : p.Ra) - r0;
+    const int lastrow = (int)(rows < T ? rows : T) - 1;
+    constexpr int BIAS = 1024;  // keeps the lanes' offsets from falling below 0
+    const uint8_t *src = (isb ? p.bq : p.aq) + r0 * rowbytes - BIAS;
+    uint32_t voff[2];
+#pragma unroll
+    for (int n = 0; n < 2; ++n) {
+        const int want = (wave & 1) * 16 + n * 8 + (lane >> 3), chunk = ((lane & 7) ^ (lane >> 3) ^ n * 5) << 4;
+        voff[n] = (uint32_t)((want < lastrow ? want : lastrow) * rowbytes + (chunk < rowbytes ? chunk : rowbytes - 16) + BIAS - n * 1024);
+    }
+    const uint32_t lds_dst = lds0 + (uint32_t)wave * 2048u;
+    const int koff_last = rowbytes > 128 ? rowbytes - 128 : 0;
+    auto issue = [&](int s, uint32_t to) {  // stage s into buffer `to`
+        const uint8_t *at = src + (s * 128 < koff_last ? s * 128 : koff_last);
+        const int on = __builtin_amdgcn_readfirstlane(s < nstages ? -1 : 0);
+        asm volatile("s_mov_b32 m0, %0\n\ts_mov_b32 exec_lo, %1\n\ts_mov_b32 exec_hi, %1\n\tglobal_load_lds_dwordx4 %2, %4\n\t"
+                     "global_load_lds_dwordx4 %3, %4 offset:1024\n\ts_mov_b64 exec, -1" ::"s"(lds_dst + to * SMALL_STAGE), "s"(on),
+                     "v"(voff[0]), "v"(voff[1]), "s"(at)
+                     : "memory");
+    };
+
+    // fragments: a lane holds chunks kb and 4 + kb of row lane % 16's 128 bytes (E2M1: of the stage's two K-steps, E4M3: both halves
+    // of its one)
+    const int r16 = lane & 15, kb = lane >> 4, g1 = (lane >> 3) & 1, r7 = lane & 7;
+    const uint32_t foff = (uint32_t)(g1 * 1024 + r7 * 128 + ((kb ^ r7 ^ g1 * 5) << 4));
+    const uint8_t *fa_at[2], *fb_at[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        fa_at[h] = smem + (foff ^ (uint32_t)(h << 6)) + wm * 2048;
+        fb_at[h] = smem + (foff ^ (uint32_t)(h << 6)) + T * 128 + wn * 2048;
+    }
+    const uint8_t *sa_at = smem + OFF_SB + (wm * 16 + r16) * 64, *sb_at = smem + OFF_SB + (T + wn * 16 + r16) * 64;
+    // byte i of the register: the scale of block 4 i + kb of the stage
+    const uint32_t perm_sel = FMT ? (uint32_t)kb : (uint32_t)(kb | (4 + kb) << 8);
+    v4f acc = {0.f, 0.f, 0.f, 0.f};
+    v4i fa[2][2], fb[2][2];
+    uint2 ra[2], rb[2];
+    auto read_stage = [&](int s, int buf, auto set_) {
+        constexpr int set = decltype(set_)::value;
+        const int in = s & (BATCH_STAGES - 1), slot = FMT ? in >> 1 : in;
+        const int at = ((s / BATCH_STAGES) & 1) * SMALL_SC + ((slot ^ (r16 >> 2)) << 3) + (FMT ? (in & 1) * 4 : 0);
+        if (FMT) {
+            ra[set] = make_uint2(*reinterpret_cast<const uint32_t *>(sa_at + at), 0u);
+            rb[set] = make_uint2(*reinterpret_cast<const uint32_t *>(sb_at + at), 0u);
+        } else {
+            ra[set] = *reinterpret_cast<const uint2 *>(sa_at + at);
+            rb[set] = *reinterpret_cast<const uint2 *>(sb_at + at);
+        }
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            fb[set][h] = *reinterpret_cast<const v4i *>(fb_at[h] + buf * SMALL_STAGE);
+            fa[set][h] = *reinterpret_cast<const v4i *>(fa_at[h] + buf * SMALL_STAGE);
+        }
+    };
+    if (nstages > 0) {
+#pragma unroll
+        for (int s = 0; s < NBUF - 1; ++s) issue(s, s);
+        asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * (NBUF - 2)) : "memory");
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): with scalar loads still out the loop could not wait for single reads
+        read_stage(0, 0, IC<0>{});
+        int s = 0;
+        // Stage s, buffer j, register set j % 2: stage s + 1 has landed, everyone has the fragments of stage s - 1.  (After the last
+        // stage this reads a buffer that nothing was loaded into, for nobody.)
+        auto advance = [&](auto j_) {
+            constexpr int j = decltype(j_)::value, set = j & 1;
+            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * (NBUF - 3)) : "memory");
+            const int sa = (int)__builtin_amdgcn_perm(ra[set].y, ra[set].x, perm_sel);
+            const int sb = (int)__builtin_amdgcn_perm(rb[set].y, rb[set].x, perm_sel);
+            read_stage(s + 1, (j + 1) % NBUF, IC<1 - set>{});
+            issue(s + NBUF - 1, (j + NBUF - 1) % NBUF);
+            const v4i b0 = fb[set][0], a0 = fa[set][0], b1 = fb[set][1], a1 = fa[set][1];
+            if constexpr (FMT) {
+                const v8i b8 = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w}, a8 = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
+                acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(b8, a8, acc, 0, 0, 0, sb, 0, sa);
+            } else {
+                const v8i b8 = {b0.x, b0.y, b0.z, b0.w, 0, 0, 0, 0}, a8 = {a0.x, a0.y, a0.z, a0.w, 0, 0, 0, 0};
+                acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(b8, a8, acc, 4, 4, 0, sb, 0, sa);
+                const v8i b9 = {b1.x, b1.y, b1.z, b1.w, 0, 0, 0, 0}, a9 = {a1.x, a1.y, a1.z, a1.w, 0, 0, 0, 0};
+                acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(b9, a9, acc, 4, 4, 1, sb, 1, sa);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            ++s;
+        };
+        for (;;) {
+#define MXFP4_ADVANCE(J)                    \
+    if constexpr ((J) < NBUF) {             \
+        advance(IC<(J) < NBUF ? (J) : 0>{}); \
+        if (s == nstages) goto done;        \
+    }
+            MXFP4_ADVANCE(0) MXFP4_ADVANCE(1) MXFP4_ADVANCE(2) MXFP4_ADVANCE(3)
+            MXFP4_ADVANCE(4) MXFP4_ADVANCE(5) MXFP4_ADVANCE(6) MXFP4_ADVANCE(7)
+#undef MXFP4_ADVANCE
+        }
+    }
+done:
+    // a lane holds columns 4 kb .. +3 of row r16 of the wave's 16 x 16: straight to memory
+    const int64_t row = m0 + wm * 16 + r16, col = n0 + wn * 16 + 4 * kb;
+    const int64_t left = p.Rb - col;
+    if (row < p.Ra) store4(p, row, col, left, p.vec && left >= 4, acc);
 }
 
 }  // namespace
@@ -1337,19 +1586,29 @@ static hipError_t launch_any_f(const GemmArgs &g, hipStream_t st)
     return hipGetLastError();
 }
 
+static EdgeGemm edge_args(const GemmArgs &g, int tm, int tn)
+{
+    return EdgeGemm{g.aq, g.as, g.bq, g.bs, g.Ra, g.Rb, g.C, g.out, g.ld, (int)((g.Ra + tm - 1) / tm), (int)((g.Rb + tn - 1) / tn),
+                    g.out_fp32, g.accumulate, (g.ld % 4) == 0 && (reinterpret_cast<uintptr_t>(g.out) % (g.out_fp32 ? 16 : 8)) == 0};
+}
+static uint32_t edge_groups(const EdgeGemm &p) { return ((uint32_t)(p.tiles_m * p.tiles_n) + 7u) & ~7u; }
+
 template <int FMT, int WM, int WN, int NWN, int NBUF>
 static hipError_t launch_edge_f(const GemmArgs &g0, const GemmArgs *g1, hipStream_t st)
 {
     using Tile = EdgeTile<WM, WN, NWN, NBUF>;
-    auto args = [](const GemmArgs &g) {
-        return EdgeGemm{g.aq, g.as, g.bq, g.bs, g.Ra, g.Rb, g.C, g.out, g.ld, (int)((g.Ra + Tile::TM - 1) / Tile::TM),
-                        (int)((g.Rb + Tile::TN - 1) / Tile::TN), g.out_fp32, g.accumulate,
-                        (g.ld % 4) == 0 && (reinterpret_cast<uintptr_t>(g.out) % (g.out_fp32 ? 16 : 8)) == 0};
-    };
-    auto groups = [](const EdgeGemm &p) { return ((uint32_t)(p.tiles_m * p.tiles_n) + 7u) & ~7u; };
-    const EdgeGemm p0 = args(g0), p1 = args(g1 ? *g1 : g0);
-    const uint32_t n0 = groups(p0), n1 = g1 ? groups(p1) : 0u;
+    const EdgeGemm p0 = edge_args(g0, Tile::TM, Tile::TN), p1 = edge_args(g1 ? *g1 : g0, Tile::TM, Tile::TN);
+    const uint32_t n0 = edge_groups(p0), n1 = g1 ? edge_groups(p1) : 0u;
     hipLaunchKernelGGL((gemm_edge_kernel<FMT, WM, WN, NWN, NBUF>), dim3(n0 + n1), dim3(64 * Tile::WAVES), 0, st, p0, p1, n0);
+    return hipGetLastError();
+}
+
+template <int FMT, int NBUF>
+static hipError_t launch_small_f(const GemmArgs &g0, const GemmArgs *g1, hipStream_t st)
+{
+    const EdgeGemm p0 = edge_args(g0, SMALL, SMALL), p1 = edge_args(g1 ? *g1 : g0, SMALL, SMALL);
+    const uint32_t n0 = edge_groups(p0), n1 = g1 ? edge_groups(p1) : 0u;
+    hipLaunchKernelGGL((gemm_small_kernel<FMT, NBUF>), dim3(n0 + n1), dim3(320), 0, st, p0, p1, n0);
     return hipGetLastError();
 }
 
@@ -1435,10 +1694,30 @@ static GemmRoute any_route(const GemmArgs &g)
     return edge.us < NO_ROUTE ? GemmRoute{ROUTE_EDGE_64 + edge.tile, edge.us} : GemmRoute{ROUTE_ANY_SHAPE, NO_ROUTE};
 }
 
+// Of the products (or pairs) on 64 x 64 tiles, those on 32 x 32 ones: the number of these, else 0.  They are faster up to two workgroups per
+// compute unit: time on 64 x 64 tiles over time on 32 x 32 ones, MXFP4 (MXFP8), at 1, 2, 4, 8, 16, 56 stages: up to 256 tiles 1.1 1.15
+// 1.15 1.3 1.45 1.8 (1.05 1.15 1.2 1.23 1.37 1.6), 320 to 512 tiles 0.98 1.04 1.02 1.14 1.2 1.25 (0.95 1.03 1.07 1.06 1.16 1.15), 560 and 640
+// tiles 0.9 0.95 0.94 1.01 1.04 1.1 (0.9 0.95 0.97 0.94 0.99 0.99), 1024 tiles 0.6 to 0.8.
+static int small_tiles(const GemmArgs &g0, const GemmArgs *g1)
+{
+    auto tiles = [](const GemmArgs &g) { return ((g.Ra + SMALL - 1) / SMALL) * ((g.Rb + SMALL - 1) / SMALL); };
+    auto one_stage = [](const GemmArgs &g) { return (g.a_fmt ? g.C : g.C / 2) <= 128; };
+    const int64_t t = tiles(g0) + (g1 ? tiles(*g1) : 0);
+    return t <= NUM_CUS || (t <= 2 * NUM_CUS && !one_stage(g0) && !(g1 && one_stage(*g1))) ? (int)t : 0;
+}
+
 static hipError_t launch_edge(const GemmArgs &g0, const GemmArgs *g1, int tile, hipStream_t st)
 {
     if (tile == 2) return g0.a_fmt ? launch_edge_f<1, 2, 2, 4, 3>(g0, g1, st) : launch_edge_f<0, 2, 2, 4, 3>(g0, g1, st);
     if (tile == 1) return g0.a_fmt ? launch_edge_f<1, 2, 1, 2, 3>(g0, g1, st) : launch_edge_f<0, 2, 1, 2, 3>(g0, g1, st);
+    if (const int small = small_tiles(g0, g1)) {
+        // (eight stage buffers with a workgroup per compute unit at most: 1.2 times as fast from 32 stages of operands that come
+        // from memory on, the same or 0.97 times up to 16)
+        const GemmArgs &longer = g1 && g1->C > g0.C ? *g1 : g0;
+        if (small <= NUM_CUS && (longer.a_fmt ? longer.C : longer.C / 2) > 16 * 128)
+            return g0.a_fmt ? launch_small_f<1, 8>(g0, g1, st) : launch_small_f<0, 8>(g0, g1, st);
+        return g0.a_fmt ? launch_small_f<1, 4>(g0, g1, st) : launch_small_f<0, 4>(g0, g1, st);
+    }
     return g0.a_fmt ? launch_edge_f<1, 1, 1, 2, 4>(g0, g1, st) : launch_edge_f<0, 1, 1, 2, 4>(g0, g1, st);
 }
 

@@ -1,0 +1,57 @@
+"""GPU tests: the ragged-shape kernel's 32 x 32 tiles (outputs of up to 512 of them): edges of tiles, rows of the scale arrays at every
+alignment, last stages of one block up to whole, rows of less than a stage, arrays of less than 8 scale bytes, both numbers of stage buffers, two products in a launch."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2605_09825_amd as mx
+from test_gpu_gemm import gpu
+
+pytestmark = pytest.mark.gpu
+
+# rows, columns, C: E2M1 stages hold 8 blocks of 32, E4M3 stages 4; batches of scale bytes 64
+SHAPES = [(33, 64, 64), (1, 33, 544), (33, 36, 288), (64, 33, 256), (32, 32, 2080), (65, 97, 2016), (3, 70, 4128),
+          (24, 500, 4320), (3, 68, 64), (100, 36, 8160), (511, 1000, 608), (257, 256, 1024)]
+
+
+def operands(rows, C, fmt, seed):
+    rng = np.random.default_rng(seed)
+    q = rng.integers(0, 256, (rows, C // 2 if fmt == mx.FMT_E2M1 else C), dtype=np.uint8)
+    if fmt == mx.FMT_E4M3:
+        q = (q & 0x80) | (q & 0x07) | 0x38  # magnitudes 1 .. 1.875: no bits of a product are dropped
+    return q, rng.integers(120, 131, (rows, C // 32), dtype=np.uint8)
+
+
+@pytest.mark.parametrize("fmt", [mx.FMT_E2M1, mx.FMT_E4M3])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_against_the_oracle(shape, fmt):
+    Ra, Rb, C = shape
+    fmts = dict(a_format=fmt, b_format=fmt)
+    ld = Rb + 1 + Ra % 4
+    if (Ra + 31) // 32 * ((Rb + 31) // 32) > 1:  # (of the short ones at least one call: the others are the any-shape kernel's)
+        assert mx.ROUTE_EDGE_64 in [mx.mxfp4_gemm_route(Ra, Rb, C, out_dtype=mx.OUT_FP32, **fmts), mx.mxfp4_gemm_route(
+            Ra, Rb, C, ld_out=ld, out_dtype=mx.OUT_FP32, accumulate=True, **fmts)]
+    (aq, as_), (bq, bs) = operands(Ra, C, fmt, 1), operands(Rb, C, fmt, 2)
+    want, absum = oracle.gemm_fmt(aq, as_, fmt, bq, bs, fmt)
+    canvas = torch.full((Ra, ld), 0.5, device="cuda:0")
+    a, sa, b, sb = gpu(aq), gpu(as_), gpu(bq), gpu(bs)
+    mx.mxfp4_gemm(a, sa, b, sb, out=canvas[:, :Rb], accumulate=True, **fmts)
+    dense = mx.mxfp4_gemm(a, sa, b, sb, **fmts)
+    half = mx.mxfp4_gemm(a, sa, b, sb, out_dtype=mx.OUT_BF16, **fmts)
+    assert (np.abs(dense.cpu().numpy().astype(np.float64) - want) <= 1e-5 * absum).all()  # the bound of the public contract
+    assert torch.equal(canvas[:, :Rb], dense + 0.5) and bool((canvas[:, Rb:] == 0.5).all())
+    assert torch.equal(half, dense.to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("shapes", [((33, 70, 480), (65, 36, 4128)), ((200, 96, 2016), (96, 128, 224))])
+def test_two_products_in_a_launch(shapes):
+    assert mx.mxfp4_gemm_pair_route(*shapes)[:1] + mx.mxfp4_gemm_pair_route(*shapes)[2:3] == (mx.PAIR_EDGE, 0)
+    ops, outs = [], []
+    for n, (Ra, Rb, C) in enumerate(shapes):
+        ops.append([tuple(map(gpu, operands(R, C, mx.FMT_E2M1, 10 * n + R))) for R in (Ra, Rb)])
+        outs.append(torch.empty((Ra, Rb), device="cuda:0", dtype=(torch.bfloat16, torch.float32)[n]))
+    mx.mxfp4_gemm_pair(*ops[0], outs[0], *ops[1], outs[1])
+    for ((a, sa), (b, sb)), out in zip(ops, outs):
+        single = mx.mxfp4_gemm(a, sa, b, sb, out_dtype=mx.OUT_FP32 if out.dtype == torch.float32 else mx.OUT_BF16)
+        assert torch.equal(out, single)
