@@ -117,9 +117,12 @@ def _check(call: str, status: int) -> None:
 
 
 def _stream_ptr(stream) -> int:
+    # (the handle of the current device's current stream, without the Stream object that torch.cuda.current_stream()
+    # builds around it: 2.9 us of the 8 us that a call of a small product took on the host)
+    if stream is not None:
+        return int(stream.cuda_stream)
     import torch
-    s = torch.cuda.current_stream() if stream is None else stream
-    return int(s.cuda_stream)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t) -> Optional[int]:
