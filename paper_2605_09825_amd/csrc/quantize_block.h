@@ -31,11 +31,20 @@ __host__ __device__ __forceinline__ uint32_t rand32(RngKey k, uint64_t idx)
     return mix32(mix32((uint32_t)idx + k.seed_lo_mul) ^ (uint32_t)(idx >> 32) ^ k.seed_hi_mix);
 }
 
-// the same for element i (0..31) of a block: low = low index word of its first element plus seed_lo_mul, high = high index
-// word ^ seed_hi_mix
-__device__ __forceinline__ uint32_t rand32_in_block(uint32_t low, uint32_t high, int i)
+// The same for element i (0..31) of a block, but for the last step (x ^= x >> 16): low = low index word of its first element plus
+// seed_lo_mul, mixed_high = h ^ h >> 16 with h = high index word ^ seed_hi_mix.  (Two such steps with an xor between them undo each other:
+// what ends the first mix32 and what begins the second become one xor.)
+__device__ __forceinline__ uint32_t rand32_in_block(uint32_t low, uint32_t mixed_high, int i)
 {
-    return mix32(mix32(low + (uint32_t)i) ^ high);
+    uint32_t x = low + (uint32_t)i;
+    x ^= x >> 16;
+    x *= 0x9E3779B9u;
+    x ^= x >> 15;
+    x *= 0xBB67AE85u;
+    x ^= mixed_high;
+    x *= 0x9E3779B9u;
+    x ^= x >> 15;
+    return x * 0xBB67AE85u;
 }
 
 RngKey make_key(uint64_t seed)
@@ -66,21 +75,25 @@ __device__ __forceinline__ void butterflies(float (&v)[32])
     }
 }
 
-// Stochastic rounding of t (already divided by the block scale) to an E2M1 code, sign in bit 3.  The magnitude a = min(|t|,
-// 6) lies between two neighbours of the grid; with f its distance from the lower one in grid steps, it goes up iff
-// u < f, u = (2 R + 1) 2^-24, R = r >> 9.  As integers: let y be the code of the lower neighbour times 2^24 plus f 2^24,
-// rounded up.  2 R + 1 < f 2^24 holds iff y's fraction is at least 2 R + 2, i.e. iff adding 2 (2^23 - 1 - R) carries into
-// the code.  From 1 upwards y is a's bit pattern shifted (a grid step is half an octave), below 1 it is a 2^25.
-// The kernels that round stochastically are bound by their vector instructions (two dependent multiply rounds of the
-// counter hash and this): 33 instructions per element and block, 42 with the comparison in floating point; 16384 x 4096
-// row-wise 69 -> 57 us, column-wise 81 -> 64, both 149 -> 122 (29, 39 and 53 us rounding to nearest).
-__device__ __forceinline__ uint32_t sr_code(float t, uint32_t r)
+// Stochastic rounding of v to an E2M1 code under the scale 2^(sb - 127), in the top four bits of the result (sign in bit 31).  With
+// a = min(|v| / scale, 6) between two neighbours of the grid and f its distance from the lower one in grid steps, the magnitude goes up
+// iff u < f, u = (2 R + 1) 2^-24, R = r >> 9.  As integers: let y be the code of the lower neighbour times 2^28 plus f 2^28, rounded up.
+// 16 (2 R + 1) < f 2^28 holds iff y's fraction is at least 32 R + 17, i.e. iff adding 2^28 - 32 R - 17 carries into the code.  Below 2 the
+// grid is uniform and y is a 2^29; from 1 upwards y is a's bit pattern shifted (a grid step is half an octave), which is the smaller
+// of the two from 2 on.  (|v| / scale is below 8, so a 2^29 fits 32 bits without the clamp.)
+// The kernels that round stochastically are bound by their vector instructions, each as dear as the next (the integer products of the
+// counter hash too): 23 per element and block; 30 with a comparison to select y, sign and code packed apart and the whole hash, 42 with
+// the rounding decided in floating point.  16384 x 4096, us, with 42, 30 and 23: row-wise 69, 61, 53, column-wise 76, 61, 57, both 149, 119,
+// 104 (29, 39 and 53 rounding to nearest).
+// hash: the counter hash before its last step, r = hash ^ hash >> 16
+__device__ __forceinline__ uint32_t sr_code(float v, int to_2_29, uint32_t hash)
 {
-    const float a = fminf(fabsf(t), 6.0f);
-    const uint32_t low = (uint32_t)__builtin_ceilf(a * 0x1p25f);
-    const uint32_t high = (__float_as_uint(a) << 2) + 0x04000000u;  // 1.0 -> 2 << 24, ... 6.0 -> 7 << 24
-    const uint32_t y = (a < 1.0f ? low : high) | ((__float_as_uint(t) >> 4) & 0x08000000u);
-    return (y + ((~r >> 9) << 1)) >> 24;
+    const float a = __builtin_fabsf(__builtin_ldexpf(v, to_2_29));
+    const uint32_t low = (uint32_t)__builtin_ceilf(a);
+    const float clamped = __builtin_amdgcn_fmed3f(a, 0x1p29f, 0x1.8p31f);
+    const uint32_t high = (__float_as_uint(clamped) << 6) + 0xA0000000u;  // 2^29 -> 2 << 28, ... 6 2^29 -> 7 << 28
+    const uint32_t y = (low < high ? low : high) + ((~(hash >> 4 ^ hash >> 20) & 0x0FFFFFE0u) | 15u);
+    return __float_as_uint(__builtin_copysignf(__uint_as_float(y), v));
 }
 
 // Optional sign flips and rotation of one block, in place (App. A.2).
@@ -163,15 +176,16 @@ __device__ __forceinline__ void encode_scaled(const float (&v)[32], uint32_t ama
             w[j] = r;
         }
     } else {
-        float inv = __uint_as_float((254u - sb) << 23);  // 2^-(sb-127); field in [2,254]
+        const int to_2_29 = 29 + 127 - (int)sb;
         // (a block starts at a multiple of 32: its elements share the index's high word)
         const uint32_t low = (uint32_t)idx0 + key.seed_lo_mul, high = (uint32_t)(idx0 >> 32) ^ key.seed_hi_mix;
+        const uint32_t mixed = high ^ high >> 16;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             uint32_t r = 0;
 #pragma unroll
             for (int e = 7; e >= 0; --e)
-                r = (r << 4) | sr_code(v[8 * j + e] * inv, rand32_in_block(low, high, 8 * j + e));
+                r = __builtin_amdgcn_alignbit(r, sr_code(v[8 * j + e], to_2_29, rand32_in_block(low, mixed, 8 * j + e)), 28);
             w[j] = r;
         }
     }
