@@ -11,10 +11,10 @@
 //   * row-wise: a lane reads its 64 contiguous bytes with four 16-byte loads; lanes
 //     of a wave cover 4 KiB of contiguous memory, so every fetched line is used.
 //   * column-wise: a lane owns two adjacent columns over 32 rows (32 dword loads,
-//     256 contiguous bytes per wave and row); the eight waves of a workgroup take
-//     eight consecutive row blocks, and the packed codes are regrouped through LDS
-//     so that each output row receives 128 contiguous bytes.
-//   * both at once: the column-wise workgroup tile, whose 256 x 128 elements are also
+//     256 contiguous bytes per wave and row); the four or eight waves of a workgroup
+//     take consecutive row blocks, and the packed codes are regrouped through LDS
+//     so that each output row receives 64 or 128 contiguous bytes.
+//   * both at once: the column-wise workgroup tile, whose elements are also
 //     parked in LDS and read back as row-wise blocks; memory delivers the tensor once
 //     for the two outputs.
 //   * 32 x 32 geometry (App. D): the same kernel with the block maxima reduced over the
@@ -86,7 +86,7 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const RowJob job0, c
 }
 
 // ---- column-wise (32x1) ------------------------------------------------------------------
-// Workgroup tile: 256 rows (8 row blocks, one per wave) x 128 columns (2 per lane).
+// Workgroup tile: RB row blocks of 32 (one per wave) x 128 columns (2 per lane).
 
 // MODE_DUAL: additionally emit the row-wise quantisation q_row[rows][cols/2], s_row[rows][cols/32] of the
 // same tile (needs cols % 32 == 0).  Each wave parks its 32 x 128 elements in LDS and reads them back as
@@ -97,7 +97,6 @@ __global__ __launch_bounds__(256) void quantize_rows_kernel(const RowJob job0, c
 // q/s or q_row/s_row).  Each phase runs twice over its data: first the maxima, reduced across the 16 lanes
 // that share a region, then the codes.
 constexpr int MODE_COLS = 0, MODE_DUAL = 1, MODE_2D = 2;
-constexpr int LDS_S_BYTES = CT_COLS * CT_RB;
 
 __device__ __forceinline__ uint32_t max_across(uint32_t m, int xor_mask)
 {
@@ -112,16 +111,15 @@ struct TileJob {
     int64_t rows, cols, ld;
     uint8_t *q, *s, *q_row, *s_row;
     uint32_t col_groups, nblocks, band_rows;
-    int s_vec8, s_row_vec4, streaming;
+    int s_vec, s_row_vec4, streaming;
     RngKey key, key_row;  // stochastic-rounding streams of the column-wise and of the row-wise output
 };
 
 // STREAM: the tensor is larger than the last-level cache: it is read with non-temporal loads and its codes are
 // written with non-temporal stores (a compile-time choice: as a run-time branch around the loads the compiler
 // merges the two sides and the hint is lost).
-template <int HAD, int RND, int MODE, int STREAM>
-__global__ __launch_bounds__(512) void quantize_cols_kernel(const TileJob job0, const TileJob job1,
-                                                            uint32_t sign_mask)
+template <int HAD, int RND, int MODE, int STREAM, int RB>
+__global__ __launch_bounds__(64 * RB) void quantize_cols_kernel(const TileJob job0, const TileJob job1, uint32_t sign_mask)
 {
     const bool second = blockIdx.x >= job0.nblocks;  // uniform: everything below is selected per workgroup
     const uint16_t *__restrict__ x = second ? job1.x : job0.x;
@@ -134,7 +132,7 @@ __global__ __launch_bounds__(512) void quantize_cols_kernel(const TileJob job0, 
     const uint32_t col_groups = second ? job1.col_groups : job0.col_groups;
     const uint32_t nb = second ? job1.nblocks : job0.nblocks;
     const uint32_t band_rows = second ? job1.band_rows : job0.band_rows;
-    const int s_vec8 = second ? job1.s_vec8 : job0.s_vec8, s_row_vec4 = second ? job1.s_row_vec4 : job0.s_row_vec4;
+    const int s_vec = second ? job1.s_vec : job0.s_vec, s_row_vec4 = second ? job1.s_row_vec4 : job0.s_row_vec4;
     constexpr int streaming = STREAM;
     const RngKey key = second ? job1.key : job0.key, key_row = second ? job1.key_row : job0.key_row;
     const uint32_t bid = blockIdx.x - (second ? job0.nblocks : 0u);
@@ -147,12 +145,12 @@ __global__ __launch_bounds__(512) void quantize_cols_kernel(const TileJob job0, 
     // the codes of wave w start w * SKEW bytes into its slice, so that the 8 lanes that later gather one output
     // row from the 8 slices hit different banks (the column-wise-only slice has the odd pitch built in)
     constexpr int SKEW = PARK ? 16 : 0;
-    static_assert(SLICE >= CT_COLS * 16 + (CT_RB - 1) * SKEW + (PARK ? 0 : 16), "the codes of a wave must fit its slice");
-    __shared__ __attribute__((aligned(16))) uint8_t lds[CT_RB * SLICE + LDS_S_BYTES];
-    uint8_t(*lds_s)[CT_RB] = reinterpret_cast<uint8_t(*)[CT_RB]>(lds + CT_RB * SLICE);
+    static_assert(SLICE >= CT_COLS * 16 + (RB - 1) * SKEW + (PARK ? 0 : 16), "the codes of a wave must fit its slice");
+    __shared__ __attribute__((aligned(16))) uint8_t lds[RB * SLICE + CT_COLS * RB];
+    uint8_t(*lds_s)[RB] = reinterpret_cast<uint8_t(*)[RB]>(lds + RB * SLICE);
 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    // Tile order.  A tile contributes only 8 scale bytes per column (4 per row in the row-wise output), far less
+    // Tile order.  A tile contributes only RB scale bytes per column (4 per row in the row-wise output), far less
     // than the 64 bytes the memory side writes at once, and the 8 XCDs (workgroup id mod 8) have separate L2s
     // that cannot merge each other's partial writes.  With band_rows > 0 each XCD takes a contiguous run of the
     // tile sequence, and the sequence walks the grid in bands of band_rows tile rows, tile rows fastest, so that
@@ -174,7 +172,7 @@ __global__ __launch_bounds__(512) void quantize_cols_kernel(const TileJob job0, 
         by = band * band_rows + (in - bx * gm);
     }
     const int64_t c0 = (int64_t)bx * CT_COLS;
-    const int64_t rb0 = (int64_t)by * CT_RB;
+    const int64_t rb0 = (int64_t)by * RB;
     const int64_t nrb = rows >> 5;
     const int64_t rb = rb0 + w;
     const int64_t col = c0 + 2 * lane;
@@ -301,22 +299,23 @@ __global__ __launch_bounds__(512) void quantize_cols_kernel(const TileJob job0, 
     // outstanding global stores (the row-wise output, which nobody in the workgroup reads back)
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
-    // each output row (input column) receives its 8 x 16 bytes from 8 consecutive lanes
-    const int ch = tid & 7;
+    // each output row (input column) receives its RB x 16 bytes from RB consecutive lanes
+    const int ch = tid & (RB - 1);
 #pragma unroll
     for (int pass = 0; pass < 2; ++pass) {
-        const int cl = (tid >> 3) + 64 * pass;
+        const int cl = tid / RB + 64 * pass;
         if (c0 + cl < cols && rb0 + ch < nrb)
             store_codes(reinterpret_cast<uint4 *>(q + (c0 + cl) * (rows >> 1) + (rb0 + ch) * 16),
                         reinterpret_cast<const uint4 *>(lds + ch * (SLICE + SKEW))[cl], streaming);
     }
     if (tid < CT_COLS && c0 + tid < cols) {
         uint8_t *dst = s + (c0 + tid) * nrb + rb0;
-        if (s_vec8 && rb0 + CT_RB <= nrb) {
-            *reinterpret_cast<uint2 *>(dst) = *reinterpret_cast<const uint2 *>(&lds_s[tid][0]);
+        if (s_vec && rb0 + RB <= nrb) {
+            if constexpr (RB == 8) *reinterpret_cast<uint2 *>(dst) = *reinterpret_cast<const uint2 *>(&lds_s[tid][0]);
+            else *reinterpret_cast<uint32_t *>(dst) = *reinterpret_cast<const uint32_t *>(&lds_s[tid][0]);
         } else {
 #pragma unroll
-            for (int k = 0; k < CT_RB; ++k)
+            for (int k = 0; k < RB; ++k)
                 if (rb0 + k < nrb) dst[k] = lds_s[tid][k];
         }
     }
@@ -364,7 +363,7 @@ hipError_t launch_rows_h(const QuantArgs &a, const QuantArgs *b, hipStream_t st)
 }
 
 template <int MODE>
-TileJob make_job(const QuantArgs &a)
+TileJob make_job(const QuantArgs &a, int rb)
 {
     const int64_t nrb = a.rows / 32;
     TileJob j;
@@ -372,10 +371,10 @@ TileJob make_job(const QuantArgs &a)
     j.q = a.q; j.s = a.s; j.q_row = a.q_row; j.s_row = a.s_row;
     // column groups fastest: neighbouring workgroups read neighbouring memory
     j.col_groups = (uint32_t)((a.cols + CT_COLS - 1) / CT_COLS);
-    j.nblocks = (uint32_t)(j.col_groups * ((nrb + CT_RB - 1) / CT_RB));
-    j.band_rows = j.nblocks < 2048 ? 0u : (MODE == MODE_COLS ? 16u : 2u);
+    j.nblocks = (uint32_t)(j.col_groups * ((nrb + rb - 1) / rb));
+    j.band_rows = j.nblocks < (uint32_t)(16384 / rb) ? 0u : (uint32_t)(8 / rb) * (MODE == MODE_COLS ? 16u : 2u);
     j.streaming = beyond_llc(a.rows, a.cols);
-    j.s_vec8 = ((nrb % 8) == 0) && ((reinterpret_cast<uintptr_t>(a.s) % 8) == 0);
+    j.s_vec = ((nrb % rb) == 0) && ((reinterpret_cast<uintptr_t>(a.s) % rb) == 0);
     j.s_row_vec4 = MODE != MODE_COLS && a.s_row != nullptr && (((a.cols / 32) % 4) == 0) &&
                    ((reinterpret_cast<uintptr_t>(a.s_row) % 4) == 0);
     j.key = make_key(a.seed);
@@ -383,23 +382,40 @@ TileJob make_job(const QuantArgs &a)
     return j;
 }
 
+// Waves, and so blocks of 32 rows, per workgroup of the column-wise kernels.  Four where the vector instructions or the chain through one
+// workgroup are what bounds (stochastic rounding, both axes, few tiles): the halves of a tile of eight then run on compute units of their own,
+// and wait for each other less.  Eight, whose output rows get whole 128-byte lines, where memory does: the column-wise kernel alone from
+// 512 tiles of eight on, everything beyond the last-level cache.  Eight / four waves, us, rounding to nearest: both axes 2080 x 1440 7.7 / 6.7,
+// 8192 x 4096 24.3 / 23.8, 16384 x 4096 42.4 / 39.6, 16384 x 14336 154 / 173; column-wise 2080 x 1440 5.2 / 4.6, 8192 x 4096 15.2 / 15.5, 8192 x
+// 14336 47.0 / 51.4; stochastic both axes 2080 x 1440 18.5 / 11.7, 16384 x 4096 118 / 117, column-wise 16384 x 14336 192 / 182.
+int cols_waves(const QuantArgs &a, const QuantArgs *b, int mode)
+{
+    if (a.rounding != RND_RNE) return 4;
+    if (beyond_llc(a.rows, a.cols) && (!b || beyond_llc(b->rows, b->cols))) return 8;
+    const int64_t groups = cols_groups(a.rows, a.cols) + (b ? cols_groups(b->rows, b->cols) : 0);
+    return mode != MODE_COLS || groups < 512 ? 4 : 8;
+}
+
 // b == nullptr: one tensor.  Otherwise both tensors in one launch (same rotation, rounding and base seed).
 template <int HAD, int MODE>
 hipError_t launch_cols_h(const QuantArgs &a, const QuantArgs *b, hipStream_t st)
 {
-    const TileJob j0 = make_job<MODE>(a);
+    const int rb = cols_waves(a, b, MODE);
+    const TileJob j0 = make_job<MODE>(a, rb);
     TileJob j1 = j0;
     j1.nblocks = 0;
-    if (b) j1 = make_job<MODE>(*b);
+    if (b) j1 = make_job<MODE>(*b, rb);
     dim3 grid(j0.nblocks + j1.nblocks);
     const uint32_t sign_mask = sign_mask_of(a.seed);
     const bool streaming = j0.streaming && (!b || j1.streaming);  // (two tensors in one launch: only if both want it)
-#define MXFP4_LAUNCH_COLS(R, S) \
-    hipLaunchKernelGGL((quantize_cols_kernel<HAD, R, MODE, S>), grid, dim3(COLS_THREADS), 0, st, j0, j1, sign_mask)
-    if (a.rounding == RND_RNE) {
-        if (streaming) MXFP4_LAUNCH_COLS(RND_RNE, 1); else MXFP4_LAUNCH_COLS(RND_RNE, 0);
+#define MXFP4_LAUNCH_COLS(R, S, W) \
+    hipLaunchKernelGGL((quantize_cols_kernel<HAD, R, MODE, S, W>), grid, dim3(64 * W), 0, st, j0, j1, sign_mask)
+    if (a.rounding != RND_RNE) {
+        if (streaming) MXFP4_LAUNCH_COLS(RND_SR, 1, 4); else MXFP4_LAUNCH_COLS(RND_SR, 0, 4);
+    } else if (streaming) {
+        MXFP4_LAUNCH_COLS(RND_RNE, 1, 8);
     } else {
-        if (streaming) MXFP4_LAUNCH_COLS(RND_SR, 1); else MXFP4_LAUNCH_COLS(RND_SR, 0);
+        if (rb == 4) MXFP4_LAUNCH_COLS(RND_RNE, 0, 4); else if constexpr (MODE == MODE_COLS) MXFP4_LAUNCH_COLS(RND_RNE, 0, 8);
     }
 #undef MXFP4_LAUNCH_COLS
     return hipGetLastError();

@@ -205,8 +205,8 @@ __device__ __forceinline__ void store_codes(uint4 *p, uint4 v, int streaming)
     }
 }
 
-// ---- column-wise workgroup tile: 256 rows (8 row blocks, one per wave) x 128 columns (2 per lane) ----
-constexpr int CT_COLS = 128, CT_RB = 8;
+// ---- column-wise workgroup tile: a row block of 32 per wave x 128 columns (2 per lane) ----
+constexpr int CT_COLS = 128;
 constexpr int RAW_PITCH = 272;  // bytes per parked row: 256 + 16, so that the 16-byte reads below (16 lanes =
                                 // 4 rows x 4 blocks per issue) and the dword writes touch every bank once
 

@@ -68,19 +68,24 @@ __global__ __launch_bounds__(256) void quantize_rows_fp8_kernel(const uint16_t *
     s[g] = (uint8_t)sb;
 }
 
-// column-wise: the tile and lane assignment of quantize_cols_kernel; an output row receives 8 x 32 = 256
-// contiguous bytes per tile
-template <int HAD>
-__global__ __launch_bounds__(512) void quantize_cols_fp8_kernel(const uint16_t *__restrict__ x, int64_t rows,
+// RB: waves, and so blocks of 32 rows, per workgroup of the column-wise kernels.  Four (an output row receives a whole 128-byte line) up to
+// 2^26 elements, where more and smaller workgroups fill the chip better and wait for each other less; eight beyond, where the longer pieces
+// do.  Both axes, eight / four waves, us: 2080 x 1440 7.0 / 6.0, 8192 x 4096 26.8 / 25.0, 8192 x 6144 37.3 / 35.2, 8192 x 14336 119 / 123.
+bool eight_waves(const QuantArgs &a) { return a.rows * a.cols > (int64_t(1) << 26); }
+
+// column-wise: the tile and lane assignment of quantize_cols_kernel; an output row receives 4 x 32 = 128
+// contiguous bytes per tile (RB = 4)
+template <int HAD, int RB>
+__global__ __launch_bounds__(64 * RB) void quantize_cols_fp8_kernel(const uint16_t *__restrict__ x, int64_t rows,
                                                                 int64_t cols, int64_t ld, uint32_t sign_mask,
                                                                 uint8_t *__restrict__ q, uint8_t *__restrict__ s,
                                                                 uint32_t col_groups)
 {
-    __shared__ uint4 lds_q[CT_RB][2][CT_COLS + 1];
-    __shared__ uint8_t lds_s[CT_COLS][CT_RB];
+    __shared__ uint4 lds_q[RB][2][CT_COLS + 1];
+    __shared__ uint8_t lds_s[CT_COLS][RB];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const uint32_t by = blockIdx.x / col_groups, bx = blockIdx.x - by * col_groups;
-    const int64_t c0 = (int64_t)bx * CT_COLS, rb0 = (int64_t)by * CT_RB, nrb = rows >> 5;
+    const int64_t c0 = (int64_t)bx * CT_COLS, rb0 = (int64_t)by * RB, nrb = rows >> 5;
     const int64_t rb = rb0 + w, col = c0 + 2 * lane;
     uint32_t raw[32];
     if ((rb < nrb) && (col < cols)) {
@@ -105,17 +110,17 @@ __global__ __launch_bounds__(512) void quantize_cols_fp8_kernel(const uint16_t *
         lds_s[2 * lane + j][w] = (uint8_t)sb;
     }
     __syncthreads();
-    // 16 consecutive threads write the 256 bytes one output row receives from this tile
+    // 8 consecutive threads write the 128 bytes one output row receives from this tile
 #pragma unroll
     for (int pass = 0; pass < 4; ++pass) {
-        const int idx = pass * 512 + tid, cl = idx >> 4, k = idx & 15, b = k >> 1, half = k & 1;
+        const int idx = pass * (64 * RB) + tid, cl = idx / (2 * RB), k = idx & (2 * RB - 1), b = k >> 1, half = k & 1;
         if (c0 + cl < cols && rb0 + b < nrb)
             *reinterpret_cast<uint4 *>(q + (c0 + cl) * rows + (rb0 + b) * 32 + half * 16) = lds_q[b][half][cl];
     }
     if (tid < CT_COLS && c0 + tid < cols) {
         uint8_t *dst = s + (c0 + tid) * nrb + rb0;
 #pragma unroll
-        for (int k = 0; k < CT_RB; ++k)
+        for (int k = 0; k < RB; ++k)
             if (rb0 + k < nrb) dst[k] = lds_s[tid][k];
     }
 }
@@ -125,27 +130,26 @@ __global__ __launch_bounds__(512) void quantize_cols_fp8_kernel(const uint16_t *
 // the other 16 are still in flight), reads them back as row blocks, two per lane and four lanes per row, so that
 // a row of the tile leaves as 128 contiguous bytes, and then reuses the slice to regroup its column-wise codes:
 // wave w keeps the low 16 bytes of every column's 32 at w * SKEW into its slice and the high 16 bytes FP8_HALF
-// further on, which lets the 16 lanes that later gather one output row's 256 bytes from the 8 slices hit every
-// bank once.
+// further on, so that the 8 lanes that later gather one output row's 128 bytes from the 4 slices hit different banks.
 constexpr int FP8_SLICE = 32 * RAW_PITCH, FP8_HALF = (CT_COLS + 1) * 16, FP8_SKEW = 32;
-static_assert(2 * FP8_HALF + (CT_RB - 1) * FP8_SKEW <= FP8_SLICE, "the codes of a wave must fit its slice");
+static_assert(2 * FP8_HALF + (8 - 1) * FP8_SKEW <= FP8_SLICE, "the codes of a wave must fit its slice");
 
 // ROW4: the row-wise output is MXFP4 instead (rotation HAD_ROW, rounding RND_ROW under key_row: what the MXFP4
 // kernels write), the column-wise one stays MXFP8 under rotation HAD: a tensor that feeds one MXFP4 and one MXFP8
 // GEMM of the stage-wise recipe (X and W when only Fprop is in MXFP4, X and dY when Fprop and Dgrad are).
-template <int HAD, bool ROW4, int HAD_ROW, int RND_ROW>
-__global__ __launch_bounds__(512) void quantize_dual_fp8_kernel(const uint16_t *__restrict__ x, int64_t rows,
+template <int HAD, bool ROW4, int HAD_ROW, int RND_ROW, int RB>
+__global__ __launch_bounds__(64 * RB) void quantize_dual_fp8_kernel(const uint16_t *__restrict__ x, int64_t rows,
                                                                 int64_t cols, int64_t ld, uint32_t sign_mask,
                                                                 uint8_t *__restrict__ q, uint8_t *__restrict__ s,
                                                                 uint8_t *__restrict__ q_row,
                                                                 uint8_t *__restrict__ s_row, uint32_t col_groups,
                                                                 int s_row_vec4, RngKey key_row)
 {
-    __shared__ __attribute__((aligned(16))) uint8_t lds[CT_RB * FP8_SLICE + CT_COLS * CT_RB];
-    uint8_t(*lds_s)[CT_RB] = reinterpret_cast<uint8_t(*)[CT_RB]>(lds + CT_RB * FP8_SLICE);
+    __shared__ __attribute__((aligned(16))) uint8_t lds[RB * FP8_SLICE + CT_COLS * RB];
+    uint8_t(*lds_s)[RB] = reinterpret_cast<uint8_t(*)[RB]>(lds + RB * FP8_SLICE);
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const uint32_t by = blockIdx.x / col_groups, bx = blockIdx.x - by * col_groups;
-    const int64_t c0 = (int64_t)bx * CT_COLS, rb0 = (int64_t)by * CT_RB, nrb = rows >> 5;
+    const int64_t c0 = (int64_t)bx * CT_COLS, rb0 = (int64_t)by * RB, nrb = rows >> 5;
     const int64_t rb = rb0 + w, col = c0 + 2 * lane;
     uint32_t raw[32];
     if ((rb < nrb) && (col < cols)) {
@@ -222,10 +226,10 @@ __global__ __launch_bounds__(512) void quantize_dual_fp8_kernel(const uint16_t *
     }
     // workgroup barrier for the LDS traffic only (it does not wait for the row-wise stores still in flight)
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    // 16 consecutive threads write the 256 bytes one output row receives from this tile
+    // 8 consecutive threads write the 128 bytes one output row receives from this tile
 #pragma unroll
     for (int pass = 0; pass < 4; ++pass) {
-        const int idx = pass * 512 + tid, cl = idx >> 4, k = idx & 15, b = k >> 1, half = k & 1;
+        const int idx = pass * (64 * RB) + tid, cl = idx / (2 * RB), k = idx & (2 * RB - 1), b = k >> 1, half = k & 1;
         if (c0 + cl < cols && rb0 + b < nrb)
             *reinterpret_cast<uint4 *>(q + (c0 + cl) * rows + (rb0 + b) * 32 + half * 16) =
                 *reinterpret_cast<const uint4 *>(lds + b * (FP8_SLICE + FP8_SKEW) + half * FP8_HALF + cl * 16);
@@ -233,7 +237,7 @@ __global__ __launch_bounds__(512) void quantize_dual_fp8_kernel(const uint16_t *
     if (tid < CT_COLS && c0 + tid < cols) {
         uint8_t *dst = s + (c0 + tid) * nrb + rb0;
 #pragma unroll
-        for (int k = 0; k < CT_RB; ++k)
+        for (int k = 0; k < RB; ++k)
             if (rb0 + k < nrb) dst[k] = lds_s[tid][k];
     }
 }
@@ -243,11 +247,15 @@ hipError_t launch_fp8_h(const QuantArgs &a, bool cols_axis, hipStream_t st)
 {
     const uint32_t sign_mask = sign_mask_of(a.seed);
     if (cols_axis) {
-        const int64_t nrb = a.rows / 32;
+        const int64_t nrb = a.rows / 32, rb = eight_waves(a) ? 8 : 4;
         const uint32_t col_groups = (uint32_t)((a.cols + CT_COLS - 1) / CT_COLS);
-        dim3 grid((unsigned)(col_groups * ((nrb + CT_RB - 1) / CT_RB)));
-        hipLaunchKernelGGL((quantize_cols_fp8_kernel<HAD>), grid, dim3(512), 0, st, a.x, a.rows, a.cols, a.ld,
-                           sign_mask, a.q, a.s, col_groups);
+        const dim3 grid((unsigned)(col_groups * ((nrb + rb - 1) / rb)));
+        if (rb == 8)
+            hipLaunchKernelGGL((quantize_cols_fp8_kernel<HAD, 8>), grid, dim3(512), 0, st, a.x, a.rows, a.cols, a.ld, sign_mask,
+                               a.q, a.s, col_groups);
+        else
+            hipLaunchKernelGGL((quantize_cols_fp8_kernel<HAD, 4>), grid, dim3(256), 0, st, a.x, a.rows, a.cols, a.ld, sign_mask,
+                               a.q, a.s, col_groups);
     } else {
         const int64_t bpr = a.cols / 32, nblocks = a.rows * bpr;
         const unsigned grid = (unsigned)((nblocks + 255) / 256);
@@ -260,13 +268,15 @@ hipError_t launch_fp8_h(const QuantArgs &a, bool cols_axis, hipStream_t st)
 template <int HAD, bool ROW4, int HAD_ROW, int RND_ROW>
 hipError_t launch_fp8_dual_h(const QuantArgs &a, hipStream_t st)
 {
-    const int64_t nrb = a.rows / 32;
+    const int64_t nrb = a.rows / 32, rb = eight_waves(a) ? 8 : 4;
     const uint32_t col_groups = (uint32_t)((a.cols + CT_COLS - 1) / CT_COLS);
-    dim3 grid((unsigned)(col_groups * ((nrb + CT_RB - 1) / CT_RB)));
+    const dim3 grid((unsigned)(col_groups * ((nrb + rb - 1) / rb)));
     const int s_row_vec4 = (((a.cols / 32) % 4) == 0) && ((reinterpret_cast<uintptr_t>(a.s_row) % 4) == 0);
-    hipLaunchKernelGGL((quantize_dual_fp8_kernel<HAD, ROW4, HAD_ROW, RND_ROW>), grid, dim3(512), 0, st, a.x, a.rows,
-                       a.cols, a.ld, sign_mask_of(a.seed), a.q, a.s, a.q_row, a.s_row, col_groups, s_row_vec4,
-                       make_key(a.seed_row));
+#define MXFP4_DUAL8(W) \
+    hipLaunchKernelGGL((quantize_dual_fp8_kernel<HAD, ROW4, HAD_ROW, RND_ROW, W>), grid, dim3(64 * W), 0, st, a.x, a.rows, a.cols, \
+                       a.ld, sign_mask_of(a.seed), a.q, a.s, a.q_row, a.s_row, col_groups, s_row_vec4, make_key(a.seed_row))
+    if (rb == 8) MXFP4_DUAL8(8); else MXFP4_DUAL8(4);
+#undef MXFP4_DUAL8
     return hipGetLastError();
 }
 

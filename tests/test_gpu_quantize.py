@@ -175,3 +175,14 @@ def test_blocks_that_expose_the_rotation_rounding_order(golden_dir):
     assert np.array_equal(qf.cpu().numpy(), qo) and np.array_equal(sf.cpu().numpy(), so)
     qo, so = oracle.quantize(synth.as_u16(sq), oracle.AXIS_LAST, oracle.HAD_DET)
     assert np.array_equal(ql.cpu().numpy(), qo) and np.array_equal(sl.cpu().numpy(), so)
+
+
+@pytest.mark.parametrize("shape", [(96, 66), (160, 130), (4128, 4098), (4160, 130)])
+@pytest.mark.parametrize("rnd", [mx.RNE, mx.SR])
+def test_column_wise_workgroups_of_four_and_eight_waves(shape, rnd):
+    # a last workgroup with fewer row blocks than waves, columns in no whole tile, scale rows of odd length: the row-wise kernel on the
+    # transposed tensor is the reference, byte for byte
+    x = synth.normal(*shape, 1.0, 3, synth.STREAM_X).to("cuda:0")
+    q, s = mx.mxfp4_quantize(x, mx.AXIS_FIRST, mx.HAD_DET, rnd, 11)
+    qt, st = mx.mxfp4_quantize(x.T.contiguous(), mx.AXIS_LAST, mx.HAD_DET, rnd, 11)
+    assert torch.equal(q, qt) and torch.equal(s, st)
