@@ -982,7 +982,9 @@ struct EdgeGemm {
     void *out;
     int64_t ld;
     int tiles_m, tiles_n;
-    int out_fp32, accumulate, vec;  // vec: four consecutive outputs may be stored at once
+    int out_fp32, accumulate;
+    int vec;  // bits: 1 four consecutive outputs may be stored at once, 2 sixteen bytes of them, 4 rows are whole cache lines,
+              // 8 rows are whole 4 bytes (but not 16)
 };
 
 // The tile (tm x tn) of workgroup `bid`: each XCD (workgroup id mod 8) takes a contiguous run of the tile sequence, which walks the grid in
@@ -1275,7 +1277,7 @@ __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm 
     const int rl = lane / CHUNKS, ch = lane % CHUNKS;
     const int64_t col = n0 + wn * 32 * WN + ch * 4;
     const int64_t left = p.Rb - col;
-    const bool whole = p.vec && left >= 4;
+    const bool whole = (p.vec & 1) && left >= 4;
 #pragma unroll
     for (int i = 0; i < WM; ++i) {
 #pragma unroll
@@ -1530,7 +1532,230 @@ done:
     // a lane holds columns 4 kb .. +3 of row r16 of the wave's 16 x 16: straight to memory
     const int64_t row = m0 + wm * 16 + r16, col = n0 + wn * 16 + 4 * kb;
     const int64_t left = p.Rb - col;
-    if (row < p.Ra) store4(p, row, col, left, p.vec && left >= 4, acc);
+    if (row < p.Ra) store4(p, row, col, left, (p.vec & 1) && left >= 4, acc);
+}
+
+// ---- ragged-shape kernel, 128 x 64 tiles, rows of at most two stages ------------------------------
+// 256 bytes of codes per row are 16 matrix instructions per wave and tile: what such a product takes is the writing of its output,
+// and on gemm_edge_kernel's tiles, of which a compute unit holds one or two, it took 2 to 2.5 times as long as that (a tile's first loads, its
+// few instructions and its stores one after the other, the rows of a bf16 tile stored in 64-byte pieces).  Here a workgroup loads its whole
+// contraction at once and keeps no ring: S stages of 24 KiB and 3 KiB of scale bytes, five or three workgroups per compute unit, whose
+// loads, instructions and stores overlap; the output leaves in 128- or 256-byte rows of the tile, past the caches where these are whole
+// lines, else through them, so that neighbouring tiles' halves of a line meet.
+// Measured back to back in a graph, us, gemm_edge_kernel on the tiles it was given / this: MXFP4, bf16 output, 9624 x 20560 x 32 218 / 99 (4.0
+// TB/s of output), 12008 x 3400 x 512 43.1 / 32.0, 12526 x 9728 x 256 80 / 55, 2273 x 7832 x 256 19.6 / 12.1, rows of 3003 elements 2000 x 3000 x 480
+// 13.2 / 9.7; fp32 8192 x 8192 x 512 69.9 / 62.6, added to 2048 x 3072 x 384 13.7 / 10.8; MXFP8 12008 x 3400 x 256 41.2 / 30.4.  With three
+// stages (75 KiB, two workgroups per unit) it was the slower: 2048 x 3072 x 768 9.2 / 9.9.
+template <int S>
+struct ShortTile {
+    static constexpr int TM = 128, TN = 64, ROWS = TM + TN, STAGE = ROWS * 128, OFF_S = S * STAGE, LDS = OFF_S + ROWS * 16;
+};
+
+template <int FMT, int S>
+__global__ __launch_bounds__(256) void gemm_short_kernel(const EdgeGemm p0, const EdgeGemm p1, const uint32_t groups0)
+{
+    const bool second = blockIdx.x >= groups0;  // uniform
+    const EdgeGemm &p = second ? p1 : p0;
+    const uint32_t bid = blockIdx.x - (second ? groups0 : 0u);
+    using Tile = ShortTile<S>;
+    constexpr int TM = Tile::TM, TN = Tile::TN;
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[Tile::LDS];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+
+    int64_t m0, n0;
+    if (!edge_tile(p, bid, TM, TN, m0, n0)) return;
+    const int rowbytes = (int)(FMT ? p.C : (p.C >> 1)), nkb = (int)(p.C >> 5);  // at most 128 S, 4 S (E4M3) or 8 S
+    const int nstages = (rowbytes + 127) >> 7;
+    const int last_a = (int)(p.Ra - m0 < TM ? p.Ra - m0 : TM) - 1, last_b = (int)(p.Rb - n0 < TN ? p.Rb - n0 : TN) - 1;
+
+    // Scale bytes: 16 per row in LDS, zeros behind the end of the row (as in gemm_edge_kernel); piece i: 8 of them, of row (tid + 256 i) / 2
+    uint64_t piece[2] = {0, 0};
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int idx = tid + 256 * i, r = idx >> 1, col = (idx & 1) * 8, left = nkb - col;
+        if (r >= Tile::ROWS || left <= 0) continue;
+        const bool isb = r >= TM;
+        const int64_t r0 = isb ? n0 : m0, total = (isb ? p.Rb : p.Ra) * nkb;
+        const int want = isb ? r - TM : r, last = isb ? last_b : last_a;
+        const int64_t at = (r0 + (want < last ? want : last)) * nkb + col;
+        const uint8_t *base = isb ? p.bs : p.as;
+        if (total >= 8) {
+            const int64_t from = at < total - 8 ? at : total - 8;  // (the array's last bytes: loaded from further ahead)
+            const Bytes8 t = *reinterpret_cast<const Bytes8 *>(base + from);
+            piece[i] = (t.v[0] | (uint64_t)t.v[1] << 32) >> (8 * (int)(at - from));
+        } else {
+            for (int k = 0; k < left; ++k) piece[i] |= (uint64_t)base[at + k] << (8 * k);
+        }
+        if (left < 8) piece[i] &= (uint64_t(1) << (8 * left)) - 1;
+    }
+    // codes: load n of wave w and stage s moves 8-row group 6 w + n, chunks beyond the end of a row are its last one again
+#pragma unroll
+    for (int n = 0; n < 6; ++n) {
+        const int group = wave * 6 + n;
+        const bool isb = group >= TM / 8;
+        const int want = (isb ? group - TM / 8 : group) * 8 + (lane >> 3), last = isb ? last_b : last_a;
+        const uint8_t *base = isb ? p.bq + n0 * rowbytes : p.aq + m0 * rowbytes;
+        const int row = (want < last ? want : last) * rowbytes, chunk = ((lane & 7) ^ (lane >> 3) ^ (n & 1)) << 4;
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const int at = s * 128 + chunk < rowbytes - 16 ? s * 128 + chunk : rowbytes - 16;
+            if (s < nstages) dma16(lds0 + (uint32_t)(s * Tile::STAGE + group * 1024), (uint32_t)(row + at), base);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        if (tid + 256 * i < 2 * Tile::ROWS)
+            *reinterpret_cast<uint2 *>(smem + Tile::OFF_S + (tid + 256 * i) * 8) = make_uint2((uint32_t)piece[i], (uint32_t)(piece[i] >> 32));
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+
+    // fragments and scale bytes as in gemm_edge_kernel
+    const int fr = lane & 31, fh = lane >> 5;
+    const uint32_t foff = (uint32_t)((fr >> 3) * 1024 + (fr & 7) * 128 + ((fh ^ (fr & 7) ^ ((fr >> 3) & 1)) << 4));
+    const uint32_t perm_sel = FMT ? (fh ? 0x03010301u : 0x02000200u) : (fh ? 0x07050301u : 0x06040200u);
+    v16f acc[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        if (s >= nstages) break;
+        const uint8_t *st = smem + s * Tile::STAGE;
+        auto frag = [&](int row0, int kk) { return *reinterpret_cast<const v4i *>(st + row0 * 128 + (foff ^ (uint32_t)(kk << 5))); };
+        auto scale = [&](int row0) {
+            const uint8_t *q = smem + Tile::OFF_S + (row0 + fr) * 16 + s * (FMT ? 4 : 8);
+            if (FMT) return (int)__builtin_amdgcn_perm(0u, *reinterpret_cast<const uint32_t *>(q), perm_sel);
+            const uint2 w = *reinterpret_cast<const uint2 *>(q);
+            return (int)__builtin_amdgcn_perm(w.y, w.x, perm_sel);
+        };
+        v4i fa[2][4], fb[4];
+        int sa[2];
+        const int sb = scale(TM + wn * 32);
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) fb[kk] = frag(TM + wn * 32, kk);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            sa[i] = scale(wm * 64 + i * 32);
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) fa[i][kk] = frag(wm * 64 + i * 32, kk);
+        }
+        auto step = [&](auto k_) {
+            constexpr int k = decltype(k_)::value;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                if constexpr (FMT) {
+                    const v4i b0 = fb[2 * k], b1 = fb[2 * k + 1], a0 = fa[i][2 * k], a1 = fa[i][2 * k + 1];
+                    const v8i b8 = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w}, a8 = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
+                    acc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(b8, a8, acc[i], 0, 0, k, sb, k, sa[i]);
+                } else {
+                    const v4i b0 = fb[k], a0 = fa[i][k];
+                    const v8i b8 = {b0.x, b0.y, b0.z, b0.w, 0, 0, 0, 0}, a8 = {a0.x, a0.y, a0.z, a0.w, 0, 0, 0, 0};
+                    acc[i] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(b8, a8, acc[i], 4, 4, k, sb, k, sa[i]);
+                }
+            }
+        };
+        step(IC<0>{}), step(IC<1>{});
+        if constexpr (!FMT) step(IC<2>{}), step(IC<3>{});
+    }
+
+    // The tile is put together in LDS, 16-byte chunk c of row r at chunk c ^ r (mod the chunks of a row), and leaves in whole rows.
+    const bool lines = p.vec & 4;
+    if (!p.out_fp32) {
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");  // everyone has multiplied
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int qd = 0; qd < 4; ++qd) {
+                const int r = wm * 64 + i * 32 + fr, c = wn * 4 + qd;
+                *reinterpret_cast<uint2 *>(smem + r * 128 + ((c ^ (r & 7)) << 4) + fh * 8) =
+                    make_uint2(pack_bf16(acc[i][4 * qd], acc[i][4 * qd + 1]), pack_bf16(acc[i][4 * qd + 2], acc[i][4 * qd + 3]));
+            }
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        uint16_t *const out = reinterpret_cast<uint16_t *>(p.out) + m0 * p.ld + n0;
+        const int cols = (int)(p.Rb - n0 < TN ? p.Rb - n0 : TN);
+        if (p.vec & 2) {
+            const int c = lane & 7;
+#pragma unroll
+            for (int it = 0; it < 4; ++it) {
+                const int r = wave * 32 + it * 8 + (lane >> 3);
+                const v4u v = *reinterpret_cast<const v4u *>(smem + r * 128 + ((c ^ (r & 7)) << 4));
+                if (r > last_a) continue;
+                uint16_t *o = out + r * p.ld + c * 8;
+                if (c * 8 + 8 <= cols) {
+                    if (lines) __builtin_nontemporal_store(v, reinterpret_cast<v4u *>(o));
+                    else *reinterpret_cast<v4u *>(o) = v;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        if (c * 8 + e < cols) o[e] = (uint16_t)(v[e >> 1] >> (16 * (e & 1)));
+                }
+            }
+        } else if (p.vec & 8) {  // rows of whole 4 bytes: two columns a lane
+            const int c = lane & 31;
+#pragma unroll 4
+            for (int it = 0; it < 16; ++it) {
+                const int r = wave * 32 + it * 2 + (lane >> 5);
+                const uint32_t v = *reinterpret_cast<const uint32_t *>(smem + r * 128 + (((c >> 2) ^ (r & 7)) << 4) + (c & 3) * 4);
+                if (r > last_a || c * 2 >= cols) continue;
+                uint16_t *o = out + r * p.ld + c * 2;
+                if (c * 2 + 1 < cols) *reinterpret_cast<uint32_t *>(o) = v;
+                else *o = (uint16_t)v;
+            }
+        } else {
+#pragma unroll 4
+            for (int it = 0; it < 32; ++it) {
+                const int r = wave * 32 + it;
+                const uint16_t v = *reinterpret_cast<const uint16_t *>(smem + r * 128 + (((lane >> 3) ^ (r & 7)) << 4) + (lane & 7) * 2);
+                if (r <= last_a && lane < cols) out[r * p.ld + lane] = v;
+            }
+        }
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {  // rows 32 i .. +31 of either half of the tile
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+        for (int qd = 0; qd < 4; ++qd) {
+            const int r = wm * 32 + fr, c = wn * 8 + qd * 2 + fh;
+            *reinterpret_cast<v4f *>(smem + r * 256 + ((c ^ (r & 15)) << 4)) =
+                (v4f){acc[i][4 * qd], acc[i][4 * qd + 1], acc[i][4 * qd + 2], acc[i][4 * qd + 3]};
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        float *const out = reinterpret_cast<float *>(p.out) + m0 * p.ld + n0;
+        const int cols = (int)(p.Rb - n0 < TN ? p.Rb - n0 : TN);
+        auto tile_row = [&](int r) { return (r >> 5) * 64 + i * 32 + (r & 31); };
+        if (p.vec & 1) {
+            const int c = lane & 15;
+#pragma unroll
+            for (int it = 0; it < 4; ++it) {
+                const int r = wave * 16 + it * 4 + (lane >> 4), row = tile_row(r);
+                v4f v = *reinterpret_cast<const v4f *>(smem + r * 256 + ((c ^ (r & 15)) << 4));
+                if (row > last_a) continue;
+                float *o = out + row * p.ld + c * 4;
+                if (c * 4 + 4 <= cols) {
+                    if (p.accumulate) v += *reinterpret_cast<const v4f *>(o);
+                    if (lines) __builtin_nontemporal_store(v, reinterpret_cast<v4f *>(o));
+                    else *reinterpret_cast<v4f *>(o) = v;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (c * 4 + e < cols) o[e] = p.accumulate ? (o[e] + v[e]) : v[e];
+                }
+            }
+        } else {  // a column a lane
+#pragma unroll 4
+            for (int it = 0; it < 16; ++it) {
+                const int r = wave * 16 + it, row = tile_row(r);
+                const float v = *reinterpret_cast<const float *>(smem + r * 256 + (((lane >> 2) ^ (r & 15)) << 4) + (lane & 3) * 4);
+                if (row > last_a || lane >= cols) continue;
+                float *o = out + row * p.ld + lane;
+                *o = p.accumulate ? *o + v : v;
+            }
+        }
+    }
 }
 
 }  // namespace
@@ -1588,8 +1813,11 @@ static hipError_t launch_any_f(const GemmArgs &g, hipStream_t st)
 
 static EdgeGemm edge_args(const GemmArgs &g, int tm, int tn)
 {
+    const int64_t pitch = g.ld * (g.out_fp32 ? 4 : 2);
+    auto rows_at = [&](int bytes) { return pitch % bytes == 0 && reinterpret_cast<uintptr_t>(g.out) % bytes == 0; };
+    const int vec = rows_at(g.out_fp32 ? 16 : 8) + 2 * rows_at(16) + 4 * rows_at(128) + 8 * (rows_at(4) && !rows_at(16));
     return EdgeGemm{g.aq, g.as, g.bq, g.bs, g.Ra, g.Rb, g.C, g.out, g.ld, (int)((g.Ra + tm - 1) / tm), (int)((g.Rb + tn - 1) / tn),
-                    g.out_fp32, g.accumulate, (g.ld % 4) == 0 && (reinterpret_cast<uintptr_t>(g.out) % (g.out_fp32 ? 16 : 8)) == 0};
+                    g.out_fp32, g.accumulate, vec};
 }
 static uint32_t edge_groups(const EdgeGemm &p) { return ((uint32_t)(p.tiles_m * p.tiles_n) + 7u) & ~7u; }
 
@@ -1637,6 +1865,14 @@ static bool edge_eligible(const GemmArgs &g)
     return g.a_fmt == g.b_fmt && g.C < (int64_t(1) << 24) && g.Ra < (int64_t(1) << 31);
 }
 
+// stages (128 bytes of codes per row) of the longer of one or two products
+static int64_t edge_stages(const GemmArgs &g0, const GemmArgs *g1)
+{
+    auto stages = [](const GemmArgs &g) { return ((g.a_fmt ? g.C : g.C / 2) + 127) / 128; };
+    const int64_t s0 = stages(g0), s1 = g1 ? stages(*g1) : 0;
+    return s0 > s1 ? s0 : s1;
+}
+
 // The tile shape with the lowest estimate for one product, or two of one format side by side, among those whose tiles, a
 // workgroup each, make a grid that can be launched (us = NO_ROUTE: none does).
 constexpr double NO_ROUTE = 1e30;
@@ -1660,6 +1896,8 @@ static EdgeChoice choose_edge(const GemmArgs &g0, const GemmArgs *g1 = nullptr)
     auto short_rows = [](const GemmArgs &g) { return (g.a_fmt ? g.C : g.C / 2) <= 512; };
     if (short_rows(g0) && (!g1 || short_rows(*g1)) && tiles(g0) + (g1 ? tiles(*g1) : 0) <= 2 * NUM_CUS) return best;
     const double mid = cost(128, 64, 256, 512, 9.3, 1.5), large = cost(128, 256, 512, 256, 10.5, 3.5);
+    // (more tiles than that, at most two stages: gemm_short_kernel, never the slower one over the 24 sizes measured)
+    if (edge_stages(g0, g1) <= 2 && mid < NO_ROUTE) return EdgeChoice{1, mid};
     if (mid <= best.us) best = EdgeChoice{1, mid};
     if (large <= best.us) best = EdgeChoice{2, large};
     return best;
@@ -1694,6 +1932,16 @@ static GemmRoute any_route(const GemmArgs &g)
     return edge.us < NO_ROUTE ? GemmRoute{ROUTE_EDGE_64 + edge.tile, edge.us} : GemmRoute{ROUTE_ANY_SHAPE, NO_ROUTE};
 }
 
+template <int FMT, int S>
+static hipError_t launch_short_f(const GemmArgs &g0, const GemmArgs *g1, hipStream_t st)
+{
+    using Tile = ShortTile<S>;
+    const EdgeGemm p0 = edge_args(g0, Tile::TM, Tile::TN), p1 = edge_args(g1 ? *g1 : g0, Tile::TM, Tile::TN);
+    const uint32_t n0 = edge_groups(p0), n1 = g1 ? edge_groups(p1) : 0u;
+    hipLaunchKernelGGL((gemm_short_kernel<FMT, S>), dim3(n0 + n1), dim3(256), 0, st, p0, p1, n0);
+    return hipGetLastError();
+}
+
 // Of the products (or pairs) on 64 x 64 tiles, those on 32 x 32 ones: the number of these, else 0.  They are faster up to two workgroups per
 // compute unit: time on 64 x 64 tiles over time on 32 x 32 ones, MXFP4 (MXFP8), at 1, 2, 4, 8, 16, 56 stages: up to 256 tiles 1.1 1.15
 // 1.15 1.3 1.45 1.8 (1.05 1.15 1.2 1.23 1.37 1.6), 320 to 512 tiles 0.98 1.04 1.02 1.14 1.2 1.25 (0.95 1.03 1.07 1.06 1.16 1.15), 560 and 640
@@ -1709,6 +1957,11 @@ static int small_tiles(const GemmArgs &g0, const GemmArgs *g1)
 static hipError_t launch_edge(const GemmArgs &g0, const GemmArgs *g1, int tile, hipStream_t st)
 {
     if (tile == 2) return g0.a_fmt ? launch_edge_f<1, 2, 2, 4, 3>(g0, g1, st) : launch_edge_f<0, 2, 2, 4, 3>(g0, g1, st);
+    if (tile == 1) {
+        const int stages = edge_stages(g0, g1);
+        if (stages <= 1) return g0.a_fmt ? launch_short_f<1, 1>(g0, g1, st) : launch_short_f<0, 1>(g0, g1, st);
+        if (stages == 2) return g0.a_fmt ? launch_short_f<1, 2>(g0, g1, st) : launch_short_f<0, 2>(g0, g1, st);
+    }
     if (tile == 1) return g0.a_fmt ? launch_edge_f<1, 2, 1, 2, 3>(g0, g1, st) : launch_edge_f<0, 2, 1, 2, 3>(g0, g1, st);
     if (const int small = small_tiles(g0, g1)) {
         // (eight stage buffers with a workgroup per compute unit at most: 1.2 times as fast from 32 stages of operands that come
