@@ -650,10 +650,38 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
             return mine ? (row * (int)ld + col) * ESIZE : (int)0x80000000u;
         };
         auto rag_put = [&](int row, int col, auto v) {
-            const int off = rag_offset(row, col);
-            if constexpr (ACC) v += __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0));
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), rsrc, off, 0, 2 /* nt */);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), rsrc, rag_offset(row, col), 0, 2 /* nt */);
         };
+        // ACC: the values added to are loaded eight at a time (whole narrow tiles: a batch ahead).  Loaded one by one in front of their
+        // stores, which the compiler must keep in that order, they were 32 or 64 round trips to memory per tile.  fp32 added to, us, before /
+        // now: 6144 x 4096 x 8192 131 / 120, 28672 x 4096 x 8192 690 / 515, 4096 x 14336 x 4096 233 / 165, 1024 x 4096 x 8192 (narrow) 42.1 /
+        // 33.7; moved back 10000 x 8576 x 1760 344 / 210, 4320 x 1440 x 2080 27.9 / 21.7; MXFP8 4096 x 4096 x 2048 52.3 / 44.2.
+        constexpr int RPS = NJ == 2 ? 4 : 2;  // fp32 rows per store instruction
+        constexpr bool AHEAD = ACC && !RAG && NJ == 2;
+        v4f prev[AHEAD ? 2 : 1][8];
+        auto load_prev = [&](int first, int set) {
+            if (first >= (NJ == 2 ? 32 : 64)) return;
+            const float *from = reinterpret_cast<const float *>(out) + (row0 + first * RPS + lane / (64 / RPS)) * ld + col0 + lane % (64 / RPS) * 4;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) prev[set][u] = *reinterpret_cast<const v4f *>(from + (int64_t)(u * RPS) * ld);
+        };
+        auto rag_put8 = [&](int row, int col, const v4f (&buf)[8]) {  // RAG: rows row + RPS u
+            int off[8];
+            v4f old[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                off[u] = rag_offset(row + RPS * u, col);
+                if constexpr (ACC) old[u] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off[u], 0, 0));
+            }
+            __builtin_amdgcn_sched_barrier(0);  // (without it the offsets of later batches are worked out here and the sums spill)
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                v4f v = buf[u];
+                if constexpr (ACC) v += old[u];
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), rsrc, off[u], 0, 2 /* nt */);
+            }
+        };
+        if constexpr (AHEAD) load_prev(0, 0);
         if constexpr (NJ == 2 && !OUT_FP32) {
             // Narrow tile, bf16: the wave's 128 rows x 64 columns are 16 KiB, one pass.  A row is 8 chunks of 16
             // bytes; chunk c of row r sits at position c ^ ((r >> 1) & 7): the 8-byte writes of a quarter wave
@@ -715,22 +743,22 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     v4f buf[8];
+                    if constexpr (ACC && !RAG) load_prev(8 * (2 * pass + h + (AHEAD ? 1 : 0)), AHEAD ? 1 - h : 0);
 #pragma unroll
                     for (int u = 0; u < 8; ++u) {
                         const int r = (8 * h + u) * 4 + rl;
                         buf[u] = *reinterpret_cast<const v4f *>(epi + r * 256 + ((ch ^ (r & 15)) << 4));
                     }
                     __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (RAG) {
+                        rag_put8(pass * 64 + 8 * h * 4 + rl, ch * 4, buf);
+                    } else {
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        if constexpr (RAG) {
-                            rag_put(pass * 64 + (8 * h + u) * 4 + rl, ch * 4, buf[u]);
-                            continue;
+                        for (int u = 0; u < 8; ++u) {
+                            v4f v = buf[u];
+                            if constexpr (ACC) v += prev[AHEAD ? h : 0][u];
+                            __builtin_nontemporal_store(v, reinterpret_cast<v4f *>(obase + (int64_t)((8 * h + u) * 4) * ld));
                         }
-                        v4f *o = reinterpret_cast<v4f *>(obase + (int64_t)((8 * h + u) * 4) * ld);
-                        v4f v = buf[u];
-                        if (ACC) v += *o;
-                        __builtin_nontemporal_store(v, o);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -803,22 +831,22 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     v4f buf[8];
+                    if constexpr (ACC && !RAG) load_prev(8 * (2 * pass + h + (AHEAD ? 1 : 0)), AHEAD ? 1 - h : 0);
 #pragma unroll
                     for (int u = 0; u < 8; ++u) {
                         const int r = (8 * h + u) * 2 + rl;
                         buf[u] = *reinterpret_cast<const v4f *>(epi + r * 512 + ((ch ^ r) << 4));
                     }
                     __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (RAG) {
+                        rag_put8(pass * 32 + 8 * h * 2 + rl, ch * 4, buf);
+                    } else {
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        if constexpr (RAG) {
-                            rag_put(pass * 32 + (8 * h + u) * 2 + rl, ch * 4, buf[u]);
-                            continue;
+                        for (int u = 0; u < 8; ++u) {
+                            v4f v = buf[u];
+                            if constexpr (ACC) v += prev[AHEAD ? h : 0][u];
+                            __builtin_nontemporal_store(v, reinterpret_cast<v4f *>(obase + (int64_t)((8 * h + u) * 2) * ld));
                         }
-                        v4f *o = reinterpret_cast<v4f *>(obase + (int64_t)((8 * h + u) * 2) * ld);
-                        v4f v = buf[u];
-                        if (ACC) v += *o;
-                        __builtin_nontemporal_store(v, o);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
