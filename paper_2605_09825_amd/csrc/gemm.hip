@@ -1030,19 +1030,19 @@ __device__ __forceinline__ bool edge_tile(const EdgeGemm &p, uint32_t bid, int t
     return true;
 }
 
-// four consecutive outputs of one row from column col on, at once (whole) or as many of them as are left
+// four consecutive outputs of one row from column col on, at once (whole: what they are added to is in v already) or as many of them as
+// are left
+template <bool ACC>
 __device__ __forceinline__ void store4(const EdgeGemm &p, int64_t row, int64_t col, int64_t left, bool whole, const v4f v)
 {
     if (p.out_fp32) {
         float *o = reinterpret_cast<float *>(p.out) + row * p.ld + col;
         if (whole) {
-            v4f t = v;
-            if (p.accumulate) t += *reinterpret_cast<const v4f *>(o);
-            __builtin_nontemporal_store(t, reinterpret_cast<v4f *>(o));
+            __builtin_nontemporal_store(v, reinterpret_cast<v4f *>(o));
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                if (e < left) o[e] = p.accumulate ? (o[e] + v[e]) : v[e];
+                if (e < left) o[e] = ACC && p.accumulate ? (o[e] + v[e]) : v[e];
         }
     } else {
         uint16_t *o = reinterpret_cast<uint16_t *>(p.out) + row * p.ld + col;
@@ -1059,7 +1059,8 @@ __device__ __forceinline__ void store4(const EdgeGemm &p, int64_t row, int64_t c
 }
 
 // A launch may carry two independent problems: workgroups 0 .. groups0-1 (a multiple of 8) work on p0, the others on p1.
-template <int FMT, int WM, int WN, int NWN, int NBUF>
+// ACC: a product of the launch is added to its output.
+template <int FMT, int WM, int WN, int NWN, int NBUF, bool ACC>
 __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm p0, const EdgeGemm p1, const uint32_t groups0)
 {
     const bool second = blockIdx.x >= groups0;  // uniform
@@ -1308,6 +1309,16 @@ __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm 
     const bool whole = (p.vec & 1) && left >= 4;
 #pragma unroll
     for (int i = 0; i < WM; ++i) {
+      // values added to: all at once, under the way through LDS; one by one in front of their stores 6656 x 11008 x 768 took 190 us, now 146,
+      // 13888 x 6912 x 576 250, now 194
+      v4f old[32 / RPI];
+      if (ACC && p.accumulate && whole) {
+#pragma unroll
+        for (int u = 0; u < 32 / RPI; ++u) {
+            const int64_t row = m0 + wm * 32 * WM + 32 * i + u * RPI + rl;
+            if (row < p.Ra) old[u] = *reinterpret_cast<const v4f *>(reinterpret_cast<const float *>(p.out) + row * p.ld + col);
+        }
+      }
 #pragma unroll
       for (int j = 0; j < WN; ++j)
 #pragma unroll
@@ -1320,9 +1331,10 @@ __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm 
       for (int u = 0; u < 32 / RPI; ++u) {
         const int r = u * RPI + rl;
         const int64_t row = m0 + wm * 32 * WM + 32 * i + r;
-        const v4f v = *reinterpret_cast<const v4f *>(epi + r * PITCH + ((ch ^ (r & (CHUNKS - 1))) << 4));
+        v4f v = *reinterpret_cast<const v4f *>(epi + r * PITCH + ((ch ^ (r & (CHUNKS - 1))) << 4));
         if (row >= p.Ra) continue;
-        store4(p, row, col, left, whole, v);
+        if (ACC && p.accumulate && whole) v += old[u];
+        store4<ACC>(p, row, col, left, whole, v);
       }
     }
 }
@@ -1560,7 +1572,10 @@ done:
     // a lane holds columns 4 kb .. +3 of row r16 of the wave's 16 x 16: straight to memory
     const int64_t row = m0 + wm * 16 + r16, col = n0 + wn * 16 + 4 * kb;
     const int64_t left = p.Rb - col;
-    if (row < p.Ra) store4(p, row, col, left, (p.vec & 1) && left >= 4, acc);
+    if (row >= p.Ra) return;
+    const bool whole = (p.vec & 1) && left >= 4;
+    if (p.accumulate && whole) acc += *reinterpret_cast<const v4f *>(reinterpret_cast<const float *>(p.out) + row * p.ld + col);
+    store4<true>(p, row, col, left, whole, acc);
 }
 
 // ---- ragged-shape kernel, 128 x 64 tiles, rows of at most two stages ------------------------------
@@ -1757,20 +1772,27 @@ __global__ __launch_bounds__(256) void gemm_short_kernel(const EdgeGemm p0, cons
         auto tile_row = [&](int r) { return (r >> 5) * 64 + i * 32 + (r & 31); };
         if (p.vec & 1) {
             const int c = lane & 15;
+            v4f v[4], old[4];  // (what they are added to: all loads before the first store)
 #pragma unroll
             for (int it = 0; it < 4; ++it) {
                 const int r = wave * 16 + it * 4 + (lane >> 4), row = tile_row(r);
-                v4f v = *reinterpret_cast<const v4f *>(smem + r * 256 + ((c ^ (r & 15)) << 4));
+                v[it] = *reinterpret_cast<const v4f *>(smem + r * 256 + ((c ^ (r & 15)) << 4));
+                old[it] = (v4f){0.f, 0.f, 0.f, 0.f};
+                if (p.accumulate && row <= last_a && c * 4 + 4 <= cols) old[it] = *reinterpret_cast<const v4f *>(out + row * p.ld + c * 4);
+            }
+#pragma unroll
+            for (int it = 0; it < 4; ++it) {
+                const int r = wave * 16 + it * 4 + (lane >> 4), row = tile_row(r);
                 if (row > last_a) continue;
                 float *o = out + row * p.ld + c * 4;
                 if (c * 4 + 4 <= cols) {
-                    if (p.accumulate) v += *reinterpret_cast<const v4f *>(o);
-                    if (lines) __builtin_nontemporal_store(v, reinterpret_cast<v4f *>(o));
-                    else *reinterpret_cast<v4f *>(o) = v;
+                    if (p.accumulate) v[it] += old[it];
+                    if (lines) __builtin_nontemporal_store(v[it], reinterpret_cast<v4f *>(o));
+                    else *reinterpret_cast<v4f *>(o) = v[it];
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        if (c * 4 + e < cols) o[e] = p.accumulate ? (o[e] + v[e]) : v[e];
+                        if (c * 4 + e < cols) o[e] = p.accumulate ? (o[e] + v[it][e]) : v[it][e];
                 }
             }
         } else {  // a column a lane
@@ -1855,7 +1877,10 @@ static hipError_t launch_edge_f(const GemmArgs &g0, const GemmArgs *g1, hipStrea
     using Tile = EdgeTile<WM, WN, NWN, NBUF>;
     const EdgeGemm p0 = edge_args(g0, Tile::TM, Tile::TN), p1 = edge_args(g1 ? *g1 : g0, Tile::TM, Tile::TN);
     const uint32_t n0 = edge_groups(p0), n1 = g1 ? edge_groups(p1) : 0u;
-    hipLaunchKernelGGL((gemm_edge_kernel<FMT, WM, WN, NWN, NBUF>), dim3(n0 + n1), dim3(64 * Tile::WAVES), 0, st, p0, p1, n0);
+    if (g0.accumulate || (g1 && g1->accumulate))
+        hipLaunchKernelGGL((gemm_edge_kernel<FMT, WM, WN, NWN, NBUF, true>), dim3(n0 + n1), dim3(64 * Tile::WAVES), 0, st, p0, p1, n0);
+    else
+        hipLaunchKernelGGL((gemm_edge_kernel<FMT, WM, WN, NWN, NBUF, false>), dim3(n0 + n1), dim3(64 * Tile::WAVES), 0, st, p0, p1, n0);
     return hipGetLastError();
 }
 
