@@ -265,16 +265,18 @@ int mxfp4_gemm_route(int64_t R_a, int64_t R_b, int64_t C, int a_format, int b_fo
  *   route[0] an mxfp4_gemm_pair_kind;
  *   route[1] NARROW_BESIDE_WIDE: the problem on narrow tiles; EDGE: the problem whose tiles start first; else 0;
  *   route[2] SIDE_BY_SIDE: workgroups per XCD (of 32) that problem 0 gets; NARROW_BESIDE_WIDE: those that take a narrow
- *            tile first; EDGE: 0, 1, 2 for 64 x 64 (few outputs: 32 x 32), 128 x 64, 128 x 256 tiles;
- *            else 0;
- *   route[3] NARROW_BESIDE_WIDE: tiles of the other problem that those workgroups add; else 0.
+ *            tile first; EDGE: 0, 1, 2 for 64 x 64 (few outputs: 32 x 32), 128 x 64, 128 x 256 tiles of the
+ *            ragged-shape kernel, 3 for the tiled kernel with its last tiles moved back; else 0;
+ *   route[3] NARROW_BESIDE_WIDE: tiles of the other problem that those workgroups add; EDGE with moved-back tiles: workgroups
+ *            per XCD (of 32) that problem 0 gets, plus 32 if it is on 256 x 128 tiles (else 256 x 256), plus 64 if problem 1
+ *            is; else 0.
  * Host-only.  Returns what mxfp4_gemm_pair would for these sizes and types, or MXFP4_EINVAL.
  */
 typedef enum {
     MXFP4_PAIR_APART = 0,              /* one after the other (mxfp4_gemm_route of each), or one of them empty    */
     MXFP4_PAIR_SIDE_BY_SIDE = 1,       /* both on 256 x 256 tiles, on disjoint sets of compute units              */
     MXFP4_PAIR_NARROW_BESIDE_WIDE = 2, /* few 256 x 128 tiles of the one beside many 256 x 256 ones of the other  */
-    MXFP4_PAIR_EDGE = 3                /* both on the ragged-shape kernel                                         */
+    MXFP4_PAIR_EDGE = 3                /* both on a kernel for ragged sizes (route[2] tells which)                */
 } mxfp4_gemm_pair_kind;
 int mxfp4_gemm_pair_route(int64_t R_a0, int64_t R_b0, int64_t C0, int format0, int64_t ld_out0, int out_dtype0,
                           int64_t R_a1, int64_t R_b1, int64_t C1, int format1, int64_t ld_out1, int out_dtype1,

@@ -949,6 +949,39 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_rag_kernel(const TileGemm p,
     }
 }
 
+// The same for two independent products of ragged sizes (Dgrad and Wgrad of a layer whose widths are in no whole tiles): as in
+// gemm_tile_pair_kernel the first n0 of every XCD's 32 workgroups work on p0, the others on p1; each product is cut into 256 x 256 tiles or,
+// where that fills its share of the chip better, into 256 x 128 ones (narrow0, narrow1).  Side by side on 128 x 256 tiles of
+// gemm_edge_kernel, or one after the other with half the chip idle, such a pair took 1.04 to 1.42 times as long.  us, before / now, layers of
+// M x N x K: 2080 x 4320 x 1440 36.4 / 31.8, 4128 x 4320 x 4064 138 / 116, 1760 x 3584 x 2400 34.0 / 27.7, 1728 x 10112 x 3008 105 / 84; dW added
+// to: 2592 x 5344 x 1280 46.5 / 36.7, 2336 x 2336 x 2336 40.2 / 31.6, 4320 x 2016 x 3264 67.1 / 47.2.
+template <bool OUT0, bool ACC1>
+__global__ __launch_bounds__(256, 1) void gemm_tile_rag_pair_kernel(const TileGemm p0, const int64_t Ra0, const int64_t Rb0, const int narrow0,
+                                                                    const TileGemm p1, const int64_t Ra1, const int64_t Rb1,
+                                                                    const int narrow1, const int n0)
+{
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[LDS_BYTES];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem;
+    const int xcd = blockIdx.x & 7, lw = blockIdx.x >> 3;
+    if (lw < n0) {
+        const int T = p0.tiles_m * p0.tiles_n;
+        if (narrow0)
+            gemm_tile_body<OUT0, false, 0, 2, true, true>(p0.aq, p0.as, p0.bq, p0.bs, p0.C, p0.out, p0.ld, p0.tiles_m, p0.tiles_n,
+                                                          lw * 8 + xcd, (uint32_t)n0 * 8, smem, lds0, 0, T, Ra0, Rb0);
+        else
+            gemm_tile_body<OUT0, false, 0, 4, false, true>(p0.aq, p0.as, p0.bq, p0.bs, p0.C, p0.out, p0.ld, p0.tiles_m, p0.tiles_n,
+                                                           lw * 8 + xcd, (uint32_t)n0 * 8, smem, lds0, 0, T, Ra0, Rb0);
+    } else {
+        const int T = p1.tiles_m * p1.tiles_n;
+        if (narrow1)
+            gemm_tile_body<true, ACC1, 0, 2, true, true>(p1.aq, p1.as, p1.bq, p1.bs, p1.C, p1.out, p1.ld, p1.tiles_m, p1.tiles_n,
+                                                         (lw - n0) * 8 + xcd, (uint32_t)(32 - n0) * 8, smem, lds0, 0, T, Ra1, Rb1);
+        else
+            gemm_tile_body<true, ACC1, 0, 4, false, true>(p1.aq, p1.as, p1.bq, p1.bs, p1.C, p1.out, p1.ld, p1.tiles_m, p1.tiles_n,
+                                                          (lw - n0) * 8 + xcd, (uint32_t)(32 - n0) * 8, smem, lds0, 0, T, Ra1, Rb1);
+    }
+}
+
 // Two independent GEMMs in one launch of 256 workgroups (Dgrad and Wgrad of one layer): on every XCD the
 // first n0 of its 32 workgroups work on p0, the others on p1, each set walking its own problem's tiles.
 // The CUs are split in proportion to the work, so both problems end on full rounds of tiles.  Measured on
@@ -993,7 +1026,7 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_pair_kernel(const TileGemm p
 // 20 % (C = 4064: 181 us), because every 128-byte row piece then takes two line requests.
 // Measured back to back in a graph, bf16 output, the any-shape kernel / the fastest tile of this one: MXFP4 8192 x 6144 x 4064
 // 902 / 181 us (now on moved-back tiles, 121), 16000 x 1000 x 3008 238 / 47, 2080 x 4320 x 1440 69 / 21, 2048 x 3072 x 768
-// 33 / 9, 200 x 4096 x 4096 31 / 8.5, 24 x 6144 x 4096 23.5 / 7.9, 256 x 512 x 512 6.3 / 3.8; MXFP8 8192 x 6144 x 4064
+// 33 / 9, 200 x 4096 x 4096 31 / 8.5, 24 x 6144 x 4096 23.5 / 7.9 (now on 32 x 32 tiles, 5.6); MXFP8 8192 x 6144 x 4064
 // 1335 / 273 (on moved-back tiles 199), 200 x 4096 x 4096 45.5 / 11.9 us.
 template <int WM, int WN, int NWN, int NBUF>
 struct EdgeTile {
@@ -2102,12 +2135,16 @@ static void rag_tiles(const GemmArgs &g, int cus, int64_t *tiles, int64_t *whole
     else if (rem != 0 && 2 * rem <= cus && T / cus <= 4) *whole = T - rem;
 }
 
+static TileGemm rag_args(const GemmArgs &g)
+{
+    return TileGemm{g.aq, g.as, g.bq, g.bs, g.C, g.out, g.ld, (int)((g.Ra + TILE - 1) / TILE), (int)((g.Rb + TILE - 1) / TILE)};
+}
+
 static hipError_t launch_rag(const GemmArgs &g, int cus, hipStream_t st)
 {
     int64_t tiles, whole;
     rag_tiles(g, cus, &tiles, &whole);
-    const TileGemm p{g.aq, g.as, g.bq, g.bs, g.C, g.out, g.ld, (int)((g.Ra + TILE - 1) / TILE),
-                     (int)((g.Rb + TILE - 1) / TILE)};
+    const TileGemm p = rag_args(g);
     const dim3 grid((unsigned)cus);
 #define MXFP4_RAG(O, A, F) \
     hipLaunchKernelGGL((gemm_tile_rag_kernel<O, A, F>), grid, dim3(256), 0, st, p, g.Ra, g.Rb, (int)whole)
@@ -2191,16 +2228,40 @@ static double plan_cost(const GemmArgs &g, const GemmPlan &plan, int cus)
     return us;
 }
 
-// (rows that are not whole cache lines apart: every 128-byte piece is two line requests, of which the narrow tile has half
-// as many again per product)
+// The same of moved-back tiles (rows that are not whole cache lines apart: every 128-byte piece is two line requests, of which the narrow
+// tile has half as many again per product)
+static bool split_lines(const GemmArgs &g) { return (g.a_fmt ? g.C : g.C / 2) % 128 != 0; }
+static double rag_wide_round(const GemmArgs &g) { return wide_round(g) * (split_lines(g) ? 1.2 : 1.05); }
+static double rag_narrow_round(const GemmArgs &g) { return narrow_round(g) * (split_lines(g) ? 1.3 : 1.05); }
+
 static double rag_cost(const GemmArgs &g, int cus)
 {
     if (!rag_eligible(g)) return NO_ROUTE;
     int64_t tiles, whole;
     rag_tiles(g, cus, &tiles, &whole);
-    const bool split_lines = (g.a_fmt ? g.C : g.C / 2) % 128 != 0;
-    return rounds_of(whole, cus) * wide_round(g) * (split_lines ? 1.2 : 1.05) +
-           rounds_of(2 * (tiles - whole), cus) * narrow_round(g) * (split_lines ? 1.3 : 1.05) + 1.0;
+    return rounds_of(whole, cus) * rag_wide_round(g) + rounds_of(2 * (tiles - whole), cus) * rag_narrow_round(g) + 1.0;
+}
+
+// How two products share a launch of gemm_tile_rag_pair_kernel: tile shapes and split of the chip with the lowest estimate.
+struct RagPairChoice {
+    int n0, narrow0, narrow1;
+    double us;
+};
+static RagPairChoice choose_rag_pair(const GemmArgs &g0, const GemmArgs &g1, int cus)
+{
+    RagPairChoice best{0, 0, 0, NO_ROUTE};
+    if (cus != NUM_CUS || g0.a_fmt || g1.a_fmt || !g1.out_fp32 || !rag_eligible(g0) || !rag_eligible(g1)) return best;
+    if (tile_eligible(g0, TILE / 2) && tile_eligible(g1, TILE / 2)) return best;  // (whole tiles: the launches for these)
+    auto tiles = [](const GemmArgs &g) { return ((g.Ra + TILE - 1) / TILE) * ((g.Rb + TILE - 1) / TILE); };
+    for (int n0 = 1; n0 < 32; ++n0)
+        for (int shapes = 0; shapes < 4; ++shapes) {
+            const int narrow0 = shapes & 1, narrow1 = shapes >> 1;
+            const double a = rounds_of(tiles(g0) << narrow0, 8 * n0) * (narrow0 ? rag_narrow_round(g0) : rag_wide_round(g0));
+            const double b = rounds_of(tiles(g1) << narrow1, 256 - 8 * n0) * (narrow1 ? rag_narrow_round(g1) : rag_wide_round(g1));
+            const double us = (a > b ? a : b) + 1.0;
+            if (us < best.us) best = RagPairChoice{n0, narrow0, narrow1, us};
+        }
+    return best;
 }
 
 // How a call runs: its plan, or the whole product as one block on the ragged-shape kernel or on the tiled kernel for
@@ -2275,6 +2336,22 @@ static MixChoice choose_mix(const GemmArgs &gn, const GemmArgs &gw, int cus)
     return best;
 }
 
+static hipError_t launch_rag_pair(const GemmArgs &g0, const GemmArgs &g1, int split, hipStream_t st)
+{
+    const TileGemm p0 = rag_args(g0), p1 = rag_args(g1);
+    const int n0 = split & 31, narrow0 = (split >> 5) & 1, narrow1 = (split >> 6) & 1;
+#define MXFP4_RAG_PAIR(O0, A1)                                                                                                     \
+    hipLaunchKernelGGL((gemm_tile_rag_pair_kernel<O0, A1>), dim3(NUM_CUS), dim3(256), 0, st, p0, g0.Ra, g0.Rb, narrow0, p1, g1.Ra, \
+                       g1.Rb, narrow1, n0)
+    if (g0.out_fp32) {
+        if (g1.accumulate) MXFP4_RAG_PAIR(true, true); else MXFP4_RAG_PAIR(true, false);
+    } else {
+        if (g1.accumulate) MXFP4_RAG_PAIR(false, true); else MXFP4_RAG_PAIR(false, false);
+    }
+#undef MXFP4_RAG_PAIR
+    return hipGetLastError();
+}
+
 static hipError_t launch_mix(const GemmArgs &gn, const GemmArgs &gw, int n1, int cut, hipStream_t st)
 {
     const TileGemm pn = tile_args(gn, TILE / 2), pw = tile_args(gw);
@@ -2326,7 +2403,11 @@ GemmPairRoute route_gemm_pair(const GemmArgs &g0, const GemmArgs &g1, int cus)
         const MixChoice mix1 = choose_mix(g1, g0, cus), mix0 = choose_mix(g0, g1, cus);
         const MixChoice mix = mix1.us <= mix0.us ? mix1 : mix0;
         const double apart = route_gemm(g0, cus).us + route_gemm(g1, cus).us + 4.0;
-        if (mix.us < apart && mix.us < both.us)
+        const RagPairChoice rag = choose_rag_pair(g0, g1, cus);
+        // (0.95: of long products the split's estimate is worth less than that, 8672 x 7328 x 10016 took 859 us in one launch, 794 apart)
+        if (rag.us < 0.95 * apart && rag.us < both.us && rag.us < mix.us)
+            r = GemmPairRoute{PAIR_EDGE, 0, EDGE_MOVED_BACK, rag.n0 + 32 * rag.narrow0 + 64 * rag.narrow1};
+        else if (mix.us < apart && mix.us < both.us)
             r = GemmPairRoute{PAIR_NARROW_BESIDE_WIDE, mix1.us <= mix0.us ? 1 : 0, mix.n1, mix.cut};
         else if (both.us < apart)
             r = GemmPairRoute{PAIR_EDGE, g1.C > g0.C ? 1 : 0, both.tile, 0};
@@ -2362,6 +2443,7 @@ hipError_t launch_gemm_pair(const GemmArgs &g0, const GemmArgs &g1, hipStream_t 
     }
     if (r.kind == PAIR_NARROW_BESIDE_WIDE)
         return r.first ? launch_mix(g1, g0, r.n, r.cut, st) : launch_mix(g0, g1, r.n, r.cut, st);
+    if (r.kind == PAIR_EDGE && r.n == EDGE_MOVED_BACK) return launch_rag_pair(g0, g1, r.cut, st);
     if (r.kind == PAIR_EDGE) return r.first ? launch_edge(g1, &g0, r.n, st) : launch_edge(g0, &g1, r.n, st);
     hipError_t e = launch_gemm(g0, st);
     if (e != hipSuccess) return e;

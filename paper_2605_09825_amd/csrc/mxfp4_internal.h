@@ -85,8 +85,10 @@ struct GemmRoute {
 GemmRoute route_gemm(const GemmArgs &g, int cus);
 // How two independent GEMMs run.  first: the problem on narrow tiles (PAIR_NARROW_BESIDE_WIDE) or the one whose tiles start
 // first (PAIR_EDGE); n: workgroups per XCD of problem 0 (PAIR_SIDE_BY_SIDE) or of the narrow one, or the edge tile shape
-// (0, 1, 2); cut: tiles of the wide product that the workgroups with a narrow tile add.
+// (0, 1, 2; EDGE_MOVED_BACK: both on the tiled kernel for ragged sizes); cut: tiles of the wide product that the workgroups with a narrow
+// tile add, or for EDGE_MOVED_BACK the workgroups per XCD of problem 0, plus 32 and 64 where problem 0 and 1 are on 256 x 128 tiles.
 enum GemmPairKind { PAIR_APART = 0, PAIR_SIDE_BY_SIDE = 1, PAIR_NARROW_BESIDE_WIDE = 2, PAIR_EDGE = 3 };
+constexpr int EDGE_MOVED_BACK = 3;
 struct GemmPairRoute {
     int kind, first, n, cut;
 };
