@@ -12,7 +12,7 @@ constexpr int64_t LLC_BYTES = int64_t(256) << 20;
 constexpr bool beyond_llc(int64_t rows, int64_t cols) { return rows * cols * 2 > LLC_BYTES; }
 
 // Workgroups of the MXFP4 quantisers: row-wise 256 threads for 256 blocks, column-wise 512 threads for 128 columns x 8
-// block rows.
+// block rows (or 256 threads for 128 columns x 4 block rows: twice the workgroups of the same number of threads in all).
 constexpr int ROWS_THREADS = 256, COLS_THREADS = 512;
 constexpr int64_t rows_groups(int64_t rows, int64_t cols) { return (rows * (cols / 32) + 255) / 256; }
 constexpr int64_t cols_groups(int64_t rows, int64_t cols) { return ((cols + 127) / 128) * ((rows / 32 + 7) / 8); }

@@ -39,7 +39,7 @@ __device__ __forceinline__ void encode_block(float (&v)[32], uint32_t sign_mask,
 // One lane per block.  nblocks = rows * (cols/32); block g is row g / bpr, column block g % bpr.
 // A launch may carry two tensors (the two operands of a GEMM): workgroups 0 .. groups-1 of the first job, then those of
 // the second.  Small tensors cost a launch and little else: a forward call of 256 x 512 x 512 went from 15.0 to 11.4 us
-// with one launch for X and W, one of 200 x 4096 x 4096 from 19.4 to 17.3 us.
+// with one launch for X and W (9.7 with a GEMM on 32 x 32 tiles behind it), one of 200 x 4096 x 4096 from 19.4 to 17.3 us.
 struct RowJob {
     const uint16_t *x;
     int64_t nblocks, bpr, ld;
