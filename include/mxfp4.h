@@ -252,7 +252,7 @@ typedef enum {
     MXFP4_ROUTE_BLOCKS = 0,        /* the blocks of mxfp4_gemm_plan, a launch each                           */
     MXFP4_ROUTE_ANY_SHAPE = 1,     /* the any-shape kernel                                                   */
     MXFP4_ROUTE_EDGE_64 = 2,       /* the ragged-shape kernel on 64 x 64 (few outputs: 32 x 32),             */
-    MXFP4_ROUTE_EDGE_128 = 3,      /*   on 128 x 64 (rows of at most 256 bytes of codes: loaded at once)     */
+    MXFP4_ROUTE_EDGE_128 = 3,      /*   on 128 x 64 (rows of at most 256 bytes of codes may be loaded whole) */
     MXFP4_ROUTE_EDGE_256 = 4,      /*   or on 128 x 256 tiles                                                */
     MXFP4_ROUTE_RAGGED_TILED = 5   /* the tiled kernel with its last row and column of tiles moved back      */
 } mxfp4_gemm_route_kind;

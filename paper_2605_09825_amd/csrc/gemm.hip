@@ -1962,6 +1962,20 @@ static int64_t edge_stages(const GemmArgs &g0, const GemmArgs *g1)
 // The tile shape with the lowest estimate for one product, or two of one format side by side, among those whose tiles, a
 // workgroup each, make a grid that can be launched (us = NO_ROUTE: none does).
 constexpr double NO_ROUTE = 1e30;
+
+// Whether 128 x 64 tiles run as gemm_short_kernel: at most two stages, and output rows that are not whole cache lines apart, or more
+// than 4096 tiles.  Such rows it stores in longer pieces: 2048 x 3000 x 288 bf16 10.2 us on 128 x 256 tiles, 7.5 on this, added to in
+// fp32 16.5, 11.4; 512 x 10000 x 512 9.1, 7.1.  Where each row starts a line the other kernels' stores are as good, and few tiles are
+// done sooner there: 2048 x 4096 x 512 8.2, 9.6 (1024 tiles), 4096 x 4096 x 512
+// 14.1, 14.9 (2048 tiles), 512 x 7040 x 512 fp32 6.6, 8.0; many overlap here: 8192 x 8192 x 512 fp32 69.9, 62.6, 12526 x 9728 x 256 80, 55.
+static bool runs_short(const GemmArgs &g0, const GemmArgs *g1)
+{
+    auto fits = [](const GemmArgs &g) {
+        return g.ld * (g.out_fp32 ? 4 : 2) % 128 != 0 || (g.Ra + 127) / 128 * ((g.Rb + 63) / 64) > 4096;
+    };
+    return edge_stages(g0, g1) <= 2 && fits(g0) && (!g1 || fits(*g1));
+}
+
 struct EdgeChoice {
     int tile;  // 0: 64 x 64, 1: 128 x 64, 2: 128 x 256
     double us;
@@ -1982,8 +1996,7 @@ static EdgeChoice choose_edge(const GemmArgs &g0, const GemmArgs *g1 = nullptr)
     auto short_rows = [](const GemmArgs &g) { return (g.a_fmt ? g.C : g.C / 2) <= 512; };
     if (short_rows(g0) && (!g1 || short_rows(*g1)) && tiles(g0) + (g1 ? tiles(*g1) : 0) <= 2 * NUM_CUS) return best;
     const double mid = cost(128, 64, 256, 512, 9.3, 1.5), large = cost(128, 256, 512, 256, 10.5, 3.5);
-    // (more tiles than that, at most two stages: gemm_short_kernel, never the slower one over the 24 sizes measured)
-    if (edge_stages(g0, g1) <= 2 && mid < NO_ROUTE) return EdgeChoice{1, mid};
+    if (runs_short(g0, g1) && mid < NO_ROUTE) return EdgeChoice{1, mid};
     if (mid <= best.us) best = EdgeChoice{1, mid};
     if (large <= best.us) best = EdgeChoice{2, large};
     return best;
@@ -2043,8 +2056,8 @@ static int small_tiles(const GemmArgs &g0, const GemmArgs *g1)
 static hipError_t launch_edge(const GemmArgs &g0, const GemmArgs *g1, int tile, hipStream_t st)
 {
     if (tile == 2) return g0.a_fmt ? launch_edge_f<1, 2, 2, 4, 3>(g0, g1, st) : launch_edge_f<0, 2, 2, 4, 3>(g0, g1, st);
-    if (tile == 1) {
-        const int stages = edge_stages(g0, g1);
+    if (tile == 1 && runs_short(g0, g1)) {
+        const int64_t stages = edge_stages(g0, g1);
         if (stages <= 1) return g0.a_fmt ? launch_short_f<1, 1>(g0, g1, st) : launch_short_f<0, 1>(g0, g1, st);
         if (stages == 2) return g0.a_fmt ? launch_short_f<1, 2>(g0, g1, st) : launch_short_f<0, 2>(g0, g1, st);
     }
