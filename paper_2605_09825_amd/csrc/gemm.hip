@@ -17,6 +17,7 @@
 #include <type_traits>
 
 #include "mxfp4_internal.h"
+#include "scale_batches.h"
 
 namespace mxfp4 {
 namespace {
@@ -1384,7 +1385,7 @@ __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm 
 //     its waits hold up nobody's direct-to-LDS loads.
 // NBUF stage buffers: 4 (40 KiB, four workgroups per compute unit) or 8 (72 KiB).
 // Measured back to back in a graph, bf16 output, 64 x 64 tiles / this: MXFP4 24 x 6144 x 4096 8.0 / 5.6 us, 256 x 512 x 512
-// 4.1 / 3.6, 100 x 1000 x 14336 20.9 / 11.3, 500 x 1000 x 1440 6.3 / 5.5; MXFP8 24 x 6144 x 4096 11.1 / 7.2.  What is left at 24 x 6144
+// 4.1 / 3.6, 100 x 1000 x 14336 20.6 / 12.1, 500 x 1000 x 1440 6.3 / 5.5; MXFP8 24 x 6144 x 4096 11.1 / 7.2.  What is left at 24 x 6144
 // x 4096: 1.7 us of launch, 1.4 us until the first stage and its scale bytes are there, 0.12 us per stage.
 // The same on 64 x 64 tiles (V_MFMA_SCALE_F32_32X32X64_F8F6F4) was 20 % faster than gemm_edge_kernel's from 32 stages on and
 // slower below 16: not built.
@@ -1401,6 +1402,7 @@ __global__ __launch_bounds__(320) void gemm_small_kernel(const EdgeGemm p0, cons
     constexpr int T = SMALL, OFF_SB = NBUF * SMALL_STAGE;
     constexpr int SB = FMT ? 4 : 8;   // scale bytes per row and stage
     constexpr int BATCH_STAGES = 64 / SB;
+    static_assert(scale_batch_drained(2, BATCH_STAGES) && scale_batch_in_time(1, BATCH_STAGES), "scale buffers refilled too early or too late");
     __shared__ __attribute__((aligned(1024))) uint8_t smem[OFF_SB + 2 * SMALL_SC];
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -1493,9 +1495,12 @@ __global__ __launch_bounds__(320) void gemm_small_kernel(const EdgeGemm p0, cons
         if (nbatches > 1) load(1);
         for (int s = 0; s <= nstages; ++s) {  // (as many barriers as the others have)
             asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-            if (s % BATCH_STAGES == 0 && s / BATCH_STAGES + 1 < nbatches) {  // nobody reads the batch before the last any more
-                write(s / BATCH_STAGES + 1);
-                if (s / BATCH_STAGES + 2 < nbatches) load(s / BATCH_STAGES + 2);
+            // Batch b goes where batch b - 2 was: one stage after its last stage was read, since the others pass the barrier in between
+            // with those reads on their way (its waits are for their loads) and have the bytes in registers at this one.
+            const int b = s / BATCH_STAGES + 1;
+            if (s == scale_batch_barrier(b, BATCH_STAGES) && b < nbatches) {
+                write(b);
+                if (b + 1 < nbatches) load(b + 1);
             }
         }
         return;

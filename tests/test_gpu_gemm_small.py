@@ -55,3 +55,21 @@ def test_two_products_in_a_launch(shapes):
     for ((a, sa), (b, sb)), out in zip(ops, outs):
         single = mx.mxfp4_gemm(a, sa, b, sb, out_dtype=mx.OUT_FP32 if out.dtype == torch.float32 else mx.OUT_BF16)
         assert torch.equal(out, single)
+
+
+@pytest.mark.parametrize("fmt", [mx.FMT_E2M1, mx.FMT_E4M3])
+@pytest.mark.parametrize("C", [4128, 8160, 14336])
+@pytest.mark.parametrize("rows", [100, 500])  # one workgroup per compute unit and eight stage buffers; two and four
+def test_more_batches_of_scale_bytes_than_buffers(rows, C, fmt):
+    # scale bytes over 2^50: one taken from another batch shows.  The same rows among more of them run on 64 x 64 tiles, bit for bit
+    rng = np.random.default_rng(C + rows + fmt)
+    def operand(R):
+        q = rng.integers(0, 256, (R, C // 2 if fmt == mx.FMT_E2M1 else C), dtype=np.uint8)
+        return gpu(q & 0xF7 if fmt == mx.FMT_E4M3 else q), gpu(rng.integers(100, 150, (R, C // 32), dtype=np.uint8))
+    (aq, as_), (bq, bs) = operand(1000), operand(1000)
+    kw = dict(a_format=fmt, b_format=fmt, out_dtype=mx.OUT_FP32)
+    assert mx.mxfp4_gemm_route(1000, 1000, C, fmt, fmt, ld_out=1001) == mx.ROUTE_EDGE_64
+    out = [torch.empty((R, 1001), device="cuda:0") for R in (rows, 1000)]
+    for o in out:
+        mx.mxfp4_gemm(aq[:len(o)], as_[:len(o)], bq, bs, out=o[:, :1000], **kw)
+    assert torch.equal(out[0][:, :1000], out[1][:rows, :1000])
