@@ -1049,19 +1049,24 @@ struct EdgeGemm {
               // 8 rows are whole 4 bytes (but not 16)
 };
 
-// The tile (tm x tn) of workgroup `bid`: each XCD (workgroup id mod 8) takes a contiguous run of the tile sequence, which walks the grid in
-// groups of GROUP_M tile rows (as the tiled kernel does).  False: no tile (the grid is padded to whole rows of 8).
-__device__ __forceinline__ bool edge_tile(const EdgeGemm &p, uint32_t bid, int tm, int tn, int64_t &m0, int64_t &n0)
+// Whether workgroup `bid` has a tile (the grid is padded to whole rows of 8) is asked apart from which one: as one function with both
+// answers the compiler loads the operands' pointers only behind the divisions, 0.2 us later (200 x 4096 x 4096 8.42 us, 8.24 like this).
+__device__ __forceinline__ bool edge_has_tile(const EdgeGemm &p, uint32_t bid)
+{
+    const int T = p.tiles_m * p.tiles_n;
+    return (int)(bid >> 3) < (T >> 3) + ((int)(bid & 7) < (T & 7) ? 1 : 0);
+}
+// The tile (tm x tn) of workgroup `bid`, which has one: each XCD (workgroup id mod 8) takes a contiguous run of the tile sequence, which walks the grid in
+// groups of GROUP_M tile rows (as the tiled kernel does).
+__device__ __forceinline__ void edge_tile(const EdgeGemm &p, uint32_t bid, int tm, int tn, int64_t &m0, int64_t &n0)
 {
     const int T = p.tiles_m * p.tiles_n, xcd = bid & 7, per = T >> 3, rem = T & 7;
-    if ((int)(bid >> 3) >= per + (xcd < rem ? 1 : 0)) return false;
     const int L = (xcd < rem ? xcd * (per + 1) : rem * (per + 1) + (xcd - rem) * per) + (int)(bid >> 3);
     const int span = GROUP_M * p.tiles_n, grp = L / span, first = grp * GROUP_M, in = L - grp * span;
     const int gm = p.tiles_m - first < GROUP_M ? p.tiles_m - first : GROUP_M;
     // (uniform, but the division ran in the vector unit: put them where the loads want their base)
     m0 = (int64_t)__builtin_amdgcn_readfirstlane(first + in % gm) * tm;
     n0 = (int64_t)__builtin_amdgcn_readfirstlane(in / gm) * tn;
-    return true;
 }
 
 // four consecutive outputs of one row from column col on, at once (whole: what they are added to is in v already) or as many of them as
@@ -1111,7 +1116,8 @@ __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm 
     const int wm = wave / NWN, wn = wave % NWN;
 
     int64_t m0, n0;
-    if (!edge_tile(p, bid, TM, TN, m0, n0)) return;
+    if (!edge_has_tile(p, bid)) return;
+    edge_tile(p, bid, TM, TN, m0, n0);
 
     const int64_t rowbytes = FMT ? p.C : (p.C >> 1);
     const int nkb = (int)(p.C >> 5);
@@ -1409,7 +1415,8 @@ __global__ __launch_bounds__(320) void gemm_small_kernel(const EdgeGemm p0, cons
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
     int64_t m0, n0;
-    if (!edge_tile(p, bid, T, T, m0, n0)) return;
+    if (!edge_has_tile(p, bid)) return;
+    edge_tile(p, bid, T, T, m0, n0);
     const int rowbytes = (int)(FMT ? p.C : (p.C >> 1)), nkb = (int)(p.C >> 5);
     const int nstages = (rowbytes + 127) >> 7;
 
@@ -1647,7 +1654,8 @@ __global__ __launch_bounds__(256) void gemm_short_kernel(const EdgeGemm p0, cons
     const int wm = wave >> 1, wn = wave & 1;
 
     int64_t m0, n0;
-    if (!edge_tile(p, bid, TM, TN, m0, n0)) return;
+    if (!edge_has_tile(p, bid)) return;
+    edge_tile(p, bid, TM, TN, m0, n0);
     const int rowbytes = (int)(FMT ? p.C : (p.C >> 1)), nkb = (int)(p.C >> 5);  // at most 128 S, 4 S (E4M3) or 8 S
     const int nstages = (rowbytes + 127) >> 7;
     const int last_a = (int)(p.Ra - m0 < TM ? p.Ra - m0 : TM) - 1, last_b = (int)(p.Rb - n0 < TN ? p.Rb - n0 : TN) - 1;
