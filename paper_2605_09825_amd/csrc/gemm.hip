@@ -1349,14 +1349,19 @@ __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm 
     const bool whole = (p.vec & 1) && left >= 4;
 #pragma unroll
     for (int i = 0; i < WM; ++i) {
-      // values added to: all at once, under the way through LDS; one by one in front of their stores 6656 x 11008 x 768 took 190 us, now 146,
-      // 13888 x 6912 x 576 250, now 194
-      v4f old[32 / RPI];
-      if (ACC && p.accumulate && whole) {
+      // Values added to: all at once, under the way through LDS (rows beyond the last are the last again, for nobody), and all added before
+      // the first store, since a wait for a load is one for the stores before it too.  us, one by one in front of their stores / loaded at once
+      // but added one by one / like this: 6656 x 11008 x 768 198 / 148 / 146, 768 x 800 x 256 4.4 / 4.6 / 4.0, 3520 x 2304 x 896 20.1 / 20.9 /
+      // 19.4; beside a product that is not added to: dY 256 x 2048 of a layer 1536 wide 8.7 / 9.8 / 8.9, 1888 x 256 of 7424 19.5 / 23.2 / 18.4.
+      constexpr int NU = 32 / RPI;
+      const int64_t row0 = m0 + wm * 32 * WM + 32 * i + rl;
+      const bool add = ACC && p.accumulate && whole;
+      v4f v[NU], old[NU];
+      if (add) {
 #pragma unroll
-        for (int u = 0; u < 32 / RPI; ++u) {
-            const int64_t row = m0 + wm * 32 * WM + 32 * i + u * RPI + rl;
-            if (row < p.Ra) old[u] = *reinterpret_cast<const v4f *>(reinterpret_cast<const float *>(p.out) + row * p.ld + col);
+        for (int u = 0; u < NU; ++u) {
+            const int64_t row = row0 + u * RPI < p.Ra ? row0 + u * RPI : p.Ra - 1;
+            old[u] = *reinterpret_cast<const v4f *>(reinterpret_cast<const float *>(p.out) + row * p.ld + col);
         }
       }
 #pragma unroll
@@ -1367,14 +1372,22 @@ __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm 
             *reinterpret_cast<v4f *>(epi + fr * PITCH + ((c ^ (fr & (CHUNKS - 1))) << 4)) =
                 (v4f){acc[i][j][4 * qd + 0], acc[i][j][4 * qd + 1], acc[i][j][4 * qd + 2], acc[i][j][4 * qd + 3]};
         }
-#pragma unroll
-      for (int u = 0; u < 32 / RPI; ++u) {
+      auto read = [&](int u) {
         const int r = u * RPI + rl;
-        const int64_t row = m0 + wm * 32 * WM + 32 * i + r;
-        v4f v = *reinterpret_cast<const v4f *>(epi + r * PITCH + ((ch ^ (r & (CHUNKS - 1))) << 4));
-        if (row >= p.Ra) continue;
-        if (ACC && p.accumulate && whole) v += old[u];
-        store4<ACC>(p, row, col, left, whole, v);
+        return *reinterpret_cast<const v4f *>(epi + r * PITCH + ((ch ^ (r & (CHUNKS - 1))) << 4));
+      };
+      if constexpr (ACC) {
+#pragma unroll
+        for (int u = 0; u < NU; ++u) v[u] = read(u);
+        if (add) {
+#pragma unroll
+          for (int u = 0; u < NU; ++u) v[u] += old[u];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        if constexpr (!ACC) v[u] = read(u);
+        if (row0 + u * RPI < p.Ra) store4<ACC>(p, row0 + u * RPI, col, left, whole, v[u]);
       }
     }
 }
@@ -1818,21 +1831,24 @@ __global__ __launch_bounds__(256) void gemm_short_kernel(const EdgeGemm p0, cons
         auto tile_row = [&](int r) { return (r >> 5) * 64 + i * 32 + (r & 31); };
         if (p.vec & 1) {
             const int c = lane & 15;
-            v4f v[4], old[4];  // (what they are added to: all loads before the first store)
+            const bool whole = c * 4 + 4 <= cols, add = p.accumulate && whole;
+            v4f v[4], old[4];  // (what they are added to: all loads and sums before the first store)
 #pragma unroll
             for (int it = 0; it < 4; ++it) {
                 const int r = wave * 16 + it * 4 + (lane >> 4), row = tile_row(r);
                 v[it] = *reinterpret_cast<const v4f *>(smem + r * 256 + ((c ^ (r & 15)) << 4));
-                old[it] = (v4f){0.f, 0.f, 0.f, 0.f};
-                if (p.accumulate && row <= last_a && c * 4 + 4 <= cols) old[it] = *reinterpret_cast<const v4f *>(out + row * p.ld + c * 4);
+                if (add) old[it] = *reinterpret_cast<const v4f *>(out + (row < last_a ? row : last_a) * p.ld + c * 4);
+            }
+            if (add) {
+#pragma unroll
+                for (int it = 0; it < 4; ++it) v[it] += old[it];
             }
 #pragma unroll
             for (int it = 0; it < 4; ++it) {
                 const int r = wave * 16 + it * 4 + (lane >> 4), row = tile_row(r);
                 if (row > last_a) continue;
                 float *o = out + row * p.ld + c * 4;
-                if (c * 4 + 4 <= cols) {
-                    if (p.accumulate) v[it] += old[it];
+                if (whole) {
                     if (lines) __builtin_nontemporal_store(v[it], reinterpret_cast<v4f *>(o));
                     else *reinterpret_cast<v4f *>(o) = v[it];
                 } else {
