@@ -16,6 +16,7 @@
 // then owns 4 consecutive output columns of one output row.
 #include <type_traits>
 
+#include "edge_rules.h"
 #include "mxfp4_internal.h"
 #include "scale_batches.h"
 
@@ -1402,7 +1403,7 @@ __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm 
 //     counts stay constants; the ragged last stage is moved back to end with the row;
 //   * a fifth wave brings the scale bytes (8-byte loads at any alignment, 64 bytes per row in a batch, written to LDS a batch ahead):
 //     its waits hold up nobody's direct-to-LDS loads.
-// NBUF stage buffers: 4 (40 KiB, four workgroups per compute unit) or 8 (72 KiB).
+// NBUF stage buffers: 4 (40 KiB, four workgroups per compute unit) or 8 (72 KiB).  Rows are of at least 128 bytes of codes (small_gains), or empty.
 // Measured back to back in a graph, bf16 output, 64 x 64 tiles / this: MXFP4 24 x 6144 x 4096 8.0 / 5.6 us, 256 x 512 x 512
 // 4.1 / 3.6, 100 x 1000 x 14336 20.6 / 12.1, 500 x 1000 x 1440 6.3 / 5.5; MXFP8 24 x 6144 x 4096 11.1 / 7.2.  What is left at 24 x 6144
 // x 4096: 1.7 us of launch, 1.4 us until the first stage and its scale bytes are there, 0.12 us per stage.
@@ -1486,8 +1487,8 @@ __global__ __launch_bounds__(320) void gemm_small_kernel(const EdgeGemm p0, cons
         auto write = [&](int b) {
             if (b == nbatches - 1 && valid < SB) {
                 // the last stage's codes are moved back to end with the row: so are its scale bytes, zeros in front of them for the
-                // blocks that the stage before has had (products below 2^-254 * 2^24); a row of less than a stage has them behind
-                auto fix = [&](uint64_t v) { return nkb < SB ? v & ((uint64_t(1) << (8 * valid)) - 1) : v << (8 * (SB - valid)); };
+                // blocks that the stage before has had (products below 2^-254 * 2^24)
+                auto fix = [&](uint64_t v) { return v << (8 * (SB - valid)); };
 #pragma unroll
                 for (int j = 0; j < NP; ++j) {
                     const int s = b * BATCH_STAGES + (lane & 7) * (FMT ? 2 : 1);
@@ -1540,10 +1541,10 @@ __global__ __launch_bounds__(320) void gemm_small_kernel(const EdgeGemm p0, cons
 #pragma unroll
     for (int n = 0; n < 2; ++n) {
         const int want = (wave & 1) * 16 + n * 8 + (lane >> 3), chunk = ((lane & 7) ^ (lane >> 3) ^ n * 5) << 4;
-        voff[n] = (uint32_t)((want < lastrow ? want : lastrow) * rowbytes + (chunk < rowbytes ? chunk : rowbytes - 16) + BIAS - n * 1024);
+        voff[n] = (uint32_t)((want < lastrow ? want : lastrow) * rowbytes + chunk + BIAS - n * 1024);
     }
     const uint32_t lds_dst = lds0 + (uint32_t)wave * 2048u;
-    const int koff_last = rowbytes > 128 ? rowbytes - 128 : 0;
+    const int koff_last = rowbytes - 128;
     auto issue = [&](int s, uint32_t to) {  // stage s into buffer `to`
         const uint8_t *at = src + (s * 128 < koff_last ? s * 128 : koff_last);
         const int on = __builtin_amdgcn_readfirstlane(s < nstages ? -1 : 0);
@@ -1980,30 +1981,19 @@ static bool edge_eligible(const GemmArgs &g)
     return g.a_fmt == g.b_fmt && g.C < (int64_t(1) << 24) && g.Ra < (int64_t(1) << 31);
 }
 
-// stages (128 bytes of codes per row) of the longer of one or two products
-static int64_t edge_stages(const GemmArgs &g0, const GemmArgs *g1)
+static EdgeProduct edge_product(const GemmArgs &g)
 {
-    auto stages = [](const GemmArgs &g) { return ((g.a_fmt ? g.C : g.C / 2) + 127) / 128; };
-    const int64_t s0 = stages(g0), s1 = g1 ? stages(*g1) : 0;
-    return s0 > s1 ? s0 : s1;
+    return EdgeProduct{g.Ra, g.Rb, g.a_fmt ? g.C : g.C / 2, g.ld * (g.out_fp32 ? 4 : 2), g.a_fmt != 0, g.out_fp32 != 0, g.accumulate != 0};
+}
+static bool runs_short(const GemmArgs &g0, const GemmArgs *g1)
+{
+    const EdgeProduct p0 = edge_product(g0), p1 = g1 ? edge_product(*g1) : p0;
+    return runs_short(p0, g1 ? &p1 : nullptr);
 }
 
 // The tile shape with the lowest estimate for one product, or two of one format side by side, among those whose tiles, a
 // workgroup each, make a grid that can be launched (us = NO_ROUTE: none does).
 constexpr double NO_ROUTE = 1e30;
-
-// Whether 128 x 64 tiles run as gemm_short_kernel: at most two stages, and output rows that are not whole cache lines apart, or more
-// than 4096 tiles.  Such rows it stores in longer pieces: 2048 x 3000 x 288 bf16 10.2 us on 128 x 256 tiles, 7.5 on this, added to in
-// fp32 16.5, 11.4; 512 x 10000 x 512 9.1, 7.1.  Where each row starts a line the other kernels' stores are as good, and few tiles are
-// done sooner there: 2048 x 4096 x 512 8.2, 9.6 (1024 tiles), 4096 x 4096 x 512
-// 14.1, 14.9 (2048 tiles), 512 x 7040 x 512 fp32 6.6, 8.0; many overlap here: 8192 x 8192 x 512 fp32 69.9, 62.6, 12526 x 9728 x 256 80, 55.
-static bool runs_short(const GemmArgs &g0, const GemmArgs *g1)
-{
-    auto fits = [](const GemmArgs &g) {
-        return g.ld * (g.out_fp32 ? 4 : 2) % 128 != 0 || (g.Ra + 127) / 128 * ((g.Rb + 63) / 64) > 4096;
-    };
-    return edge_stages(g0, g1) <= 2 && fits(g0) && (!g1 || fits(*g1));
-}
 
 struct EdgeChoice {
     int tile;  // 0: 64 x 64, 1: 128 x 64, 2: 128 x 256
@@ -2070,28 +2060,16 @@ static hipError_t launch_short_f(const GemmArgs &g0, const GemmArgs *g1, hipStre
     return hipGetLastError();
 }
 
-// Of the products (or pairs) on 64 x 64 tiles, those on 32 x 32 ones: the number of these, else 0.  They are faster up to two workgroups per
-// compute unit: time on 64 x 64 tiles over time on 32 x 32 ones, MXFP4 (MXFP8), at 1, 2, 4, 8, 16, 56 stages: up to 256 tiles 1.1 1.15
-// 1.15 1.3 1.45 1.8 (1.05 1.15 1.2 1.23 1.37 1.6), 320 to 512 tiles 0.98 1.04 1.02 1.14 1.2 1.25 (0.95 1.03 1.07 1.06 1.16 1.15), 560 and 640
-// tiles 0.9 0.95 0.94 1.01 1.04 1.1 (0.9 0.95 0.97 0.94 0.99 0.99), 1024 tiles 0.6 to 0.8.
-static int small_tiles(const GemmArgs &g0, const GemmArgs *g1)
-{
-    auto tiles = [](const GemmArgs &g) { return ((g.Ra + SMALL - 1) / SMALL) * ((g.Rb + SMALL - 1) / SMALL); };
-    auto one_stage = [](const GemmArgs &g) { return (g.a_fmt ? g.C : g.C / 2) <= 128; };
-    const int64_t t = tiles(g0) + (g1 ? tiles(*g1) : 0);
-    return t <= NUM_CUS || (t <= 2 * NUM_CUS && !one_stage(g0) && !(g1 && one_stage(*g1))) ? (int)t : 0;
-}
-
 static hipError_t launch_edge(const GemmArgs &g0, const GemmArgs *g1, int tile, hipStream_t st)
 {
     if (tile == 2) return g0.a_fmt ? launch_edge_f<1, 2, 2, 4, 3>(g0, g1, st) : launch_edge_f<0, 2, 2, 4, 3>(g0, g1, st);
+    const EdgeProduct p0 = edge_product(g0), p1 = g1 ? edge_product(*g1) : p0;
     if (tile == 1 && runs_short(g0, g1)) {
-        const int64_t stages = edge_stages(g0, g1);
-        if (stages <= 1) return g0.a_fmt ? launch_short_f<1, 1>(g0, g1, st) : launch_short_f<0, 1>(g0, g1, st);
-        if (stages == 2) return g0.a_fmt ? launch_short_f<1, 2>(g0, g1, st) : launch_short_f<0, 2>(g0, g1, st);
+        if (edge_stages(p0) <= 1 && edge_stages(p1) <= 1) return g0.a_fmt ? launch_short_f<1, 1>(g0, g1, st) : launch_short_f<0, 1>(g0, g1, st);
+        return g0.a_fmt ? launch_short_f<1, 2>(g0, g1, st) : launch_short_f<0, 2>(g0, g1, st);
     }
     if (tile == 1) return g0.a_fmt ? launch_edge_f<1, 2, 1, 2, 3>(g0, g1, st) : launch_edge_f<0, 2, 1, 2, 3>(g0, g1, st);
-    if (const int small = small_tiles(g0, g1)) {
+    if (const int small = small_tiles(p0, g1 ? &p1 : nullptr)) {
         // (eight stage buffers with a workgroup per compute unit at most: 1.2 times as fast from 32 stages of operands that come
         // from memory on, the same or 0.97 times up to 16)
         const GemmArgs &longer = g1 && g1->C > g0.C ? *g1 : g0;

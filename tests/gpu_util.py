@@ -1,5 +1,11 @@
 """Helpers shared by the GPU parity tests: move seeded host tensors to the device, call the
 library through its Python binding (= the C ABI), bring results back as numpy."""
+import ctypes
+import functools
+import os
+import subprocess
+import tempfile
+
 import numpy as np
 import torch
 
@@ -51,3 +57,44 @@ def assert_runs_on(kernel, Ra, Rb, C, fmt=0, **kw):
     if kernel in kinds:
         plan = mx.mxfp4_gemm_plan(Ra, Rb, C, fmt, fmt)
         assert len(plan) == 1 and plan[0][0] == kinds[kernel], (kernel, plan)
+
+
+@functools.lru_cache(maxsize=None)
+def _edge_rules():
+    """csrc/edge_rules.h, which the launches ask too, as a host library."""
+    csrc = os.path.join(os.path.dirname(mx.__file__), "csrc")
+    src = '''#include "edge_rules.h"
+    extern "C" int kernel(int tile, int n, const int64_t *v)
+    {
+        const mxfp4::EdgeProduct p0{v[0], v[1], v[2], v[3], v[4] != 0, v[5] != 0, v[6] != 0};
+        const mxfp4::EdgeProduct p1{v[7], v[8], v[9], v[10], v[11] != 0, v[12] != 0, v[13] != 0};
+        if (tile == 0) return mxfp4::small_tiles(p0, n > 1 ? &p1 : nullptr) ? 1 : 0;
+        return tile == 1 && mxfp4::runs_short(p0, n > 1 ? &p1 : nullptr) ? 2 : 0;
+    }'''
+    with tempfile.TemporaryDirectory() as tmp:
+        so = os.path.join(tmp, "edge_rules.so")
+        subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", csrc, "-x", "c++", "-", "-o", so], input=src, text=True, check=True)
+        return ctypes.CDLL(so)
+
+
+def edge_kernel(*products):
+    """The kernel of the ragged-shape family that one product, or a pair of them, runs on: "32x32", "short", "64x64", "128x64" or "128x256" (None:
+    a kernel of another kind).  A product: dict(shape=(Ra, Rb, C), fmt=, out_dtype=, accumulate=, ld=), all but the shape optional."""
+    full, flat = [], []
+    for p in products:
+        Ra, Rb, C = p["shape"]
+        p = dict(dict(fmt=mx.FMT_E2M1, out_dtype=mx.OUT_BF16, accumulate=False, ld=Rb), **p)
+        full.append(p)
+        flat += [Ra, Rb, C if p["fmt"] == mx.FMT_E4M3 else C // 2, p["ld"] * (4 if p["out_dtype"] == mx.OUT_FP32 else 2),
+                 p["fmt"] == mx.FMT_E4M3, p["out_dtype"] == mx.OUT_FP32, p["accumulate"]]
+    if len(products) == 1:
+        tile = mx.mxfp4_gemm_route(*p["shape"], p["fmt"], p["fmt"], ld_out=p["ld"], out_dtype=p["out_dtype"],
+                                   accumulate=p["accumulate"]) - mx.ROUTE_EDGE_64
+    else:
+        a, b = full
+        kind, _, tile, _ = mx.mxfp4_gemm_pair_route(a["shape"], b["shape"], (a["fmt"], b["fmt"]), (a["out_dtype"], b["out_dtype"]), b["accumulate"])
+        tile = tile if kind == mx.PAIR_EDGE else -1
+    if not 0 <= tile <= 2:
+        return None
+    which = _edge_rules().kernel(tile, len(products), (ctypes.c_int64 * 14)(*(flat + flat)[:14]))
+    return ("64x64", "128x64", "128x256")[tile] if which == 0 else ("32x32", "short")[which - 1]

@@ -1,11 +1,15 @@
 """GPU tests: the ragged-shape kernel's 32 x 32 tiles (outputs of up to 512 of them): edges of tiles, rows of the scale arrays at every
-alignment, last stages of one block up to whole, rows of less than a stage, arrays of less than 8 scale bytes, both numbers of stage buffers, two products in a launch."""
+alignment, last stages of one block up to whole, arrays of less than 8 scale bytes, both numbers of stage buffers, two products in a launch; with
+them sizes that are faster on 64 x 64 tiles (rows of less than a stage)."""
 import numpy as np
 import pytest
 import torch
 
 import oracle
 import paper_2605_09825_amd as mx
+import test_gpu_linear_launches as launches
+from gpu_util import edge_kernel
+from test_gpu_fp8 import rand_fp4, rand_fp8
 from test_gpu_gemm import gpu
 
 pytestmark = pytest.mark.gpu
@@ -73,3 +77,48 @@ def test_more_batches_of_scale_bytes_than_buffers(rows, C, fmt):
     for o in out:
         mx.mxfp4_gemm(aq[:len(o)], as_[:len(o)], bq, bs, out=o[:, :1000], **kw)
     assert torch.equal(out[0][:, :1000], out[1][:rows, :1000])
+
+
+# the fewest stages that run on these tiles: whole, and with a ragged last one, up to 256 tiles and beyond; arrays of less than 8 scale bytes
+@pytest.mark.parametrize("shape,fmt", [((64, 33, 256), mx.FMT_E2M1), ((33, 36, 288), mx.FMT_E2M1), ((500, 512, 480), mx.FMT_E2M1),
+                                       ((511, 1000, 512), mx.FMT_E2M1), ((511, 1000, 1056), mx.FMT_E2M1), ((33, 64, 128), mx.FMT_E4M3),
+                                       ((33, 36, 288), mx.FMT_E4M3), ((500, 510, 352), mx.FMT_E4M3), ((511, 1000, 256), mx.FMT_E4M3),
+                                       ((511, 1000, 928), mx.FMT_E4M3), ((1, 100, 128), mx.FMT_E4M3)])
+def test_fewest_stages(shape, fmt):
+    Ra, Rb, _ = shape
+    call = dict(shape=shape, fmt=fmt, out_dtype=mx.OUT_FP32)
+    assert "32x32" in (edge_kernel(call), edge_kernel(dict(call, ld=Rb + 1 + Ra % 4, accumulate=True)))
+    test_against_the_oracle(shape, fmt)
+
+
+# Each product alone runs on 32 x 32 tiles, the pair, of more than 512 of them, on 64 x 64 ones: another matrix instruction, the same bits
+@pytest.mark.parametrize("shapes", [((640, 640, 1024), (640, 640, 2048)), ((608, 608, 1440), (608, 608, 1440)), ((512, 1000, 4128), (1000, 300, 512))])
+def test_pairs_beside_single_products(shapes):
+    products = [dict(shape=s, out_dtype=d) for s, d in zip(shapes, (mx.OUT_BF16, mx.OUT_FP32))]
+    assert [edge_kernel(p) for p in products] == ["32x32", "32x32"] and edge_kernel(*products) == "64x64"
+    rng = np.random.default_rng(sum(shapes[0]))
+    ops = [[tuple(map(gpu, rand_fp4(rng, R, C))) for R in (Ra, Rb)] for Ra, Rb, C in shapes]
+    outs = [torch.empty(s[:2], device="cuda:0", dtype=t) for s, t in zip(shapes, (torch.bfloat16, torch.float32))]
+    mx.mxfp4_gemm_pair(*ops[0], outs[0], *ops[1], outs[1])
+    for ((a, sa), (b, sb)), out, p in zip(ops, outs, products):
+        assert torch.equal(out, mx.mxfp4_gemm(a, sa, b, sb, out_dtype=p["out_dtype"]))
+
+
+def test_backward_pairs_beside_single_products():
+    M = N = K = 640
+    product = dict(shape=(M, N, K), fmt=mx.FMT_E4M3)
+    assert edge_kernel(product) == "32x32" and edge_kernel(product, dict(product, out_dtype=mx.OUT_FP32)) == "64x64"
+    launches.test_backward_products_equal_the_single_gemm_calls((M, N, K), mx.FMT_E4M3, mx.OUT_BF16, False)
+
+
+@pytest.mark.parametrize("C", [512, 1440, 4096])
+@pytest.mark.parametrize("fmt", [mx.FMT_E2M1, mx.FMT_E4M3])
+def test_any_codes_as_on_larger_tiles(C, fmt):
+    rng = np.random.default_rng(C + fmt)
+    (aq, sa), (bq, sb) = [tuple(map(gpu, (rand_fp8 if fmt else rand_fp4)(rng, R, C))) for R in (1500, 640)]
+    kw = dict(a_format=fmt, b_format=fmt, out_dtype=mx.OUT_FP32)
+    assert [edge_kernel(dict(shape=(R, 640, C), fmt=fmt, out_dtype=mx.OUT_FP32, ld=641)) for R in (640, 1500)] == ["32x32", "64x64"]
+    out = [torch.empty((R, 641), device="cuda:0") for R in (640, 1500)]
+    for o in out:
+        mx.mxfp4_gemm(aq[:len(o)], sa[:len(o)], bq, sb, out=o[:, :640], **kw)
+    assert torch.equal(out[0][:, :640], out[1][:640, :640])
