@@ -41,10 +41,20 @@ constexpr int small_tiles(const EdgeProduct &p0, const EdgeProduct *p1)
 // fp32 16.5, 11.4; 512 x 10000 x 512 9.1, 7.1.  Where each row starts a line the other kernels' stores are as good, and few tiles are
 // done sooner there: 2048 x 4096 x 512 8.2, 9.6 (1024 tiles), 4096 x 4096 x 512
 // 14.1, 14.9 (2048 tiles), 512 x 7040 x 512 fp32 6.6, 8.0; many overlap here: 8192 x 8192 x 512 fp32 69.9, 62.6, 12526 x 9728 x 256 80, 55.
+// An fp32 product alone stays on the other kernels' tiles, too,
+//   * with two stages and 769 to 1024 tiles, of which 768 run at once (the last round nearly empty costs more than its rows gain): 608 x 10368 x 512
+//     10.2 us, on this 11.6, MXFP8 1152 x 5960 x 192 10.7, 11.7; rows in no whole 16 bytes only if it is added to (1280 x 5764 x 480 1.1
+//     times as long);
+//   * added to with at most 512 tiles, which the others hold at once: 1920 x 1360 x 64 6.9, 8.0, 5369 x 656 x 32 7.3, 8.4, 1280 x 2536 x 480 1.07
+//     times as long.
 constexpr bool runs_short(const EdgeProduct &p0, const EdgeProduct *p1)
 {
     auto fits = [](const EdgeProduct &p) { return edge_stages(p) <= 2 && (p.pitch % 128 != 0 || edge_tiles(p, 128, 64) > 4096); };
-    return fits(p0) && (!p1 || fits(*p1));
+    if (!fits(p0) || (p1 && !fits(*p1))) return false;
+    if (p1 || !p0.fp32) return true;
+    const int64_t tiles = edge_tiles(p0, 128, 64);
+    if (edge_stages(p0) == 2 && tiles > 768 && tiles <= 1024 && (p0.accumulate || p0.pitch % 16 == 0)) return false;
+    return !p0.accumulate || tiles > 512;
 }
 
 }  // namespace mxfp4

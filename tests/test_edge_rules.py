@@ -41,6 +41,11 @@ def holds(condition):
     # short rows: up to two stages, rows of the output in no whole cache lines or more than 4096 tiles
     "shrt(shorts(600, 256, 120)) && !shrt(shorts(600, 272, 120)) && !shrt(shorts(4096, 256, 128)) && shrt(shorts(4097, 256, 128))",
     "shrt(shorts(600, 16, 120), shorts(1, 256, 120)) && !shrt(shorts(600, 16, 120), shorts(1, 256, 128)) && !shrt(shorts(600, 16, 120), shorts(1, 272, 120))",
+    # ... of fp32 products alone not those with two stages and a last round that is nearly empty, nor few tiles that are added to
+    "shrt(shorts(768, 256, 144, true)) && !shrt(shorts(769, 256, 144, true)) && !shrt(shorts(1024, 144, 144, true)) && shrt(shorts(1025, 256, 144, true))",
+    "shrt(shorts(800, 128, 144, true)) && shrt(shorts(800, 256, 120, true)) && !shrt(shorts(800, 256, 120, true, true)) && shrt(shorts(800, 256, 144))",
+    "!shrt(shorts(512, 128, 144, true, true)) && shrt(shorts(513, 128, 144, true, true)) && shrt(shorts(300, 128, 144, true))",
+    "shrt(shorts(800, 256, 144), shorts(10, 256, 144, true, true))",
 ])
 def test_rule(condition):
     assert holds(condition) and not holds("!(%s)" % condition)
