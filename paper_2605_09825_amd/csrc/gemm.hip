@@ -2273,6 +2273,11 @@ static RagPairChoice choose_rag_pair(const GemmArgs &g0, const GemmArgs &g1, int
     if (cus != NUM_CUS || g0.a_fmt || g1.a_fmt || !g1.out_fp32 || !rag_eligible(g0) || !rag_eligible(g1)) return best;
     if (tile_eligible(g0, TILE / 2) && tile_eligible(g1, TILE / 2)) return best;  // (whole tiles: the launches for these)
     auto tiles = [](const GemmArgs &g) { return ((g.Ra + TILE - 1) / TILE) * ((g.Rb + TILE - 1) / TILE); };
+    // Tiles of 1.4 times the outputs' area, narrow outputs for the most part: what is done twice takes what sharing the launch gives.  15 such
+    // layers of M x N x K took the same as on gemm_edge_kernel on average (2496 x 8704 x 544 39.5 / 30.2 us, 4032 x 10400 x 544 63 / 58, 8416 x 14080
+    // x 288 73 / 86), the others 0.85 times.
+    auto area = [&](const GemmArgs &g) { return (double)tiles(g) * TILE * TILE / ((double)g.Ra * (double)g.Rb); };
+    if (area(g0) + area(g1) >= 2 * 1.4) return best;
     for (int n0 = 1; n0 < 32; ++n0)
         for (int shapes = 0; shapes < 4; ++shapes) {
             const int narrow0 = shapes & 1, narrow1 = shapes >> 1;
@@ -2424,8 +2429,9 @@ GemmPairRoute route_gemm_pair(const GemmArgs &g0, const GemmArgs &g1, int cus)
         const MixChoice mix = mix1.us <= mix0.us ? mix1 : mix0;
         const double apart = route_gemm(g0, cus).us + route_gemm(g1, cus).us + 4.0;
         const RagPairChoice rag = choose_rag_pair(g0, g1, cus);
-        // (0.95: of long products the split's estimate is worth less than that, 8672 x 7328 x 10016 took 859 us in one launch, 794 apart)
-        if (rag.us < 0.95 * apart && rag.us < both.us && rag.us < mix.us)
+        // (0.95: of long products the split's estimate is worth less than that, 8672 x 7328 x 10016 took 859 us in one launch, 794 apart; 0.98: of
+        // 35 layers nearer to the ragged-shape kernel's estimate 8 were slower, 8448 x 15744 x 320 113 us, 92 on that)
+        if (rag.us < 0.95 * apart && rag.us < 0.98 * both.us && rag.us < mix.us)
             r = GemmPairRoute{PAIR_EDGE, 0, EDGE_MOVED_BACK, rag.n0 + 32 * rag.narrow0 + 64 * rag.narrow1};
         else if (mix.us < apart && mix.us < both.us)
             r = GemmPairRoute{PAIR_NARROW_BESIDE_WIDE, mix1.us <= mix0.us ? 1 : 0, mix.n1, mix.cut};

@@ -89,6 +89,14 @@ def test_pairs():
     assert pair(*dgrad_wgrad(8192, 6144, 4096), compute_units=128)[0] in (mx.PAIR_APART, mx.PAIR_EDGE)
 
 
+def test_moved_back_pairs_but_for_narrow_outputs():
+    MOVED_BACK = 3
+    for layer in ((2080, 4320, 1440), (4128, 4320, 4064), (2592, 5344, 1280), (4960, 1120, 4960)):
+        assert pair(*dgrad_wgrad(*layer))[::2] == (mx.PAIR_EDGE, MOVED_BACK)
+    for layer in ((2496, 8704, 544), (8448, 15744, 320), (8096, 7232, 288)):  # 288 to 544 columns: up to 1.78 times the outputs in tiles
+        assert pair(*dgrad_wgrad(*layer))[2] < MOVED_BACK
+
+
 def test_more_tiles_than_a_grid_can_hold():
     # A launch holds fewer than 2^32 threads along a dimension: 2^24 workgroups on 64 x 64 or 128 x 64 tiles, 2^23 on
     # 128 x 256 ones.  Beyond that the next larger tile, then the any-shape kernel, whose grid has two dimensions.
