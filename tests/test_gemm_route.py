@@ -91,6 +91,7 @@ def test_pairs():
 
 def test_moved_back_pairs_but_for_narrow_outputs():
     MOVED_BACK = 3
+    dgrad_wgrad = lambda M, N, K: ((M, K, N), (N, K, M))
     for layer in ((2080, 4320, 1440), (4128, 4320, 4064), (2592, 5344, 1280), (4960, 1120, 4960)):
         assert pair(*dgrad_wgrad(*layer))[::2] == (mx.PAIR_EDGE, MOVED_BACK)
     for layer in ((2496, 8704, 544), (8448, 15744, 320), (8096, 7232, 288)):  # 288 to 544 columns: up to 1.78 times the outputs in tiles
