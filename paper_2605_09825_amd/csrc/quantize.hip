@@ -382,18 +382,11 @@ TileJob make_job(const QuantArgs &a, int rb)
     return j;
 }
 
-// Waves, and so blocks of 32 rows, per workgroup of the column-wise kernels.  Four where the vector instructions or the chain through one
-// workgroup are what bounds (stochastic rounding, both axes, few tiles): the halves of a tile of eight then run on compute units of their own,
-// and wait for each other less.  Eight, whose output rows get whole 128-byte lines, where memory does: the column-wise kernel alone from
-// 512 tiles of eight on, everything beyond the last-level cache.  Eight / four waves, us, rounding to nearest: both axes 2080 x 1440 7.7 / 6.7,
-// 8192 x 4096 24.3 / 23.8, 16384 x 4096 42.4 / 39.6, 16384 x 14336 154 / 173; column-wise 2080 x 1440 5.2 / 4.6, 8192 x 4096 15.2 / 15.5, 8192 x
-// 14336 47.0 / 51.4; stochastic both axes 2080 x 1440 18.5 / 11.7, 16384 x 4096 118 / 117, column-wise 16384 x 14336 192 / 182.
 int cols_waves(const QuantArgs &a, const QuantArgs *b, int mode)
 {
-    if (a.rounding != RND_RNE) return 4;
-    if (beyond_llc(a.rows, a.cols) && (!b || beyond_llc(b->rows, b->cols))) return 8;
-    const int64_t groups = cols_groups(a.rows, a.cols) + (b ? cols_groups(b->rows, b->cols) : 0);
-    return mode != MODE_COLS || groups < 512 ? 4 : 8;
+    const bool beyond_a = beyond_llc(a.rows, a.cols), beyond_b = b ? beyond_llc(b->rows, b->cols) : beyond_a;
+    return cols_waves(ColsLaunch{a.rounding != RND_RNE, a.hadamard != HAD_NONE, mode == MODE_2D, a.q_row || (b && b->q_row),
+                                 cols_groups(a.rows, a.cols) + (b ? cols_groups(b->rows, b->cols) : 0), beyond_a || beyond_b, beyond_a && beyond_b});
 }
 
 // b == nullptr: one tensor.  Otherwise both tensors in one launch (same rotation, rounding and base seed).
@@ -415,7 +408,8 @@ hipError_t launch_cols_h(const QuantArgs &a, const QuantArgs *b, hipStream_t st)
     } else if (streaming) {
         MXFP4_LAUNCH_COLS(RND_RNE, 1, 8);
     } else {
-        if (rb == 4) MXFP4_LAUNCH_COLS(RND_RNE, 0, 4); else if constexpr (MODE == MODE_COLS) MXFP4_LAUNCH_COLS(RND_RNE, 0, 8);
+        if (rb == 4) MXFP4_LAUNCH_COLS(RND_RNE, 0, 4);
+        else if constexpr (MODE != MODE_2D || HAD == HAD_NONE) MXFP4_LAUNCH_COLS(RND_RNE, 0, 8);
     }
 #undef MXFP4_LAUNCH_COLS
     return hipGetLastError();

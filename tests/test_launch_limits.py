@@ -30,6 +30,16 @@ def holds(condition):
     "!wgrad_operands_share_launch(ONE << 31, 8, 8) && !wgrad_operands_share_launch(32, ONE << 40, 8)",
     # ... and while both are stored alike: one of them beyond the last-level cache
     "!wgrad_operands_share_launch(4096, 64, 32896) && wgrad_operands_share_launch(4096, 32776, 32896)",
+    # waves of the column-wise workgroups (stochastic, rotated, regions, both axes, tiles, some beyond the last-level cache, all): stochastic four;
+    # one axis eight from 512 tiles on; both axes eight from 1536 on, unless rotated; beyond the cache eight, rotated regions only if all are
+    "cols_waves({true, false, false, true, 9999, true, true}) == 4 && cols_waves({false, true, true, true, 9999, true, true}) == 8",
+    "cols_waves({false, true, false, false, 511, false, false}) == 4 && cols_waves({false, true, false, false, 512, false, false}) == 8",
+    "cols_waves({false, false, true, false, 511, false, false}) == 4 && cols_waves({false, false, true, false, 512, false, false}) == 8",
+    "cols_waves({false, false, false, true, 1535, false, false}) == 4 && cols_waves({false, false, false, true, 1536, false, false}) == 8",
+    "cols_waves({false, false, true, true, 1535, false, false}) == 4 && cols_waves({false, false, true, true, 1536, false, false}) == 8",
+    "cols_waves({false, true, false, true, 4096, false, false}) == 4 && cols_waves({false, true, true, true, 4096, false, false}) == 4",
+    "cols_waves({false, true, false, true, 4096, true, false}) == 8 && cols_waves({false, true, true, true, 4096, true, false}) == 4",
+    "cols_waves({false, false, true, true, 300, true, false}) == 8 && cols_waves({false, true, true, false, 4096, true, false}) == 4",
 ])
 def test_rule(condition):
     assert holds(condition) and not holds("!(%s)" % condition)
