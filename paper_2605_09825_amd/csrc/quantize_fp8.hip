@@ -73,8 +73,7 @@ __global__ __launch_bounds__(256) void quantize_rows_fp8_kernel(const uint16_t *
 // do.  Both axes, eight / four waves, us: 2080 x 1440 7.0 / 6.0, 8192 x 4096 26.8 / 25.0, 8192 x 6144 37.3 / 35.2, 8192 x 14336 119 / 123.
 bool eight_waves(const QuantArgs &a) { return a.rows * a.cols > (int64_t(1) << 26); }
 
-// column-wise: the tile and lane assignment of quantize_cols_kernel; an output row receives 4 x 32 = 128
-// contiguous bytes per tile (RB = 4)
+// column-wise: the tile and lane assignment of quantize_cols_kernel; an output row receives RB x 32 contiguous bytes per tile
 template <int HAD, int RB>
 __global__ __launch_bounds__(64 * RB) void quantize_cols_fp8_kernel(const uint16_t *__restrict__ x, int64_t rows,
                                                                 int64_t cols, int64_t ld, uint32_t sign_mask,
@@ -110,7 +109,7 @@ __global__ __launch_bounds__(64 * RB) void quantize_cols_fp8_kernel(const uint16
         lds_s[2 * lane + j][w] = (uint8_t)sb;
     }
     __syncthreads();
-    // 8 consecutive threads write the 128 bytes one output row receives from this tile
+    // 2 RB consecutive threads write the 32 RB bytes one output row receives from this tile
 #pragma unroll
     for (int pass = 0; pass < 4; ++pass) {
         const int idx = pass * (64 * RB) + tid, cl = idx / (2 * RB), k = idx & (2 * RB - 1), b = k >> 1, half = k & 1;
@@ -130,7 +129,7 @@ __global__ __launch_bounds__(64 * RB) void quantize_cols_fp8_kernel(const uint16
 // the other 16 are still in flight), reads them back as row blocks, two per lane and four lanes per row, so that
 // a row of the tile leaves as 128 contiguous bytes, and then reuses the slice to regroup its column-wise codes:
 // wave w keeps the low 16 bytes of every column's 32 at w * SKEW into its slice and the high 16 bytes FP8_HALF
-// further on, so that the 8 lanes that later gather one output row's 128 bytes from the 4 slices hit different banks.
+// further on, so that the 2 RB lanes that later gather one output row's bytes from the RB slices hit different banks.
 constexpr int FP8_SLICE = 32 * RAW_PITCH, FP8_HALF = (CT_COLS + 1) * 16, FP8_SKEW = 32;
 static_assert(2 * FP8_HALF + (8 - 1) * FP8_SKEW <= FP8_SLICE, "the codes of a wave must fit its slice");
 
@@ -226,7 +225,7 @@ __global__ __launch_bounds__(64 * RB) void quantize_dual_fp8_kernel(const uint16
     }
     // workgroup barrier for the LDS traffic only (it does not wait for the row-wise stores still in flight)
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    // 8 consecutive threads write the 128 bytes one output row receives from this tile
+    // 2 RB consecutive threads write the 32 RB bytes one output row receives from this tile
 #pragma unroll
     for (int pass = 0; pass < 4; ++pass) {
         const int idx = pass * (64 * RB) + tid, cl = idx / (2 * RB), k = idx & (2 * RB - 1), b = k >> 1, half = k & 1;
