@@ -68,10 +68,12 @@ __global__ __launch_bounds__(256) void quantize_rows_fp8_kernel(const uint16_t *
     s[g] = (uint8_t)sb;
 }
 
-// RB: waves, and so blocks of 32 rows, per workgroup of the column-wise kernels.  Four (an output row receives a whole 128-byte line) up to
-// 2^26 elements, where more and smaller workgroups fill the chip better and wait for each other less; eight beyond, where the longer pieces
-// do.  Both axes, eight / four waves, us: 2080 x 1440 7.0 / 6.0, 8192 x 4096 26.8 / 25.0, 8192 x 6144 37.3 / 35.2, 8192 x 14336 119 / 123.
-bool eight_waves(const QuantArgs &a) { return a.rows * a.cols > (int64_t(1) << 26); }
+// Four waves, and so blocks of 32 rows, per workgroup of the column-wise kernels (an output row receives a whole 128-byte line) up to 2^25
+// elements, where more and smaller workgroups fill the chip better and wait for each other less; eight beyond, where memory bounds and the longer
+// pieces do.  Time with four over time with eight, forward calls (their quantisations and GEMM) with X or W of so many times 2^25 elements: 0.25 0.91
+// to 0.98, 0.5 0.91 to 1.0, 1.0 0.94 to 1.02, 1.5 and 1.75 1.0 to 1.03, 2 1.0 to 1.02, 3 and more 1.01 to 1.05 (back to back, on inputs that stay in
+// the last-level cache, four are 0.93 up to 2).
+bool eight_waves(const QuantArgs &a) { return a.rows * a.cols > (int64_t(1) << 25); }
 
 // column-wise: the tile and lane assignment of quantize_cols_kernel; an output row receives RB x 32 contiguous bytes per tile
 template <int HAD, int RB>

@@ -1,5 +1,5 @@
 """GPU tests: the column-wise quantisers' workgroups of eight waves, which large tensors alone get: both axes without a rotation, two tensors of which
-one is beyond the last-level cache, MXFP8 beyond 2^26 elements, MXFP8 beside MXFP4.  Ragged everywhere; byte for byte the row-wise kernels on
+one is beyond the last-level cache, MXFP8 beyond 2^25 elements, MXFP8 beside MXFP4.  Ragged everywhere; byte for byte the row-wise kernels on
 the transposed tensor, or (32 x 32 regions) the same calls on parts of it that get four waves."""
 import pytest
 import torch
