@@ -81,10 +81,11 @@ __device__ __forceinline__ void butterflies(float (&v)[32])
 // 16 (2 R + 1) < f 2^28 holds iff y's fraction is at least 32 R + 17, i.e. iff adding 2^28 - 32 R - 17 carries into the code.  Below 2 the
 // grid is uniform and y is a 2^29; from 1 upwards y is a's bit pattern shifted (a grid step is half an octave), which is the smaller
 // of the two from 2 on.  (|v| / scale is below 8, so a 2^29 fits 32 bits without the clamp.)
-// The kernels that round stochastically are bound by their vector instructions, each as dear as the next (the integer products of the
-// counter hash too): 23 per element and block; 30 with a comparison to select y, sign and code packed apart and the whole hash, 42 with
-// the rounding decided in floating point.  16384 x 4096, us, with 42, 30 and 23: row-wise 69, 61, 53, column-wise 76, 61, 57, both 149, 119,
-// 104 (29, 39 and 53 rounding to nearest).
+// The kernels that round stochastically are bound by their vector instructions: 23 per element and block (29 with loads, stores and addresses); 30
+// with a comparison to select y, sign and code packed apart and the whole hash, 42 with the rounding decided in floating point.  With four waves per
+// SIMD an xor, a sum or a shift takes 2.4 clocks of it, the others here (products of 32 bits as much as a fused shift or a conversion) 4.2: 23 are
+// 38 us of 16384 x 4096, 29 are 46.  That tensor, us, with 42, 30 and 23: row-wise 69, 61, 53, column-wise 76, 61, 57, both 149, 119, 104 (29, 39 and
+// 53 rounding to nearest).
 // hash: the counter hash before its last step, r = hash ^ hash >> 16
 __device__ __forceinline__ uint32_t sr_code(float v, int to_2_29, uint32_t hash)
 {
