@@ -1350,21 +1350,25 @@ __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm 
     const bool whole = (p.vec & 1) && left >= 4;
 #pragma unroll
     for (int i = 0; i < WM; ++i) {
-      // Values added to: all at once, under the way through LDS (rows beyond the last are the last again, for nobody), and all added before
-      // the first store, since a wait for a load is one for the stores before it too.  us, one by one in front of their stores / loaded at once
-      // but added one by one / like this: 6656 x 11008 x 768 198 / 148 / 146, 768 x 800 x 256 4.4 / 4.6 / 4.0, 3520 x 2304 x 896 20.1 / 20.9 /
-      // 19.4; beside a product that is not added to: dY 256 x 2048 of a layer 1536 wide 8.7 / 9.8 / 8.9, 1888 x 256 of 7424 19.5 / 23.2 / 18.4.
+      // Values added to: all at once (rows beyond the last are the last again, for nobody), and all added before the first store, since a wait
+      // for a load is one for the stores before it too.  us, one by one in front of their stores / loaded at once but added one by one / like
+      // this: 6656 x 11008 x 768 198 / 148 / 146, 768 x 800 x 256 4.4 / 4.6 / 4.1, 3520 x 2304 x 896 20.1 / 20.9 / 19.4.
+      // The wide tile, one per compute unit, loads them before its way through LDS (13888 x 6912 x 576 193, behind it 194; 6688 x 3072 x 992 46.6,
+      // 47.4), the others, several there, behind it: beside a product that is not added to, M x N x K of the layer, 2400 x 256 x 4352 14.7, behind
+      // it 14.1 (one by one 14.1), 2048 x 256 x 4864 13.3, 12.7 (12.6), 256 x 2048 x 1536 9.0, 8.8 (8.8).
       constexpr int NU = 32 / RPI;
       const int64_t row0 = m0 + wm * 32 * WM + 32 * i + rl;
       const bool add = ACC && p.accumulate && whole;
       v4f v[NU], old[NU];
-      if (add) {
+      auto load_old = [&]() {
+        if (!add) return;
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
             const int64_t row = row0 + u * RPI < p.Ra ? row0 + u * RPI : p.Ra - 1;
             old[u] = *reinterpret_cast<const v4f *>(reinterpret_cast<const float *>(p.out) + row * p.ld + col);
         }
-      }
+      };
+      if constexpr (WN > 1) load_old();
 #pragma unroll
       for (int j = 0; j < WN; ++j)
 #pragma unroll
@@ -1377,6 +1381,7 @@ __global__ __launch_bounds__(128 * NWN, 2) void gemm_edge_kernel(const EdgeGemm 
         const int r = u * RPI + rl;
         return *reinterpret_cast<const v4f *>(epi + r * PITCH + ((ch ^ (r & (CHUNKS - 1))) << 4));
       };
+      if constexpr (WN == 1) load_old();
       if constexpr (ACC) {
 #pragma unroll
         for (int u = 0; u < NU; ++u) v[u] = read(u);
