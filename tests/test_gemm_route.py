@@ -98,6 +98,13 @@ def test_moved_back_pairs_but_for_narrow_outputs():
         assert pair(*dgrad_wgrad(*layer))[2] < MOVED_BACK
 
 
+def test_weight_gradients_of_a_few_tokens_that_are_added_to():
+    dgrad_wgrad = lambda M, N, K: ((M, K, N), (N, K, M))
+    for layer in ((256, 8192, 2304), (512, 14080, 1024), (32, 8384, 2784)):
+        assert pair(*dgrad_wgrad(*layer))[::2] == pair(*dgrad_wgrad(544, *layer[1:]), accumulate1=True)[::2] == (mx.PAIR_EDGE, 2)
+        assert pair(*dgrad_wgrad(*layer), accumulate1=True)[::2] == (mx.PAIR_EDGE, 1)
+
+
 def test_more_tiles_than_a_grid_can_hold():
     # A launch holds fewer than 2^32 threads along a dimension: 2^24 workgroups on 64 x 64 or 128 x 64 tiles, 2^23 on
     # 128 x 256 ones.  Beyond that the next larger tile, then the any-shape kernel, whose grid has two dimensions.

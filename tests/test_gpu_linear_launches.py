@@ -114,3 +114,13 @@ def test_narrow_beside_wide_equals_the_single_gemm_calls(case, swap):
         out0, out1 = torch.full_like(want0, 3.0), base.clone()
         mx.mxfp4_gemm_pair(*ops[0], out0, *ops[1], out1, accumulate1=acc)
         assert torch.equal(out0, want0) and torch.equal(out1, want1)
+
+
+# the weight gradient of a few tokens, added to: 128 x 64 tiles at any size up to 512 tokens, in MXFP8 up to 256
+@pytest.mark.parametrize("shape", [(32, 8384, 2784), (256, 4128, 2080), (512, 8192, 2304), (544, 8192, 2304)])
+@pytest.mark.parametrize("fmt", [mx.FMT_E2M1, mx.FMT_E4M3])
+def test_weight_gradients_of_a_few_tokens_added_to(shape, fmt):
+    M, N, K = shape
+    _, _, tile, _ = mx.mxfp4_gemm_pair_route((M, K, N), (N, K, M), (fmt, fmt), (mx.OUT_BF16, mx.OUT_FP32), True)
+    assert (tile == 1) == (M <= (256 if fmt else 512))
+    test_backward_products_equal_the_single_gemm_calls(shape, fmt, mx.OUT_BF16, True)
