@@ -140,11 +140,15 @@ __global__ __launch_bounds__(256) void gemm_any_kernel(const uint8_t *__restrict
 
 
 // ---- tiled kernel: 256 x 256 output tile per workgroup, K consumed in stages of 256 ---------
-// 4 waves (2 x 2), each a 128 x 128 sub-tile = 4 x 4 tiles of V_MFMA_SCALE_F32_32X32X64_F8F6F4
-// (256 accumulator registers per lane); a narrow variant works on 256 x 128 tiles (sub-tile 128 x 64, 4 x 2
+// 4 waves (2 x 2), each a 128 x 128 sub-tile = 8 x 8 tiles of V_MFMA_SCALE_F32_16X16X128_F8F6F4
+// (256 accumulator registers per lane); a narrow variant works on 256 x 128 tiles (sub-tile 128 x 64, 8 x 4
 // instruction tiles) with the same data path, see gemm_tile_body.  With FP4 operands that instruction takes, per lane l,
-// the 32 K-elements 32*(l/32).. of row l%32 of each operand (one MX block, 16 bytes) and the
-// block's scale byte; the result holds, in register e of lane l, D[8*(e/4) + 4*(l/32) + e%4][l%32].
+// the 32 K-elements 32*(l/16).. of row l%16 of each operand (one MX block, 16 bytes) and the
+// block's scale byte; the result holds, in register e of lane l, D[4*(l/16) + e][l%16].
+// The chip is power-limited here (see gemm_tile_body), and this form takes less energy than V_MFMA_SCALE_F32_32X32X64: per
+// product it moves half the sums.  Matrix instructions alone, fragments of normal operands in registers: 6.7 PFLOP/s in the 32 x 32 form,
+// 7.5 in this one; with a stage's fragment reads from LDS 6.1 and 6.95 (9.9 and 9.85 with all-zero codes, where power plays no part).
+// The sums are the same bits.
 //
 // Data path: packed codes go global -> LDS with the direct-to-LDS loads (no registers), one
 // instruction per 8 rows x 128 bytes (whole cache lines: the memory pipeline's cost is per
@@ -156,9 +160,7 @@ __global__ __launch_bounds__(256) void gemm_any_kernel(const uint8_t *__restrict
 // Scale bytes: one row has 8 per stage, far too little for a request of its own, so they
 // come in batches of 4 stages (32 bytes per row, two lanes per row), double-buffered; the
 // four load instructions of the next batch are spread over the four stages of the current one.
-// A byte permute puts the 4 scale bytes a lane needs in one stage into one register, from which
-// the instruction's byte selector picks the K-step.
-// Two LDS stage buffers; fragments are double-buffered in registers across the 4 K-steps.
+// Two LDS stage buffers; fragments are double-buffered in registers across the 2 K-steps.
 // Epilogue: every wave transposes its sub-tile through its own LDS slice so that global
 // stores are whole 256- or 512-byte row segments.
 constexpr int TILE = 256;                       // output tile edge
@@ -169,6 +171,7 @@ constexpr int OFF_A = 0, OFF_B = OP_BYTES;
 constexpr int SCALE_BATCH = 4;                  // stages per scale batch
 constexpr int SC_OP_BYTES = TILE * 8 * SCALE_BATCH;  // 8 KiB per operand and batch
 constexpr int SC_BUF_BYTES = 2 * SC_OP_BYTES;        // 16 KiB
+constexpr int SC_PIECE_BYTES = SC_OP_BYTES / 2;      // half an operand's rows: 4 KiB
 constexpr int OFF_SC = 2 * STAGE_BYTES;              // scale buffers behind the two stage buffers
 constexpr int LDS_BYTES = 2 * STAGE_BYTES + 2 * SC_BUF_BYTES;  // 163840 = all of the CU's LDS
 constexpr int GROUP_M = 4;                      // tile rows per rasterisation group
@@ -218,14 +221,14 @@ struct __attribute__((packed, aligned(1))) Bytes4 { uint32_t v; };
 // The whole tiled GEMM as seen by one workgroup: `wg` of `nwg` workgroups share the problem (the ids are
 // virtual: a launch may run two problems side by side on disjoint sets of CUs).  smem: the workgroup's
 // LDS_BYTES of LDS, lds0 its LDS address.
-// FMT: element format of both operands.  0 = E2M1: a stage (128 bytes per row) holds 256 K-elements = 4
-// instruction K-steps, one fragment (16 bytes per lane) each.  1 = E4M3: a stage holds 128 K-elements = 2
-// instruction K-steps of 32 bytes per lane.  The instruction wants, from lane group h, the elements 16h .. +15
-// and 32 + 16h .. +15 of its 64 (probed), which are exactly the two 16-byte fragments the E2M1 path fetches
-// for its K-steps 2j and 2j+1: so data movement, LDS layout and fragment reads are the same for both formats,
-// and only the matrix instructions differ (16 per two phases instead of 16 per phase, taking two fragments).
-// NJ: 32-column groups of a wave's sub-tile.  4: the 256 x 256 tile (wave sub-tile 128 x 128, 16 matrix
-// instructions per K-step).  2 (E2M1 only): a 256 x 128 tile (sub-tile 128 x 64, 8 instructions per K-step) for
+// FMT: element format of both operands.  0 = E2M1: a stage (128 bytes per row) holds 256 K-elements = 2
+// instruction K-steps, one fragment (16 bytes per lane) each.  1 = E4M3: a stage holds 128 K-elements = 1
+// instruction K-step of 32 bytes per lane.  The instruction wants, from lane group g, the elements 16g .. +15
+// and 64 + 16g .. +15 of its 128 (probed), which are exactly the two 16-byte fragments the E2M1 path fetches
+// for its K-steps 0 and 1: so data movement, LDS layout and fragment reads are the same for both formats,
+// and only the matrix instructions differ (half as many, taking two fragments each).
+// NJ: 32-column groups of a wave's sub-tile.  4: the 256 x 256 tile (wave sub-tile 128 x 128, 64 matrix
+// instructions per K-step).  2 (E2M1 only): a 256 x 128 tile (sub-tile 128 x 64, 32 instructions per K-step) for
 // outputs that have too few 256 x 256 tiles to fill the chip, and for the part-filled last round of others;
 // it moves 1.5 times the operand bytes per flop, so it is only used where compute units would idle otherwise.
 // l_lo, l_hi: the body works on tiles l_lo .. l_hi-1 of the tile sequence only (l_hi < 0: all of them).
@@ -238,6 +241,12 @@ struct __attribute__((packed, aligned(1))) Bytes4 { uint32_t v; };
 // in fp32).  Scale rows then start at any byte, so they go through registers: a 16-byte load per lane takes the place of
 // every direct-to-LDS scale load, and its bytes are written to LDS one stage later, right behind the barrier that has
 // waited for all loads anyway; hence the loads run two stages ahead, not one.
+// What bounds it: power.  With normal operands the clock settles at 1.7 to 1.8 GHz (2.4 with all-zero codes), and whatever moves data costs
+// clock: without the operand loads 8192 x 6144 x 16384 takes 276 us instead of 322, without the fragment reads no less.  Beside that every
+// instruction between two matrix instructions counts (16 clocks each, three others fit): taking the scalar arithmetic of a stage from 70 to
+// 25 instructions, in idle slots, gave 322 -> 311 us.  us, in the 32 x 32 form / this one, both on one card: bf16 8192 x 6144 x 4096 93.8 /
+// 89.3, x 16384 313.7 / 298.4 (5.53 PFLOP/s); fp32 6144 x 4096 x 8192 95.7 / 92.9, 4096 x 4096 x 8192 added to 71.5 / 68.7; narrow tiles
+// 8192 x 1024 x 4096 20.2 / 19.7; MXFP8 8192 x 8192 x 4096 202 / 187 (2.94 PFLOP/s).
 template <bool OUT_FP32, bool ACC, int FMT, int NJ, bool HALVES = false, bool RAG = false>
 __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, const uint8_t *__restrict__ as,
                                                const uint8_t *__restrict__ bq, const uint8_t *__restrict__ bs,
@@ -252,7 +261,6 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
     constexpr int TILE_N = 64 * NJ;          // B rows (output columns) per tile
     constexpr int BROWS = TILE_N / 4;        // B rows one wave loads per stage: 64 or 32
     constexpr int NLOADS = 8 + BROWS / 8;    // direct-to-LDS loads per wave and stage: 16 or 12
-    constexpr int NSLOT = 4 * NJ;            // matrix instructions per K-step
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 1, wn = wave & 1;
@@ -309,19 +317,25 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
     const uint32_t lds_wave_b = lds0 + OFF_B + (uint32_t)wave * (uint32_t)(BROWS * 128);
     const uint32_t svoff = (uint32_t)((lane >> 1) * nkb) + (uint32_t)((lane & 1) << 4);
 
-    // load n (0..15) of stage s of tile t for this wave, in issue order: n = 0..3 A's 8-row groups 0..3,
+    // load n (0..15) of a stage for this wave, in issue order: n = 0..3 A's 8-row groups 0..3,
     // 4..7 B's groups 0..3, 8..11 A's groups 4..7, 12..15 B's groups 4..7 (the narrow tile has no 12..15: a
     // wave loads only 32 rows of B).  The four loads of a run share one M0
     // (the LDS address of the operand's group 4; the groups sit at immediate offsets (g - 4) KiB from it);
     // `force` makes a load set M0 itself (where scale loads, which set their own, are issued in between).
-    auto issue_load = [&](const TileSrc &t, int s, int buf, auto nc, auto force) {
+    // ld_a, ld_b, ld_buf: the stage being loaded and the offset of the stage buffer it goes to; both move on once per stage, in phase 1.
+    const uint8_t *ld_a = nullptr, *ld_b = nullptr;
+    uint32_t ld_buf = 0;
+    int64_t ld_k = 0;  // RAG: the stage's offset in a row
+    auto issue_load = [&](auto nc, auto force) {
         constexpr int n = decltype(nc)::value, op = (n >> 2) & 1, g = (n >> 3) * 4 + (n & 3);
         static_assert(n < NLOADS, "no such load for this tile shape");
         constexpr bool setm0 = decltype(force)::value || (n & 3) == 0;
-        int64_t koff = (int64_t)s * (STAGE_K / 2);
-        if (RAG && koff > rowbytes - STAGE_K / 2) koff = rowbytes - STAGE_K / 2;
-        dma16_run<(g - 4) * 1024, setm0>((op ? lds_wave_b : lds_wave_a) + buf * STAGE_BYTES + 4096, dvo[g],
-                                         (op ? t.b : t.a) + koff);
+        dma16_run<(g - 4) * 1024, setm0>((op ? lds_wave_b : lds_wave_a) + 4096 + ld_buf, dvo[g], op ? ld_b : ld_a);
+    };
+    const int64_t k_last = rowbytes - STAGE_K / 2;
+    auto set_load = [&](const TileSrc &t, int s) {  // (s = 0 or 1; every row has more stages)
+        ld_k = s * (STAGE_K / 2);
+        ld_a = t.a + ld_k, ld_b = t.b + ld_k;
     };
     using no_force = std::false_type;
     using force_m0 = std::true_type;
@@ -332,12 +346,12 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
     // instruction j (0..3) of batch b for this wave: j>>1 = operand, j&1 = which 32 of its 64 rows
     // Batch b of a tile lives in scale buffer (b ^ par) & 1; par alternates between tiles so that
     // a tile's first batch never lands in the buffer its predecessor's last batch is still read from.
-    // (narrow tile: a wave has only 32 rows of B, so instruction 3 repeats instruction 2: the same bytes to the
-    // same place, which keeps the stage bodies free of branches)
+    // Its 1 KiB (32 rows x 32 bytes) lie at piece j, wave: so that the place follows from the counter of stages in two operations.
+    // (narrow tile: a wave has only 32 rows of B, so instruction 3 repeats instruction 2: the same bytes again, which keeps the stage
+    // bodies free of branches)
     auto scales_dst = [&](int b, int j, int par) {
         if (NJ == 2 && j == 3) j = 2;
-        const int rows0 = (j >> 1) ? wave * BROWS : wave * 64;
-        return lds0 + OFF_SC + ((b ^ par) & 1) * SC_BUF_BYTES + (j >> 1) * SC_OP_BYTES + (rows0 + (j & 1) * 32) * 32;
+        return lds0 + OFF_SC + ((b ^ par) & 1) * SC_BUF_BYTES + j * SC_PIECE_BYTES + wave * 1024;
     };
     auto scales_src = [&](const TileSrc &t, int b, int j) {
         if (NJ == 2 && j == 3) j = 2;
@@ -361,214 +375,302 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
     };
 
     // ---- fragment reads: per-lane offsets ---------------------------------------------------
-    const int fr = lane & 31, fh = lane >> 5;
-    const int fm = (fr & 7) ^ ((fr >> 3) & 1);
+    // Lane l of an instruction holds row l % 16 of its 16 and block l / 16 of its four.
+    constexpr int NB = 2 * NJ;  // 16-column groups of the wave's sub-tile (its rows: 8 groups)
+    const int fr = lane & 15, fg = lane >> 4;
+    const int fm = (fr & 7) ^ (fr >> 3);
     const uint32_t fl0 = (uint32_t)((fr >> 3) * 1024 + (fr & 7) * 128);
-    uint32_t foff[4];
+    // LDS offsets of this lane's piece of A's and B's first fragment in K-step kk, in the buffer of the stage whose fragments are next
+    uint32_t ra[2], rb[2];
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) foff[kk] = fl0 + (uint32_t)((((kk << 1) | fh) ^ fm) << 4);
-    // RAG: keeps the scale bytes of the blocks that the last stage does not repeat (byte k: block 2k + fh of the stage)
+    for (int kk = 0; kk < 2; ++kk) {
+        const uint32_t f = fl0 + (uint32_t)((((kk << 2) | fg) ^ fm) << 4);
+        ra[kk] = f + OFF_A + wm * 16 * 1024;
+        rb[kk] = f + OFF_B + wn * (NJ * 4) * 1024;
+    }
+    auto other_buffer = [&](uint32_t &at) {
+        at ^= STAGE_BYTES;
+        asm volatile("" : "+v"(at));
+    };
+    // RAG: keeps the scale bytes of the blocks that the last stage does not repeat (bytes as settle_scales leaves them)
     uint32_t last_mask = 0xFFFFFFFFu;
     if (RAG) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if (2 * k + fh < nstages * SC_STAGE - (int)nkb) last_mask &= ~(0xFFu << (8 * k));
+        const int again = nstages * SC_STAGE - (int)nkb;
+        if (fg < again) last_mask = FMT ? 0u : 0xFFFF0000u;
+        if (!FMT && 4 + fg < again) last_mask = 0u;
     }
-    const uint32_t a_frag0 = OFF_A + wm * 16 * 1024, b_frag0 = OFF_B + wn * (NJ * 4) * 1024;
-    const uint32_t sa_frag0 = OFF_SC + (wm * 128 + fr) * 32;
-    const uint32_t sb_frag0 = OFF_SC + SC_OP_BYTES + (wn * (32 * NJ) + fr) * 32;
-    // scale bytes of one stage -> one register whose byte k is the lane's block in instruction K-step k
-    const uint32_t perm_sel = FMT ? (fh ? 0x03010301u : 0x02000200u) : (fh ? 0x07050301u : 0x06040200u);
+    // (the wave's 64-row pieces of A, and of B on the wide tile, were loaded by one wave in two halves; the narrow tile's by two waves)
+    const uint32_t sa_row0 = OFF_SC + wm * 2048 + (lane >> 5) * SC_PIECE_BYTES + (lane & 31) * 32;
+    const uint32_t sb_row0 = OFF_SC + SC_OP_BYTES + wn * 2048 + (lane >> 5) * (NJ == 4 ? SC_PIECE_BYTES : 1024) + (lane & 31) * 32;
 
-    v4i fa[FMT ? 4 : 2][4], fb[FMT ? 4 : 2][4];
-    uint2 sraw[8];
-    int sa_cur[4], sb_cur[4];
-    // One fragment fetch (f = 0..7: A0,B0,A1,B1,...) of K-step kk of buffer buf into register set `set`.
-    auto read_one = [&](int buf, int kk, int set, int f) {
-        const uint8_t *p = smem + buf * STAGE_BYTES + foff[kk] + (f >> 1) * 4096;
-        if (f & 1)
-            fb[set][f >> 1] = *reinterpret_cast<const v4i *>(p + b_frag0);
-        else
-            fa[set][f >> 1] = *reinterpret_cast<const v4i *>(p + a_frag0);
+    v4i fa[2][8], fb[2][NB];
+    // Scale bytes of a stage.  A lane reads those of ONE row, 64 rows (four fragments) per instruction, and the wave then turns the 4 x 4
+    // square of (fragment, block) over its four lane groups, so that lane group g holds block g of all four; the instruction's byte
+    // selector picks the fragment.  (Read per fragment, by all four lane groups alike, they took a fifth of the LDS' time.)
+    // E2M1: set q = 0, 1: A's rows 64 q .. +63; 2, 3: B's.  word (q, f & 1): bytes {K-step 0: fragments f, f + 2; K-step 1: f, f + 2}.
+    // E4M3: set 0: A, 1: B.  word (q, f & 1): bytes {fragments f, f + 2, f + 4, f + 6}.
+    constexpr int SETS = FMT ? 2 : 2 + NJ / 2;
+    uint32_t sc_cur[SETS][2], sc_old[SETS][2];  // (sc_old: for phases 2 and 3, while the next stage's arrive in sc_cur)
+    uint32_t raw[SETS][2];
+    // One fragment: rows 16 i .. 16 i + 15 of the wave's part of A or B, 16-byte chunks 4 kk .. 4 kk + 3.
+    auto read_a = [&](int kk, int i) { fa[kk][i] = *reinterpret_cast<const v4i *>(smem + ra[kk] + i * 2048); };
+    auto read_b = [&](int kk, int j) { fb[kk][j] = *reinterpret_cast<const v4i *>(smem + rb[kk] + j * 2048); };
+    // Byte sb = SC_STAGE s of a row's scales, where the stage s begins, lies sc_place(sb, par) behind sa_row0 or sb_row0
+    const int sb_lim = RAG ? (int)nkb - 32 : (nstages - BATCH) * SC_STAGE;  // where the last batch begins
+    auto sc_place = [&](int sb, int par) {
+        const int at = RAG ? (sb < (int)nkb - SC_STAGE ? sb : (int)nkb - SC_STAGE) : sb;
+        const int first = (sb & ~31) < sb_lim ? (sb & ~31) : sb_lim;
+        return (uint32_t)(at - first) + (uint32_t)(((sb & 32) << 9) ^ (par << 14));
     };
-    // The 8 scale bytes of stage s for fragment row f (0..7: A0,B0,A1,B1,...), raw.
-    auto read_scale_one = [&](int s, int f, int par) {
-        const int b = s / BATCH;
-        if constexpr (RAG) {
-            const int at = s * SC_STAGE < (int)nkb - SC_STAGE ? s * SC_STAGE : (int)nkb - SC_STAGE;
-            const uint8_t *p = smem + ((b ^ par) & 1) * SC_BUF_BYTES + (at - rag_first(b)) + (f >> 1) * 1024 +
-                               ((f & 1) ? sb_frag0 : sa_frag0);
-            if (FMT) {
-                sraw[f] = make_uint2(reinterpret_cast<const Bytes4 *>(p)->v, 0u);
-            } else {
+    // piece n (0 .. 3; the narrow tile has no 3): A's rows 0 .. 63, B's, A's 64 .. 127, B's
+    auto read_scales = [&](uint32_t place, int n) {
+        const uint8_t *p = smem + (((n & 1) ? sb_row0 : sa_row0) + place) + (n >> 1) * 1024;
+        if (FMT) {
+            raw[n & 1][n >> 1] = reinterpret_cast<const Bytes4 *>(p)->v;
+        } else {
+            const int q = (n & 1) * 2 + (n >> 1);
+            if constexpr (RAG) {
                 const Bytes8 v = *reinterpret_cast<const Bytes8 *>(p);
-                sraw[f] = make_uint2(v.v[0], v.v[1]);
+                raw[q][0] = v.v[0], raw[q][1] = v.v[1];
+            } else {
+                const uint2 v = *reinterpret_cast<const uint2 *>(p);
+                raw[q][0] = v.x, raw[q][1] = v.y;
             }
-            return;
-        }
-        const uint8_t *p = smem + ((b ^ par) & 1) * SC_BUF_BYTES + (s - batch_first(b)) * SC_STAGE + (f >> 1) * 1024;
-        if (FMT)
-            sraw[f] = make_uint2(*reinterpret_cast<const uint32_t *>(p + ((f & 1) ? sb_frag0 : sa_frag0)), 0u);
-        else
-            sraw[f] = *reinterpret_cast<const uint2 *>(p + ((f & 1) ? sb_frag0 : sa_frag0));
-    };
-    // raw scale bytes -> one register per fragment row whose bytes are K blocks fh, 2+fh, 4+fh, 6+fh
-    auto permute_scales = [&]() {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            sa_cur[i] = (int)__builtin_amdgcn_perm(sraw[2 * i].y, sraw[2 * i].x, perm_sel);
-            if (i < NJ) sb_cur[i] = (int)__builtin_amdgcn_perm(sraw[2 * i + 1].y, sraw[2 * i + 1].x, perm_sel);
         }
     };
+    // Step 0 .. 3 of turning set q; `last`: these are the scales of a tile's last stage.  raw = two words x, y of bytes 0 .. 3 of the row.
+    auto settle_scales = [&](int q, int step, bool last) {
+        uint32_t *r = raw[q];
+        if (step == 0) {  // {x0, x1, y0, y1} and {x2, x3, y2, y3}
+            const uint32_t x = r[0], y = r[1];
+            r[0] = __builtin_amdgcn_perm(y, x, 0x05040100u);
+            r[1] = __builtin_amdgcn_perm(y, x, 0x07060302u);
+        } else if (step == 1) {  // lane groups 0, 1 and 2, 3: the first word of the upper for the second of the lower
+            const auto w = __builtin_amdgcn_permlane32_swap(r[0], r[1], false, false);
+            r[0] = w[0], r[1] = w[1];
+        } else if (step == 2) {
+            const uint32_t x = r[0], y = r[1];
+            r[0] = __builtin_amdgcn_perm(y, x, 0x06020400u);
+            r[1] = __builtin_amdgcn_perm(y, x, 0x07030501u);
+        } else {  // lane groups 0, 2 and 1, 3
+            const auto w = __builtin_amdgcn_permlane16_swap(r[0], r[1], false, false);
+            sc_cur[q][0] = w[0], sc_cur[q][1] = w[1];
+            if (RAG && last) sc_cur[q][0] &= last_mask, sc_cur[q][1] &= last_mask;
+        }
+    };
+    // E2M1: the sets in the order their bytes are read in
+    auto settle_set = [](int n) { return (n & 1) * 2 + (n >> 1); };
+    // (opaque: as a plain assignment the compiler keeps one register and copies all of them at the end of a stage)
+    auto age_scales = [&](int n) { asm volatile("v_mov_b32 %0, %1" : "=v"(sc_old[n >> 1][n & 1]) : "v"(sc_cur[n >> 1][n & 1])); };
 
     // Stage s of a tile lives in stage buffer (s & 1) ^ bp.  The hand-over loads put the next tile's stage 0
     // into the buffer after the current tile's last one, so with an odd number of stages the parity flips
     // from tile to tile.
     int bp = 0;
-    v16f acc[4][4];
-    const v16f zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    v4f acc[8][NB];
 
-    // One matrix instruction: tile (n/4, n%4) of the wave's 4 x 4, fragments from register set SET,
-    // K-step KK selects the scale byte.
-#define MXFP4_MMA(SET, KK, N, FRESH)                                                                            \
-    {                                                                                                           \
-        constexpr int i_ = (N) / NJ, j_ = (N) % NJ;                                                             \
-        v8i fb8 = {fb[SET][j_].x, fb[SET][j_].y, fb[SET][j_].z, fb[SET][j_].w, 0, 0, 0, 0};                     \
-        v8i fa8 = {fa[SET][i_].x, fa[SET][i_].y, fa[SET][i_].z, fa[SET][i_].w, 0, 0, 0, 0};                     \
-        acc[i_][j_] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb8, fa8, (FRESH) ? zero16 : acc[i_][j_], \
-                                                                      4, 4, KK, sb_cur[j_], KK, sa_cur[i_]);    \
-    }
-    // E4M3: instruction n (0..15) of instruction K-step KS (0/1): fragments 2*KS (low half) and 2*KS+1
-#define MXFP8_MMA(KS, N, FRESH)                                                                                 \
-    {                                                                                                           \
-        constexpr int i_ = (N) >> 2, j_ = (N) & 3;                                                              \
-        v8i fb8 = {fb[2 * (KS)][j_].x, fb[2 * (KS)][j_].y, fb[2 * (KS)][j_].z, fb[2 * (KS)][j_].w,              \
-                   fb[2 * (KS) + 1][j_].x, fb[2 * (KS) + 1][j_].y, fb[2 * (KS) + 1][j_].z, fb[2 * (KS) + 1][j_].w}; \
-        v8i fa8 = {fa[2 * (KS)][i_].x, fa[2 * (KS)][i_].y, fa[2 * (KS)][i_].z, fa[2 * (KS)][i_].w,              \
-                   fa[2 * (KS) + 1][i_].x, fa[2 * (KS) + 1][i_].y, fa[2 * (KS) + 1][i_].z, fa[2 * (KS) + 1][i_].w}; \
-        acc[i_][j_] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb8, fa8, (FRESH) ? zero16 : acc[i_][j_], \
-                                                                      0, 0, KS, sb_cur[j_], KS, sa_cur[i_]);    \
-    }
-    // phase P (0..3) of a stage, slot N (0..15): E2M1 issues instruction N of K-step P; E4M3 issues, in even
-    // slots, instruction N/2 (+8 in odd phases) of K-step P/2
-#define MXFP4_SLOT_MMA(P, N, FRESH)                                                                             \
-    if constexpr (FMT == 0) {                                                                                   \
-        if constexpr ((N) < NSLOT) {                                                                            \
-            MXFP4_MMA((P) & 1, P, N, FRESH)                                                                     \
-        }                                                                                                       \
-    } else if constexpr (((N) & 1) == 0) {                                                                      \
-        MXFP8_MMA((P) >> 1, ((N) >> 1) + 8 * ((P) & 1), FRESH)                                                  \
+    // One matrix instruction: tile (I, J) of the wave's 8 x NB, fragments and scale bytes of K-step KK.  In assembly, so that the sum stays
+    // where it is: with four registers per sum and none to spare the compiler moves a quarter of them about at every change of stage body.
+    // What the compiler then leaves to this code: two instructions between a vector instruction and the matrix instruction that reads its
+    // result (scales are settled at least one slot ahead), and the wait before the epilogue reads the sums (below).
+#define MXFP4_MFMA(FIRST, SECOND, SB, SA, SELB, SELA, FORMATS, FRESH)                                            \
+    if constexpr (FRESH)                                                                                        \
+        asm volatile("v_mfma_scale_f32_16x16x128_f8f6f4 %0, %1, %2, 0, %3, %4 op_sel:[%5,%6,0] op_sel_hi:[%7,%8,0]" FORMATS \
+                     : "=a"(acc[i_][j_])                                                                        \
+                     : "v"(FIRST), "v"(SECOND), "v"(SB), "v"(SA), "n"((SELB) & 1), "n"((SELA) & 1), "n"((SELB) >> 1), "n"((SELA) >> 1)); \
+    else                                                                                                        \
+        asm volatile("v_mfma_scale_f32_16x16x128_f8f6f4 %0, %1, %2, %0, %3, %4 op_sel:[%5,%6,0] op_sel_hi:[%7,%8,0]" FORMATS \
+                     : "+a"(acc[i_][j_])                                                                        \
+                     : "v"(FIRST), "v"(SECOND), "v"(SB), "v"(SA), "n"((SELB) & 1), "n"((SELA) & 1), "n"((SELB) >> 1), "n"((SELA) >> 1));
+    // Instruction G of phase P (GAPS of them).  E2M1: phase P is K-step P/2 on rows 64 (P%2) .. +63 of the sub-tile, columns to and fro, so
+    // that consecutive instructions share a fragment.  E4M3 (instructions twice as long; both fragments of a row are one K-step's): phase P
+    // is the quarter (P/2, P%2) of the sub-tile.
+#define MXFP4_SLOT_MMA(P, G, MODE)                                                                              \
+    if constexpr (FMT == 0 && (G) < GAPS) {                                                                     \
+        constexpr int kk_ = (P) >> 1, i_ = 4 * ((P) & 1) + (G) / NB, c_ = (G) % NB, j_ = (i_ & 1) ? NB - 1 - c_ : c_; \
+        constexpr int qb_ = 2 + (j_ >> 2), qa_ = i_ >> 2;                                                       \
+        MXFP4_MFMA(fb[kk_][j_], fa[kk_][i_], (kk_ ? sc_old[qb_][j_ & 1] : sc_cur[qb_][j_ & 1]),                  \
+                   (kk_ ? sc_old[qa_][i_ & 1] : sc_cur[qa_][i_ & 1]), 2 * kk_ + ((j_ >> 1) & 1), 2 * kk_ + ((i_ >> 1) & 1), \
+                   " cbsz:4 blgp:4", (MODE) == 3 && (P) < 2)                                                    \
+    }                                                                                                           \
+    if constexpr (FMT == 1 && (G) < GAPS) {                                                                     \
+        constexpr int i_ = 4 * ((P) >> 1) + ((G) >> 2) % 4, j_ = 4 * ((P) & 1) + ((G) & 3);                      \
+        const v8i fb8 = {fb[0][j_].x, fb[0][j_].y, fb[0][j_].z, fb[0][j_].w, fb[1][j_].x, fb[1][j_].y, fb[1][j_].z, fb[1][j_].w}; \
+        const v8i fa8 = {fa[0][i_].x, fa[0][i_].y, fa[0][i_].z, fa[0][i_].w, fa[1][i_].x, fa[1][i_].y, fa[1][i_].z, fa[1][i_].w}; \
+        MXFP4_MFMA(fb8, fa8, ((P) < 2 ? sc_cur[1][j_ & 1] : sc_old[1][j_ & 1]), ((P) < 2 ? sc_cur[0][i_ & 1] : sc_old[0][i_ & 1]), \
+                   (j_ >> 1), (i_ >> 1), "", (MODE) == 3)                                                       \
     }
 #define MXFP4_PIN() __builtin_amdgcn_sched_barrier(0);
-    // E2M1: the 8 fragment reads of a K-step go into the even slots, B0..B3 then A0..A3 (instruction n of the
-    // next K-step needs A[n/4] and B[n%4]: every fragment is at least 8 slots old when first used), so that LDS
-    // reads alternate with the direct-to-LDS loads of the odd slots instead of arriving in bursts.
-    // Narrow tile (8 slots per K-step): the 6 fragment reads go into slots 0..5, B0, B1, then A0..A3 (instruction
-    // n needs A[n/2] and B[n%2]); the loads take the odd slots of K-step 0 and every slot of K-step 3.
-#define MXFP4_FRAG_SLOT(N) (!FMT && (NJ == 4 ? ((N) & 1) == 0 : (N) < 6))
-#define MXFP4_FRAG_OF(N)                                                                       \
-    (NJ == 4 ? (((N) >> 1) < 4 ? 2 * ((N) >> 1) + 1 : 2 * (((N) >> 1) - 4)) : ((N) < 2 ? 2 * (N) + 1 : 2 * ((N)-2)))
-    // load slots of K-step 0 (second half of a stage's loads: 8, 9, ...) and of K-step 3 (first half: 0..7)
-    // (the ..._OF values are clamped to an existing load where the slot has none: the call is discarded there, but
-    // the compiler still instantiates it)
-#define MXFP4_LOAD0_SLOT(N) (((N) & 1) && 8 + ((N) >> 1) < NLOADS)
-#define MXFP4_LOAD0_OF(N) (8 + ((N) >> 1) < NLOADS ? 8 + ((N) >> 1) : 8)
-#define MXFP4_LOAD3_SLOT(N) (NJ == 4 ? ((N) & 1) : (N) < 8)
-#define MXFP4_LOAD3_OF(N) (NJ == 4 ? ((N) >> 1) : ((N) < 8 ? (N) : 0))
+    constexpr int GAPS = FMT ? 16 : 8 * NJ;  // matrix instructions per phase
+    // The barrier stands in front of this instruction of phase 2.  Loads of the stage after next go out from there on, LOADS_LATE of them up to
+    // the stage's end and the rest in the next one's phase 0.
+    constexpr int BAR = FMT ? 4 : NJ == 4 ? 14 : 8, LATE_GAPS = 2 * GAPS - BAR, LOADS_LATE = NJ == 4 ? 12 : 8;
+    // item of a list of `count` that goes in front of instruction G, one every `step` from `first` on; -1: none
+#define MXFP4_AT(G, FIRST, STEP, COUNT) ((G) >= (FIRST) && ((G) - (FIRST)) % (STEP) == 0 && ((G) - (FIRST)) / (STEP) < (COUNT) ? ((G) - (FIRST)) / (STEP) : -1)
+#define MXFP4_32(M) M(0) M(1) M(2) M(3) M(4) M(5) M(6) M(7) M(8) M(9) M(10) M(11) M(12) M(13) M(14) M(15) \
+    M(16) M(17) M(18) M(19) M(20) M(21) M(22) M(23) M(24) M(25) M(26) M(27) M(28) M(29) M(30) M(31)
 #define MXFP4_16(M) M(0) M(1) M(2) M(3) M(4) M(5) M(6) M(7) M(8) M(9) M(10) M(11) M(12) M(13) M(14) M(15)
+    // The fragments fetched in each part of a stage, in order (n-th of its list); `late`, behind the barrier, are the next stage's first.
+    //   E2M1     late: A0, all of B, A1 (K-step 0) | phase 0: A2 .. A7, (wide tile:) K-step 1's B0, B1 | 1: the rest of B, A0 .. A3 | 2: A4 .. A7
+    //   E4M3     late: A0 .. A3, in phase 3 B0 .. B3, two halves each | phase 0: B4 .. B7 | 1: A4 .. A7
+    constexpr int LATE = 3;
+    auto fetch = [&](int part, int n) {
+        if (FMT) {
+            const int f = n >> 1, h = n & 1;
+            if (part == LATE) { if (f < 4) read_a(h, f); else read_b(h, f - 4); }
+            if (part == 0) read_b(h, 4 + f);
+            if (part == 1) read_a(h, 4 + f);
+        } else {
+            constexpr int EARLY = NJ == 4 ? 2 : 0;  // fragments of K-step 1's B that phase 0 fetches
+            if (part == LATE) { if (n >= 1 && n <= NB) read_b(0, n - 1); else read_a(0, n ? 1 : 0); }
+            if (part == 0) { if (n < 6) read_a(0, 2 + n); else read_b(1, n - 6); }
+            if (part == 1) { if (n < NB - EARLY) read_b(1, EARLY + n); else read_a(1, n - (NB - EARLY)); }
+            if (part == 2) read_a(1, 4 + n);
+        }
+    };
 
-    // One stage = 4 K-steps of 16 (narrow tile: 8) matrix instructions.  Everything else is threaded between them,
-    // one item per matrix instruction, and pinned there with scheduling barriers: with a single
+    // One stage = 4 phases of 32 matrix instructions (narrow tile: 16; E4M3: 16, twice as long).  Everything else is
+    // threaded between them, evenly, and pinned there with scheduling barriers: with a single
     // wave per SIMD any stall of the wave (a burst of loads filling the memory pipeline's queue,
-    // a late fragment) idles the matrix unit, so loads are issued a few at a time.
-    //   K-step 0: fragments of K-step 1; second half of the next stage's direct-to-LDS loads
-    //   K-step 1: fragments of K-step 2           K-step 2: fragments of K-step 3
-    //   barrier (this stage's buffer is free, the next stage has landed)
-    //   K-step 3: fragments + scales of the next stage's K-step 0; first half of the loads of
-    //             the stage after next, into the buffer just freed; one scale load
+    // a late fragment) idles the matrix unit, and an instruction of 16 clocks covers three others.
+    //   phase 0: the rest of the next stage's direct-to-LDS loads
+    //   phases 0, 1, 2: fragments (see fetch)
+    //   barrier in phase 2 (this stage's buffer is free, the next stage has landed)
+    //   behind it: the next stage's first fragments and its scales; most of the loads of
+    //              the stage after next, into the buffer just freed; one scale load
     // The main loop's body must stay one basic block (no data-dependent branches), or the matrix
     // instructions get sunk behind the branches; so the last two stages of a tile, which hand
     // over to the next tile, are separate instantiations (MODE 1 and 2).
-    //   MODE 3: stage 0: as MODE 0, and its first K-step starts the accumulators from zero
+    //   MODE 3: stage 0: as MODE 0, and every accumulator's first instruction starts from zero
     //   MODE 0: stage 1 <= s <= nstages-3 of tile `cur`
-    //   MODE 1: stage nstages-2: its K-step 3 starts loading stage 0 and scale batch 0 of tile `nxt`
-    //   MODE 2: stage nstages-1: its K-step 0 finishes stage 0; K-step 3 issues the first load of
+    //   MODE 1: stage nstages-2: behind its barrier it starts loading stage 0 and scale batch 0 of tile `nxt`
+    //   MODE 2: stage nstages-1: its phase 0 finishes stage 0; behind the barrier it issues the first load of
     //           nxt's scale batch 1 and fetches nothing (the epilogue follows)
     auto stage = [&](const TileSrc &cur, const TileSrc &nxt, int par, int par_nxt, int s, auto mode) {
         constexpr int MODE = decltype(mode)::value;
-        const int buf = (s & 1) ^ bp;
-        // destination and source of the stage's one scale load: worked out in idle slots of K-step 1, used
-        // in K-step 3
-        uint32_t sc_dst = 0;
+        // Place of the next stage's scales, and destination and source of this stage's one scale load (piece (s + 1) & 3 of the batch after
+        // that of stage s + 1): worked out a step at a time in idle slots of phase 1, used in phase 3.
+        uint32_t sc_next = 0, sc_dst = 0, sc_off = 0;
         const uint8_t *sc_src = nullptr;
-#define MXFP4_K0(N)                                                                              \
-        if (FMT && (N) < 8) read_one(buf, 2, 2, (N));                                            \
-        if (MXFP4_FRAG_SLOT(N)) read_one(buf, 1, 1, MXFP4_FRAG_OF(N));                           \
-        if constexpr (MODE != 2 && MXFP4_LOAD0_SLOT(N)) issue_load(cur, s + 1, buf ^ 1, IC<MXFP4_LOAD0_OF(N)>{}, no_force{}); \
-        if constexpr (MODE == 2 && MXFP4_LOAD0_SLOT(N)) issue_load(nxt, 0, buf ^ 1, IC<MXFP4_LOAD0_OF(N)>{}, no_force{});     \
-        MXFP4_SLOT_MMA(0, N, MODE == 3) MXFP4_PIN()
-        MXFP4_16(MXFP4_K0)
-#undef MXFP4_K0
-#define MXFP4_K1(N)                                                                              \
-        if (FMT && (N) < 8) read_one(buf, 3, 3, (N));                                            \
-        if (MXFP4_FRAG_SLOT(N)) read_one(buf, 2, 0, MXFP4_FRAG_OF(N));                           \
-        if (!RAG && (MODE == 0 || MODE == 3) && (N) == (NJ == 4 ? 9 : 4)) {                              \
-            sc_dst = scales_dst((s + 1) / BATCH + 1, (s + 1) & 3, par);                          \
-            asm volatile("" : "+s"(sc_dst));                                                     \
-        }                                                                                        \
-        if (!RAG && (MODE == 0 || MODE == 3) && (N) == (NJ == 4 ? 12 : 6)) {                             \
-            sc_src = scales_src(cur, (s + 1) / BATCH + 1, (s + 1) & 3);                          \
-            asm volatile("" : "+s"(sc_src));                                                     \
-        }                                                                                        \
-        MXFP4_SLOT_MMA(1, N, FMT && MODE == 3) MXFP4_PIN()
-        MXFP4_16(MXFP4_K1)
-#undef MXFP4_K1
-#define MXFP4_K2(N)                                                                              \
-        if (!FMT && NJ == 4 && (N) < 8) read_one(buf, 3, 1, (N)); /* (early: the barrier below waits for them) */ \
-        if (NJ == 2 && MXFP4_FRAG_SLOT(N)) read_one(buf, 3, 1, MXFP4_FRAG_OF(N));                \
-        MXFP4_SLOT_MMA(2, N, false) MXFP4_PIN()
-        MXFP4_16(MXFP4_K2)
-#undef MXFP4_K2
-        // every wave has fetched its last fragments of this buffer, and this wave's loads of the
-        // next stage have landed: after the barrier the buffer may be refilled and the other read
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-#define MXFP4_K3(N)                                                                              \
-        if (FMT && MODE != 2 && (N) < 8) read_one(buf ^ 1, 0, 0, (N));                            \
-        if (MODE != 2 && MXFP4_FRAG_SLOT(N)) read_one(buf ^ 1, 0, 0, MXFP4_FRAG_OF(N));           \
-        if (FMT && MODE != 2 && (N) < 8) read_one(buf ^ 1, 1, 1, (N));                            \
-        if (MODE != 2 && NJ == 4 && (N) < 8) read_scale_one(s + 1, (N), par);                     \
-        if (MODE != 2 && NJ == 2 && (N) < 6) read_scale_one(s + 1, MXFP4_FRAG_OF(N), par);        \
-        if (!RAG && (MODE == 0 || MODE == 3) && (N) == 0) dma16(sc_dst, svoff, sc_src);          \
-        if (RAG && (MODE == 0 || MODE == 3) && (N) == 0) {                                       \
-            rag_store((s + 1) / BATCH + 1, (s + 1) & 3, par, sp[4]);                             \
-            sp[4] = rag_load(cur, (s + 2) / BATCH + 1, (s + 2) & 3);                             \
-        }                                                                                        \
-        if (RAG && MODE == 1 && (N) < 5) sp[(N) < 5 ? (N) : 0] = rag_load(nxt, (N) / 4, (N) & 3); \
-        if (RAG && MODE == 2 && (N) < 5) rag_store((N) / 4, (N) & 3, par_nxt, sp[(N) < 5 ? (N) : 0]); \
-        if (RAG && MODE == 2 && (N) == 5) sp[4] = rag_load(nxt, 1, 1);                           \
-        if constexpr ((MODE == 0 || MODE == 3) && MXFP4_LOAD3_SLOT(N))                           \
-            issue_load(cur, s + 2, buf, IC<MXFP4_LOAD3_OF(N)>{}, no_force{});                    \
-        if (MODE != 2 && NJ == 4 && (N) == 13) __builtin_amdgcn_s_waitcnt(FMT ? 0xC07F : 0xC37F); /* lgkmcnt(0 / 3): see below */ \
-        if (MODE != 2 && NJ == 2 && (N) == 6) __builtin_amdgcn_s_waitcnt(0xC07F); /* lgkmcnt(0) */ \
-        if constexpr (MODE == 1 && MXFP4_LOAD3_SLOT(N))                                          \
-            issue_load(nxt, 0, buf, IC<MXFP4_LOAD3_OF(N)>{}, force_m0{});                        \
-        if (!RAG && MODE == 1 && !((N) & 1) && (N) < 2 * (NJ == 4 ? 4 : 3)) issue_scales(nxt, 0, (N) >> 1, par_nxt); \
-        if (!RAG && MODE == 2 && (N) == 1) issue_scales(nxt, 1, 0, par_nxt);                             \
-        MXFP4_SLOT_MMA(3, N, false) MXFP4_PIN()
-        MXFP4_16(MXFP4_K3)
-#undef MXFP4_K3
-        // (the scale bytes were fetched in the first half of K-step 3 and have long landed: the explicit wait
-        // in slot 13 -- for everything but the E2M1 schedule's three younger fragment reads -- tells the compiler
-        // so, which otherwise puts a counter wait in front of every permute)
-        if (MODE != 2) permute_scales();
-        if (RAG && MODE == 1) {  // (the scales of the last stage)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                sa_cur[i] &= (int)last_mask;
-                if (i < NJ) sb_cur[i] &= (int)last_mask;
+        const int sb = SC_STAGE * (s + 1);
+        constexpr bool STEADY = MODE == 0 || MODE == 3;
+        auto step = [&](int n) {
+            if (n == 0 && MODE != 2) {
+                if (MODE == 1) ld_a = nxt.a;
+                else if (RAG) ld_k = ld_k + STAGE_K / 2 < k_last ? ld_k + STAGE_K / 2 : k_last, ld_a = cur.a + ld_k;
+                else ld_a += STAGE_K / 2;
+                asm volatile("" : "+s"(ld_a));
             }
-        }
+            if (n == 1 && MODE != 2) {
+                if (MODE == 1) ld_b = nxt.b;
+                else if (RAG) ld_b = cur.b + ld_k;
+                else ld_b += STAGE_K / 2;
+                asm volatile("" : "+s"(ld_b));
+                ld_buf ^= STAGE_BYTES;
+                asm volatile("" : "+s"(ld_buf));
+            }
+            if (n == 2 && MODE != 2) {
+                const int first = (sb & ~31) < sb_lim ? (sb & ~31) : sb_lim;
+                sc_next = (uint32_t)((RAG && sb > (int)nkb - SC_STAGE ? (int)nkb - SC_STAGE : sb) - first);
+                asm volatile("" : "+s"(sc_next));
+            }
+            if (n == 3 && MODE != 2) {
+                sc_next += (uint32_t)(((sb & 32) << 9) ^ (par << 14));
+                asm volatile("" : "+s"(sc_next));
+            }
+            if (n == 4 && !RAG && STEADY) {
+                const int first = (sb & ~31) + 32;
+                sc_off = (uint32_t)(first < sb_lim ? first : sb_lim);
+                asm volatile("" : "+s"(sc_off));
+            }
+            if (n == 5 && !RAG && STEADY) {
+                sc_dst = FMT ? (uint32_t)(((sb & 12) << 10) | ((sb & 32) << 9)) : (uint32_t)((sb & 56) << 9);
+                asm volatile("" : "+s"(sc_dst));
+                sc_dst = (sc_dst ^ (uint32_t)(((par ^ 1) << 14))) + lds0 + OFF_SC + wave * 1024;
+                asm volatile("" : "+s"(sc_dst));
+            }
+            if (n == 6 && !RAG && STEADY) {
+                sc_src = (sb & 2 * SC_STAGE) ? cur.bs : cur.as;
+                asm volatile("" : "+s"(sc_src));
+            }
+            if (n == 7 && !RAG && STEADY) {  // (narrow tile: piece 3 is piece 2 again)
+                const bool second = (sb & SC_STAGE) && !(NJ == 2 && (sb & 2 * SC_STAGE));
+                sc_off += second ? (uint32_t)(32 * nkb) : 0u;
+                asm volatile("" : "+s"(sc_off));
+            }
+        };
+        // Behind the barrier, in front of the L-th instruction from there (LATE_GAPS of them, of phases 2 and 3)
+        auto late = [&](auto l) {
+            constexpr int L = decltype(l)::value, P3 = L - (GAPS - BAR);
+            constexpr int f_ = FMT ? (P3 < 0 ? MXFP4_AT(L, 2, 1, 8) : P3 < 8 ? 8 + P3 : -1) : NJ == 4 ? MXFP4_AT(L, 5, 4, 10) : MXFP4_AT(L, 4, 3, 6);
+            constexpr int r_ = FMT ? MXFP4_AT(L, 1, 2, 4) : NJ == 4 ? MXFP4_AT(L, 4, 4, 4) : MXFP4_AT(L, 1, 2, 3);
+            constexpr int d_ = FMT ? MXFP4_AT(L, 1, 2, 12) : NJ == 4 ? MXFP4_AT(L, 2, 4, 12) : MXFP4_AT(L, 0, 3, 8);
+            constexpr int w_ = MXFP4_AT(L, 0, 2, 5);  // RAG: scale piece on its way
+            // step of settling.  Wide: two in every four gaps, then three
+            constexpr int t_ = FMT ? MXFP4_AT(L, 17, 1, 8) : NJ == 2 ? MXFP4_AT(L, 11, 1, 12)
+                               : L < 33 ? (L >= 19 && L % 4 == 3 ? (L - 19) / 2 : L >= 19 && L % 4 == 0 ? (L - 20) / 2 + 1 : -1)
+                                        : (L >= 34 && L < 44 && L % 4 != 1 ? 8 + (L - 34) / 4 * 3 + (L - 34) % 4 : -1);
+            if constexpr (MODE != 2 && f_ >= 0) fetch(LATE, f_);
+            if constexpr (MODE != 2 && r_ >= 0) read_scales(sc_next, r_);
+            if constexpr (MODE != 2 && t_ >= 0) settle_scales(FMT ? t_ >> 2 : settle_set(t_ >> 2), t_ & 3, MODE == 1);
+            if (!RAG && STEADY && L == 0) dma16(sc_dst, svoff + sc_off, sc_src);
+            if (RAG && STEADY && L == 0) {
+                rag_store((s + 1) / BATCH + 1, (s + 1) & 3, par, sp[4]);
+                sp[4] = rag_load(cur, (s + 2) / BATCH + 1, (s + 2) & 3);
+            }
+            if constexpr (RAG && MODE == 1 && w_ >= 0) sp[w_] = rag_load(nxt, w_ / 4, w_ & 3);
+            if constexpr (RAG && MODE == 2 && w_ >= 0) rag_store(w_ / 4, w_ & 3, par_nxt, sp[w_]);
+            if (RAG && MODE == 2 && L == LATE_GAPS - 1) sp[4] = rag_load(nxt, 1, 1);
+            if constexpr (STEADY && d_ >= 0) issue_load(IC<d_ < 0 ? 0 : d_>{}, no_force{});
+            if constexpr (MODE == 1 && d_ >= 0) issue_load(IC<d_ < 0 ? 0 : d_>{}, force_m0{});
+            if constexpr (!RAG && MODE == 1 && w_ >= 0 && w_ < (NJ == 4 ? 4 : 3)) issue_scales(nxt, 0, w_, par_nxt);
+            if (!RAG && MODE == 2 && L == 1) issue_scales(nxt, 1, 0, par_nxt);
+        };
+#define MXFP4_K0(G)                                                                              \
+        {                                                                                        \
+            constexpr int f_ = FMT ? MXFP4_AT(G, 1, 2, 8) : NJ == 4 ? MXFP4_AT(G, 2, 4, 8) : MXFP4_AT(G, 1, 2, 6); \
+            constexpr int d_ = FMT ? MXFP4_AT(G, 0, 2, 4) : NJ == 4 ? MXFP4_AT(G, 0, 4, 4) : MXFP4_AT(G, 0, 2, 4); \
+            constexpr int a_ = FMT ? MXFP4_AT(G, 8, 2, 4) : NJ == 4 ? MXFP4_AT(G, 3, 2, 8) : MXFP4_AT(G, 8, 1, 6); \
+            if constexpr (f_ >= 0) fetch(0, f_);                                                 \
+            if constexpr (a_ >= 0) age_scales(a_);                                               \
+            if constexpr (d_ >= 0) issue_load(IC<LOADS_LATE + (d_ < 0 ? 0 : d_)>{}, no_force{}); \
+        }                                                                                        \
+        MXFP4_SLOT_MMA(0, G, MODE) MXFP4_PIN()
+        MXFP4_32(MXFP4_K0)
+#undef MXFP4_K0
+#define MXFP4_K1(G)                                                                              \
+        {                                                                                        \
+            constexpr int f_ = FMT ? MXFP4_AT(G, 0, 2, 8) : NJ == 4 ? MXFP4_AT(G, 0, 3, 10) : MXFP4_AT(G, 0, 2, 8); \
+            constexpr int n_ = !FMT && NJ == 4 ? MXFP4_AT(G, 1, 4, 8) : MXFP4_AT(G, 1, 2, 8);     \
+            if constexpr (f_ >= 0) fetch(1, f_);                                                 \
+            if constexpr (n_ >= 0) step(n_);                                                     \
+        }                                                                                        \
+        if (!FMT && (G) == GAPS - 2) other_buffer(ra[0]); /* (K-step 0's fragments have all been fetched) */ \
+        if (!FMT && (G) == GAPS - 1) other_buffer(rb[0]);                                        \
+        MXFP4_SLOT_MMA(1, G, MODE) MXFP4_PIN()
+        MXFP4_32(MXFP4_K1)
+#undef MXFP4_K1
+#define MXFP4_K2(G)                                                                              \
+        if constexpr (!FMT && (G) < 2 * 4 && (G) % 2 == 0) fetch(2, (G) / 2); /* (early: the barrier waits for them) */ \
+        if (FMT && (G) < 2) other_buffer(ra[(G) & 1]); /* (the stage's fragments have all been fetched) */ \
+        if (FMT && (G) >= 2 && (G) < 4) other_buffer(rb[(G) & 1]);                               \
+        if constexpr ((G) == BAR) {                                                              \
+            /* every wave has fetched its last fragments of this buffer, and this wave's loads of the next stage have landed: */ \
+            /* after the barrier the buffer may be refilled and the other read */                \
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                                     \
+            __syncthreads();                                                                     \
+        }                                                                                        \
+        if constexpr ((G) >= BAR && (G) < GAPS) late(IC<((G) >= BAR ? (G) - BAR : 0)>{});        \
+        MXFP4_SLOT_MMA(2, G, MODE) MXFP4_PIN()
+        MXFP4_32(MXFP4_K2)
+#undef MXFP4_K2
+#define MXFP4_K3(G)                                                                              \
+        if constexpr ((G) < GAPS) late(IC<GAPS - BAR + (G)>{});                                  \
+        if (!FMT && (G) == GAPS - 2) other_buffer(ra[1]);                                        \
+        if (!FMT && (G) == GAPS - 1) other_buffer(rb[1]);                                        \
+        MXFP4_SLOT_MMA(3, G, MODE) MXFP4_PIN()
+        MXFP4_32(MXFP4_K3)
+#undef MXFP4_K3
     };
     using mode_main = std::integral_constant<int, 0>;
     using mode_penult = std::integral_constant<int, 1>;
@@ -578,7 +680,8 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
     // ---- first tile: fill the pipeline --------------------------------------------------------
     // all of stage 0, the first 8 loads of stage 1, scale batch 0 and the first load of batch 1
     TileSrc cur = tile_src(lw);
-#define MXFP4_FILL(N) if constexpr ((N) < NLOADS) issue_load(cur, 0, 0, IC<((N) < NLOADS ? (N) : 0)>{}, no_force{});
+    set_load(cur, 0);
+#define MXFP4_FILL(N) if constexpr ((N) < NLOADS) issue_load(IC<((N) < NLOADS ? (N) : 0)>{}, no_force{});
     MXFP4_16(MXFP4_FILL)
 #undef MXFP4_FILL
     if constexpr (RAG) {
@@ -604,22 +707,26 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
         // here); after the barrier start stage 1's first half and fetch the first fragments
         if (lloc == lw) asm volatile("s_waitcnt vmcnt(1)" ::: "memory");  // (later tiles waited before the epilogue)
         __syncthreads();
-#define MXFP4_FILL(N) if constexpr ((N) < 8) issue_load(cur, 1, bp ^ 1, IC<((N) & 7)>{}, no_force{});
+        set_load(cur, 1);
+        ld_buf ^= STAGE_BYTES;
+#define MXFP4_FILL(N) if constexpr ((N) < LOADS_LATE) issue_load(IC<((N) < LOADS_LATE ? (N) : 0)>{}, no_force{});
         MXFP4_16(MXFP4_FILL)
 #undef MXFP4_FILL
 #pragma unroll
-        for (int f = 0; f < 8; ++f) {
-            if ((f & 1) && (f >> 1) >= NJ) continue;  // (narrow tile: two B fragments only)
-            read_one(bp, 0, 0, f);
-            if (FMT) read_one(bp, 1, 1, f);
-            read_scale_one(0, f, par);
-        }
-        permute_scales();
+        for (int n = 0; n < (FMT ? 16 : NB + 2); ++n) fetch(LATE, n);
+#pragma unroll
+        for (int n = 0; n < (NJ == 4 ? 4 : 3); ++n) read_scales(sc_place(0, par), n);
+#pragma unroll
+        for (int t = 0; t < 4 * SETS; ++t) settle_scales(FMT ? t >> 2 : settle_set(t >> 2), t & 3, false);
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_nop 1");  // (between them and the first matrix instruction)
 
         stage(cur, nxt, par, par_nxt, 0, mode_first{});
         for (int s = 1; s + 2 < nstages; ++s) stage(cur, nxt, par, par_nxt, s, mode_main{});
         stage(cur, nxt, par, par_nxt, nstages - 2, mode_penult{});
         stage(cur, nxt, par, par_nxt, nstages - 1, mode_last{});
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_nop 15\n\ts_nop 7" ::: "memory");  // (the last sums are written 19 clocks' worth of instructions after they are issued)
         __builtin_amdgcn_sched_barrier(0);
         // the next tile's stage 0 and scale batch 0 have been on their way for at least two K-steps: make
         // sure they have landed now, before any store is issued (only the one scale load of batch 1 issued
@@ -630,13 +737,12 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
         // The output is stored non-temporally: it is not read again here, and written the ordinary way it
         // pushes the operands of the kernels that follow (the next quantisers, the next GEMM) out of the
         // last-level cache -- measured on the 8B fused-QKV layer: 10 % of a whole forward + backward step.
-        // A lane owns row fr of each 32-row group and, per 32-column group, columns 8*q + 4*fh + {0..3}.
+        // A lane owns row fr of each 16-row group and, per 16-column group, columns 4*fg + {0..3}.
         // The last stage's buffer is free (all waves passed the last barrier; the other one may already hold
         // the next tile's stage 0): each wave transposes its sub-tile through its own 16 KiB slice of it, 64
         // (bf16) or 32 (fp32) rows at a time, and writes whole 256- / 512-byte row segments.  Rows are
-        // stored unpadded; 16-byte chunk c of row r sits at chunk c ^ (r & 15) (bf16: and its two 8-byte
-        // halves swap when r & 16), which keeps both the 8/16-byte writes and the 16-byte reads
-        // conflict-free.
+        // stored unpadded; 16-byte chunk c of row r sits at chunk c ^ (r & 15), which keeps both the 8/16-byte writes and the 16-byte
+        // reads conflict-free.
         uint8_t *epi = smem + ((((nstages - 1) & 1) ^ bp) ? STAGE_BYTES : 0) + wave * 16384;
         const int64_t row0 = cur.m0 + wm * 128, col0 = cur.n0 + wn * (32 * NJ);
         // RAG: a tile that was moved back stores only what is its own: the others' pieces get an offset beyond the buffer,
@@ -689,18 +795,17 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
             // bytes; chunk c of row r sits at position c ^ ((r >> 1) & 7): the 8-byte writes of a quarter wave
             // (16 rows, one chunk) and the 16-byte reads (2 rows x 8 chunks) then cover all banks evenly.
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+            for (int i = 0; i < 8; ++i) {
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
-#pragma unroll
-                    for (int qd = 0; qd < 4; ++qd) {
-                        const int r = i * 32 + fr, c = j * 4 + qd;
-                        uint2 pk;
-                        pk.x = pack_bf16(acc[i][j][4 * qd + 0], acc[i][j][4 * qd + 1]);
-                        pk.y = pack_bf16(acc[i][j][4 * qd + 2], acc[i][j][4 * qd + 3]);
-                        *reinterpret_cast<uint2 *>(epi + r * 128 + ((c ^ ((r >> 1) & 7)) << 4) + (fh << 3)) = pk;
-                        if (qd == 3) __builtin_amdgcn_sched_barrier(0);
-                    }
+                for (int j = 0; j < 4; ++j) {
+                    const int r = i * 16 + fr, c = j * 2 + (fg >> 1);
+                    uint2 pk;
+                    pk.x = pack_bf16(acc[i][j][0], acc[i][j][1]);
+                    pk.y = pack_bf16(acc[i][j][2], acc[i][j][3]);
+                    *reinterpret_cast<uint2 *>(epi + r * 128 + ((c ^ ((r >> 1) & 7)) << 4) + ((fg & 1) << 3)) = pk;
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
             // 8 lanes x 16 bytes = one 128-byte row segment; 8 rows per instruction
             int rl = lane >> 3, ch = lane & 7;
             if (RAG) asm volatile("" : "+v"(rl), "+v"(ch));  // (else every offset is worked out ahead of the tile loop)
@@ -726,18 +831,14 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
 #pragma unroll
             for (int pass = 0; pass < 2; ++pass) {
 #pragma unroll
-                for (int ii = 0; ii < 2; ++ii)
+                for (int ii = 0; ii < 4; ++ii) {
 #pragma unroll
-                    for (int j = 0; j < 2; ++j)
-#pragma unroll
-                        for (int qd = 0; qd < 4; ++qd) {
-                            const int i = 2 * pass + ii;
-                            const int r = ii * 32 + fr, c = j * 8 + qd * 2 + fh;
-                            *reinterpret_cast<v4f *>(epi + r * 256 + ((c ^ (r & 15)) << 4)) =
-                                (v4f){acc[i][j][4 * qd + 0], acc[i][j][4 * qd + 1], acc[i][j][4 * qd + 2],
-                                      acc[i][j][4 * qd + 3]};
-                            if (qd == 3) __builtin_amdgcn_sched_barrier(0);
-                        }
+                    for (int j = 0; j < 4; ++j) {
+                        const int r = ii * 16 + fr, c = j * 4 + fg;
+                        *reinterpret_cast<v4f *>(epi + r * 256 + ((c ^ (r & 15)) << 4)) = acc[4 * pass + ii][j];
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
                 // 16 lanes x 16 bytes = one 256-byte row segment; 4 rows per instruction
                 int rl = lane >> 4, ch = lane & 15;
                 if (RAG) asm volatile("" : "+v"(rl), "+v"(ch));  // (else every offset is worked out ahead of the tile loop)
@@ -769,20 +870,17 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
 #pragma unroll
             for (int pass = 0; pass < 2; ++pass) {
 #pragma unroll
-                for (int ii = 0; ii < 2; ++ii)
+                for (int ii = 0; ii < 4; ++ii)
 #pragma unroll
-                    for (int j = 0; j < 4; ++j)
-#pragma unroll
-                        for (int qd = 0; qd < 4; ++qd) {
-                            const int i = 2 * pass + ii;
-                            const int r = ii * 32 + fr, c = j * 4 + qd;
-                            uint2 pk;
-                            pk.x = pack_bf16(acc[i][j][4 * qd + 0], acc[i][j][4 * qd + 1]);
-                            pk.y = pack_bf16(acc[i][j][4 * qd + 2], acc[i][j][4 * qd + 3]);
-                            *reinterpret_cast<uint2 *>(epi + r * 256 + ((c ^ (r & 15)) << 4) +
-                                                       ((fh ^ ((r >> 4) & 1)) << 3)) = pk;
-                            if (qd == 3) __builtin_amdgcn_sched_barrier(0);  // one 32x32 tile at a time
-                        }
+                    for (int j = 0; j < 8; ++j) {
+                        const int i = 4 * pass + ii;
+                        const int r = ii * 16 + fr, c = j * 2 + (fg >> 1);
+                        uint2 pk;
+                        pk.x = pack_bf16(acc[i][j][0], acc[i][j][1]);
+                        pk.y = pack_bf16(acc[i][j][2], acc[i][j][3]);
+                        *reinterpret_cast<uint2 *>(epi + r * 256 + ((c ^ (r & 15)) << 4) + ((fg & 1) << 3)) = pk;
+                        if (j & 4) __builtin_amdgcn_sched_barrier(0);
+                    }
                 // 16 lanes x 16 bytes = one 256-byte row segment; 4 rows per instruction.  Eight LDS reads are
                 // issued before the first store needs its data, so their latencies overlap; the row pointer
                 // is one per-lane base plus a scalar multiple of the leading dimension.
@@ -804,10 +902,8 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
 #pragma unroll
                     for (int u = 0; u < 8; ++u) {
                         const int r4 = (8 * h + u) * 4;
-                        v4i v = buf[u];
-                        if ((r4 >> 4) & 1) v = (v4i){v.z, v.w, v.x, v.y};
-                        if constexpr (RAG) rag_put(pass * 64 + r4 + rl, ch * 8, v);
-                        else __builtin_nontemporal_store(v, reinterpret_cast<v4i *>(obase + (int64_t)r4 * ld));
+                        if constexpr (RAG) rag_put(pass * 64 + r4 + rl, ch * 8, buf[u]);
+                        else __builtin_nontemporal_store(buf[u], reinterpret_cast<v4i *>(obase + (int64_t)r4 * ld));
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -816,14 +912,12 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
 #pragma unroll
             for (int pass = 0; pass < 4; ++pass) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
+                for (int ii = 0; ii < 2; ++ii)
 #pragma unroll
-                    for (int qd = 0; qd < 4; ++qd) {
-                        const int c = j * 8 + qd * 2 + fh;
-                        *reinterpret_cast<v4f *>(epi + fr * 512 + ((c ^ fr) << 4)) =
-                            (v4f){acc[pass][j][4 * qd + 0], acc[pass][j][4 * qd + 1], acc[pass][j][4 * qd + 2],
-                                  acc[pass][j][4 * qd + 3]};
-                        if (qd == 3) __builtin_amdgcn_sched_barrier(0);
+                    for (int j = 0; j < 8; ++j) {
+                        const int r = ii * 16 + fr, c = j * 4 + fg;
+                        *reinterpret_cast<v4f *>(epi + r * 512 + ((c ^ r) << 4)) = acc[2 * pass + ii][j];
+                        if ((j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
                     }
                 // 32 lanes x 16 bytes = one 512-byte row segment; 2 rows per instruction; reads batched by
                 // eight as above
@@ -862,17 +956,12 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
     }
     // nothing may still be writing this workgroup's LDS when it retires
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-#undef MXFP4_MMA
-#undef MXFP8_MMA
+#undef MXFP4_MFMA
 #undef MXFP4_SLOT_MMA
 #undef MXFP4_PIN
+#undef MXFP4_AT
+#undef MXFP4_32
 #undef MXFP4_16
-#undef MXFP4_FRAG_SLOT
-#undef MXFP4_FRAG_OF
-#undef MXFP4_LOAD0_SLOT
-#undef MXFP4_LOAD0_OF
-#undef MXFP4_LOAD3_SLOT
-#undef MXFP4_LOAD3_OF
 }
 
 struct TileGemm {
