@@ -8,7 +8,7 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmxfp4.so")
-SOURCES = ["api.hip", "quantize.hip", "quantize_fp8.hip", "gemm.hip"]
+SOURCES = ["api.hip", "quantize.hip", "quantize_fp8.hip", "gemm.hip", "linear_small.hip"]
 
 # -ffp-contract=off: the quantiser's fp32 butterflies must round after every operation.
 # The -target-feature pair switches packed-fp32 code generation off (device pass only; the

@@ -577,6 +577,12 @@ int mxfp4_linear_workspace_layout(int64_t M, int64_t N, int64_t K, const mxfp4_l
     return MXFP4_OK;
 }
 
+static bool apart(const void *a, size_t a_bytes, const void *b, size_t b_bytes)
+{
+    const uintptr_t p = reinterpret_cast<uintptr_t>(a), q = reinterpret_cast<uintptr_t>(b);
+    return p + a_bytes <= q || q + b_bytes <= p;
+}
+
 int mxfp4_linear_fwd(const void *x, const void *w, void *y, int64_t M, int64_t N, int64_t K,
                      const mxfp4_linear_cfg *cfg, void *workspace, size_t workspace_bytes, void *hip_stream)
 {
@@ -591,6 +597,17 @@ int mxfp4_linear_fwd(const void *x, const void *w, void *y, int64_t M, int64_t N
     if (!aligned(workspace, 256) || !aligned(x, 16) || !aligned(w, 16) || !aligned(y, 16)) return MXFP4_EALIGN;
     uint8_t *ws = static_cast<uint8_t *>(workspace);
     if (F.fprop == MXFP4_FMT_E2M1 && cfg->geometry == MXFP4_GEOM_1D) {
+        // The smallest calls are one launch (not where y lies over an input: its tiles are written while others still read)
+        const size_t y_bytes = (size_t)M * N * (cfg->y_dtype == MXFP4_OUT_FP32 ? 4 : 2);
+        if (small_linear(M, N, K, cfg->rounding) && apart(y, y_bytes, x, (size_t)M * K * 2) && apart(y, y_bytes, w, (size_t)N * K * 2)) {
+            if (!device_ok()) return MXFP4_EDEVICE;
+            const QuantArgs a{static_cast<const uint16_t *>(x), M, K, K, cfg->hadamard, cfg->rounding, operand_seed(cfg, STREAM_X),
+                              ws + L.xq, ws + L.xs};
+            const QuantArgs b{static_cast<const uint16_t *>(w), N, K, K, cfg->hadamard, cfg->rounding, operand_seed(cfg, STREAM_W),
+                              ws + L.wq, ws + L.ws};
+            return launch_linear_small(a, b, y, cfg->y_dtype == MXFP4_OUT_FP32, static_cast<hipStream_t>(hip_stream)) == hipSuccess
+                       ? MXFP4_OK : MXFP4_EDEVICE;
+        }
         // X and W, both row-wise in MXFP4: one launch for the two tensors
         rc = quantize_axis_pair(MXFP4_AXIS_LAST, cfg, x, M, K, STREAM_X, ws + L.xq, ws + L.xs, w, N, K, STREAM_W,
                                 ws + L.wq, ws + L.ws, hip_stream);

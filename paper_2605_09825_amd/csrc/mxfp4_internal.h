@@ -27,6 +27,10 @@ constexpr uint64_t SEED_BASE_MASK = 0xFFFFFFFFFFFFull;
 // (b, if not null: a second tensor in the same launch, same hadamard, rounding and base seed; the two grids together
 // must fit one, see launch_limits.h)
 hipError_t launch_quantize_rows(const QuantArgs &a, hipStream_t st, const QuantArgs *b = nullptr);
+// The smallest forward calls: X and W (dense, blocks along rows, same hadamard, rounding and base seed) quantised and multiplied in one
+// launch, y[x.rows][w.rows] dense and apart from both.  small_linear: whether that is the faster way (see linear_small.hip)
+bool small_linear(int64_t M, int64_t N, int64_t K, int rounding);
+hipError_t launch_linear_small(const QuantArgs &x, const QuantArgs &w, void *y, int out_fp32, hipStream_t st);
 // blocks down columns (32x1): q[cols][rows/2], s[cols][rows/32]
 // (b, if not null: as above)
 hipError_t launch_quantize_cols(const QuantArgs &a, hipStream_t st, const QuantArgs *b = nullptr);
