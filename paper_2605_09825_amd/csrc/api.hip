@@ -685,9 +685,26 @@ int mxfp4_linear_bwd(const void *dy, const void *x, const void *w, void *dx, voi
         return MXFP4_EALIGN;
     if ((N % 8) != 0 || (K % 8) != 0) return MXFP4_EALIGN;  // dense bf16 rows must stay 16-byte aligned
     uint8_t *ws = static_cast<uint8_t *>(workspace);
+    const bool all_4 = dx && dw && F.dgrad == MXFP4_FMT_E2M1 && F.wgrad == MXFP4_FMT_E2M1 && cfg->geometry == MXFP4_GEOM_1D;
+    const bool together = all_4 && backward_operands_share_launch(M, N, K, cfg->rounding != MXFP4_RNE, cfg->hadamard != MXFP4_HAD_NONE);
     const bool dw_alone = dw && !dx && F.wgrad == MXFP4_FMT_E2M1 && cfg->geometry == MXFP4_GEOM_1D &&
                           wgrad_operands_share_launch(M, N, K);
-    if (dw_alone) {  // dY and X, both column-wise in MXFP4: one launch for the two tensors
+    if (together) {  // dY both ways, W and X column-wise: one launch for the three tensors
+        QuantArgs gy;
+        rc = prep_dual(dy, M, N, N, cfg->hadamard, cfg->rounding, operand_seed(cfg, STREAM_DY), operand_seed(cfg, STREAM_DYT), ws + L.gq,
+                       ws + L.gs, ws + L.gtq, ws + L.gts, gy);
+        if (rc >= 0) return rc;
+        rc = check_quantize(w, N, K, K, MXFP4_AXIS_FIRST, cfg->hadamard, cfg->rounding, ws + L.wtq, ws + L.wts);
+        if (rc >= 0) return rc;
+        rc = check_quantize(x, M, K, K, MXFP4_AXIS_FIRST, cfg->hadamard, cfg->rounding, ws + L.xtq, ws + L.xts);
+        if (rc >= 0) return rc;
+        if (!device_ok()) return MXFP4_EDEVICE;
+        const QuantArgs a{static_cast<const uint16_t *>(w), N, K, K, cfg->hadamard, cfg->rounding, operand_seed(cfg, STREAM_WT),
+                          ws + L.wtq, ws + L.wts};
+        const QuantArgs b{static_cast<const uint16_t *>(x), M, K, K, cfg->hadamard, cfg->rounding, operand_seed(cfg, STREAM_XT),
+                          ws + L.xtq, ws + L.xts};
+        if (launch_quantize_backward(gy, a, b, static_cast<hipStream_t>(hip_stream)) != hipSuccess) return MXFP4_EDEVICE;
+    } else if (dw_alone) {  // dY and X, both column-wise in MXFP4: one launch for the two tensors
         rc = quantize_axis_pair(MXFP4_AXIS_FIRST, cfg, dy, M, N, STREAM_DYT, ws + L.gtq, ws + L.gts, x, M, K, STREAM_XT,
                                 ws + L.xtq, ws + L.xts, hip_stream);
         if (rc != MXFP4_OK) return rc;
@@ -697,12 +714,12 @@ int mxfp4_linear_bwd(const void *dy, const void *x, const void *w, void *dx, voi
                               F.wgrad, STREAM_DYT, dw ? ws + L.gtq : nullptr, dw ? ws + L.gts : nullptr, hip_stream);
         if (rc != MXFP4_OK) return rc;
     }
-    if (dx && dw && F.dgrad == MXFP4_FMT_E2M1 && F.wgrad == MXFP4_FMT_E2M1 && cfg->geometry == MXFP4_GEOM_1D) {
+    if (all_4 && !together) {
         // W and X, both column-wise in MXFP4: one launch for the two tensors
         rc = quantize_axis_pair(MXFP4_AXIS_FIRST, cfg, w, N, K, STREAM_WT, ws + L.wtq, ws + L.wts, x, M, K, STREAM_XT,
                                 ws + L.xtq, ws + L.xts, hip_stream);
         if (rc != MXFP4_OK) return rc;
-    } else {
+    } else if (!all_4) {
         if (dx) {
             rc = quantize_operand(cfg, w, N, K, 0, 0, nullptr, nullptr, F.dgrad, STREAM_WT, ws + L.wtq, ws + L.wts,
                                   hip_stream);

@@ -53,4 +53,15 @@ constexpr bool wgrad_operands_share_launch(int64_t M, int64_t N, int64_t K)
            grid_fits(cols_groups(M, N) + cols_groups(M, K), COLS_THREADS);
 }
 
+// dY [M][N] both ways and W [N][K] and X [M][K] column-wise in one launch: where both launches would be workgroups of four waves, no
+// tensor lies beyond the last-level cache, and one grid holds them.
+constexpr bool backward_operands_share_launch(int64_t M, int64_t N, int64_t K, bool stochastic, bool rotated)
+{
+    const int64_t lim = int64_t(1) << 31;  // (keeps the products below in range)
+    return M < lim && N < lim && K < lim && !beyond_llc(M, N) && !beyond_llc(N, K) && !beyond_llc(M, K) &&
+           cols_waves(ColsLaunch{stochastic, rotated, false, true, cols_groups(M, N), false, false}) == 4 &&
+           cols_waves(ColsLaunch{stochastic, rotated, false, false, cols_groups(N, K) + cols_groups(M, K), false, false}) == 4 &&
+           grid_fits(cols_groups(M, N) + cols_groups(N, K) + cols_groups(M, K), COLS_THREADS);
+}
+
 }  // namespace mxfp4

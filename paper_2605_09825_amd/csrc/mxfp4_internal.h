@@ -37,6 +37,9 @@ hipError_t launch_quantize_cols(const QuantArgs &a, hipStream_t st, const QuantA
 // both from one pass over x: q, s as launch_quantize_cols; q_row, s_row as launch_quantize_rows
 // (b, if not null: as above)
 hipError_t launch_quantize_dual(const QuantArgs &a, const QuantArgs *b, hipStream_t st);
+// dy as launch_quantize_dual, w and x as launch_quantize_cols, in one launch (same hadamard, rounding and base seed; only where
+// backward_operands_share_launch says so, see launch_limits.h)
+hipError_t launch_quantize_backward(const QuantArgs &dy, const QuantArgs &w, const QuantArgs &x, hipStream_t st);
 // one scale per 32 x 32 region; the pair q, s (column-wise layout) or the pair q_row, s_row (row-wise layout)
 // may be null
 hipError_t launch_quantize_2d(const QuantArgs &a, const QuantArgs *b, hipStream_t st);

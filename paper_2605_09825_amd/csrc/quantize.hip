@@ -115,38 +115,38 @@ struct TileJob {
     RngKey key, key_row;  // stochastic-rounding streams of the column-wise and of the row-wise output
 };
 
+// LDS of a workgroup: per wave one slice that first holds the wave's parked 32 x 128 elements (DUAL, 2D) and then its
+// (CT_COLS + 1) x 16 bytes of column-wise codes waiting to be regrouped; behind the slices the scale bytes
+// of all waves.  A wave only ever touches its own slice until the one barrier before the regrouped stores.
+template <int MODE>
+constexpr int SLICE_BYTES = MODE != MODE_COLS ? 32 * RAW_PITCH : (CT_COLS + 1) * 16;
+template <int MODE, int RB>
+constexpr int TILE_LDS_BYTES = RB * SLICE_BYTES<MODE> + CT_COLS * RB;
+
+// One workgroup's tile, the bid-th of the job.
 // STREAM: the tensor is larger than the last-level cache: it is read with non-temporal loads and its codes are
 // written with non-temporal stores (a compile-time choice: as a run-time branch around the loads the compiler
 // merges the two sides and the hint is lost).
 template <int HAD, int RND, int MODE, int STREAM, int RB>
-__global__ __launch_bounds__(64 * RB) void quantize_cols_kernel(const TileJob job0, const TileJob job1, uint32_t sign_mask)
+__device__ __forceinline__ void quantize_tile(const TileJob &job, const uint32_t bid, const uint32_t sign_mask, uint8_t *const lds)
 {
-    const bool second = blockIdx.x >= job0.nblocks;  // uniform: everything below is selected per workgroup
-    const uint16_t *__restrict__ x = second ? job1.x : job0.x;
-    const int64_t rows = second ? job1.rows : job0.rows, cols = second ? job1.cols : job0.cols;
-    const int64_t ld = second ? job1.ld : job0.ld;
-    uint8_t *__restrict__ q = second ? job1.q : job0.q;
-    uint8_t *__restrict__ s = second ? job1.s : job0.s;
-    uint8_t *__restrict__ q_row = second ? job1.q_row : job0.q_row;
-    uint8_t *__restrict__ s_row = second ? job1.s_row : job0.s_row;
-    const uint32_t col_groups = second ? job1.col_groups : job0.col_groups;
-    const uint32_t nb = second ? job1.nblocks : job0.nblocks;
-    const uint32_t band_rows = second ? job1.band_rows : job0.band_rows;
-    const int s_vec = second ? job1.s_vec : job0.s_vec, s_row_vec4 = second ? job1.s_row_vec4 : job0.s_row_vec4;
+    const uint16_t *__restrict__ x = job.x;
+    const int64_t rows = job.rows, cols = job.cols, ld = job.ld;
+    uint8_t *__restrict__ q = job.q;
+    uint8_t *__restrict__ s = job.s;
+    uint8_t *__restrict__ q_row = job.q_row;
+    uint8_t *__restrict__ s_row = job.s_row;
+    const uint32_t col_groups = job.col_groups, nb = job.nblocks, band_rows = job.band_rows;
+    const int s_vec = job.s_vec, s_row_vec4 = job.s_row_vec4;
     constexpr int streaming = STREAM;
-    const RngKey key = second ? job1.key : job0.key, key_row = second ? job1.key_row : job0.key_row;
-    const uint32_t bid = blockIdx.x - (second ? job0.nblocks : 0u);
+    const RngKey key = job.key, key_row = job.key_row;
 
-    // LDS: per wave one slice that first holds the wave's parked 32 x 128 elements (DUAL, 2D) and then its
-    // (CT_COLS + 1) x 16 bytes of column-wise codes waiting to be regrouped; behind the slices the scale bytes
-    // of all waves.  A wave only ever touches its own slice until the one barrier before the regrouped stores.
     constexpr bool PARK = (MODE != MODE_COLS);
-    constexpr int SLICE = PARK ? 32 * RAW_PITCH : (CT_COLS + 1) * 16;
+    constexpr int SLICE = SLICE_BYTES<MODE>;
     // the codes of wave w start w * SKEW bytes into its slice, so that the 8 lanes that later gather one output
     // row from the 8 slices hit different banks (the column-wise-only slice has the odd pitch built in)
     constexpr int SKEW = PARK ? 16 : 0;
     static_assert(SLICE >= CT_COLS * 16 + (RB - 1) * SKEW + (PARK ? 0 : 16), "the codes of a wave must fit its slice");
-    __shared__ __attribute__((aligned(16))) uint8_t lds[RB * SLICE + CT_COLS * RB];
     uint8_t(*lds_s)[RB] = reinterpret_cast<uint8_t(*)[RB]>(lds + RB * SLICE);
 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -321,6 +321,33 @@ __global__ __launch_bounds__(64 * RB) void quantize_cols_kernel(const TileJob jo
     }
 }
 
+template <int HAD, int RND, int MODE, int STREAM, int RB>
+__global__ __launch_bounds__(64 * RB) void quantize_cols_kernel(const TileJob job0, const TileJob job1, uint32_t sign_mask)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t lds[TILE_LDS_BYTES<MODE, RB>];
+    const bool second = blockIdx.x >= job0.nblocks;  // uniform: the job is selected per workgroup
+    const TileJob job = second ? job1 : job0;
+    quantize_tile<HAD, RND, MODE, STREAM, RB>(job, blockIdx.x - (second ? job0.nblocks : 0u), sign_mask, lds);
+}
+
+// The operands of a backward call in one launch: dY both ways (both), W and X column-wise.  Small layers' quantisers are launches and their
+// ends more than traffic: one end instead of two and no wait between them.  Whole backward calls of M x N x K, us, two launches / one: unrotated 64 x
+// 512 x 512 12.0 / 8.8, 2080 x 4320 x 1440 48.0 / 43.4, 4096 x 4096 x 2040 66.8 / 65.8; H32 256 x 1024 x 1024 14.2 / 10.7, 2048 x 3072 x 768
+// 27.0 / 22.6; stochastic 2080 x 4320 x 1440 71.4 / 62.4.
+template <int HAD, int RND>
+__global__ __launch_bounds__(256) void quantize_backward_kernel(const TileJob both, const TileJob cols0, const TileJob cols1, uint32_t sign_mask)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t lds[TILE_LDS_BYTES<MODE_DUAL, 4>];
+    if (blockIdx.x < both.nblocks) {  // (uniform, as below)
+        quantize_tile<HAD, RND, MODE_DUAL, 0, 4>(both, blockIdx.x, sign_mask, lds);
+        return;
+    }
+    const uint32_t bid = blockIdx.x - both.nblocks;
+    const bool second = bid >= cols0.nblocks;
+    const TileJob job = second ? cols1 : cols0;
+    quantize_tile<HAD, RND, MODE_COLS, 0, 4>(job, bid - (second ? cols0.nblocks : 0u), sign_mask, lds);
+}
+
 RowJob make_row_job(const QuantArgs &a)
 {
     RowJob j;
@@ -415,6 +442,17 @@ hipError_t launch_cols_h(const QuantArgs &a, const QuantArgs *b, hipStream_t st)
     return hipGetLastError();
 }
 
+template <int HAD>
+hipError_t launch_backward_h(const QuantArgs &dy, const QuantArgs &w, const QuantArgs &x, hipStream_t st)
+{
+    const TileJob j0 = make_job<MODE_DUAL>(dy, 4), j1 = make_job<MODE_COLS>(w, 4), j2 = make_job<MODE_COLS>(x, 4);
+    const dim3 grid(j0.nblocks + j1.nblocks + j2.nblocks);
+    const uint32_t sign_mask = sign_mask_of(dy.seed);
+    if (dy.rounding != RND_RNE) hipLaunchKernelGGL((quantize_backward_kernel<HAD, RND_SR>), grid, dim3(256), 0, st, j0, j1, j2, sign_mask);
+    else hipLaunchKernelGGL((quantize_backward_kernel<HAD, RND_RNE>), grid, dim3(256), 0, st, j0, j1, j2, sign_mask);
+    return hipGetLastError();
+}
+
 template <int MODE>
 hipError_t launch_cols_mode(const QuantArgs &a, const QuantArgs *b, hipStream_t st)
 {
@@ -448,6 +486,17 @@ hipError_t launch_quantize_cols(const QuantArgs &a, hipStream_t st, const QuantA
 hipError_t launch_quantize_dual(const QuantArgs &a, const QuantArgs *b, hipStream_t st)
 {
     return launch_cols_mode<MODE_DUAL>(a, b, st);
+}
+
+hipError_t launch_quantize_backward(const QuantArgs &dy, const QuantArgs &w, const QuantArgs &x, hipStream_t st)
+{
+    switch (dy.hadamard) {
+        case HAD_NONE: return launch_backward_h<HAD_NONE>(dy, w, x, st);
+        case HAD_DET: return launch_backward_h<HAD_DET>(dy, w, x, st);
+        case HAD_RANDSIGN: return launch_backward_h<HAD_RANDSIGN>(dy, w, x, st);
+        case HAD_RANDSIGN16: return launch_backward_h<HAD_RANDSIGN16>(dy, w, x, st);
+        default: return launch_backward_h<HAD_DET16>(dy, w, x, st);
+    }
 }
 
 hipError_t launch_quantize_2d(const QuantArgs &a, const QuantArgs *b, hipStream_t st)
