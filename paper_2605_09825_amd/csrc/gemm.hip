@@ -1021,8 +1021,8 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_mix_kernel(const TileGemm pn
 }
 
 // Ragged sizes on the same tiles: t_main tiles of the sequence on 256 x 256, then (MXFP4) the rest in halves.  Measured,
-// bf16 output, gemm_edge_kernel / this one: 8192 x 6144 x 4064 181 / 121 us (3.4 PFLOP/s; MXFP8 273 / 199), 8192 x 28640 x
-// 4064 806 / 540, 4096 x 4096 x 4000 58 / 43; 4010 x 6144 x 4096 60 us, against 68 as a tiled interior and a strip.
+// bf16 output, gemm_edge_kernel / this one: 8192 x 6144 x 4064 181 / 112 us (3.7 PFLOP/s; MXFP8 273 / 188), 4096 x 4096 x 4000
+// 58 / 39; 4010 x 6144 x 4096 54 us (with 32 x 32 x 64 instructions 116, 196, 40.4 and 55.2).
 template <bool OUT_FP32, bool ACC, int FMT>
 __global__ __launch_bounds__(256, 1) void gemm_tile_rag_kernel(const TileGemm p, const int64_t Ra, const int64_t Rb,
                                                                const int t_main)
@@ -1112,13 +1112,13 @@ __global__ __launch_bounds__(256, 1) void gemm_tile_pair_kernel(const TileGemm p
 // FMT as in gemm_tile_body.  Built as 64 x 64 (4 stage buffers, 68 KiB of LDS, two workgroups per CU), 128 x 64 (3, 78 KiB,
 // two) and 128 x 256 tiles (8 waves, 3, 156 KiB; with two stage buffers 8192 x 6112 x 4064 took 185 us, with three 173);
 // 128 x 128 tiles on 4 waves were never the fastest, 256 x 256 tiles on 8 waves were slower for MXFP4 (210 against 156 us).
-// What bounds it now: at 8192 x 6144 x 4096 (153 us, 2.7 PFLOP/s, against 104 us of the tiled kernel) LDS traffic, 176 KiB
+// What bounds it now: at 8192 x 6144 x 4096 (153 us, 2.7 PFLOP/s, against 89 us of the tiled kernel) LDS traffic, 176 KiB
 // per 128 x 256 stage against 1024 clocks of matrix instructions; rows that are not whole cache lines apart cost another
 // 20 % (C = 4064: 181 us), because every 128-byte row piece then takes two line requests.
 // Measured back to back in a graph, bf16 output, the any-shape kernel / the fastest tile of this one: MXFP4 8192 x 6144 x 4064
-// 902 / 181 us (now on moved-back tiles, 121), 16000 x 1000 x 3008 238 / 47, 2080 x 4320 x 1440 69 / 21, 2048 x 3072 x 768
+// 902 / 181 us (now on moved-back tiles, 112), 16000 x 1000 x 3008 238 / 47, 2080 x 4320 x 1440 69 / 21, 2048 x 3072 x 768
 // 33 / 9, 200 x 4096 x 4096 31 / 8.5, 24 x 6144 x 4096 23.5 / 7.9 (now on 32 x 32 tiles, 5.6); MXFP8 8192 x 6144 x 4064
-// 1335 / 273 (on moved-back tiles 199), 200 x 4096 x 4096 45.5 / 11.9 us.
+// 1335 / 273 (on moved-back tiles 188), 200 x 4096 x 4096 45.5 / 11.9 us.
 template <int WM, int WN, int NWN, int NBUF>
 struct EdgeTile {
     static constexpr int WAVES = 2 * NWN, TM = 64 * WM, TN = 32 * WN * NWN, ROWS = TM + TN;
