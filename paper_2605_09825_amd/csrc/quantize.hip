@@ -321,13 +321,28 @@ __device__ __forceinline__ void quantize_tile(const TileJob &job, const uint32_t
     }
 }
 
+// Field by field: both jobs are loaded and the values selected.  Selected as a whole, the address is, and its loads wait for that of nblocks:
+// 0.3 us per launch (2048 x 3072 x 768 forward and backward 35.8 / 36.5 us).
+__device__ __forceinline__ TileJob pick_job(bool second, const TileJob &a, const TileJob &b)
+{
+    TileJob j;
+    j.x = second ? b.x : a.x;
+    j.rows = second ? b.rows : a.rows, j.cols = second ? b.cols : a.cols, j.ld = second ? b.ld : a.ld;
+    j.q = second ? b.q : a.q, j.s = second ? b.s : a.s, j.q_row = second ? b.q_row : a.q_row, j.s_row = second ? b.s_row : a.s_row;
+    j.col_groups = second ? b.col_groups : a.col_groups, j.nblocks = second ? b.nblocks : a.nblocks;
+    j.band_rows = second ? b.band_rows : a.band_rows;
+    j.s_vec = second ? b.s_vec : a.s_vec, j.s_row_vec4 = second ? b.s_row_vec4 : a.s_row_vec4;
+    j.streaming = 0;  // (the launch's: a template parameter)
+    j.key = second ? b.key : a.key, j.key_row = second ? b.key_row : a.key_row;
+    return j;
+}
+
 template <int HAD, int RND, int MODE, int STREAM, int RB>
 __global__ __launch_bounds__(64 * RB) void quantize_cols_kernel(const TileJob job0, const TileJob job1, uint32_t sign_mask)
 {
     __shared__ __attribute__((aligned(16))) uint8_t lds[TILE_LDS_BYTES<MODE, RB>];
     const bool second = blockIdx.x >= job0.nblocks;  // uniform: the job is selected per workgroup
-    const TileJob job = second ? job1 : job0;
-    quantize_tile<HAD, RND, MODE, STREAM, RB>(job, blockIdx.x - (second ? job0.nblocks : 0u), sign_mask, lds);
+    quantize_tile<HAD, RND, MODE, STREAM, RB>(pick_job(second, job0, job1), blockIdx.x - (second ? job0.nblocks : 0u), sign_mask, lds);
 }
 
 // The operands of a backward call in one launch: dY both ways (both), W and X column-wise.  Small layers' quantisers are launches and their
@@ -344,8 +359,7 @@ __global__ __launch_bounds__(256) void quantize_backward_kernel(const TileJob bo
     }
     const uint32_t bid = blockIdx.x - both.nblocks;
     const bool second = bid >= cols0.nblocks;
-    const TileJob job = second ? cols1 : cols0;
-    quantize_tile<HAD, RND, MODE_COLS, 0, 4>(job, bid - (second ? cols0.nblocks : 0u), sign_mask, lds);
+    quantize_tile<HAD, RND, MODE_COLS, 0, 4>(pick_job(second, cols0, cols1), bid - (second ? cols0.nblocks : 0u), sign_mask, lds);
 }
 
 RowJob make_row_job(const QuantArgs &a)
