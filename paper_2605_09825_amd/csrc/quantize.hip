@@ -180,16 +180,23 @@ __device__ __forceinline__ void quantize_tile(const TileJob &job, const uint32_t
     const bool want_row = (MODE == MODE_DUAL) || (MODE == MODE_2D && q_row != nullptr);
     const bool want_col = (MODE != MODE_2D) || (q != nullptr);
 
+    // (Rows are used in the order they are loaded in.  Left to itself the compiler may put row 15 behind most of rows 16 .. 31, and the wait for the
+    // first half is then one for nearly all 32: 32 x 32 regions, 3232 x 1024 x 128 forward and backward 38.5 us, 37.8 with the barrier.)
     uint32_t raw[32];
     if (active) {
         const uint16_t *p = x + (rb * 32) * ld + col;
         if constexpr (STREAM) {  // read once: keep it out of the way of the output in the caches
 #pragma unroll
-            for (int i = 0; i < 32; ++i)
+            for (int i = 0; i < 32; ++i) {
+                if (i == 16) __builtin_amdgcn_sched_barrier(0);
                 raw[i] = __builtin_nontemporal_load(reinterpret_cast<const uint32_t *>(p + i * ld));
+            }
         } else {
 #pragma unroll
-            for (int i = 0; i < 32; ++i) raw[i] = *reinterpret_cast<const uint32_t *>(p + i * ld);
+            for (int i = 0; i < 32; ++i) {
+                if (i == 16) __builtin_amdgcn_sched_barrier(0);
+                raw[i] = *reinterpret_cast<const uint32_t *>(p + i * ld);
+            }
         }
     } else {
 #pragma unroll
