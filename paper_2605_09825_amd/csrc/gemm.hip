@@ -213,6 +213,30 @@ struct TileSrc {
     int dm, dn;  // RAG: rows and columns at the tile's start that belong to its neighbours
 };
 
+// Slots behind a stage's barrier (see gemm_tile_body): the step of settling the next stage's scales that goes in front of the slot-th matrix
+// instruction from there, -1: none.  One a slot; wide tile: two in every four slots, then three.
+template <int FMT, int NJ>
+constexpr int settle_step(int slot)
+{
+    if (FMT) return slot >= 17 && slot < 25 ? slot - 17 : -1;
+    if (NJ == 2) return slot >= 11 && slot < 23 ? slot - 11 : -1;
+    if (slot < 33) return slot < 19 ? -1 : slot % 4 == 3 ? (slot - 19) / 2 : slot % 4 == 0 ? (slot - 20) / 2 + 1 : -1;
+    return slot >= 34 && slot < 44 && slot % 4 != 1 ? 8 + (slot - 34) / 4 * 3 + (slot - 34) % 4 : -1;
+}
+// every step once, in order, and two matrix instructions between the last and the first one of the next stage, which reads what it leaves
+template <int FMT, int NJ>
+constexpr bool settled_in_time(int slots, int steps)
+{
+    int next = 0, last = slots;
+    for (int slot = 0; slot < slots; ++slot) {
+        if (settle_step<FMT, NJ>(slot) < 0) continue;
+        if (settle_step<FMT, NJ>(slot) != next) return false;
+        ++next;
+        last = slot;
+    }
+    return next == steps && last + 2 <= slots;
+}
+
 // 16 or 8 bytes at any address
 struct __attribute__((packed, aligned(1))) Bytes16 { uint32_t v[4]; };
 struct __attribute__((packed, aligned(1))) Bytes8 { uint32_t v[2]; };
@@ -471,8 +495,12 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
 
     // One matrix instruction: tile (I, J) of the wave's 8 x NB, fragments and scale bytes of K-step KK.  In assembly, so that the sum stays
     // where it is: with four registers per sum and none to spare the compiler moves a quarter of them about at every change of stage body.
-    // What the compiler then leaves to this code: two instructions between a vector instruction and the matrix instruction that reads its
-    // result (scales are settled at least one slot ahead), and the wait before the epilogue reads the sums (below).
+    // What the compiler then leaves to this code, and every change of it has to keep:
+    //   * two wait states between a vector instruction and a matrix instruction that reads its result: the scales, which are settled at least
+    //     two matrix instructions ahead (settled_in_time) and aged a phase ahead, and any copy that the compiler puts at a change of stage body
+    //     (the wait that every stage body begins with; its time does not show: 8192 x 6144 x 4096 forward and backward 345.2 / 345.3 us);
+    //   * 19 between a matrix instruction and anything but itself that touches its sums: the wait before the epilogue reads them (below).
+    // The fragments come from LDS, for whose loads the compiler waits.  tests/test_codegen.py looks for both in the built library.
 #define MXFP4_MFMA(FIRST, SECOND, SB, SA, SELB, SELA, FORMATS, FRESH)                                            \
     if constexpr (FRESH)                                                                                        \
         asm volatile("v_mfma_scale_f32_16x16x128_f8f6f4 %0, %1, %2, 0, %3, %4 op_sel:[%5,%6,0] op_sel_hi:[%7,%8,0]" FORMATS \
@@ -505,6 +533,7 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
     // The barrier stands in front of this instruction of phase 2.  Loads of the stage after next go out from there on, LOADS_LATE of them up to
     // the stage's end and the rest in the next one's phase 0.
     constexpr int BAR = FMT ? 4 : NJ == 4 ? 14 : 8, LATE_GAPS = 2 * GAPS - BAR, LOADS_LATE = NJ == 4 ? 12 : 8;
+    static_assert(settled_in_time<FMT, NJ>(LATE_GAPS, 4 * SETS), "scales are read by the matrix instruction behind them too early");
     // item of a list of `count` that goes in front of instruction G, one every `step` from `first` on; -1: none
 #define MXFP4_AT(G, FIRST, STEP, COUNT) ((G) >= (FIRST) && ((G) - (FIRST)) % (STEP) == 0 && ((G) - (FIRST)) / (STEP) < (COUNT) ? ((G) - (FIRST)) / (STEP) : -1)
 #define MXFP4_32(M) M(0) M(1) M(2) M(3) M(4) M(5) M(6) M(7) M(8) M(9) M(10) M(11) M(12) M(13) M(14) M(15) \
@@ -548,6 +577,8 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
     //           nxt's scale batch 1 and fetches nothing (the epilogue follows)
     auto stage = [&](const TileSrc &cur, const TileSrc &nxt, int par, int par_nxt, int s, auto mode) {
         constexpr int MODE = decltype(mode)::value;
+        asm volatile("s_nop 1");  // (no vector instruction's result is read before this has passed, see MXFP4_MFMA)
+        __builtin_amdgcn_sched_barrier(0);
         // Place of the next stage's scales, and destination and source of this stage's one scale load (piece (s + 1) & 3 of the batch after
         // that of stage s + 1): worked out a step at a time in idle slots of phase 1, used in phase 3.
         uint32_t sc_next = 0, sc_dst = 0, sc_off = 0;
@@ -606,10 +637,7 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
             constexpr int r_ = FMT ? MXFP4_AT(L, 1, 2, 4) : NJ == 4 ? MXFP4_AT(L, 4, 4, 4) : MXFP4_AT(L, 1, 2, 3);
             constexpr int d_ = FMT ? MXFP4_AT(L, 1, 2, 12) : NJ == 4 ? MXFP4_AT(L, 2, 4, 12) : MXFP4_AT(L, 0, 3, 8);
             constexpr int w_ = MXFP4_AT(L, 0, 2, 5);  // RAG: scale piece on its way
-            // step of settling.  Wide: two in every four gaps, then three
-            constexpr int t_ = FMT ? MXFP4_AT(L, 17, 1, 8) : NJ == 2 ? MXFP4_AT(L, 11, 1, 12)
-                               : L < 33 ? (L >= 19 && L % 4 == 3 ? (L - 19) / 2 : L >= 19 && L % 4 == 0 ? (L - 20) / 2 + 1 : -1)
-                                        : (L >= 34 && L < 44 && L % 4 != 1 ? 8 + (L - 34) / 4 * 3 + (L - 34) % 4 : -1);
+            constexpr int t_ = settle_step<FMT, NJ>(L);
             if constexpr (MODE != 2 && f_ >= 0) fetch(LATE, f_);
             if constexpr (MODE != 2 && r_ >= 0) read_scales(sc_next, r_);
             if constexpr (MODE != 2 && t_ >= 0) settle_scales(FMT ? t_ >> 2 : settle_set(t_ >> 2), t_ & 3, MODE == 1);
@@ -719,7 +747,6 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
 #pragma unroll
         for (int t = 0; t < 4 * SETS; ++t) settle_scales(FMT ? t >> 2 : settle_set(t >> 2), t & 3, false);
         __builtin_amdgcn_sched_barrier(0);
-        asm volatile("s_nop 1");  // (between them and the first matrix instruction)
 
         stage(cur, nxt, par, par_nxt, 0, mode_first{});
         for (int s = 1; s + 2 < nstages; ++s) stage(cur, nxt, par, par_nxt, s, mode_main{});
