@@ -599,7 +599,7 @@ int mxfp4_linear_fwd(const void *x, const void *w, void *y, int64_t M, int64_t N
     if (F.fprop == MXFP4_FMT_E2M1 && cfg->geometry == MXFP4_GEOM_1D) {
         // The smallest calls are one launch (not where y lies over an input: its tiles are written while others still read)
         const size_t y_bytes = (size_t)M * N * (cfg->y_dtype == MXFP4_OUT_FP32 ? 4 : 2);
-        if (small_linear(M, N, K, cfg->rounding) && apart(y, y_bytes, x, (size_t)M * K * 2) && apart(y, y_bytes, w, (size_t)N * K * 2)) {
+        if (small_linear(M, N, K, cfg->rounding != MXFP4_RNE) && apart(y, y_bytes, x, (size_t)M * K * 2) && apart(y, y_bytes, w, (size_t)N * K * 2)) {
             if (!device_ok()) return MXFP4_EDEVICE;
             const QuantArgs a{static_cast<const uint16_t *>(x), M, K, K, cfg->hadamard, cfg->rounding, operand_seed(cfg, STREAM_X),
                               ws + L.xq, ws + L.xs};

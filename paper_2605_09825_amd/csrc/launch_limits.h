@@ -64,4 +64,15 @@ constexpr bool backward_operands_share_launch(int64_t M, int64_t N, int64_t K, b
            grid_fits(cols_groups(M, N) + cols_groups(N, K) + cols_groups(M, K), COLS_THREADS);
 }
 
+// The smallest forward calls, X [M][K] and W [N][K], in one launch of 32 x 32 tiles.  Up to 256 tiles (one per compute unit) of rows of at most 512
+// elements, what the kernel holds: with H32 the quantising takes 1 us per 256 elements of a row, the second launch's end of the wait 2 us.
+// Stochastic rounding takes three times as long (512 x 512 x 384 in a graph 7.1 us in two launches, 7.8 in one; 256 x 512 x 512 6.9
+// and 9.7) and stops at 256.
+constexpr int SMALL_LINEAR_TILE = 32, SMALL_LINEAR_BLOCKS = 16;  // (blocks of 32 elements per row)
+constexpr bool small_linear(int64_t M, int64_t N, int64_t K, bool stochastic)
+{
+    if (M > (1 << 20) || N > (1 << 20) || K > 32 * (stochastic ? SMALL_LINEAR_BLOCKS / 2 : SMALL_LINEAR_BLOCKS)) return false;
+    return ((M + SMALL_LINEAR_TILE - 1) / SMALL_LINEAR_TILE) * ((N + SMALL_LINEAR_TILE - 1) / SMALL_LINEAR_TILE) <= 256;
+}
+
 }  // namespace mxfp4

@@ -4,9 +4,10 @@
 // two launches and the wait of the second for the first.  Here a workgroup owns a 32 x 32 tile of Y: it quantises the tile's 32 rows of X and
 // 32 rows of W into LDS (one lane per block, the arithmetic of the row-wise quantiser), multiplies them from there, and the workgroups of
 // the first tile column (row) also write X's (W's) codes and scales to the workspace, where a call leaves them.  Every row is
-// quantised once per tile beside it, which is why the rule below stops at a few blocks per lane.
+// quantised once per tile beside it, which is why the rule (small_linear) stops at a few blocks per lane.
 // us, two launches / one, called from Python and in a graph: 256 x 512 x 512 unrotated 9.8 / 5.9 and 5.6 / 3.9, H32 9.8 / 6.0 and 5.8 / 4.8;
 // 256 x 1024 x 128 9.9 / 5.9 and 5.9 / 2.8; 16 x 2048 x 256 stochastic 9.9 / 5.9 and 7.0 / 5.7.
+#include "launch_limits.h"
 #include "mxfp4_internal.h"
 #include "quantize_block.h"
 
@@ -19,9 +20,9 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int TILE = 32;
+constexpr int TILE = SMALL_LINEAR_TILE;
 constexpr int THREADS = 512;                   // (256: H32, 256 x 512 x 512 5.8 us in a graph, 4.8 with 512)
-constexpr int MAX_BLOCKS = 16;                 // blocks per row: K <= 512
+constexpr int MAX_BLOCKS = SMALL_LINEAR_BLOCKS;
 constexpr int PITCH = MAX_BLOCKS * 16 + 16;    // bytes of codes per row in LDS, 16 more than whole banks: 16 rows of one chunk cover them all
 
 struct SmallLinear {
@@ -145,16 +146,6 @@ void launch_h(const SmallLinear &p, int rounding, int out_fp32, uint32_t tiles, 
 }
 
 }  // namespace
-
-// Up to 256 tiles (one per compute unit) of rows of at most 512 elements: with H32 the quantising takes 1 us per 256 elements of a row, the second
-// launch's end of the wait 2 us.  Stochastic rounding takes three times as long (512 x 512 x 384 in a graph 7.1 us in two launches, 7.8 in
-// one; 256 x 512 x 512 6.9 and 9.7) and stops at 256.
-bool small_linear(int64_t M, int64_t N, int64_t K, int rounding)
-{
-    if (M > (1 << 20) || N > (1 << 20) || K > 32 * MAX_BLOCKS) return false;
-    const int64_t tiles = ((M + TILE - 1) / TILE) * ((N + TILE - 1) / TILE);
-    return tiles <= 256 && K <= (rounding == RND_RNE ? 512 : 256);
-}
 
 hipError_t launch_linear_small(const QuantArgs &x, const QuantArgs &w, void *y, int out_fp32, hipStream_t st)
 {

@@ -28,8 +28,7 @@ constexpr uint64_t SEED_BASE_MASK = 0xFFFFFFFFFFFFull;
 // must fit one, see launch_limits.h)
 hipError_t launch_quantize_rows(const QuantArgs &a, hipStream_t st, const QuantArgs *b = nullptr);
 // The smallest forward calls: X and W (dense, blocks along rows, same hadamard, rounding and base seed) quantised and multiplied in one
-// launch, y[x.rows][w.rows] dense and apart from both.  small_linear: whether that is the faster way (see linear_small.hip)
-bool small_linear(int64_t M, int64_t N, int64_t K, int rounding);
+// launch, y[x.rows][w.rows] dense and apart from both (only where small_linear says so, see launch_limits.h)
 hipError_t launch_linear_small(const QuantArgs &x, const QuantArgs &w, void *y, int out_fp32, hipStream_t st);
 // blocks down columns (32x1): q[cols][rows/2], s[cols][rows/32]
 // (b, if not null: as above)

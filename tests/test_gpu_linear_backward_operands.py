@@ -9,9 +9,10 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-# one block; a last tile of one row block and of a few columns in each tensor; the sizes around the rule: W and X of 512 tiles and
-# one fewer (2 x 256 of 256 x 128; the rest is then two launches, also with stochastic rounding where the rule has no such limit)
-@pytest.mark.parametrize("shape", [(32, 32, 8), (160, 288, 136), (416, 96, 264), (2080, 4320, 1440), (4096, 4096, 2048), (4096, 3840, 2048)])
+# one block; a last tile of one row block and of a few columns in each tensor; W and X of 496 tiles of 256 x 128, of 511 (the most in one launch, which
+# tests/test_launch_limits.py pins) and of 512 (two launches, rounded to nearest; with stochastic rounding one)
+@pytest.mark.parametrize("shape", [(32, 32, 8), (160, 288, 136), (416, 96, 264), (2080, 4320, 1440), (4096, 4096, 2048), (4096, 3840, 2048),
+                                   (256, 18432, 896), (256, 16128, 1024)])
 @pytest.mark.parametrize("had,rnd", [(mx.HAD_NONE, mx.RNE), (mx.HAD_RANDSIGN, mx.SR), (mx.HAD_DET16, mx.RNE)])
 def test_backward_operands_equal_the_single_quantiser_calls(shape, had, rnd):
     M, N, K = shape

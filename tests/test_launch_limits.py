@@ -1,4 +1,4 @@
-"""CPU-only checks of the host rules about launch grids (plain C++ constants): which tensors share a launch."""
+"""CPU-only checks of the host rules about launch grids (plain C++ constants): which tensors and calls share a launch."""
 import os
 import shutil
 import subprocess
@@ -40,6 +40,23 @@ def holds(condition):
     "cols_waves({false, true, false, true, 4096, false, false}) == 4 && cols_waves({false, true, true, true, 4096, false, false}) == 4",
     "cols_waves({false, true, false, true, 4096, true, false}) == 8 && cols_waves({false, true, true, true, 4096, true, false}) == 4",
     "cols_waves({false, false, true, true, 300, true, false}) == 8 && cols_waves({false, true, true, false, 4096, true, false}) == 4",
+    # dY, W and X of a backward call (stochastic, rotated): together while W and X are fewer than 512 tiles, unless rounding is stochastic
+    "cols_groups(18432, 896) + cols_groups(256, 896) == 511 && cols_groups(16128, 1024) + cols_groups(256, 1024) == 512",
+    "backward_operands_share_launch(256, 18432, 896, false, false) && backward_operands_share_launch(256, 18432, 896, false, true)",
+    "!backward_operands_share_launch(256, 16128, 1024, false, false) && !backward_operands_share_launch(256, 16128, 1024, false, true)",
+    "backward_operands_share_launch(256, 16128, 1024, true, false) && backward_operands_share_launch(256, 16128, 1024, true, true)",
+    # ... while dY is fewer than 1536 tiles, unless rotated
+    "cols_groups(78592, 640) == 1535 && cols_groups(65536, 768) == 1536",
+    "backward_operands_share_launch(78592, 640, 128, false, false) && !backward_operands_share_launch(65536, 768, 128, false, false)",
+    "backward_operands_share_launch(65536, 768, 128, false, true) && backward_operands_share_launch(65536, 768, 128, true, false)",
+    # ... and while each of the three is within the last-level cache
+    "backward_operands_share_launch(16384, 8192, 8192, true, false)",
+    "!backward_operands_share_launch(16384, 8224, 32, true, true) && !backward_operands_share_launch(32, 16384, 8224, true, true)",
+    "!backward_operands_share_launch(16384, 32, 8224, true, true) && !backward_operands_share_launch(ONE << 31, 32, 32, true, true)",
+    # a forward call in one launch (stochastic): 256 tiles of 32 x 32, rows of 16 blocks, or of 8
+    "small_linear(1, 1, 32, false) && small_linear(512, 512, 512, false) && !small_linear(513, 512, 512, false) && !small_linear(512, 513, 32, true)",
+    "small_linear(32, 32 * 256, 512, false) && !small_linear(32, 32 * 257, 64, false) && !small_linear(ONE << 40, ONE << 40, 32, false)",
+    "!small_linear(1, 1, 544, false) && small_linear(1, 1, 256, true) && !small_linear(1, 1, 288, true)",
 ])
 def test_rule(condition):
     assert holds(condition) and not holds("!(%s)" % condition)
