@@ -439,13 +439,7 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
     // One fragment: rows 16 i .. 16 i + 15 of the wave's part of A or B, 16-byte chunks 4 kk .. 4 kk + 3.
     auto read_a = [&](int kk, int i) { fa[kk][i] = *reinterpret_cast<const v4i *>(smem + ra[kk] + i * 2048); };
     auto read_b = [&](int kk, int j) { fb[kk][j] = *reinterpret_cast<const v4i *>(smem + rb[kk] + j * 2048); };
-    // Byte sb = SC_STAGE s of a row's scales, where the stage s begins, lies sc_place(sb, par) behind sa_row0 or sb_row0
-    const int sb_lim = RAG ? (int)nkb - 32 : (nstages - BATCH) * SC_STAGE;  // where the last batch begins
-    auto sc_place = [&](int sb, int par) {
-        const int at = RAG ? (sb < (int)nkb - SC_STAGE ? sb : (int)nkb - SC_STAGE) : sb;
-        const int first = (sb & ~31) < sb_lim ? (sb & ~31) : sb_lim;
-        return (uint32_t)(at - first) + (uint32_t)(((sb & 32) << 9) ^ (par << 14));
-    };
+    const int sb_lim = RAG ? (int)nkb - 32 : (nstages - BATCH) * SC_STAGE;  // byte of a row's scales where the last batch begins
     // piece n (0 .. 3; the narrow tile has no 3): A's rows 0 .. 63, B's, A's 64 .. 127, B's
     auto read_scales = [&](uint32_t place, int n) {
         const uint8_t *p = smem + (((n & 1) ? sb_row0 : sa_row0) + place) + (n >> 1) * 1024;
@@ -579,7 +573,7 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
         constexpr int MODE = decltype(mode)::value;
         asm volatile("s_nop 1");  // (no vector instruction's result is read before this has passed, see MXFP4_MFMA)
         __builtin_amdgcn_sched_barrier(0);
-        // Place of the next stage's scales, and destination and source of this stage's one scale load (piece (s + 1) & 3 of the batch after
+        // Place of the next stage's scales (behind sa_row0 or sb_row0), and destination and source of this stage's one scale load (piece (s + 1) & 3 of the batch after
         // that of stage s + 1): worked out a step at a time in idle slots of phase 1, used in phase 3.
         uint32_t sc_next = 0, sc_dst = 0, sc_off = 0;
         const uint8_t *sc_src = nullptr;
@@ -706,7 +700,7 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
     using mode_first = std::integral_constant<int, 3>;
 
     // ---- first tile: fill the pipeline --------------------------------------------------------
-    // all of stage 0, the first 8 loads of stage 1, scale batch 0 and the first load of batch 1
+    // all of stage 0, scale batch 0 and the first load of batch 1
     TileSrc cur = tile_src(lw);
     set_load(cur, 0);
 #define MXFP4_FILL(N) if constexpr ((N) < NLOADS) issue_load(IC<((N) < NLOADS ? (N) : 0)>{}, no_force{});
@@ -732,7 +726,7 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
         // first stage again into buffers that are idle by then (no branches in the stage bodies)
         const TileSrc nxt = (lloc + nwg_x < count_x) ? tile_src(lloc + nwg_x) : cur;
         // entering a tile: its stage 0 and first scale batch have landed (first tile: wait for them
-        // here); after the barrier start stage 1's first half and fetch the first fragments
+        // here); after the barrier start most of stage 1's loads (LOADS_LATE) and fetch the first fragments
         if (lloc == lw) asm volatile("s_waitcnt vmcnt(1)" ::: "memory");  // (later tiles waited before the epilogue)
         __syncthreads();
         set_load(cur, 1);
@@ -743,7 +737,7 @@ __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, c
 #pragma unroll
         for (int n = 0; n < (FMT ? 16 : NB + 2); ++n) fetch(LATE, n);
 #pragma unroll
-        for (int n = 0; n < (NJ == 4 ? 4 : 3); ++n) read_scales(sc_place(0, par), n);
+        for (int n = 0; n < (NJ == 4 ? 4 : 3); ++n) read_scales((uint32_t)(par << 14), n);
 #pragma unroll
         for (int t = 0; t < 4 * SETS; ++t) settle_scales(FMT ? t >> 2 : settle_set(t >> 2), t & 3, false);
         __builtin_amdgcn_sched_barrier(0);
