@@ -270,7 +270,9 @@ struct __attribute__((packed, aligned(1))) Bytes4 { uint32_t v; };
 // instruction between two matrix instructions counts (16 clocks each, three others fit): taking the scalar arithmetic of a stage from 70 to
 // 25 instructions, in idle slots, gave 322 -> 311 us.  us, in the 32 x 32 form / this one, both on one card: bf16 8192 x 6144 x 4096 93.8 /
 // 89.3, x 16384 313.7 / 298.4 (5.53 PFLOP/s); fp32 6144 x 4096 x 8192 95.7 / 92.9, 4096 x 4096 x 8192 added to 71.5 / 68.7; narrow tiles
-// 8192 x 1024 x 4096 20.2 / 19.7; MXFP8 8192 x 8192 x 4096 202 / 187 (2.94 PFLOP/s).
+// 8192 x 1024 x 4096 20.2 / 19.7; MXFP8 8192 x 8192 x 4096 202 / 187 (2.94 PFLOP/s).  The power control's state counts: on another card,
+// 2.5 s back to back and, in brackets, the 20 launches soon after a second's pause: 8192 x 6144 x 4096 99.3 / 95.6 (103.5 / 98.0),
+// x 16384 339.5 / 320.5 (392.8 / 386.6); MXFP8 8192 x 6144 x 4096 161.1 / 149.2 (190.5 / 174.9).
 template <bool OUT_FP32, bool ACC, int FMT, int NJ, bool HALVES = false, bool RAG = false>
 __device__ __forceinline__ void gemm_tile_body(const uint8_t *__restrict__ aq, const uint8_t *__restrict__ as,
                                                const uint8_t *__restrict__ bq, const uint8_t *__restrict__ bs,

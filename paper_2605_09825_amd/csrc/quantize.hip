@@ -353,9 +353,11 @@ __global__ __launch_bounds__(64 * RB) void quantize_cols_kernel(const TileJob jo
 }
 
 // The operands of a backward call in one launch: dY both ways (both), W and X column-wise.  Small layers' quantisers are launches and their
-// ends more than traffic: one end instead of two and no wait between them.  Whole backward calls of M x N x K, us, two launches / one: unrotated 64 x
-// 512 x 512 12.0 / 8.8, 2080 x 4320 x 1440 48.0 / 43.4, 4096 x 4096 x 2040 66.8 / 65.8; H32 256 x 1024 x 1024 14.2 / 10.7, 2048 x 3072 x 768
-// 27.0 / 22.6; stochastic 2080 x 4320 x 1440 71.4 / 62.4.
+// ends more than traffic: one end instead of two and no wait between them.  Whole backward calls of M x N x K, us in a graph, two launches / one:
+// unrotated 64 x 512 x 512 11.0 / 8.4, 2080 x 4320 x 1440 48.4 / 44.2, 16384 x 4096 x 512 102.8 / 103.0; H32 256 x 1024 x 1024 13.8 / 10.6,
+// 8192 x 4096 x 1024 71.1 / 69.3, 16384 x 4096 x 512 105.6 / 101.3; H16 with signs 2048 x 3072 x 768 29.4 / 24.3.  Stochastic rounding takes this way
+// at any size within the last-level cache: H32 2080 x 4320 x 1440 73.4 / 62.7, 512 x 11008 x 4096 125.5 / 113.7, unrotated 8192 x 4096 x 4096
+// 224.4 / 215.8, 8192 x 8192 x 8192 701 / 695, 16384 x 8160 x 8160 (dY and X of 255 MiB) 1441 / 1433, H32 1480 / 1471.
 template <int HAD, int RND>
 __global__ __launch_bounds__(256) void quantize_backward_kernel(const TileJob both, const TileJob cols0, const TileJob cols1, uint32_t sign_mask)
 {
